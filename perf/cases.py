@@ -48,15 +48,15 @@ def listed():
         # the smallest step there is: one fp32 layer, a thousand-word vocabulary (launches and latency)
         _verify("tiny fp32 step", dtype="f32", n_q_heads=8, n_kv_heads=8, head_dim=64, kv_max=256, depth=5, vocab=1000),
         # interactive decoding of a 7B model: one sequence, every layer of the stack, short tree
-        _verify("7B stack, greedy", layers=32, kv_max=2048),
+        _verify("7B stack greedy", layers=32, kv_max=2048),
         # the same with grouped heads, the default 60-node tree and sampling over a large vocabulary
-        _verify("8B GQA stack, sampling", layers=32, n_kv_heads=8, kv_max=4096, nodes_max=60, topk=10, vocab=128256,
+        _verify("8B GQA stack sampling", layers=32, n_kv_heads=8, kv_max=4096, nodes_max=60, topk=10, vocab=128256,
                 accept="sample"),
         # four sequences of a 33B model (20 of its 60 layers; each is the same work): the largest cache traffic
-        _verify("33B layers, 4 sequences", layers=20, batch=4, n_q_heads=52, n_kv_heads=52, kv_max=4096, nodes_max=60,
+        _verify("33B layers 4 sequences", layers=20, batch=4, n_q_heads=52, n_kv_heads=52, kv_max=4096, nodes_max=60,
                 topk=10),
         # long retrieval-augmented prompt of a 70B model (20 of its 80 layers)
-        _verify("70B layers, long prompt", layers=20, n_q_heads=64, n_kv_heads=8, kv_max=16384, nodes_max=60, topk=10,
+        _verify("70B layers long prompt", layers=20, n_q_heads=64, n_kv_heads=8, kv_max=16384, nodes_max=60, topk=10,
                 vocab=128256, accept="sample"),
         # a serving batch as it comes: 16 sequences of different lengths and tree sizes, temperature below 1
         _verify("ragged batch of 16", layers=4, batch=16, n_kv_heads=8, kv_min=131, kv_max=6011, nodes_min=17,
@@ -65,19 +65,19 @@ def listed():
         {"name": "sampled drafts", "kind": "accept", "batch": 1, "nodes_min": 60, "nodes_max": 60, "depth": 6, "topk": 10,
          "vocab": 128256, "temperature": 1.0, "shape_seed": 1},
         # acceptance from hidden states: a 33B head for four sequences, weights as a model stores them ...
-        {"name": "33B head, greedy", "kind": "lm_head", "batch": 4, "nodes_min": 60, "nodes_max": 60, "depth": 6,
+        {"name": "33B head greedy", "kind": "lm_head", "batch": 4, "nodes_min": 60, "nodes_max": 60, "depth": 6,
          "topk": 10, "hidden": 6656, "vocab": 32000, "accept": "greedy", "temperature": 1.0, "packed": False, "shape_seed": 1},
         # ... and an 8B head with a large vocabulary, sampling, weights repacked once ahead of time
-        {"name": "8B head, sampling", "kind": "lm_head", "batch": 1, "nodes_min": 60, "nodes_max": 60, "depth": 6,
+        {"name": "8B head sampling", "kind": "lm_head", "batch": 1, "nodes_min": 60, "nodes_max": 60, "depth": 6,
          "topk": 10, "hidden": 4096, "vocab": 128256, "accept": "sample", "temperature": 1.0, "packed": True, "shape_seed": 1},
         # draft step of one sequence: the rows of one level of the tree through sampler, layer and top-k cut
-        {"name": "draft step, 4 rows", "kind": "draft", "batch": 1, "rows": 4, "hidden": 4096, "inter": 11008,
+        {"name": "draft step 4 rows", "kind": "draft", "batch": 1, "rows": 4, "hidden": 4096, "inter": 11008,
          "n_q_heads": 32, "n_kv_heads": 32, "head_dim": 128, "kv_max": 2048, "vocab": 32000, "topk": 4, "packed": True},
         # draft step of four sequences of a 33B model, weights as a model stores them
-        {"name": "draft step, 40 rows", "kind": "draft", "batch": 4, "rows": 10, "hidden": 6656, "inter": 17920,
+        {"name": "draft step 40 rows", "kind": "draft", "batch": 4, "rows": 10, "hidden": 6656, "inter": 17920,
          "n_q_heads": 52, "n_kv_heads": 52, "head_dim": 128, "kv_max": 4096, "vocab": 32000, "topk": 10, "packed": False},
         # one cycle end to end, written as the README writes it (one 7B layer stands for the stack)
-        {"name": "one cycle, plain calls", "kind": "cycle", "batch": 1, "rows": 4, "hidden": 4096, "inter": 11008,
+        {"name": "one cycle plain calls", "kind": "cycle", "batch": 1, "rows": 4, "hidden": 4096, "inter": 11008,
          "n_q_heads": 32, "n_kv_heads": 32, "head_dim": 128, "kv_max": 2048, "nodes_min": 26, "nodes_max": 26, "depth": 6,
          "topk": 4, "vocab": 32000, "shape_seed": 1},
     ]
