@@ -34,87 +34,113 @@ using fspad_detail::bf16x8;
 using fspad_detail::f32x4;
 using fspad_detail::StreamGemm;
 
-constexpr int kWaves = 8;            // wavefronts per workgroup, 16 weight rows each (with 4, twice the
-                                     // workgroups: 166 against 158 us for the decoder layer at 4096 / 11008)
-constexpr int kSliceRows = 128;      // weight rows per workgroup
-constexpr int kChunkK = 256;         // k is cut in multiples of this
+constexpr int kSliceRows = fspad_detail::kSliceRows;   // weight rows per slice
+constexpr int kChunkK = 256;         // every k extent is a multiple of this
 constexpr int kMaxRows = 128;        // rows of X per call
+
+// How a projection is spread: its slices (of all problems that share the launch) and their stages
+// along k form one flat list, and workgroup w streams the contiguous range
+// [floor(w T / W), floor((w + 1) T / W)) of it, so that every compute unit fetches the same number of
+// bytes whatever the shape. What a workgroup sums of a slice goes to partial slot (slice + w).
+struct Split {
+  int32_t n_slices;   // all problems
+  int32_t stages;     // per slice
+  int32_t total;      // n_slices * stages
+  int32_t n_wgs;
+};
+__device__ __forceinline__ int range_begin(const Split& s, int w) { return (int)((unsigned)w * (unsigned)s.total / (unsigned)s.n_wgs); }
+// the workgroup whose range holds stage x (32 bits do: at most 2^21 stages and 256 workgroups)
+__device__ __forceinline__ int owner_of(const Split& s, int x) { return (int)((((unsigned)x + 1u) * (unsigned)s.n_wgs - 1u) / (unsigned)s.total); }
+
+// Partial sums of a launch: slot (slice + w) holds [rows][128] fp32 for the stages of the slice that
+// workgroup w summed.
+struct Partials {
+  const float* base;
+  Split split;
+  int32_t rows;
+  // sum over the slots of 4 consecutive columns (from the first slice `slice0` of a problem), in workgroup order
+  __device__ __forceinline__ f32x4 sum(int slice0, int row, int col) const {
+    const int slice = slice0 + col / kSliceRows;
+    const int w0 = owner_of(split, slice * split.stages), w1 = owner_of(split, slice * split.stages + split.stages - 1);
+    const size_t slot = (size_t)rows * kSliceRows;
+    const float* p = base + (size_t)(slice + w0) * slot + (size_t)row * kSliceRows + col % kSliceRows;
+    f32x4 a = *reinterpret_cast<const f32x4*>(p);
+    for (int w = w0 + 1; w <= w1; ++w) {
+      p += slot;
+      a += *reinterpret_cast<const f32x4*>(p);
+    }
+    return a;
+  }
+};
 
 struct PartialGemmParams {
   const char* x[2];        // [rows][K] bf16, one per problem (up / gate share a launch)
-  const char* w[2];        // [N][K] bf16
-  float* part;             // [problem][split][rows][N] fp32
+  const char* w[2];        // [N][K] bf16, row-major or (PACKED) in the tile order of fspad_pack_weight
+  float* part;
   int32_t rows, N, K;
-  int32_t n_slices, n_splits, chunks_per_split;
-  int32_t stagger;         // stages by which consecutive slices are offset along k (0: none)
-  int32_t packed;          // w is in the tile order of fspad_pack_weight
+  int32_t split;           // slices of the first problem
+  Split plan;
 };
 
-// Workgroup (slice, split) of problem blockIdx.y: X[rows, k range] . W[slice rows, k range]^T
-template <int MT, int SPS, bool PACKED = false>
-__global__ __launch_bounds__(64 * kWaves, 2) void partial_gemm_kernel(const PartialGemmParams p) {
-  typedef StreamGemm<MT, SPS, 16, kWaves, 1, PACKED> G;
-  __shared__ __attribute__((aligned(16))) char xs[2 * G::kStageBytes];
+template <int MT, bool PACKED>
+__global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void partial_gemm_kernel(const PartialGemmParams p) {
+  typedef StreamGemm<MT, PACKED> G;
+  __shared__ __attribute__((aligned(1024))) char lds[G::kLdsBytes];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, g = lane >> 4;
-  const int slice = blockIdx.x / p.n_splits, split = blockIdx.x - slice * p.n_splits, prob = blockIdx.y;
-  const int n_chunks = p.K / kChunkK;
-  const int chunk0 = split * p.chunks_per_split;
-  const int chunks = min(p.chunks_per_split, n_chunks - chunk0);
-  const int v0 = slice * kSliceRows + wave * 16;
-  const size_t k_off = (size_t)chunk0 * kChunkK * 2;
-
-  f32x4 acc[MT][1];
+  // an XCD (every eighth workgroup) takes neighbouring ranges
+  const int per_xcd = p.plan.n_wgs >> 3;
+  const int w = (p.plan.n_wgs & 7) == 0 ? (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int t0 = range_begin(p.plan, w), t1 = range_begin(p.plan, w + 1);
+  typename G::Source src;
+  src.x[0] = p.x[0]; src.x[1] = p.x[1]; src.w[0] = p.w[0]; src.w[1] = p.w[1];
+  src.split = p.split; src.n_xrows = p.rows; src.n_wrows = p.N; src.row0 = 0; src.K = p.K;
+  const int slice = t0 / p.plan.stages;
+  // every slice is walked from a stage of its own on: the ranges of an XCD would otherwise be at the same
+  // stage of k, or at few different ones, wherever the length of a range and a slice's stages have a common
+  // divisor (4096-wide rows: six stages of 16), and rows a power-of-two pitch apart then crowd a few L2 channels
+  constexpr int kRot = 3;
+  const int border = (int)((unsigned)slice * kRot % (unsigned)p.plan.stages);
+  int at = t0 - slice * p.plan.stages + border;
+  at -= at >= p.plan.stages ? p.plan.stages : 0;
+  G::run(lds, src, slice, at, border, kRot % p.plan.stages, t1 - t0, [&](int s, const f32x4 (&acc)[MT], unsigned) {
+    // lane (n, g) holds columns 16 wave + 4g .. +3 of row 16t + n
+    float* out = p.part + (size_t)(s + w) * p.rows * kSliceRows + wave * 16 + 4 * g;
 #pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // consecutive slices start their k range p.stagger stages apart and wrap around: workgroups that
-  // run at the same time then read different parts of their rows, instead of crowding the few
-  // memory channels that one k offset of rows a power-of-two pitch apart maps to
-  const int n_steps = chunks * (kChunkK / 32);
-  const int n_stages = n_steps / SPS;
-  const int first_step = (p.stagger && n_steps % SPS == 0) ? (int)(((unsigned)slice * (unsigned)p.stagger) % (unsigned)n_stages) * SPS : 0;
-  G::run(xs, p.x[prob] + k_off, p.w[prob] + (PACKED ? k_off * 16 : k_off), (size_t)p.K * 2, p.rows, p.N, 0, v0, n_steps, first_step, acc);
-
-  // lane (n, g) holds columns v0 + 4g .. +3 of row 16t + n
-  float* out = p.part + ((size_t)prob * p.n_splits + split) * p.rows * p.N;
-  const int c0 = v0 + 4 * g;
-#pragma unroll
-  for (int t = 0; t < MT; ++t) {
-    const int r = 16 * t + n;
-    if (r < p.rows && c0 < p.N) *reinterpret_cast<f32x4*>(out + (size_t)r * p.N + c0) = acc[t][0];   // N is a multiple of 4
-  }
+    for (int t = 0; t < MT; ++t) {
+      const int r = 16 * t + n;
+      if (r < p.rows) *reinterpret_cast<f32x4*>(out + (size_t)r * kSliceRows) = acc[t];
+    }
+  });
 }
 
 struct CombineParams {
-  const float* part;       // [problem][split][rows][N]
+  Partials part;
   const char* f;           // residual input [rows][N] bf16 (MODE 1)
   char* out;               // [rows][N] bf16 (MODE 2: [rows][N/2], columns below N/2)
   char* out2;              // MODE 2: [rows][N/2], columns from N/2 on
-  int32_t rows, N, n_splits, residual;
+  int32_t rows, N, residual;
 };
 
-// MODE 0: out = SiLU(sum of the gate partials) * (sum of the up partials). MODE 1: out = sum of the
-// partials (+ f). MODE 2: the N columns are two halves that go to two arrays, each half added to the
-// same residual f [rows][N/2]. Four columns per thread.
+// MODE 0: out = SiLU(gate sums) * up sums (two problems). MODE 1: out = sums (+ f). MODE 2: the N columns
+// are two halves that go to two arrays, each half added to the same residual f [rows][N/2]. Four columns
+// per thread.
 template <int MODE>
 __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-  const size_t quads = (size_t)p.rows * p.N / 4;
-  const size_t q = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (q >= quads) return;
-  const size_t plane = (size_t)p.rows * p.N;
-  f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < p.n_splits; ++s) {
-    a += *reinterpret_cast<const f32x4*>(p.part + (size_t)s * plane + 4 * q);
-    if (MODE == 0) b += *reinterpret_cast<const f32x4*>(p.part + ((size_t)p.n_splits + s) * plane + 4 * q);
-  }
+  const unsigned quads_per_row = (unsigned)p.N / 4;
+  const unsigned q = blockIdx.x * 256 + threadIdx.x;
+  if (q >= (unsigned)p.rows * quads_per_row) return;
+  const int row = (int)(q / quads_per_row), col = 4 * (int)(q - (unsigned)row * quads_per_row);
+  f32x4 a = p.part.sum(0, row, col);
   bf16x4 o;
   if (MODE == 0) {
+    const f32x4 b = p.part.sum((p.N + kSliceRows - 1) / kSliceRows, row, col);
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = (__bf16)(b[i] / (1.0f + __expf(-b[i])) * a[i]);   // a: up, b: gate
   } else if (MODE == 1) {
     if (p.residual) {
-      const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.f + 8 * q);
+      const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.f + 8 * (size_t)q);
 #pragma unroll
       for (int i = 0; i < 4; ++i) a[i] += (float)r[i];
     }
@@ -122,7 +148,6 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
     for (int i = 0; i < 4; ++i) o[i] = (__bf16)a[i];
   } else {
     const int half_n = p.N / 2;
-    const int row = (int)(4 * q / (size_t)p.N), col = (int)(4 * q - (size_t)row * p.N);
     const bool second = col >= half_n;
     const size_t at = ((size_t)row * half_n + (second ? col - half_n : col)) * 2;   // bytes
     const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.f + at);
@@ -131,7 +156,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
     *reinterpret_cast<bf16x4*>((second ? p.out2 : p.out) + at) = o;
     return;
   }
-  *reinterpret_cast<bf16x4*>(p.out + 8 * q) = o;
+  *reinterpret_cast<bf16x4*>(p.out + 8 * (size_t)q) = o;
 }
 
 // RMSNorm of one row per workgroup: out = x / sqrt(mean(x^2) + eps) * gain, fp32 arithmetic, one
@@ -176,24 +201,23 @@ __global__ __launch_bounds__(256) void rms_norm_kernel(const RmsNormParams p) {
 // values, as rms_norm_kernel would compute it from h. Every thread re-reads only what it wrote. 1024
 // threads: with the few rows of a draft step the row's loads must all be in flight at once.
 struct CombineNormParams {
-  const float* part;       // [split][rows][Hd]
+  Partials part;
   const char* residual;    // [rows][Hd] bf16
   const char* gain;        // [Hd] bf16
   char* h;                 // [rows][Hd] bf16
   char* out;               // [rows][Hd] bf16
-  int32_t rows, Hd, n_splits;
+  int32_t Hd;
   float eps;
 };
 __global__ __launch_bounds__(1024) void combine_norm_kernel(const CombineNormParams p) {
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
   __shared__ float wave_sum[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const size_t row_at = (size_t)blockIdx.x * p.Hd, plane = (size_t)p.rows * p.Hd;
+  const size_t row_at = (size_t)blockIdx.x * p.Hd;
   const int n_quads = p.Hd / 4;
   float ss = 0.f;
   for (int q = tid; q < n_quads; q += 1024) {
-    f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < p.n_splits; ++s) a += *reinterpret_cast<const f32x4*>(p.part + (size_t)s * plane + row_at + 4 * q);
+    const f32x4 a = p.part.sum(0, blockIdx.x, 4 * q);
     const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.residual + (row_at + 4 * q) * 2);
     bf16x4 o;
 #pragma unroll
@@ -229,12 +253,12 @@ __global__ __launch_bounds__(1024) void combine_norm_kernel(const CombineNormPar
 // fp64 (a position of some thousands times a frequency rounded to fp32 would already be off by
 // more than the result's bf16 rounding).
 struct QkvRopeParams {
-  const float* part;       // [split][rows][(Hq + 2 Hkv) D]
+  Partials part;
   const int32_t* positions;  // [rows]
   char* q;                 // [rows][Hq][D] bf16
   char* k;                 // [rows][Hkv][D] bf16
   char* v;                 // [rows][Hkv][D] bf16
-  int32_t rows, Hq, Hkv, D, n_splits;
+  int32_t rows, Hq, Hkv, D;
   double neg_log2_theta_2_over_d;   // -2 log2(theta) / D
 };
 __global__ __launch_bounds__(256) void qkv_rope_kernel(const QkvRopeParams p) {
@@ -246,14 +270,8 @@ __global__ __launch_bounds__(256) void qkv_rope_kernel(const QkvRopeParams p) {
   const int j = (int)(t % quads_per_head);
   const int head = (int)((t / quads_per_head) % heads);
   const int row = (int)(t / ((size_t)quads_per_head * heads));
-  const int N = heads * p.D, half = p.D / 2;
-  const size_t plane = (size_t)p.rows * N;
-  const size_t at = (size_t)row * N + (size_t)head * p.D + 4 * j;
-  f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < p.n_splits; ++s) {
-    a += *reinterpret_cast<const f32x4*>(p.part + (size_t)s * plane + at);
-    b += *reinterpret_cast<const f32x4*>(p.part + (size_t)s * plane + at + half);
-  }
+  const int half = p.D / 2;
+  const f32x4 a = p.part.sum(0, row, head * p.D + 4 * j), b = p.part.sum(0, row, head * p.D + 4 * j + half);
   char* dst;
   if (head < p.Hq) dst = p.q + ((size_t)row * p.Hq + head) * p.D * 2;
   else if (head < p.Hq + p.Hkv) dst = p.k + ((size_t)row * p.Hkv + (head - p.Hq)) * p.D * 2;
@@ -278,50 +296,64 @@ __global__ __launch_bounds__(256) void qkv_rope_kernel(const QkvRopeParams p) {
   *reinterpret_cast<bf16x4*>(dst + 8 * j + 2 * half) = ob;
 }
 
-// splits of a projector with n_slices slices and n_chunks k-chunks: as few as give a workgroup to
-// about two thirds of the compute units (measured at 4096 / 11008 and 4096 / 14336: 76 and 93 us
-// with this target, 83 and 95 us with one workgroup per unit, 84 and 97 us with two: a workgroup
-// that streams few chunks is mostly set-up, and every split adds a partial tile to write and read
-// back), never less than two chunks per split
-constexpr int kTargetWorkgroups = 180;
-void plan_splits(int n_slices, int n_chunks, int problems, int& n_splits, int& chunks_per_split) {
-  int want = (2 * kTargetWorkgroups + n_slices * problems) / (2 * n_slices * problems);   // rounded to nearest
-  if (want < 1) want = 1;
-  chunks_per_split = (n_chunks + want - 1) / want;
-  if (chunks_per_split < 2) chunks_per_split = n_chunks < 2 ? n_chunks : 2;
-  n_splits = (n_chunks + chunks_per_split - 1) / chunks_per_split;
+constexpr int kComputeUnits = 256;
+// The flat split of a projection of N columns (per problem) over K. One workgroup per compute unit, and
+// not less than two stages for each.
+Split plan_split(int N, int K, int problems, int rows) {
+  Split s{};
+  s.n_slices = problems * ((N + kSliceRows - 1) / kSliceRows);
+  s.stages = K / (rows <= 64 ? 256 : 128);
+  s.total = s.n_slices * s.stages;
+  s.n_wgs = s.total / 2 < kComputeUnits ? (s.total + 1) / 2 : kComputeUnits;
+  return s;
+}
+size_t partial_floats(const Split& s, int rows) { return (size_t)(s.n_slices + s.n_wgs) * rows * kSliceRows; }
+
+template <bool PACKED>
+void launch_partial(const PartialGemmParams& g, hipStream_t stream) {
+  const dim3 grid((unsigned)g.plan.n_wgs), block(64 * fspad_detail::kStreamWaves);
+  if (g.rows <= 16) hipLaunchKernelGGL((partial_gemm_kernel<1, PACKED>), grid, block, 0, stream, g);
+  else if (g.rows <= 32) hipLaunchKernelGGL((partial_gemm_kernel<2, PACKED>), grid, block, 0, stream, g);
+  else if (g.rows <= 48) hipLaunchKernelGGL((partial_gemm_kernel<3, PACKED>), grid, block, 0, stream, g);
+  else if (g.rows <= 64) hipLaunchKernelGGL((partial_gemm_kernel<4, PACKED>), grid, block, 0, stream, g);
+  else hipLaunchKernelGGL((partial_gemm_kernel<8, PACKED>), grid, block, 0, stream, g);
 }
 
-// measured at 4096 / 11008, 4 rows: Feature Sampler 78.4 us without the rotation, 72.1 / 72.4 / 71.5 us with
-// 1 / 3 / 5 stages between consecutive slices; decoder layer 164.5 against 158.5 / 158.3 / 158.8 us
-constexpr int kStagger = 3;
-void launch_partial(PartialGemmParams g, int problems, hipStream_t stream) {
-  g.stagger = kStagger;
-  const dim3 grid((unsigned)(g.n_slices * g.n_splits), (unsigned)problems);
-  if (g.packed) {
-    if (g.rows <= 16) hipLaunchKernelGGL((partial_gemm_kernel<1, 16, true>), grid, dim3(512), 0, stream, g);
-    else if (g.rows <= 32) hipLaunchKernelGGL((partial_gemm_kernel<2, 16, true>), grid, dim3(512), 0, stream, g);
-    else if (g.rows <= 64) hipLaunchKernelGGL((partial_gemm_kernel<4, 16, true>), grid, dim3(512), 0, stream, g);
-    else hipLaunchKernelGGL((partial_gemm_kernel<8, 8, true>), grid, dim3(512), 0, stream, g);
-    return;
-  }
-  if (g.rows <= 16) hipLaunchKernelGGL((partial_gemm_kernel<1, 16>), grid, dim3(512), 0, stream, g);
-  else if (g.rows <= 32) hipLaunchKernelGGL((partial_gemm_kernel<2, 16>), grid, dim3(512), 0, stream, g);
-  else if (g.rows <= 64) hipLaunchKernelGGL((partial_gemm_kernel<4, 16>), grid, dim3(512), 0, stream, g);
-  else hipLaunchKernelGGL((partial_gemm_kernel<8, 8>), grid, dim3(512), 0, stream, g);
+// The partial sums of one projection (or of two that share x's shape and w's), on the stream.
+fspad_status linear_partials(const void* x0, const void* x1, const void* w0, const void* w1, int rows, int N, int K,
+                             const Split& plan, float* part, bool packed, hipStream_t stream) {
+  PartialGemmParams g{};
+  g.x[0] = static_cast<const char*>(x0); g.x[1] = static_cast<const char*>(x1);
+  g.w[0] = static_cast<const char*>(w0); g.w[1] = static_cast<const char*>(w1);
+  g.part = part; g.rows = rows; g.N = N; g.K = K;
+  g.split = w1 ? plan.n_slices / 2 : plan.n_slices;
+  g.plan = plan;
+  if (packed) launch_partial<true>(g, stream);
+  else launch_partial<false>(g, stream);
+  return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
+}
+
+template <int MODE>
+fspad_status combine(const float* part, const Split& plan, const void* residual, void* out, void* out2, int rows, int N,
+                     hipStream_t stream) {
+  CombineParams c{};
+  c.part = Partials{part, plan, rows};
+  c.f = static_cast<const char*>(residual); c.out = static_cast<char*>(out);
+  c.out2 = static_cast<char*>(out2); c.rows = rows; c.N = N; c.residual = residual != nullptr;
+  const size_t quads = (size_t)rows * N / 4;
+  hipLaunchKernelGGL(combine_kernel<MODE>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, c);
+  return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
 }
 
 struct Plan {
-  int slices_up, splits_up, cps_up, slices_down, splits_down, cps_down;
+  Split up, down;
   size_t part_floats, s_bytes;
 };
 Plan make_plan(int rows, int Hd, int I) {
   Plan pl{};
-  pl.slices_up = (I + kSliceRows - 1) / kSliceRows;
-  plan_splits(pl.slices_up, Hd / kChunkK, 2, pl.splits_up, pl.cps_up);
-  pl.slices_down = (Hd + kSliceRows - 1) / kSliceRows;
-  plan_splits(pl.slices_down, I / kChunkK, 1, pl.splits_down, pl.cps_down);
-  const size_t up = (size_t)2 * pl.splits_up * rows * I, down = (size_t)pl.splits_down * rows * Hd;
+  pl.up = plan_split(I, Hd, 2, rows);
+  pl.down = plan_split(Hd, I, 1, rows);
+  const size_t up = partial_floats(pl.up, rows), down = partial_floats(pl.down, rows);
   pl.part_floats = up > down ? up : down;
   pl.s_bytes = ((size_t)rows * I * 2 + 255) & ~(size_t)255;
   return pl;
@@ -358,36 +390,13 @@ extern "C" fspad_status fspad_feature_sampler(int32_t rows, int32_t hidden_dim, 
   float* part = reinterpret_cast<float*>(s_buf + pl.s_bytes);
 
   // up and gate projectors, one launch
-  PartialGemmParams g{};
-  g.x[0] = static_cast<const char*>(f); g.x[1] = static_cast<const char*>(e);
-  g.w[0] = static_cast<const char*>(w_up); g.w[1] = static_cast<const char*>(w_gate);
-  g.part = part; g.rows = rows; g.N = intermediate_dim; g.K = hidden_dim;
-  g.n_slices = pl.slices_up; g.n_splits = pl.splits_up; g.chunks_per_split = pl.cps_up;
-  g.packed = packed;
-  launch_partial(g, 2, stream);
-  if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-  CombineParams c{};
-  c.part = part; c.f = nullptr; c.out = s_buf; c.rows = rows; c.N = intermediate_dim; c.n_splits = pl.splits_up;
-  {
-    const size_t quads = (size_t)rows * intermediate_dim / 4;
-    hipLaunchKernelGGL(combine_kernel<0>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, c);
-  }
-  if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-
+  fspad_status st;
+  if ((st = linear_partials(f, e, w_up, w_gate, rows, intermediate_dim, hidden_dim, pl.up, part, packed, stream)) != FSPAD_OK) return st;
+  if ((st = combine<0>(part, pl.up, nullptr, s_buf, nullptr, rows, intermediate_dim, stream)) != FSPAD_OK) return st;
   // down projector and residual
-  g.x[0] = s_buf; g.x[1] = nullptr; g.w[0] = static_cast<const char*>(w_down); g.w[1] = nullptr;
-  g.N = hidden_dim; g.K = intermediate_dim;
-  g.n_slices = pl.slices_down; g.n_splits = pl.splits_down; g.chunks_per_split = pl.cps_down;
-  launch_partial(g, 1, stream);
-  if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-  c.f = static_cast<const char*>(f); c.out = static_cast<char*>(eta); c.N = hidden_dim; c.n_splits = pl.splits_down;
-  c.residual = residual != 0;
-  {
-    const size_t quads = (size_t)rows * hidden_dim / 4;
-    hipLaunchKernelGGL(combine_kernel<1>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, c);
-  }
-  if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-  return FSPAD_OK;
+  if ((st = linear_partials(s_buf, nullptr, w_down, nullptr, rows, hidden_dim, intermediate_dim, pl.down, part, packed, stream)) != FSPAD_OK)
+    return st;
+  return combine<1>(part, pl.down, residual ? f : nullptr, eta, nullptr, rows, hidden_dim, stream);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -396,19 +405,9 @@ namespace {
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-struct Stage {
-  int slices, splits, cps;
-};
-Stage plan_stage(int N, int K, int problems) {
-  Stage st{};
-  st.slices = (N + kSliceRows - 1) / kSliceRows;
-  plan_splits(st.slices, K / kChunkK, problems, st.splits, st.cps);
-  return st;
-}
-
 struct LayerPlan {
   int rows, Hd, I, qkv_n, attn_n;
-  Stage qkv, o, up, down;
+  Split qkv, o, up, down;
   size_t xn_bytes, q_bytes, a_bytes, h_bytes, s_bytes, part_bytes, attn_ws_bytes;
 };
 
@@ -435,48 +434,20 @@ LayerPlan make_layer_plan(const fspad_draft_layer_desc* d, int32_t max_kv_len) {
   pl.I = d->intermediate_dim;
   pl.attn_n = a.n_q_heads * a.head_dim;
   pl.qkv_n = (a.n_q_heads + 2 * a.n_kv_heads) * a.head_dim;
-  pl.qkv = plan_stage(pl.qkv_n, pl.Hd, 1);
-  pl.o = plan_stage(pl.Hd, pl.attn_n, 1);
-  pl.up = plan_stage(pl.I, pl.Hd, 2);
-  pl.down = plan_stage(2 * pl.Hd, pl.I, 1);
+  pl.qkv = plan_split(pl.qkv_n, pl.Hd, 1, pl.rows);
+  pl.o = plan_split(pl.Hd, pl.attn_n, 1, pl.rows);
+  pl.up = plan_split(pl.I, pl.Hd, 2, pl.rows);
+  pl.down = plan_split(2 * pl.Hd, pl.I, 1, pl.rows);
   pl.xn_bytes = align256((size_t)pl.rows * pl.Hd * 2);
   pl.q_bytes = align256((size_t)pl.rows * pl.attn_n * 2);
   pl.a_bytes = pl.q_bytes;
   pl.h_bytes = pl.xn_bytes;
   pl.s_bytes = align256((size_t)pl.rows * pl.I * 2);
-  size_t part = (size_t)pl.qkv.splits * pl.rows * pl.qkv_n;
-  const size_t part_o = (size_t)pl.o.splits * pl.rows * pl.Hd;
-  const size_t part_up = (size_t)2 * pl.up.splits * pl.rows * pl.I;
-  const size_t part_down = (size_t)pl.down.splits * pl.rows * 2 * pl.Hd;
-  if (part_o > part) part = part_o;
-  if (part_up > part) part = part_up;
-  if (part_down > part) part = part_down;
+  size_t part = 0;
+  for (const Split* sp : {&pl.qkv, &pl.o, &pl.up, &pl.down}) part = partial_floats(*sp, pl.rows) > part ? partial_floats(*sp, pl.rows) : part;
   pl.part_bytes = align256(part * 4);
   pl.attn_ws_bytes = align256(fspad_tree_attn_workspace_bytes(&d->attn, max_kv_len));
   return pl;
-}
-
-fspad_status linear_partials(const void* x0, const void* x1, const void* w0, const void* w1, int problems, int rows, int N,
-                             int K, const Stage& st, float* part, bool packed, hipStream_t stream) {
-  PartialGemmParams g{};
-  g.x[0] = static_cast<const char*>(x0); g.x[1] = static_cast<const char*>(x1);
-  g.w[0] = static_cast<const char*>(w0); g.w[1] = static_cast<const char*>(w1);
-  g.part = part; g.rows = rows; g.N = N; g.K = K;
-  g.n_slices = st.slices; g.n_splits = st.splits; g.chunks_per_split = st.cps;
-  g.packed = packed;
-  launch_partial(g, problems, stream);
-  return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
-}
-
-template <int MODE>
-fspad_status combine(const float* part, const void* residual, void* out, void* out2, int rows, int N, int splits,
-                     hipStream_t stream) {
-  CombineParams c{};
-  c.part = part; c.f = static_cast<const char*>(residual); c.out = static_cast<char*>(out);
-  c.out2 = static_cast<char*>(out2); c.rows = rows; c.N = N; c.n_splits = splits; c.residual = residual != nullptr;
-  const size_t quads = (size_t)rows * N / 4;
-  hipLaunchKernelGGL(combine_kernel<MODE>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, c);
-  return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
 }
 
 fspad_status rms_norm(const void* x, const void* gain, void* out, int rows, int Hd, float eps, hipStream_t stream) {
@@ -534,12 +505,12 @@ extern "C" fspad_status fspad_draft_layer(const fspad_draft_layer_desc* desc, co
   fspad_status st;
   // q, k, v = rotary(W_qkv rmsnorm(eta))
   if ((st = rms_norm(eta, w->gain_attn, xn, pl.rows, pl.Hd, desc->rms_eps, stream)) != FSPAD_OK) return st;
-  if ((st = linear_partials(xn, nullptr, w->w_qkv, nullptr, 1, pl.rows, pl.qkv_n, pl.Hd, pl.qkv, part, packed, stream)) != FSPAD_OK)
+  if ((st = linear_partials(xn, nullptr, w->w_qkv, nullptr, pl.rows, pl.qkv_n, pl.Hd, pl.qkv, part, packed, stream)) != FSPAD_OK)
     return st;
   {
     QkvRopeParams r{};
-    r.part = part; r.positions = positions; r.q = q; r.k = static_cast<char*>(k_tree); r.v = static_cast<char*>(v_tree);
-    r.rows = pl.rows; r.Hq = a.n_q_heads; r.Hkv = a.n_kv_heads; r.D = a.head_dim; r.n_splits = pl.qkv.splits;
+    r.part = Partials{part, pl.qkv, pl.rows}; r.positions = positions; r.q = q; r.k = static_cast<char*>(k_tree); r.v = static_cast<char*>(v_tree);
+    r.rows = pl.rows; r.Hq = a.n_q_heads; r.Hkv = a.n_kv_heads; r.D = a.head_dim;
     r.neg_log2_theta_2_over_d = -2.0 * log2((double)desc->rope_theta) / (double)a.head_dim;
     const size_t threads = (size_t)pl.rows * (a.n_q_heads + 2 * a.n_kv_heads) * (a.head_dim / 8);
     hipLaunchKernelGGL(qkv_rope_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, r);
@@ -550,21 +521,21 @@ extern "C" fspad_status fspad_draft_layer(const fspad_draft_layer_desc* desc, co
                        pl.attn_ws_bytes, hip_stream);
   if (st != FSPAD_OK) return st;
   // h = eta + W_o attn
-  if ((st = linear_partials(attn, nullptr, w->w_o, nullptr, 1, pl.rows, pl.Hd, pl.attn_n, pl.o, part, packed, stream)) != FSPAD_OK)
+  if ((st = linear_partials(attn, nullptr, w->w_o, nullptr, pl.rows, pl.Hd, pl.attn_n, pl.o, part, packed, stream)) != FSPAD_OK)
     return st;
   // and its normalised form for the MLP (whose doubled down projection adds both halves to h)
   {
     CombineNormParams c{};
-    c.part = part; c.residual = static_cast<const char*>(eta); c.gain = static_cast<const char*>(w->gain_mlp);
-    c.h = h; c.out = xn; c.rows = pl.rows; c.Hd = pl.Hd; c.n_splits = pl.o.splits; c.eps = desc->rms_eps;
+    c.part = Partials{part, pl.o, pl.rows}; c.residual = static_cast<const char*>(eta); c.gain = static_cast<const char*>(w->gain_mlp);
+    c.h = h; c.out = xn; c.Hd = pl.Hd; c.eps = desc->rms_eps;
     hipLaunchKernelGGL(combine_norm_kernel, dim3((unsigned)pl.rows), dim3(1024), 0, stream, c);
     if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   }
-  if ((st = linear_partials(xn, xn, w->w_up, w->w_gate, 2, pl.rows, pl.I, pl.Hd, pl.up, part, packed, stream)) != FSPAD_OK) return st;
-  if ((st = combine<0>(part, nullptr, s, nullptr, pl.rows, pl.I, pl.up.splits, stream)) != FSPAD_OK) return st;
-  if ((st = linear_partials(s, nullptr, w->w_down, nullptr, 1, pl.rows, 2 * pl.Hd, pl.I, pl.down, part, packed, stream)) != FSPAD_OK)
+  if ((st = linear_partials(xn, xn, w->w_up, w->w_gate, pl.rows, pl.I, pl.Hd, pl.up, part, packed, stream)) != FSPAD_OK) return st;
+  if ((st = combine<0>(part, pl.up, nullptr, s, nullptr, pl.rows, pl.I, stream)) != FSPAD_OK) return st;
+  if ((st = linear_partials(s, nullptr, w->w_down, nullptr, pl.rows, 2 * pl.Hd, pl.I, pl.down, part, packed, stream)) != FSPAD_OK)
     return st;
-  return combine<2>(part, h, f_tilde, f, pl.rows, 2 * pl.Hd, pl.down.splits, stream);
+  return combine<2>(part, pl.down, h, f_tilde, f, pl.rows, 2 * pl.Hd, stream);
 }
 
 // ------------------------------------------------------------------------------------------------

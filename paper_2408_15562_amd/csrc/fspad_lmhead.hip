@@ -28,6 +28,7 @@ namespace {
 using fspad_detail::bf16x8;
 using fspad_detail::f32x4;
 using fspad_detail::StreamGemm;
+static_assert(fspad_detail::kSliceRows == 128, "tokens per slice");
 typedef const __attribute__((address_space(1))) void* GlobalPtr;
 typedef __attribute__((address_space(3))) void* LdsPtr;
 
@@ -57,6 +58,164 @@ __device__ __forceinline__ void take_better(float& v, int& i, float ov, int oi) 
   if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
 }
 
+// (value, token) in one word for the trip through LDS
+__device__ __forceinline__ unsigned long long pack_best(float v, int i) {
+  return ((unsigned long long)(unsigned)i << 32) | __float_as_uint(v);
+}
+
+// The LM head over the rows of one pass (blockIdx.y): a workgroup takes a contiguous run of 128-token
+// slices, whole ones, and streams their weights without a pause -- the copies of the next slice are in
+// flight while the statistics of the last one are formed. It starts `c0` stages into every slice and wraps
+// around (spread_phase).
+// MODE 0: per slice and row (max, first argmax) for the greedy walk. MODE 1: per slice and row
+// (max, sum of exponentials) and the logits of the draft tokens, for the sampling walk.
+template <int MT, int MODE, bool PACKED>
+__global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_kernel(const LmHeadParams p) {
+  using namespace fspad_detail;
+  typedef StreamGemm<MT, PACKED> G;
+  __shared__ __attribute__((aligned(1024))) char lds[G::kLdsBytes];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, g = lane >> 4;
+  const int w = blockIdx.x, row0 = blockIdx.y * p.rows_per_pass;
+  const int s0 = (int)((unsigned)w * (unsigned)p.n_slices / gridDim.x), s1 = (int)((unsigned)(w + 1) * (unsigned)p.n_slices / gridDim.x);
+  const int C = p.K / G::kStageK;
+  const int c0 = (int)fspad_detail::spread_phase(w, C);
+
+  // sampling: the row of thread tid's node's parent and the node's token (-1: none), for nodes below 512
+  int my_row = -1, my_tok = -1;
+  auto node_of = [&](int cnode, int& r, int& tok) {
+    const int b = cnode / p.Nmax, i = cnode - b * p.Nmax;
+    r = -1;
+    if (i == 0 || i >= p.n_nodes[b]) return;
+    const int par = p.parent[cnode];
+    tok = p.draft_tokens[cnode];
+    if (par >= 0 && par < i && tok >= 0 && tok < p.V) r = b * p.Nmax + par - row0;
+  };
+  if (MODE == 1 && tid < p.M) node_of(tid, my_row, my_tok);
+
+  typename G::Source src;
+  src.x[0] = src.x[1] = p.hidden; src.w[0] = src.w[1] = p.weights; src.split = 0x7fffffff;
+  src.n_xrows = p.M; src.n_wrows = p.V; src.row0 = row0; src.K = p.K;
+  G::run(lds, src, s0, c0, c0, 0, (s1 - s0) * C, [&](int slice, const f32x4 (&acc)[MT], unsigned spare) {
+    const int slice0 = slice * kVocabPerWg;
+    if constexpr (MODE == 1) {
+      // The 16*MT x 128 logits go to LDS as fp32, row by row, as many tiles at a time as fit
+      // (16-byte chunk c of row r at chunk c ^ (r & 15): sixteen rows written at once hit different banks).
+      constexpr int kTiles = G::kXStageBytes / 8192 < MT ? G::kXStageBytes / 8192 : MT;
+#pragma unroll
+      for (int t0 = 0; t0 < MT; t0 += kTiles) {
+        lds_barrier();
+#pragma unroll
+        for (int t = 0; t < kTiles; ++t)
+          lds_write16(spare + (unsigned)(t * 16 + n) * 512u + (((unsigned)(4 * wave + g) ^ (unsigned)n) << 4), acc[t0 + t]);
+        lds_barrier();
+        // slice statistics: sixteen lanes per row, eight logits each
+        const int sub = lane & 15;
+        for (int r = tid >> 4; r < kTiles * 16; r += 32) {   // uniform per 16 lanes
+          f32x4 v4[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) lds_read16(v4[h], spare + (unsigned)r * 512u + (((unsigned)(sub + 16 * h) ^ (unsigned)(r & 15)) << 4));
+          wait_lds<0>();
+          settled(v4[0]);
+          settled(v4[1]);
+          float x[8];
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              x[4 * h + i] = (slice0 + 4 * (sub + 16 * h) + i < p.V && v4[h][i] == v4[h][i]) ? v4[h][i] : -INFINITY;
+          float m = x[0];
+#pragma unroll
+          for (int i = 1; i < 8; ++i) m = fmaxf(m, x[i]);
+#pragma unroll
+          for (int d = 1; d < 16; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
+          float half[2] = {0.f, 0.f};   // this lane's share of tiles sub/4 and 4 + sub/4 (16 tokens each)
+          if (m > -INFINITY) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) half[i >> 2] += __builtin_amdgcn_exp2f((x[i] - m) * p.inv_t_log2e);
+          }
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            half[h] += __shfl_xor(half[h], 1);
+            half[h] += __shfl_xor(half[h], 2);
+          }
+          double dsum = (sub & 3) == 0 ? (double)half[0] + (double)half[1] : 0.0;
+#pragma unroll
+          for (int d = 4; d < 16; d <<= 1) dsum += __shfl_xor(dsum, d);
+          const int row = row0 + t0 * 16 + r;
+          if (row < p.M) {
+            const size_t slot = (size_t)row * p.n_slices + slice;
+            if ((sub & 3) == 0) {
+              p.tile_sum[slot * 8 + (sub >> 2)] = half[0];
+              p.tile_sum[slot * 8 + 4 + (sub >> 2)] = half[1];
+            }
+            if (sub == 0) {
+              p.part_max[slot] = m;
+              p.part_sum[slot] = dsum;
+            }
+          }
+        }
+        // the logits the walk will test: a node's token under the row of its parent
+        auto set_aside = [&](int cnode, int r, int tok) {
+          r -= t0 * 16;
+          const int vl = tok - slice0;
+          if (r < 0 || r >= kTiles * 16 || vl < 0 || vl >= kVocabPerWg) return;
+          float x;
+          lds_read4(x, spare + (unsigned)r * 512u + ((((unsigned)(vl >> 2) ^ (unsigned)(r & 15)) << 4) | (unsigned)(vl & 3) << 2));
+          wait_lds<0>();
+          settled(x);
+          p.node_logit[cnode] = x;
+        };
+        set_aside(tid, my_row, my_tok);
+        for (int cnode = tid + 64 * kStreamWaves; cnode < p.M; cnode += 64 * kStreamWaves) {
+          int r, tok = -1;
+          node_of(cnode, r, tok);
+          set_aside(cnode, r, tok);
+        }
+      }
+    } else {
+      // argmax over this wavefront's sixteen tokens for each row (lane column n): ascending token order
+      // inside the lane, then across the four lane groups, then across the wavefronts through LDS
+      lds_barrier();
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        float best = -INFINITY;
+        int idx = kNone;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int v = slice0 + 16 * wave + 4 * g + i;
+          const float x = acc[t][i];
+          if (v < p.V && x > best) { best = x; idx = v; }
+        }
+#pragma unroll
+        for (int d = 16; d < 64; d <<= 1) {
+          const float ov = __shfl_xor(best, d);
+          const int oi = __shfl_xor(idx, d);
+          take_better(best, idx, ov, oi);
+        }
+        if (g == 0) lds_write8(spare + (unsigned)(wave * MT * 16 + t * 16 + n) * 8u, pack_best(best, idx));
+      }
+      lds_barrier();
+      if (tid < MT * 16 && row0 + tid < p.M) {
+        unsigned long long part[kStreamWaves];
+#pragma unroll
+        for (int w8 = 0; w8 < kStreamWaves; ++w8) lds_read8(part[w8], spare + (unsigned)(w8 * MT * 16 + tid) * 8u);
+        wait_lds<0>();
+        float best = -INFINITY;
+        int idx = kNone;
+#pragma unroll
+        for (int w8 = 0; w8 < kStreamWaves; ++w8) {
+          settled(part[w8]);
+          take_better(best, idx, __uint_as_float((unsigned)part[w8]), (int)(part[w8] >> 32));
+        }
+        const size_t slot = (size_t)slice * p.M + row0 + tid;
+        p.part_max[slot] = best;
+        p.part_idx[slot] = idx;
+      }
+    }
+  });
+}
+
 // The LM head: MT, SPS, kRing, WAVES, VT as above; WAVES x VT = 8, i.e. 128 vocabulary rows per
 // workgroup: eight wavefronts of one weight tile, two per SIMD, in every shape in use (four
 // wavefronts of two tiles, one per SIMD with the whole register file, halve the LDS reads per
@@ -66,7 +225,7 @@ __device__ __forceinline__ void take_better(float& v, int& i, float ov, int oi) 
 template <int MT, int SPS, int kRing, int WAVES, int VT, int MODE, bool PACKED>
 __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 2 : 1)) void lm_head_argmax_kernel(const LmHeadParams p) {
   static_assert(WAVES * VT * 16 == kVocabPerWg, "workgroup shape");
-  typedef StreamGemm<MT, SPS, kRing, WAVES, VT, PACKED> G;
+  typedef fspad_detail::StreamGemmRegs<MT, SPS, kRing, WAVES, VT, PACKED> G;
   constexpr int kStageBytes = G::kStageBytes;
   __shared__ __attribute__((aligned(16))) char xs[2 * kStageBytes];
   __shared__ float red_val[WAVES][MT * 16];
@@ -608,6 +767,7 @@ __global__ __launch_bounds__(kWalkThreads) void lm_head_sample_walk_kernel(const
   }
 }
 
+constexpr int kComputeUnits = 256;
 int n_slices_of(int32_t V) { return (V + kVocabPerWg - 1) / kVocabPerWg; }
 // Workgroup s starts its k loop (s * kStagger) stages in and wraps around, so that the workgroups
 // running at the same time read different parts of their rows: with every workgroup at the same k
@@ -645,16 +805,19 @@ fspad_status launch_lm_head(LmHeadParams& g, int32_t hidden_dim, hipStream_t str
   const int pass_rows = g.n_passes > 1 ? (g.M + g.n_passes - 1) / g.n_passes : g.M;   // passes of equal size
   if (g.n_passes > 1) g.rows_per_pass = (pass_rows + 15) / 16 * 16;
   if ((int64_t)g.n_slices * g.n_passes > 0x7fffffff) return FSPAD_ERR_SHAPE;
-  // (a stage of the small shapes is 512 k: a hidden size that is not a multiple of it has a partial
-  // last stage, which the rotation does not handle)
-  g.stagger = (g.rows_per_pass > 64 || hidden_dim % 512 == 0) ? kStagger : 0;
-  const dim3 grid((unsigned)(g.n_slices * g.n_passes));
+  g.stagger = kStagger;
   const int r = g.rows_per_pass;
-  if (r <= 16) hipLaunchKernelGGL((lm_head_argmax_kernel<1, 16, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
-  else if (r <= 32) hipLaunchKernelGGL((lm_head_argmax_kernel<2, 16, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
-  else if (r <= 64) hipLaunchKernelGGL((lm_head_argmax_kernel<4, 16, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
-  else if (r <= 128) hipLaunchKernelGGL((lm_head_argmax_kernel<8, 8, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
-  else if (r <= 192) hipLaunchKernelGGL((lm_head_argmax_kernel<12, 4, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
+  if (r <= 128) {
+    const dim3 grid((unsigned)(g.n_slices < kComputeUnits ? g.n_slices : kComputeUnits), (unsigned)g.n_passes), block(512);
+    if (r <= 16) hipLaunchKernelGGL((lm_head_kernel<1, MODE, PACKED>), grid, block, 0, stream, g);
+    else if (r <= 32) hipLaunchKernelGGL((lm_head_kernel<2, MODE, PACKED>), grid, block, 0, stream, g);
+    else if (r <= 48) hipLaunchKernelGGL((lm_head_kernel<3, MODE, PACKED>), grid, block, 0, stream, g);
+    else if (r <= 64) hipLaunchKernelGGL((lm_head_kernel<4, MODE, PACKED>), grid, block, 0, stream, g);
+    else hipLaunchKernelGGL((lm_head_kernel<8, MODE, PACKED>), grid, block, 0, stream, g);
+    return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
+  }
+  const dim3 grid((unsigned)(g.n_slices * g.n_passes));
+  if (r <= 192) hipLaunchKernelGGL((lm_head_argmax_kernel<12, 4, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
   else hipLaunchKernelGGL((lm_head_argmax_kernel<16, 4, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
   return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
 }

@@ -45,6 +45,14 @@ def test_shapes(rows, Hd, I):
     _check(100 + rows + I, rows, Hd, I)
 
 
+@pytest.mark.parametrize("rows,Hd,I", [(48, 2048, 4352), (33, 512, 16640), (7, 2304, 4096), (70, 1024, 4352), (3, 256, 2816)])
+def test_ranges_of_the_flat_split(rows, Hd, I):
+    """Enough stages for all 256 workgroups and not (a count that is no multiple of eight), ranges that
+    begin and end inside a slice, cover several slices or a part of one; three row tiles, and the
+    half-length stages of more than 64 rows."""
+    _check(500 + rows + I, rows, Hd, I)
+
+
 def test_without_residual_and_repeatable():
     out = _check(7, 24, 512, 1024, residual=False)
     again = _check(7, 24, 512, 1024, residual=False)

@@ -32,6 +32,18 @@ def test_shapes(H, B, N, Hd, V):
     H.assert_lm_head_equal(case.gpu(), case.cpu())
 
 
+@pytest.mark.parametrize("B,N,Hd,V", [(1, 40, 512, 33000), (1, 13, 256, 66001), (2, 60, 256, 35000), (2, 46, 512, 32897)])
+def test_several_slices_per_workgroup(H, B, N, Hd, V):
+    """More than 256 slices of 128 tokens: a workgroup walks two or more of them in one stream, greedy and
+    sampling, with one, three, six and eight row tiles."""
+    case = H.LmHeadCase(6000 + N + V, B, N, Hd, V, noise=0.5)
+    H.assert_lm_head_equal(case.gpu(), case.cpu(), require_decided=False)
+    compared = 0
+    for seed in range(1, 6):
+        compared += H.assert_lm_head_sample_equal(case.gpu_sample(1.0, seed), case.cpu_sample(1.0, seed), min_compared=0.0)
+    assert compared >= 1
+
+
 def test_ragged_trees(H):
     case = H.LmHeadCase(77, 4, 40, 512, 5000, n_nodes=[40, 1, 17, 33])
     gpu, cpu = case.gpu(), case.cpu()
