@@ -14,11 +14,12 @@
 // (few rows: MHA) and merge through LDS, or take different row slabs of the same
 // keys (GQA). A second, tiny kernel merges the split-KV partials.
 //
-// fp32 path: plain VALU kernel, one wavefront per query row, used for the small
-// fp32 parity configuration.
+// fp32 path: plain VALU kernel, used for the small fp32 parity configuration.
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "fspad.h"
 
@@ -1118,81 +1119,133 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32 path: one wavefront per (sequence, query head, node); lanes over keys for the scores,
-// lanes over dims for the weighted sum. No matrix cores: fp32 inputs need fp32 products for
-// the 1e-5 tolerance of the small parity configuration.
-template <int D>
-__global__ __launch_bounds__(256) void tree_attn_f32_kernel(const AttnParams p) {
-  constexpr int DPL = D / 64;  // dims per lane in the PV phase
-  __shared__ float q_sh[4][D];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int h = blockIdx.x, b = blockIdx.z;
+// fp32 path: vector arithmetic (fp32 inputs need fp32 products and sums for the 1e-5 tolerance of the
+// small parity configuration). What bounds it is latency: a call of this size is one or two trips to
+// memory and what hangs behind them. A workgroup of eight wavefronts takes QN nodes of one query head;
+// the wavefronts take tiles of 8 * 64 / LPK keys in turn, D/4 = LPK lanes per key with four dims each, so
+// that a K or V row is one contiguous request and all requests of a tile are in flight together. The dot
+// product of a key is a sum over its LPK lanes, which leaves the score -- and so the weight -- in exactly the
+// lanes that hold the key's V entries: no exchange between the two products. The wavefronts' (max, sum,
+// output) meet in LDS once, at the end. 8 heads, D = 64, 256 keys, 26 nodes: 6.1 us (one wavefront per node, a
+// lane per key, the weights exchanged key by key for the second product: 60.6 us).
+constexpr int kF32Waves = 8;
+constexpr int kF32Loads = 8;   // K (and V) rows a lane has in flight per tile
+
+// sum over the LPK lanes that share a key, in every one of them
+template <int LPK>
+__device__ __forceinline__ float key_sum(float v) {
+  auto rotated = [](float x, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v += rotated(v, std::integral_constant<int, 0x128>{});   // row_ror 8, 4, 2, 1
+  v += rotated(v, std::integral_constant<int, 0x124>{});
+  v += rotated(v, std::integral_constant<int, 0x122>{});
+  v += rotated(v, std::integral_constant<int, 0x121>{});
+  if (LPK == 32) v += __shfl_xor(v, 16);
+  return v;
+}
+
+template <int D, int QN>
+__global__ __launch_bounds__(64 * kF32Waves) void tree_attn_f32_kernel(const AttnParams p) {
+  constexpr int LPK = D / 4, KPL = 64 / LPK;       // lanes per key, keys per load instruction
+  constexpr int kTile = kF32Loads * KPL;           // keys per wavefront and turn
+  __shared__ __attribute__((aligned(16))) float sh_o[kF32Waves][QN][D];
+  __shared__ float sh_m[kF32Waves][QN], sh_l[kF32Waves][QN];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = blockIdx.x, b = blockIdx.z, node0 = blockIdx.y * QN;
   const int g = h / p.G;
-  const int n = p.n_nodes[b], L = p.kv_len[b];
+  const int n = p.n_nodes[b], L = p.kv_len[b], total = L + n;
+  const int64_t row0 = ((int64_t)b * p.Nmax + node0) * p.Hq + h;   // (b, node0, h); the next node is Hq rows further
+  float* const out0 = reinterpret_cast<float*>(p.out) + row0 * D;
+  const int64_t node_stride = (int64_t)p.Hq * D;
+  if (node0 >= n) {
+    for (int i = tid; i < QN * D; i += 64 * kF32Waves)
+      if (node0 + i / D < p.Nmax) out0[(i / D) * node_stride + i % D] = 0.f;
+    return;
+  }
+  const int sub = lane & (LPK - 1), grp = lane / LPK;
   const float* kc = reinterpret_cast<const float*>(p.k_cache) + b * p.stride_batch + g * p.stride_head;
   const float* vc = reinterpret_cast<const float*>(p.v_cache) + b * p.stride_batch + g * p.stride_head;
   const int64_t tree_stride = (int64_t)p.Hkv * D;
-  const float* ktr = reinterpret_cast<const float*>(p.k_tree) + ((int64_t)b * p.Nmax * p.Hkv + g) * D;
-  const float* vtr = reinterpret_cast<const float*>(p.v_tree) + ((int64_t)b * p.Nmax * p.Hkv + g) * D;
+  const int64_t tree0 = ((int64_t)b * p.Nmax * p.Hkv + g) * D;
+  const float* ktr = reinterpret_cast<const float*>(p.k_tree) + tree0;
+  const float* vtr = reinterpret_cast<const float*>(p.v_tree) + tree0;
 
-  for (int node = blockIdx.y * 4 + wave; node < p.Nmax; node += gridDim.y * 4) {
-    const int64_t row = ((int64_t)b * p.Nmax + node) * p.Hq + h;
-    float* out = reinterpret_cast<float*>(p.out) + row * D;
-    if (node >= n) {
-      for (int d = lane; d < D; d += 64) out[d] = 0.f;
-      continue;
+  f32x4 q[QN], o[QN];
+  uint64_t word[QN];
+  float m[QN], l[QN];
+#pragma unroll
+  for (int t = 0; t < QN; ++t) {
+    const int node = min(node0 + t, n - 1);
+    q[t] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.q) + row0 * D + (node - node0) * node_stride + 4 * sub);
+    word[t] = p.anc_mask[b * p.Nmax + node];
+    o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m[t] = -INFINITY;
+    l[t] = 0.f;
+  }
+  for (int base = wave * kTile; base < total; base += kF32Waves * kTile) {
+    f32x4 k[kF32Loads], v[kF32Loads];
+#pragma unroll
+    for (int i = 0; i < kF32Loads; ++i) {   // (keys past the end re-read the last one; they are masked below)
+      const int j = min(base + i * KPL + grp, total - 1);
+      const bool prefix = j < L;
+      const int64_t at = prefix ? j * p.stride_token : (j - L) * tree_stride;
+      k[i] = *reinterpret_cast<const f32x4*>((prefix ? kc : ktr) + at + 4 * sub);
+      v[i] = *reinterpret_cast<const f32x4*>((prefix ? vc : vtr) + at + 4 * sub);
     }
-    const float* qrow = reinterpret_cast<const float*>(p.q) + row * D;
-    for (int d = lane; d < D; d += 64) q_sh[wave][d] = qrow[d];
-    __builtin_amdgcn_wave_barrier();
-    const uint64_t word = p.anc_mask[b * p.Nmax + node];
-    float m = -INFINITY, l = 0.f;
-    float acc[DPL];
 #pragma unroll
-    for (int e = 0; e < DPL; ++e) acc[e] = 0.f;
-    const int total = L + n;
-    for (int base = 0; base < total; base += 64) {
-      const int j = base + lane;
-      float s = -INFINITY;
-      const float* krow = nullptr;
-      if (j < L) krow = kc + (int64_t)j * p.stride_token;
-      else if (j < total && ((word >> (j - L)) & 1ull)) krow = ktr + (int64_t)(j - L) * tree_stride;
-      if (krow) {
-        float dot = 0.f;
-        for (int d = 0; d < D; d += 4) {
-          const f32x4 kv = *reinterpret_cast<const f32x4*>(krow + d);
-          dot = fmaf(q_sh[wave][d], kv[0], dot);
-          dot = fmaf(q_sh[wave][d + 1], kv[1], dot);
-          dot = fmaf(q_sh[wave][d + 2], kv[2], dot);
-          dot = fmaf(q_sh[wave][d + 3], kv[3], dot);
-        }
-        s = dot * p.scale;
+    for (int t = 0; t < QN; ++t) {
+      float s[kF32Loads], mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < kF32Loads; ++i) {
+        const float dot = key_sum<LPK>(fmaf(q[t][3], k[i][3], fmaf(q[t][2], k[i][2], fmaf(q[t][1], k[i][1], q[t][0] * k[i][0]))));
+        const int j = base + i * KPL + grp;
+        const bool seen = j < L || (j < total && ((word[t] >> (j - L)) & 1ull));
+        s[i] = seen ? dot * p.scale : -INFINITY;
+        mx = fmaxf(mx, s[i]);
       }
-      float mx = s;
-      for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-      const float mnew = fmaxf(m, mx);   // finite from the first tile on: key 0 is always visible
-      const float alpha = expf(m - mnew);
-      const float pj = expf(s - mnew);
-      float psum = pj;
-      for (int off = 32; off > 0; off >>= 1) psum += __shfl_xor(psum, off);
-      l = l * alpha + psum;
-      m = mnew;
 #pragma unroll
-      for (int e = 0; e < DPL; ++e) acc[e] *= alpha;
-      const int cnt = min(64, total - base);
-      for (int jj = 0; jj < cnt; ++jj) {
-        const float pw = __shfl(pj, jj);
-        if (pw == 0.f) continue;  // masked (wavefront-uniform)
-        const int key = base + jj;
-        const float* vrow = key < L ? vc + (int64_t)key * p.stride_token : vtr + (int64_t)(key - L) * tree_stride;
+      for (int off = LPK; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+      const float mnew = fmaxf(m[t], mx);
+      // (no key of this wavefront's visible so far: nothing to add, and no -inf minus -inf)
+      const float alpha = m[t] > -INFINITY ? expf(m[t] - mnew) : 0.f;
+      l[t] *= alpha;
+      o[t] *= alpha;
+      m[t] = mnew;
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) acc[e] = fmaf(pw, vrow[lane + 64 * e], acc[e]);
+      for (int i = 0; i < kF32Loads; ++i) {
+        const float w = s[i] == -INFINITY ? 0.f : expf(s[i] - mnew);
+        l[t] += w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[t][e] = w == 0.f ? o[t][e] : fmaf(w, v[i][e], o[t][e]);   // a masked V row may hold anything
       }
     }
-    const float inv = 1.0f / l;
+  }
 #pragma unroll
-    for (int e = 0; e < DPL; ++e) out[lane + 64 * e] = acc[e] * inv;
-    __builtin_amdgcn_wave_barrier();
+  for (int t = 0; t < QN; ++t) {
+#pragma unroll
+    for (int off = LPK; off < 64; off <<= 1) {
+      l[t] += __shfl_xor(l[t], off);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[t][e] += __shfl_xor(o[t][e], off);
+    }
+    if (grp == 0) *reinterpret_cast<f32x4*>(&sh_o[wave][t][4 * sub]) = o[t];
+    if (lane == 0) { sh_m[wave][t] = m[t]; sh_l[wave][t] = l[t]; }
+  }
+  __syncthreads();
+  for (int i = tid; i < QN * D; i += 64 * kF32Waves) {
+    const int t = i / D, d = i % D, node = node0 + t;
+    if (node >= p.Nmax) break;
+    float M = sh_m[0][t], num = 0.f, den = 0.f;
+#pragma unroll
+    for (int w = 1; w < kF32Waves; ++w) M = fmaxf(M, sh_m[w][t]);
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {   // in wavefront order: deterministic
+      const float a = sh_m[w][t] > -INFINITY ? expf(sh_m[w][t] - M) : 0.f;
+      den += a * sh_l[w][t];
+      num += a * sh_o[w][t][d];
+    }
+    out0[t * node_stride + d] = node < n ? num / den : 0.f;
   }
 }
 
@@ -1317,6 +1370,18 @@ void launch_bf16(const Plan& pl, const AttnParams& prm, hipStream_t stream) {
     case 3: hipLaunchKernelGGL((tree_attn_bf16_kernel<3, D>), grid, dim3(256), 0, stream, prm); break;
     default: hipLaunchKernelGGL((tree_attn_bf16_kernel<4, D>), grid, dim3(256), 0, stream, prm); break;
   }
+}
+
+// Nodes per workgroup of the fp32 kernel: a node of its own re-reads all of K and V through L2, which costs
+// nothing while the chip has room (one node against two: 6.1 / 8.3 us with 8 heads x 26 nodes, 256 keys, D = 64;
+// 8.1 / 8.2 us with 8 x 60; 16.9 / 18.5 us with 16 x 48, 600 keys) and is what bounds the call beyond that
+// (13.3 / 11.5 us with 16 x 60, 300 keys; 89 / 73 us with 2 x 16 x 64, 700 keys, D = 128; four nodes: 77 us).
+template <int D>
+void launch_f32(const AttnParams& prm, hipStream_t stream) {
+  const bool one = (int64_t)prm.B * prm.Hq * prm.Nmax <= 768;
+  const dim3 grid((unsigned)prm.Hq, (unsigned)(one ? prm.Nmax : (prm.Nmax + 1) / 2), (unsigned)prm.B), block(64 * kF32Waves);
+  if (one) hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1>), grid, block, 0, stream, prm);
+  else hipLaunchKernelGGL((tree_attn_f32_kernel<D, 2>), grid, block, 0, stream, prm);
 }
 
 }  // namespace
@@ -1480,9 +1545,8 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       }
     } else {
-      dim3 grid((unsigned)d.n_q_heads, (unsigned)((d.n_nodes_max + 3) / 4), (unsigned)nb);
-      if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_f32_kernel<128>, grid, dim3(256), 0, stream, sl);
-      else hipLaunchKernelGGL(tree_attn_f32_kernel<64>, grid, dim3(256), 0, stream, sl);
+      if (d.head_dim == 128) launch_f32<128>(sl, stream);
+      else launch_f32<64>(sl, stream);
       if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
     }
   }

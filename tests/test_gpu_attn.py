@@ -279,3 +279,16 @@ def test_missing_workspace_is_an_error_not_a_crash(H):
         fspad.fspad_tree_attn(case.q, case.k_tree, case.v_tree, case.k_cache, case.v_cache, case.kv_len,
                               case.n_nodes, case.mask_dev, workspace=tiny)
     assert e.value.status == 5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,Hq,Hkv", [(3, 4, 2), (26, 16, 16), (61, 16, 4)])
+@pytest.mark.parametrize("L", [0, 7, 16, 31, 33, 255, 257, 700])
+def test_fp32_nodes_per_workgroup(H, D, N, Hq, Hkv, L):
+    """One and two nodes per workgroup (by heads x nodes), at the edges of the wavefronts' key tiles
+    (16 or 32 keys, eight wavefronts), with ragged trees. Tree rows that a node does not see may hold
+    anything: the rows past n_nodes are NaN here."""
+    case = H.AttnCase(900 + N + L, 2, N, Hq, Hkv, D, L, "f32", l_cap=L + 2, kv_len=[L, L // 2], n_nodes=[N, max(1, N // 2)])
+    for t in (case.k_tree, case.v_tree):
+        t[1, max(1, N // 2):] = float("nan")
+    _check(H, case, H.TOL["f32"])
