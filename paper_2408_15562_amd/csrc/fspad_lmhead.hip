@@ -8,13 +8,11 @@
 // The GEMM is bound by streaming the V x K weight matrix once (262 MB for a 32000 x 4096 head);
 // the hidden states (a few hundred KB) are re-read by every workgroup through LDS.
 //
-// Workgroup = 128 vocabulary rows x up to 128 hidden-state rows x all of K; eight wavefronts of 16
-// vocabulary rows each. With `v_mfma_f32_16x16x32_bf16` and A = 16 weight rows, B = 16 hidden
-// rows, both operands are "8 consecutive k per lane", i.e. plain 16-byte loads of row-major data:
-// the weights go from HBM straight into registers (a ring of 16 k-steps = 16 KB requested ahead per wavefront),
-// the hidden states are staged through LDS (XOR-swizzled by 16-byte chunk so that a 16-row operand
-// read touches 16 different bank groups), double-buffered, one barrier per stage of 256 or 512 k. D[vocab][row] puts one hidden-state row per lane column, so the argmax over the
-// vocabulary is a per-lane scan plus two lane exchanges.
+// Workgroup = 128 vocabulary rows x the hidden-state rows of a pass x all of K, eight wavefronts, on
+// `v_mfma_f32_16x16x32_bf16` with A = weight rows and B = hidden rows. Up to 128 rows: StreamGemm, sixteen
+// vocabulary rows per wavefront; up to 256: WideGemm, a 2 x 4 grid of wavefronts; more: passes over the weights.
+// D[vocab][row] puts one hidden-state row per lane column, so the argmax over the vocabulary is a per-lane
+// scan plus two lane exchanges.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -29,8 +27,6 @@ using fspad_detail::bf16x8;
 using fspad_detail::f32x4;
 using fspad_detail::StreamGemm;
 static_assert(fspad_detail::kSliceRows == 128, "tokens per slice");
-typedef const __attribute__((address_space(1))) void* GlobalPtr;
-typedef __attribute__((address_space(3))) void* LdsPtr;
 
 constexpr int kVocabPerWg = 128;                            // vocabulary rows per workgroup, in every shape below
 constexpr int kNone = 0x7fffffff;
@@ -48,7 +44,6 @@ struct LmHeadParams {
   const int32_t* parent;
   const int32_t* n_nodes;
   int32_t M, V, K, n_slices, n_passes, rows_per_pass;
-  int32_t stagger;      // stages by which consecutive workgroups are offset along k (0: all start at k = 0)
   int32_t Nmax;
   float inv_t_log2e;    // sampling: log2(e) / T
 };
@@ -216,57 +211,50 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_ke
   });
 }
 
-// The LM head: MT, SPS, kRing, WAVES, VT as above; WAVES x VT = 8, i.e. 128 vocabulary rows per
-// workgroup: eight wavefronts of one weight tile, two per SIMD, in every shape in use (four
-// wavefronts of two tiles, one per SIMD with the whole register file, halve the LDS reads per
-// product but measured slower at 256 rows: 178 against 152 us on a 32000 x 6656 head).
+// The LM head over more than 128 rows per pass: one 128-token slice per workgroup against 64 * XT rows
+// (WideGemm).
 // MODE 0: per slice and row (max, first argmax) for the greedy walk. MODE 1: per slice and row
 // (max, sum of exponentials) and the logits of the draft tokens, for the sampling walk.
-template <int MT, int SPS, int kRing, int WAVES, int VT, int MODE, bool PACKED>
-__global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 2 : 1)) void lm_head_argmax_kernel(const LmHeadParams p) {
-  static_assert(WAVES * VT * 16 == kVocabPerWg, "workgroup shape");
-  typedef fspad_detail::StreamGemmRegs<MT, SPS, kRing, WAVES, VT, PACKED> G;
-  constexpr int kStageBytes = G::kStageBytes;
-  __shared__ __attribute__((aligned(16))) char xs[2 * kStageBytes];
-  __shared__ float red_val[WAVES][MT * 16];
-  __shared__ int red_idx[WAVES][MT * 16];
+template <int XT, int MODE, bool PACKED>
+__global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_wide_kernel(const LmHeadParams p) {
+  typedef fspad_detail::WideGemm<XT, PACKED> G;
+  constexpr int kThreads = 64 * fspad_detail::kStreamWaves, kRows = 64 * XT;
+  __shared__ __attribute__((aligned(1024))) char lds[G::kLdsBytes];
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, g = lane >> 4;
-  const int slice = blockIdx.x / p.n_passes, pass = blockIdx.x - slice * p.n_passes;
+  const int half = wave & 1, tile0 = (wave >> 1) * XT;   // this wavefront's 64 tokens, its first 16-row tile
+  // the passes of a slice go to one XCD (workgroups 8 apart), next to each other: its L2 fetches the weights once
+  const unsigned turn = blockIdx.x >> 3;
+  const int pass = (int)(turn % (unsigned)p.n_passes), slice = (int)(turn / (unsigned)p.n_passes) * 8 + (int)(blockIdx.x & 7);
+  if (slice >= p.n_slices) return;
   const int row0 = pass * p.rows_per_pass;
-  const int v0 = slice * kVocabPerWg + wave * (16 * VT);
-  const int n_steps = p.K >> 5;
-  // workgroup `slice` walks k from stage `first_stage` on and wraps around
-  const int first_step = p.stagger ? (int)(((unsigned)slice * (unsigned)p.stagger) % (unsigned)(n_steps / SPS)) * SPS : 0;
+  const int slice0 = slice * kVocabPerWg;
 
-  f32x4 acc[MT][VT];
+  f32x4 acc[4][XT];
 #pragma unroll
-  for (int t = 0; t < MT; ++t)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int nv = 0; nv < VT; ++nv) acc[t][nv] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // (the tile order pads the vocabulary to whole tiles of 16 rows)
-  G::run(xs, p.hidden, p.weights, (size_t)p.K * 2, p.M, PACKED ? (p.V + 15) / 16 * 16 : p.V, row0, v0, n_steps, first_step, acc);
+    for (int t = 0; t < XT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  G::run(lds, p.hidden, p.weights, p.M, p.V, row0, slice0, p.K, G::phase(slice, p.K / G::kStageK), acc);
+  __syncthreads();   // the stages are dead
 
   if constexpr (MODE == 1) {
-    // The stages are dead: the workgroup's 16*MT x 128 logits go there, as fp32, row by row
+    // The workgroup's rows x 128 logits go to LDS, as fp32, row by row
     // (16-byte chunk c of row r at chunk c ^ (r & 15): sixteen rows written at once hit different banks).
-    constexpr int kRows = MT * 16;
-    static_assert(kRows * 512 <= 2 * kStageBytes, "the logits of a workgroup fit the two stages");
-    __syncthreads();
-    float* dump = reinterpret_cast<float*>(xs);
+    static_assert(kRows * 512 <= G::kLdsBytes, "the logits of a workgroup fit the stages");
+    float* dump = reinterpret_cast<float*>(lds);
 #pragma unroll
-    for (int t = 0; t < MT; ++t)
+    for (int t = 0; t < XT; ++t)
 #pragma unroll
-      for (int nv = 0; nv < VT; ++nv) {
-        const int r = t * 16 + n, chunk = (wave * (16 * VT) + 16 * nv + 4 * g) >> 2;
-        *reinterpret_cast<f32x4*>(dump + r * 128 + ((chunk ^ (r & 15)) << 2)) = acc[t][nv];
+      for (int i = 0; i < 4; ++i) {
+        const int r = (tile0 + t) * 16 + n, chunk = 16 * half + 4 * i + g;
+        *reinterpret_cast<f32x4*>(dump + r * 128 + ((chunk ^ (r & 15)) << 2)) = acc[i][t];
       }
     __syncthreads();
     // slice statistics: sixteen lanes per row, eight logits each
     const int sub = lane & 15;
-    const int slice0 = slice * kVocabPerWg;
-    for (int r = threadIdx.x >> 4; r < kRows; r += 4 * WAVES) {   // uniform per 16 lanes
+    for (int r = threadIdx.x >> 4; r < kRows; r += kThreads / 16) {   // uniform per 16 lanes
       float x[8];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -306,7 +294,7 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 2 : 1)) void lm_head_argm
       }
     }
     // the logits the walk will test: node c's token under the row of c's parent
-    for (int cnode = threadIdx.x; cnode < p.M; cnode += 64 * WAVES) {
+    for (int cnode = threadIdx.x; cnode < p.M; cnode += kThreads) {
       const int b = cnode / p.Nmax, i = cnode - b * p.Nmax;
       if (i == 0 || i >= p.n_nodes[b]) continue;
       const int par = p.parent[cnode], tok = p.draft_tokens[cnode];
@@ -319,18 +307,20 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 2 : 1)) void lm_head_argm
     return;
   }
 
-  // argmax over this wavefront's vocabulary rows for each hidden-state row (lane column n):
-  // ascending vocabulary order inside the lane, then across the four lane groups
+  // argmax over this wavefront's tokens for each hidden-state row (lane column n): ascending order inside
+  // the lane, then across the four lane groups, then the two wavefronts that hold the row
+  float* const red_val = reinterpret_cast<float*>(lds);                 // [2][kRows]
+  int* const red_idx = reinterpret_cast<int*>(lds) + 2 * kRows;
 #pragma unroll
-  for (int t = 0; t < MT; ++t) {
+  for (int t = 0; t < XT; ++t) {
     float best = -INFINITY;
     int idx = kNone;
 #pragma unroll
-    for (int nv = 0; nv < VT; ++nv)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int v = v0 + 16 * nv + 4 * g + i;
-        const float x = acc[t][nv][i];
+      for (int e = 0; e < 4; ++e) {
+        const int v = slice0 + 64 * half + 16 * i + 4 * g + e;
+        const float x = acc[i][t][e];
         if (v < p.V && x > best) { best = x; idx = v; }
       }
 #pragma unroll
@@ -339,15 +329,15 @@ __global__ __launch_bounds__(64 * WAVES, (WAVES == 8 ? 2 : 1)) void lm_head_argm
       const int oi = __shfl_xor(idx, d);
       take_better(best, idx, ov, oi);
     }
-    if (g == 0) { red_val[wave][t * 16 + n] = best; red_idx[wave][t * 16 + n] = idx; }
+    const int r = half * kRows + (tile0 + t) * 16 + n;
+    if (g == 0) { red_val[r] = best; red_idx[r] = idx; }
   }
   __syncthreads();
-  for (int m = threadIdx.x; m < MT * 16; m += 64 * WAVES) {
-    if (row0 + m >= p.M) break;
-    float best = red_val[0][m];
-    int idx = red_idx[0][m];
-#pragma unroll
-    for (int w8 = 1; w8 < WAVES; ++w8) take_better(best, idx, red_val[w8][m], red_idx[w8][m]);
+  const int m = threadIdx.x;
+  if (m < kRows && row0 + m < p.M) {
+    float best = red_val[m];
+    int idx = red_idx[m];
+    take_better(best, idx, red_val[kRows + m], red_idx[kRows + m]);
     const size_t slot = (size_t)slice * p.M + row0 + m;
     p.part_max[slot] = best;
     p.part_idx[slot] = idx;
@@ -769,11 +759,6 @@ __global__ __launch_bounds__(kWalkThreads) void lm_head_sample_walk_kernel(const
 
 constexpr int kComputeUnits = 256;
 int n_slices_of(int32_t V) { return (V + kVocabPerWg - 1) / kVocabPerWg; }
-// Workgroup s starts its k loop (s * kStagger) stages in and wraps around, so that the workgroups
-// running at the same time read different parts of their rows: with every workgroup at the same k
-// the requests in flight differ only in address bits above the row pitch and crowd a few memory
-// channels (measured on a 32000 x 4096 head: 59.8 us without, 52.4 us with).
-constexpr int kStagger = 3;
 
 }  // namespace
 
@@ -804,8 +789,7 @@ fspad_status launch_lm_head(LmHeadParams& g, int32_t hidden_dim, hipStream_t str
   g.n_passes = (g.M + g.rows_per_pass - 1) / g.rows_per_pass;
   const int pass_rows = g.n_passes > 1 ? (g.M + g.n_passes - 1) / g.n_passes : g.M;   // passes of equal size
   if (g.n_passes > 1) g.rows_per_pass = (pass_rows + 15) / 16 * 16;
-  if ((int64_t)g.n_slices * g.n_passes > 0x7fffffff) return FSPAD_ERR_SHAPE;
-  g.stagger = kStagger;
+  if (((int64_t)g.n_slices + 7) * g.n_passes > 0x7fffffff) return FSPAD_ERR_SHAPE;
   const int r = g.rows_per_pass;
   if (r <= 128) {
     const dim3 grid((unsigned)(g.n_slices < kComputeUnits ? g.n_slices : kComputeUnits), (unsigned)g.n_passes), block(512);
@@ -816,9 +800,9 @@ fspad_status launch_lm_head(LmHeadParams& g, int32_t hidden_dim, hipStream_t str
     else hipLaunchKernelGGL((lm_head_kernel<8, MODE, PACKED>), grid, block, 0, stream, g);
     return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
   }
-  const dim3 grid((unsigned)(g.n_slices * g.n_passes));
-  if (r <= 192) hipLaunchKernelGGL((lm_head_argmax_kernel<12, 4, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
-  else hipLaunchKernelGGL((lm_head_argmax_kernel<16, 4, 16, 8, 1, MODE, PACKED>), grid, dim3(512), 0, stream, g);
+  const dim3 grid((unsigned)((g.n_slices + 7) / 8 * 8 * g.n_passes));
+  if (r <= 192) hipLaunchKernelGGL((lm_head_wide_kernel<3, MODE, PACKED>), grid, dim3(512), 0, stream, g);
+  else hipLaunchKernelGGL((lm_head_wide_kernel<4, MODE, PACKED>), grid, dim3(512), 0, stream, g);
   return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
 }
 

@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace fspad_detail {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -256,122 +258,169 @@ struct StreamGemm {
   }
 };
 
-// acc[t][nv] += sum over a k range of
-//   X[row0 + 16t + n][k] * W[v0 + 16nv + 4g + i][k]      (lane (n, g), accumulator element i)
-// for one wavefront of a workgroup of WAVES wavefronts that share X through LDS.
-// MT: 16-row tiles of X per workgroup. SPS: k-steps (of 32) per LDS stage of X (stage = 16*MT rows
-// x 32*SPS k). kRing: weight operands per 16-row weight tile that a wavefront keeps requested. VT:
-// weight tiles per wavefront. x_base / w_base point at the first k of the range, rows are row_bytes
-// apart; the range is n_steps k-steps (a multiple of 8) and is walked from first_step on, wrapping
-// around (first_step a multiple of SPS; 0 unless n_steps is a multiple of SPS). xs: 2 stages of LDS.
-// PACKED: W is stored tile by tile instead of row by row -- the 16 rows x 32 k of one operand are
-// 1 KB in lane order (lane (n, g) at byte 16 * (n + 16 g)), the k-steps of a 16-row tile follow one
-// another, then the next 16 rows. A wavefront's request is then one contiguous KB instead of sixteen
-// 64-byte pieces a row pitch apart; row_bytes is still 2 K, v0 a multiple of 16, and w_base points at
-// the first k-step of the range within tile row 0.
-template <int MT, int SPS, int kRing, int WAVES, int VT, bool PACKED = false>
-struct StreamGemmRegs {
-  static constexpr int kStageK = 32 * SPS;
-  static constexpr int kRowBytes = kStageK * 2;                        // 256, 512 or 1024
-  static constexpr int kStageBytes = MT * 16 * kRowBytes;
-  static constexpr int kChunksPerRow = kRowBytes / 16;                 // 16, 32 or 64
-  static constexpr int kRowsPerCopy = 1024 / kRowBytes;                // one copy instruction moves 1 KB
-  static constexpr int kCopiesPerWave = kStageBytes / 1024 / WAVES;
-  static_assert(kCopiesPerWave >= 1 && kRing % SPS == 0 && kRing % 4 == 0, "stage shape");
+// The same product for more rows of X than the ring's workgroup can hold sums for: 128 rows of W against
+// 64 * XT rows of X (XT = 3 or 4) and all of K, eight wavefronts.
+//
+// At these sizes neither HBM (426 MB of a 32000 x 6656 head: 65 us) nor the matrix cores (46 us for 256 rows) but
+// the operand reads bound the kernel if every wavefront keeps rows of W to itself: 16 rows x 256 take an operand of X
+// per product, twice what LDS delivers in the time of a product. So the wavefronts form a 2 x 4 grid of
+// 64 x (16 XT) tiles: 4 + XT operands for 4 XT products. Both matrices go through LDS, in stages of 64 k copied by
+// the global-to-LDS loads, one barrier per stage. Half of the wavefronts copy W (four or five stages, it comes from
+// HBM), the others X (three stages, from L2): waits count a wavefront's own requests in order, so a
+// wavefront that copied both could not wait for the near one and leave the far one in flight. 16-byte chunk c of a
+// row sits at slot c ^ (r >> 1 & 7): two rows fill the 64 banks, and the sixteen rows of an operand read touch
+// sixteen different bank groups.
+// 32000 x 6656, 240 rows, greedy acceptance: 155 -> 119 us (16 rows of W per wavefront, in registers, before);
+// four wavefronts of 64 x 128 tiles 10 % slower; what is left is split over the copies (95 us without most of
+// them) and the products (116 us with a quarter of them).
+template <int XT, bool PACKED>
+struct WideGemm {
+  static constexpr int kStageK = 64;
+  static constexpr int kWStages = XT == 4 ? 4 : 5, kXStages = 3;
+  static constexpr int kRowBytes = kStageK * 2;
+  static constexpr int kWBytes = kSliceRows * kRowBytes, kXBytes = 64 * XT * kRowBytes;
+  static constexpr int kXAt = kWStages * kWBytes;     // X behind W
+  static constexpr int kLdsBytes = kXAt + kXStages * kXBytes;
+  static constexpr int kTileBytes = 16 * kRowBytes;   // a 16-row tile of either matrix
+  static constexpr int kWCopies = 4, kXCopies = 2 * XT;   // copy instructions of a copying wavefront and stage
 
-  __device__ static __forceinline__ void run(char* xs, const char* x_base, const char* w_base, size_t row_bytes,
-                                             int n_xrows, int n_wrows, int row0, int v0, int n_steps, int first_step,
-                                             f32x4 (&acc)[MT][VT]) {
+  // Stage at which the workgroup of a slice begins, of C stages. The workgroups of an XCD (every eighth) stay
+  // within a window of 32 stages, two stages -- the 256 bytes of one L2 channel -- apart, so that they use all
+  // channels for W and find the same megabyte of X in L2; each XCD has a window of its own.
+  __device__ static __forceinline__ int phase(int slice, int C) {
+    return (int)((2u * (((unsigned)slice >> 3) & 15u) + ((unsigned)slice & 7u) * (unsigned)C / 8u) % (unsigned)C);
+  }
+
+  // acc[i][t] of lane (n, g): rows v0 + 64 (wave & 1) + 16 i + 4 g .. + 3 of W against row
+  // row0 + 16 (XT (wave >> 1) + t) + n of X. The K / 64 stages are walked from `first` on, around the end.
+  // Nothing is in flight when it returns, but other wavefronts may still be reading their last stage.
+  __device__ static __forceinline__ void run(char* lds, const char* x, const char* w, int n_xrows, int n_wrows, int row0,
+                                             int v0, int K, int first, f32x4 (&acc)[4][XT]) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
-    // weight rows of this lane (rows past the vocabulary are clamped; their columns are never taken)
-    const char* wrow[VT];
-#pragma unroll
-    for (int nv = 0; nv < VT; ++nv)
-      wrow[nv] = PACKED ? w_base + (size_t)min(v0 + 16 * nv, n_wrows - 16) * row_bytes + lane * 16
-                        : w_base + (size_t)min(v0 + 16 * nv + n, n_wrows - 1) * row_bytes + g * 16;
+    const size_t row_bytes = (size_t)K * 2;
+    const int piece = lane >> 3, slot = lane & 7;   // a copy instruction takes 8 rows x 128 bytes
 
-    // hidden-state copies of this wavefront: LDS slot s of row r receives the row's 16-byte chunk
-    // s ^ (r & 15) of the stage's k range (chunks past the end of the row are clamped: never used)
-    const char* xsrc[kCopiesPerWave];
-    int xcol[kCopiesPerWave];
+    // Wavefronts 0..3 copy W (32 rows each), 4..7 X. (Rows past the end of either matrix are clamped; their
+    // sums are never taken.)
+    const bool copies_w = wave < 4;
+    const char* base;
+    unsigned off[kXCopies > kWCopies ? kXCopies : kWCopies];
+    if (copies_w) {
+      if constexpr (PACKED) {
+        const int last = (n_wrows - 1) >> 4, tile = (v0 >> 4) + 2 * wave, t0 = min(tile, last);
+        base = w + (size_t)t0 * 16 * row_bytes;
 #pragma unroll
-    for (int i = 0; i < kCopiesPerWave; ++i) {
-      const int r = kRowsPerCopy * (wave * kCopiesPerWave + i) + lane / kChunksPerRow, s = lane % kChunksPerRow;
-      xsrc[i] = x_base + (size_t)min(row0 + r, n_xrows - 1) * row_bytes;
-      xcol[i] = s ^ (r & 15);
-    }
-    const int last_chunk = 4 * n_steps - 1;
-    // operand reads: lane (n, g) of tile t, k-step kk of the stage reads chunk 4*kk + g of row 16*t + n,
-    // kept at slot (4*kk + g) ^ n = (4*kk) ^ (g ^ n)
-    const unsigned xread = (unsigned)n * kRowBytes, xswz = (unsigned)(g ^ n) << 4;
-
-    bf16x8 xr[kCopiesPerWave];
-    auto fetch_x = [&](int stage_index) {
+        for (int i = 0; i < kWCopies; ++i)
+          off[i] = (unsigned)(min(tile + i / 2, last) - t0) * 16u * (unsigned)row_bytes + (unsigned)(i & 1) * 1024u + (unsigned)lane * 16u;
+      } else {
+        const int r0 = min(v0 + 32 * wave, n_wrows - 1);
+        base = w + (size_t)r0 * row_bytes;
 #pragma unroll
-      for (int i = 0; i < kCopiesPerWave; ++i) {
-        int stage = stage_index + first_step / SPS;
-        stage -= stage * SPS >= n_steps ? n_steps / SPS : 0;
-        const int chunk = min(stage * kChunksPerRow + xcol[i], last_chunk);
-        xr[i] = *reinterpret_cast<const bf16x8*>(xsrc[i] + ((size_t)chunk << 4));
-      }
-    };
-    auto store_x = [&](int stage_index) {
-      char* dst = xs + (stage_index & 1) * kStageBytes + wave * kCopiesPerWave * 1024 + lane * 16;
-#pragma unroll
-      for (int i = 0; i < kCopiesPerWave; ++i) *reinterpret_cast<bf16x8*>(dst + i * 1024) = xr[i];
-    };
-    // workgroup barrier that orders LDS traffic only: the weight requests in flight stay in flight
-    auto lds_barrier = [] {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
-    // k-step ks of the weights: lane (n, g) holds k = 32*ks + 8*g .. +7 of its row (steps past the end
-    // re-read the last one, so that every turn of the loop issues the same number of requests)
-    auto load_w = [&](int nv, int ks) {
-      int step = min(ks, n_steps - 1) + first_step;
-      step -= step >= n_steps ? n_steps : 0;
-      return *reinterpret_cast<const bf16x8*>(wrow[nv] + (size_t)step * (PACKED ? 1024 : 64));
-    };
-
-    // The weights are requested kRing k-steps ahead, every operand register being requested again as
-    // soon as its products are issued. The hidden states of stage j+1 are requested into registers at
-    // the top of stage j and written to the other LDS stage at its end (by then they have long
-    // arrived, and the weight requests issued after them stay in flight); the barrier at the top of a
-    // stage publishes every wavefront's share of it and retires the other one.
-    bf16x8 w[VT][kRing];
-    fetch_x(0);
-#pragma unroll
-    for (int i = 0; i < kRing; ++i)
-#pragma unroll
-      for (int nv = 0; nv < VT; ++nv) w[nv][i] = load_w(nv, i);
-    store_x(0);
-    const int n_stages = (n_steps + SPS - 1) / SPS;
-    for (int ks0 = 0; ks0 < n_steps; ks0 += kRing) {
-#pragma unroll
-      for (int kk = 0; kk < kRing; ++kk) {
-        const int ks = ks0 + kk;
-        if (kk % 4 == 0 && ks >= n_steps) break;   // K is a multiple of 256 and the ring of 4: the end falls on a multiple of 4 steps
-        if (kk % SPS == 0) {
-          lds_barrier();
-          if (ks / SPS + 1 < n_stages) fetch_x(ks / SPS + 1);
+        for (int i = 0; i < kWCopies; ++i) {
+          const int r = 8 * i + piece;
+          off[i] = (unsigned)(min(v0 + 32 * wave + r, n_wrows - 1) - r0) * (unsigned)row_bytes + (unsigned)(slot ^ ((r >> 1) & 7)) * 16u;
         }
-        const char* base = xs + ((ks / SPS) & 1) * kStageBytes + xread + ((((unsigned)kk % SPS) << 6) ^ xswz);
-        bf16x8 xf[MT];
+      }
+    } else {
+      base = x + (size_t)row0 * row_bytes;
 #pragma unroll
-        for (int t = 0; t < MT; ++t) xf[t] = *reinterpret_cast<const bf16x8*>(base + t * (16 * kRowBytes));
-#pragma unroll
-        for (int nv = 0; nv < VT; ++nv)
-#pragma unroll
-          for (int t = 0; t < MT; ++t)
-            acc[t][nv] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nv][kk], xf[t], acc[t][nv], 0, 0, 0);
-#pragma unroll
-        for (int nv = 0; nv < VT; ++nv) w[nv][kk] = load_w(nv, ks + kRing);
-        if (kk % SPS == SPS - 1 && ks / SPS + 1 < n_stages) store_x(ks / SPS + 1);
+      for (int i = 0; i < kXCopies; ++i) {
+        const int r = 8 * ((wave - 4) * kXCopies + i) + piece;
+        off[i] = (unsigned)min(r, n_xrows - 1 - row0) * (unsigned)row_bytes + (unsigned)(slot ^ ((r >> 1) & 7)) * 16u;
       }
     }
+    // the copies of this wavefront's matrix: `ahead` is the stage requested last, `to` the slot of the next
+    const int stages = K / kStageK;
+    int ahead = first, left = stages, to = 0;
+    auto request = [&] {
+      const char* const src = base + (size_t)ahead * (PACKED && copies_w ? 2048 : kRowBytes);
+      if (copies_w) {
+#pragma unroll
+        for (int i = 0; i < kWCopies; ++i)
+          __builtin_amdgcn_global_load_lds((StreamGlobalPtr)(src + off[i]), (StreamLdsPtr)(lds + to * kWBytes + (wave * kWCopies + i) * 1024), 16, 0, 0);
+        to = to == kWStages - 1 ? 0 : to + 1;
+      } else {
+#pragma unroll
+        for (int i = 0; i < kXCopies; ++i)
+          __builtin_amdgcn_global_load_lds((StreamGlobalPtr)(src + off[i]),
+                                           (StreamLdsPtr)(lds + kXAt + to * kXBytes + ((wave - 4) * kXCopies + i) * 1024), 16, 0, 0);
+        to = to == kXStages - 1 ? 0 : to + 1;
+      }
+      // (the last stage repeats: every turn issues the same number of requests)
+      if (--left > 0) ahead = ahead + 1 == stages ? 0 : ahead + 1;
+    };
 
+    // operand reads of k-step j (32 k): chunk 4 j + g of row n of a tile
+    const unsigned swizzled = (unsigned)n * kRowBytes + ((unsigned)(g ^ ((n >> 1) & 7)) << 4);
+    const unsigned wread = lds_address(lds) + (unsigned)(wave & 1) * 4u * kTileBytes + (PACKED ? (unsigned)lane * 16u : swizzled);
+    const unsigned xread = lds_address(lds) + kXAt + (unsigned)(wave >> 1) * XT * kTileBytes + swizzled;
+
+    // The operands of a k-step are read while the products of the one before it run, a few reads between
+    // them (issued in one go they would hold the wavefront up until LDS has taken them all), across the stage's
+    // end too: the barrier stands in the middle of a turn, behind the products of the stage's first half, when
+    // every wavefront has the operands of the second half in registers -- so that the stage is free as well.
+    bf16x8 wf[2][4], xf[2][XT];
+    auto multiply = [&](auto step, unsigned wa, unsigned xa) {   // the products of k-step j, the reads of the other one
+      constexpr int j = decltype(step)::value, o = 1 - j;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) settled(wf[j][i]);
+#pragma unroll
+      for (int i = 0; i < XT; ++i) settled(xf[j][i]);
+      products<PACKED ? 1024 * o : 0>(acc, wf[j], xf[j], wf[o], xf[o], PACKED ? wa : wa ^ (64u * o), xa ^ (64u * o));
+    };
+    const int lead = copies_w ? kWStages : kXStages;
+    for (int i = 0; i < lead; ++i) request();
+    if (copies_w) wait_vmem<kWCopies * (kWStages - 1)>();
+    else wait_vmem<kXCopies * (kXStages - 1)>();
+    lds_barrier();
+    unsigned wa = wread, xa = xread;
+    const unsigned wend = wread + kWStages * kWBytes, xend = xread + kXStages * kXBytes;
+    read_tiles<4, 0>(wf[0], wa);
+    read_tiles<XT, 0>(xf[0], xa);
+    for (int t = 0; t < stages; ++t) {
+      wait_lds<0>();
+      multiply(std::integral_constant<int, 0>{}, wa, xa);
+      // this wavefront's share of the next stage has landed (the ones after it may be in flight)
+      if (copies_w) wait_vmem<kWCopies * (kWStages - 2)>();
+      else wait_vmem<kXCopies * (kXStages - 2)>();
+      lds_barrier();
+      request();
+      wa = wa + kWBytes == wend ? wread : wa + kWBytes;
+      xa = xa + kXBytes == xend ? xread : xa + kXBytes;
+      multiply(std::integral_constant<int, 1>{}, wa, xa);   // (reads behind the last stage: a repeated one)
+    }
+    wait_lds<0>();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) settled(wf[0][i]);
+#pragma unroll
+    for (int i = 0; i < XT; ++i) settled(xf[0][i]);
+    wait_vmem<0>();   // the repeated requests have landed too
+  }
+
+ private:
+  // product M of a k-step (tile M / XT of W, M % XT of X) behind, for the first ones, a read for the next
+  template <int OFF, int M = 0>
+  __device__ static __forceinline__ void products(f32x4 (&acc)[4][XT], const bf16x8 (&wf)[4], const bf16x8 (&xf)[XT],
+                                                  bf16x8 (&wn)[4], bf16x8 (&xn)[XT], unsigned wa, unsigned xa) {
+    if constexpr (M < 4 * XT) {
+      if constexpr (M < 4 + XT) {
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (M < 4) lds_read16<M * kTileBytes + OFF>(wn[M], wa);
+        else lds_read16<(M - 4) * kTileBytes>(xn[M - 4], xa);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      constexpr int i = M / XT, c = M % XT;
+      acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i], xf[c], acc[i][c], 0, 0, 0);
+      products<OFF, M + 1>(acc, wf, xf, wn, xn, wa, xa);
+    }
+  }
+  template <int N, int OFF, int T = 0>
+  __device__ static __forceinline__ void read_tiles(bf16x8 (&v)[N], unsigned a) {
+    if constexpr (T < N) {
+      lds_read16<T * kTileBytes + OFF>(v[T], a);
+      read_tiles<N, OFF, T + 1>(v, a);
+    }
   }
 };
 

@@ -166,6 +166,23 @@ def test_sampling_on_exactly_representable_logits_has_no_exclusions(H, B, N, V, 
         H.assert_accept_equal(gpu, cpu)
 
 
+@pytest.mark.parametrize("B,N,Hd,V", [(3, 43, 256, 65), (3, 64, 512, 257), (4, 49, 256, 127), (4, 64, 768, 1345),
+                                      (5, 52, 256, 200), (8, 33, 512, 640)])
+def test_more_than_128_rows(H, B, N, Hd, V):
+    """One workgroup for up to 192 and up to 256 rows, at both ends of either, and passes over more; slices
+    that end in the first and in the second half of a workgroup's tokens. Greedy and sampling, and the same
+    bits from weights in tile order."""
+    case = H.LmHeadCase(5000 + 7 * N + V, B, N, Hd, V, topk=min(10, V // 2), noise=0.5)
+    gpu = case.gpu()
+    H.assert_lm_head_equal(gpu, case.cpu(), require_decided=False)
+    for a, b in zip(gpu, case.gpu(packed=True)):
+        assert np.array_equal(a, b, equal_nan=True)
+    sampled = case.gpu_sample(0.8, 1)
+    H.assert_lm_head_sample_equal(sampled, case.cpu_sample(0.8, 1), min_compared=0.0)
+    for a, b in zip(sampled, case.gpu_sample(0.8, 1, packed=True)):
+        assert np.array_equal(a, b)
+
+
 def test_sampling_exclusions_are_counted(H):
     """Runs last among the sampling tests of this file: over everything they compared, the sequences
     left out for a small margin are counted and so are those of them that really differ."""
