@@ -25,6 +25,7 @@
 namespace {
 
 using fspad_detail::exp_nonpos;
+using fspad_detail::exp_nonpos_table;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kThreads = 256;
@@ -95,6 +96,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
   __shared__ float sh_max[4];
   __shared__ int sh_idx[4];
   __shared__ double sh_sum[4];
+  __shared__ double exp2_table[32];
   const int row = blockIdx.y, chunk = blockIdx.x;
   const int b = row / p.Nmax, node = row - b * p.Nmax;
   if (row == 0 && chunk == 0)
@@ -106,22 +108,38 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
   double* const part_sum = second ? p.part_sum2 : p.part_sum;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int base = chunk * kChunk;
+  const double root = MODE == 1 && tid < 32 ? fspad_detail::kExp2Table[tid] : 0.0;
 
   float x[kPerThread];
+  if constexpr (VEC) {
 #pragma unroll
-  for (int k = 0; k < kPerThread / 4; ++k) {
-    const int e0 = base + (k * kThreads + tid) * 4;
-    if (VEC && e0 + 3 < p.V) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(rp + e0);
-      x[4 * k] = clean(v[0]); x[4 * k + 1] = clean(v[1]); x[4 * k + 2] = clean(v[2]); x[4 * k + 3] = clean(v[3]);
-    } else {
+    for (int k = 0; k < kPerThread / 4; ++k) {
+      const int e0 = base + (k * kThreads + tid) * 4;
+      if (e0 + 3 < p.V) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(rp + e0);
+        x[4 * k] = clean(v[0]); x[4 * k + 1] = clean(v[1]); x[4 * k + 2] = clean(v[2]); x[4 * k + 3] = clean(v[3]);
+      } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) x[4 * k + j] = (e0 + j < p.V) ? clean(rp[e0 + j]) : -INFINITY;
+        for (int j = 0; j < 4; ++j) x[4 * k + j] = (e0 + j < p.V) ? clean(rp[e0 + j]) : -INFINITY;
+      }
     }
+  } else {
+    // rows of any alignment, entry by entry: every load goes out before the first value is looked at (past the end:
+    // the last entry, dropped below). Under a test of its own each load was a round trip after the last:
+    // sampling, 3 x 60 rows of 151001: 66 -> 51 us. (The vector form above is faster as it is: greedy, 16 x 60 rows of
+    // 128256, 94 us against 109 us with all loads first, which takes twice the registers.)
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) x[k] = rp[min(base + ((k >> 2) * kThreads + tid) * 4 + (k & 3), p.V - 1)];
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) asm volatile("" : "+v"(x[k]));   // (or the loads move under the tests below)
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) x[k] = base + ((k >> 2) * kThreads + tid) * 4 + (k & 3) < p.V ? clean(x[k]) : -INFINITY;
   }
 
   const int64_t slot = (int64_t)row * p.n_chunks + chunk;
   if (MODE == 1) {
+    if (tid < 32) exp2_table[tid] = root;
+    __syncthreads();
     // sampling: each thread sums exp((x - its own max)/T) over its entries as soon as they arrive
     // (fp64, no waiting for the rest of the workgroup); the threads' (max, sum) pairs are then merged
     // into the chunk's: sum_c = sum_t sum_t * exp((max_t - max_c)/T).
@@ -132,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
     if (mt > -INFINITY) {
       const double mtd = (double)mt;
 #pragma unroll
-      for (int k = 0; k < kPerThread; ++k) st += exp_nonpos(((double)x[k] - mtd) * p.inv_temperature);
+      for (int k = 0; k < kPerThread; ++k) st += exp_nonpos_table(((double)x[k] - mtd) * p.inv_temperature, exp2_table);
     }
     float mw = mt;
 #pragma unroll
