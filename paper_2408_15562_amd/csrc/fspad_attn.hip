@@ -101,15 +101,17 @@ __device__ __forceinline__ AttnArgs fetch_args() {
   asm volatile("s_load_dwordx16 %0, %3, 0x0\n\ts_load_dwordx16 %1, %3, 0x40\n\ts_load_dwordx16 %2, %3, 0x80\n\ts_waitcnt lgkmcnt(0)"
                : "=&s"(a), "=&s"(b), "=&s"(c) : "s"(ka));
   auto u64 = [](int lo, int hi) { return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo; };
+  // (a pointer formed from an integer is a generic one: its accesses become flat instructions, which count as LDS accesses
+  // too and may return in any order, so that every wait for one is a wait for all that is in flight)
   AttnArgs r;
-  r.q = reinterpret_cast<const void*>(u64(a[0], a[1]));
-  r.k_tree = reinterpret_cast<const void*>(u64(a[2], a[3]));
-  r.v_tree = reinterpret_cast<const void*>(u64(a[4], a[5]));
-  r.k_cache = reinterpret_cast<const void*>(u64(a[6], a[7]));
-  r.v_cache = reinterpret_cast<const void*>(u64(a[8], a[9]));
-  r.anc_mask = reinterpret_cast<const uint64_t*>(u64(a[10], a[11]));
-  r.out = reinterpret_cast<void*>(u64(a[12], a[13]));
-  r.part = reinterpret_cast<float*>(u64(a[14], a[15]));
+  r.q = (const void*)(__attribute__((address_space(1))) const void*)u64(a[0], a[1]);
+  r.k_tree = (const void*)(__attribute__((address_space(1))) const void*)u64(a[2], a[3]);
+  r.v_tree = (const void*)(__attribute__((address_space(1))) const void*)u64(a[4], a[5]);
+  r.k_cache = (const void*)(__attribute__((address_space(1))) const void*)u64(a[6], a[7]);
+  r.v_cache = (const void*)(__attribute__((address_space(1))) const void*)u64(a[8], a[9]);
+  r.anc_mask = (const uint64_t*)(__attribute__((address_space(1))) const uint64_t*)u64(a[10], a[11]);
+  r.out = (void*)(__attribute__((address_space(1))) void*)u64(a[12], a[13]);
+  r.part = (float*)(__attribute__((address_space(1))) float*)u64(a[14], a[15]);
   r.stride_batch = (int64_t)u64(b[0], b[1]);
   r.stride_head = (int64_t)u64(b[2], b[3]);
   r.stride_token = (int64_t)u64(b[4], b[5]);
