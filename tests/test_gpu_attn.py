@@ -292,3 +292,19 @@ def test_fp32_nodes_per_workgroup(H, D, N, Hq, Hkv, L):
     for t in (case.k_tree, case.v_tree):
         t[1, max(1, N // 2):] = float("nan")
     _check(H, case, H.TOL["f32"])
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(8, 2, 128), (16, 2, 64), (28, 4, 128)])
+@pytest.mark.parametrize("N,n_nodes", [(60, [60, 5, 33, 17]), (64, [1, 16, 64, 32]), (48, [12, 12, 12, 12])])
+@pytest.mark.parametrize("splits", [0, 3, 37])
+def test_bf16_trees_smaller_than_the_largest(H, Hq, Hkv, D, N, n_nodes, splits):
+    """Shared-stage kernel, trees of different sizes: a sequence has only the slab groups that its own tree
+    fills, whole or cut; the output rows past them come out as zeros whatever was there."""
+    case = H.AttnCase(800 + N + Hq, 4, N, Hq, Hkv, D, 300, "bf16", kv_len=[300, 40, 1, 213], n_nodes=n_nodes)
+    _check(H, case, H.TOL["bf16"], **({"splits": splits} if splits else {}))
+    ref = case.run_gpu()
+    import paper_2408_15562_amd as fspad
+    out = torch.full(case.q.shape, float("nan"), dtype=torch.bfloat16, device=H.DEV)
+    fspad.fspad_tree_attn(case.q, case.k_tree, case.v_tree, case.k_cache, case.v_cache, case.kv_len, case.n_nodes, case.mask_dev,
+                          out=out)
+    assert torch.equal(out, ref.to(torch.bfloat16))
