@@ -387,7 +387,7 @@ __device__ __forceinline__ void process_block(RowState<QT, D>& st, const bf16x8 
 // to `out` directly; otherwise its un-normalised (O, max, sum) goes to partial slot unit+w and the
 // merge kernel finishes the unit.
 template <int QT, int D>
-__global__ __launch_bounds__(256, (QT <= 2 ? 2 : 1)) void tree_attn_bf16_kernel(const AttnParams) {
+__global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(const AttnParams) {
   const AttnArgs p = fetch_args();
   constexpr int KS = D / 32;
   constexpr int DT = D / 16;
@@ -1337,34 +1337,44 @@ int blocks_of(int kv_len, int n_nodes) {
 }
 
 // Workgroup count for `total_blocks` flat blocks in `units` units: two resident workgroups per
-// compute unit when the register budget allows it (one otherwise), but no workgroup with fewer
-// than 2 blocks per key-splitting wave. When all units are equally long and short (a few blocks
-// per wave), the count is a multiple of the unit count whenever that still fills three quarters of
-// the compute units: every unit is then cut into the same number of pieces and no workgroup
-// straddles two units (a second segment costs a short-lived workgroup as much as its blocks do).
-// With one piece per unit nothing is cut and nothing is merged.
+// compute unit for 16-row tiles, one otherwise, but no workgroup with fewer
+// than 2 blocks per key-splitting wave.
+// When all units are equally long, the count is a multiple of the unit count where that pays: every unit is then cut
+// into the same number of pieces, or not at all, and no workgroup straddles two units (a second segment costs a
+// workgroup as much as 20 to 30 blocks do). Measured with 4 x 52 heads, 4096 keys, 26 nodes: 208 workgroups 83 us, 512
+// unaligned ones 103 us; 4 x 40 heads, 60 nodes: 500 keys 19 us (160) against 34 (256), 4096 keys 70 against 83; 2 x 40
+// heads, 2048 keys, 60 nodes: 33 us (240) against 40 (256). One workgroup per compute unit at most: a second one
+// shares its instruction issue and finishes last (32 heads, 4096 keys, 26 nodes: 25 us against 28 with 512).
+// Not where it leaves more than two fifths of the compute units idle, nor for long streams (100 blocks of a cut
+// unit, 200 of a whole one on fewer than three quarters of them), which straddling costs less than idle units do (4 x 40 heads, 8192 keys, 4 nodes: 129 us
+// against 120; 2 x 52 heads: 94 against 84), nor where 16-row tiles fill two workgroups per unit evenly
+// (32 heads, 8192 keys, 4 nodes: 34 us against 31). Units of a few blocks per wavefront stay whole when there
+// are enough of them: the merge costs more than the blocks (2 x 32 heads, 500 keys: 13.1 us against 14.2).
 int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool uniform, int forced) {
   // wavefront sets that split a workgroup's keys: the two key groups of the shared-stage kernel, or
   // the wavefronts that do not take a row slab of their own
   const int KW = pl.shared_stage ? 2 : (pl.WS >= 4 ? 1 : 4 / pl.WS);
   // (the shared-stage kernel's eight wavefronts of up to 256 registers fill a compute unit by themselves)
-  const int64_t resident = (pl.QT <= 2 && !pl.shared_stage) ? 512 : 256;
+  // (32-row tiles spill when two workgroups share a compute unit)
+  const int64_t resident = pl.QT == 1 ? 2 * kComputeUnits : kComputeUnits;
   int64_t wgs = resident;
   const int64_t cap = total_blocks / (2 * KW);
   if (wgs > cap) wgs = cap;
   if (uniform && units <= total_blocks) {
     const int64_t rounds = (units + resident - 1) / resident;
-    if (4 * units >= 3 * rounds * resident) {
-      wgs = units;
-    } else if (units <= kComputeUnits) {
-      // short units: one workgroup per compute unit at most, since a second one on the same unit
-      // shares its instruction issue and finishes last
-      const int64_t blocks_per_unit = total_blocks / units;
+    const int64_t blocks_per_unit = total_blocks / units;
+    if (units <= kComputeUnits) {
       int64_t pieces = (blocks_per_unit + 2 * KW - 1) / (2 * KW);
       if (pieces > kComputeUnits / units) pieces = kComputeUnits / units;
-      const bool short_pieces = pieces >= 1 && blocks_per_unit <= 4 * KW * pieces;  // at most 4 blocks per wave
-      if (short_pieces && 4 * units * pieces >= 3 * (wgs < kComputeUnits ? wgs : kComputeUnits)) wgs = units * pieces;
+      if (units >= kComputeUnits / 4 && blocks_per_unit <= 5 * KW) pieces = 1;
+      const bool is_short = blocks_per_unit <= 4 * KW * pieces;   // at most 4 blocks per wave
+      const bool fills = 5 * units * pieces >= 3 * (wgs < kComputeUnits ? wgs : kComputeUnits);
+      const bool even_anyway = pl.QT == 1 && (2 * kComputeUnits) % units == 0;
+      const int64_t longest = pieces > 1 ? 100 * pieces : (4 * units >= 3 * kComputeUnits ? total_blocks : 200);
+      if (is_short ? fills || pieces == 1 : fills && !even_anyway && blocks_per_unit <= longest)
+        wgs = units * pieces;
     }
+    if (4 * units >= 3 * rounds * resident) wgs = units;   // whole units fill the chip
   }
   if (forced > 0) wgs = forced < kMaxForcedWorkgroups ? forced : kMaxForcedWorkgroups;
   if (wgs > kMaxWorkgroups) wgs = kMaxWorkgroups;  // the kernels form w * (T mod W) in 32 bits
