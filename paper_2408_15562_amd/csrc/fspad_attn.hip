@@ -151,12 +151,6 @@ __device__ __forceinline__ unsigned div_magic(unsigned x, int d, unsigned magic)
 __device__ __forceinline__ int seq_slabs(const AttnArgs& p, int n, int rows_per_slab) { return (int)((unsigned)(n * p.G + rows_per_slab - 1) / (unsigned)rows_per_slab); }
 __device__ __forceinline__ int seq_groups(const AttnArgs& p, int slabs) { return (slabs + p.WS - 1) >> p.ws_shift; }
 
-// First flat block of workgroup w under the even split: floor(w * T / W), in 32-bit arithmetic
-// (w * wg_rem < 2^30 because both stay below the 32768 workgroups a launch may have).
-__device__ __forceinline__ unsigned wg_first_block(const AttnArgs& p, unsigned w) {
-  return w * (unsigned)p.wg_quot + (w * (unsigned)p.wg_rem) / (unsigned)p.n_wgs;
-}
-
 __device__ __forceinline__ float wave_xor_max_16_32(float v) {
   v = fmaxf(v, __shfl_xor(v, 16));
   v = fmaxf(v, __shfl_xor(v, 32));
@@ -1073,21 +1067,18 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
   }
 }
 
-// Workgroup that owns flat block x under the even split: the w with first(w) <= x < first(w+1).
-// A float estimate (off by one at most for the sizes a launch can have) and a correction.
-__device__ __forceinline__ int owner_of(const AttnArgs& p, unsigned x) {
-  int w = (int)((float)x * ((float)p.n_wgs / (float)p.total_blocks));
-  w = min(w, p.n_wgs - 1);
-  while (w > 0 && wg_first_block(p, (unsigned)w) > x) --w;
-  while (w + 1 < p.n_wgs && wg_first_block(p, (unsigned)w + 1u) <= x) ++w;
-  return w;
+// Workgroup that owns flat block x under the even split: the last w with floor(w T / W) <= x, i.e.
+// floor(((x + 1) W - 1) / T). The numerator is below 2^45 and the quotient below 2^15: half a unit up, the product
+// with 1/T in fp64 is further from the next integer than its rounding can carry it.
+__device__ __forceinline__ int owner_of(const AttnArgs& p, unsigned x, double inv_total) {
+  return (int)(((double)(x + 1u) * (double)p.n_wgs - 0.5) * inv_total);
 }
 
 // Finishes every unit that was cut into several segments:
 // out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s over the unit's partial slots.
 // One thread per 4 output dims; rows of nodes past n_nodes are written as zeros.
 template <int D>
-__global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams, int rows_per_slab) {
+__global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams, int rows_per_slab, double inv_total) {
   const AttnArgs p = fetch_args();
   constexpr int TPR = D / 4;  // threads per row
   const int unit = blockIdx.y;
@@ -1098,7 +1089,7 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
   const int g = head_of(p, ub, n_groups), y = ub - g * n_groups;
   const int n_blocks = (seq_len(p, b) + kBlockKeys - 1) / kBlockKeys + (seq_nodes(p, b) + kBlockKeys - 1) / kBlockKeys;
   const unsigned fs = seq_first_block(p, b) + (unsigned)ub * (unsigned)n_blocks;
-  const int w0 = owner_of(p, fs), w1 = owner_of(p, fs + (unsigned)n_blocks - 1u);
+  const int w0 = owner_of(p, fs, inv_total), w1 = owner_of(p, fs + (unsigned)n_blocks - 1u, inv_total);
   if (w0 == w1) return;  // written directly by the one workgroup that held the whole unit
   const int rows_per_unit = p.WS * rows_per_slab;
   const int lr = blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
@@ -1596,8 +1587,8 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         const int rows_per_slab = 16 * pl.QT;
         const int rpb = 256 / (d.head_dim / 4);
         dim3 cgrid((unsigned)((pl.rows_per_unit + rpb - 1) / rpb), (unsigned)full_units);
-        if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_combine_kernel<128>, cgrid, dim3(256), 0, stream, sl, rows_per_slab);
-        else hipLaunchKernelGGL(tree_attn_combine_kernel<64>, cgrid, dim3(256), 0, stream, sl, rows_per_slab);
+        if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_combine_kernel<128>, cgrid, dim3(256), 0, stream, sl, rows_per_slab, 1.0 / (double)total);
+        else hipLaunchKernelGGL(tree_attn_combine_kernel<64>, cgrid, dim3(256), 0, stream, sl, rows_per_slab, 1.0 / (double)total);
         if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       }
     } else {

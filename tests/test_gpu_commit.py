@@ -106,3 +106,10 @@ def test_two_verification_steps_chained_on_the_device(H):
         assert np.array_equal(_bits(kc_d), _bits(H.to_dev(kc, "bf16")))
         kv_len = new_len
     assert kv_len.min() > L - 11 + 1
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Hkv", [32, 64, 65, 100])
+def test_commit_of_wide_rows(H, dtype, Hkv):
+    """Rows of one to four turns of a workgroup (1024 pieces of 16 bytes each), the last one ragged."""
+    test_commit_matches_oracle(H, 2, 5, Hkv, 128, 20, dtype, False)
