@@ -22,11 +22,12 @@
 #include <type_traits>
 
 #include "fspad.h"
+#include "stream_gemm.h"
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
+using fspad_detail::bf16x8;
+using fspad_detail::f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 
@@ -208,23 +209,28 @@ __device__ __forceinline__ void v_offsets(unsigned (&off)[8], unsigned row_bytes
   for (int j = 0; j < 8; ++j) off[j] = (unsigned)min(key_of(g4, j), nvalid - 1) * row_bytes + (unsigned)(D / 8) * col;
 }
 
-// Scalar base + per-lane byte offset.
-template <int D>
+// Scalar base + per-lane byte offset. STREAMED: with the non-temporal hint (kCacheBytes in stream_gemm.h).
+template <bool STREAMED, typename T>
+__device__ __forceinline__ T load_once(const char* p) {
+  if constexpr (STREAMED) return __builtin_nontemporal_load(reinterpret_cast<const T*>(p));
+  else return *reinterpret_cast<const T*>(p);
+}
+template <int D, bool STREAMED>
 __device__ __forceinline__ void load_k(bf16x8 (&k)[2][D / 32], const char* base, const unsigned (&off)[2]) {
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) k[kt][ks] = *reinterpret_cast<const bf16x8*>(base + off[kt] + 64 * ks);
+    for (int ks = 0; ks < D / 32; ++ks) k[kt][ks] = load_once<STREAMED, bf16x8>(base + off[kt] + 64 * ks);
 }
-template <int D>
+template <int D, bool STREAMED>
 __device__ __forceinline__ void load_v(unsigned (&v)[8][D / 32], const char* base, const unsigned (&off)[8]) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     if constexpr (D == 128) {
-      const u32x4 w = *reinterpret_cast<const u32x4*>(base + off[j]);
+      const u32x4 w = load_once<STREAMED, u32x4>(base + off[j]);
       v[j][0] = w[0]; v[j][1] = w[1]; v[j][2] = w[2]; v[j][3] = w[3];
     } else {
-      const u32x2 w = *reinterpret_cast<const u32x2*>(base + off[j]);
+      const u32x2 w = load_once<STREAMED, u32x2>(base + off[j]);
       v[j][0] = w[0]; v[j][1] = w[1];
     }
   }
@@ -380,7 +386,7 @@ __device__ __forceinline__ void process_block(RowState<QT, D>& st, const bf16x8 
 // or a few *segments* (a run of blocks of one unit). A segment that is a whole unit is written
 // to `out` directly; otherwise its un-normalised (O, max, sum) goes to partial slot unit+w and the
 // merge kernel finishes the unit.
-template <int QT, int D>
+template <int QT, int D, bool STREAMED>
 __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(const AttnParams) {
   const AttnArgs p = fetch_args();
   constexpr int KS = D / 32;
@@ -500,9 +506,9 @@ __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(
     if (active) {
       cur = locate(blk_begin);
       set_k(cur);
-      load_k<D>(kf, cur.k, koff);
+      load_k<D, STREAMED>(kf, cur.k, koff);
       set_v(cur);
-      load_v<D>(vr, cur.v, voff);
+      load_v<D, STREAMED>(vr, cur.v, voff);
     }
 
     // row of this lane in tile t: query row rr of the kv head's N*G rows = (node, head within group)
@@ -577,9 +583,9 @@ __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(
             asm volatile("" ::: "memory");  // keep the Q reads inside the loop (they are the point)
             kb += step;
             vb += step;
-            load_k<D>(kfn, kb, koff);
+            load_k<D, STREAMED>(kfn, kb, koff);
             process_block<QT, D>(st, kf, vr, q_frag, full, mask_of_tile, c, g4, [] {},
-                                 [&] { load_v<D>(vr, vb, voff); });
+                                 [&] { load_v<D, STREAMED>(vr, vb, voff); });
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -594,9 +600,9 @@ __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(
         BlockSrc nxt = cur;
         if (more) nxt = locate(blk + KW);
         if constexpr (kDeep) {
-          if (more) { set_k(nxt); load_k<D>(kfn, nxt.k, koff); }
+          if (more) { set_k(nxt); load_k<D, STREAMED>(kfn, nxt.k, koff); }
           process_block<QT, D>(st, kf, vr, q_frag, cur, mask_of_tile, c, g4, [] {},
-                               [&] { if (more) { set_v(nxt); load_v<D>(vr, nxt.v, voff); } });
+                               [&] { if (more) { set_v(nxt); load_v<D, STREAMED>(vr, nxt.v, voff); } });
           if (more) {
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
@@ -605,8 +611,8 @@ __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(
           }
         } else {
           process_block<QT, D>(st, kf, vr, q_frag, cur, mask_of_tile, c, g4,
-                               [&] { if (more) { set_k(nxt); load_k<D>(kf, nxt.k, koff); } }, [] {});
-          if (more) { set_v(nxt); load_v<D>(vr, nxt.v, voff); }
+                               [&] { if (more) { set_k(nxt); load_k<D, STREAMED>(kf, nxt.k, koff); } }, [] {});
+          if (more) { set_v(nxt); load_v<D, STREAMED>(vr, nxt.v, voff); }
         }
         if (!more) break;
         cur = nxt;
@@ -1403,14 +1409,14 @@ fspad_status check_desc(const fspad_attn_desc* d) {
   return FSPAD_OK;
 }
 
-template <int D>
+template <int D, bool STREAMED>
 void launch_bf16(const Plan& pl, const AttnParams& prm, hipStream_t stream) {
   const dim3 grid((unsigned)prm.n_wgs);
   switch (pl.QT) {
-    case 1: hipLaunchKernelGGL((tree_attn_bf16_kernel<1, D>), grid, dim3(256), 0, stream, prm); break;
-    case 2: hipLaunchKernelGGL((tree_attn_bf16_kernel<2, D>), grid, dim3(256), 0, stream, prm); break;
-    case 3: hipLaunchKernelGGL((tree_attn_bf16_kernel<3, D>), grid, dim3(256), 0, stream, prm); break;
-    default: hipLaunchKernelGGL((tree_attn_bf16_kernel<4, D>), grid, dim3(256), 0, stream, prm); break;
+    case 1: hipLaunchKernelGGL((tree_attn_bf16_kernel<1, D, STREAMED>), grid, dim3(256), 0, stream, prm); break;
+    case 2: hipLaunchKernelGGL((tree_attn_bf16_kernel<2, D, STREAMED>), grid, dim3(256), 0, stream, prm); break;
+    case 3: hipLaunchKernelGGL((tree_attn_bf16_kernel<3, D, STREAMED>), grid, dim3(256), 0, stream, prm); break;
+    default: hipLaunchKernelGGL((tree_attn_bf16_kernel<4, D, STREAMED>), grid, dim3(256), 0, stream, prm); break;
   }
 }
 
@@ -1568,10 +1574,11 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         // (head dim 64 leaves registers for three wavefronts per SIMD: three key groups; 43.1 -> 40.6 us on a
         // 64/8-head, 16384-key, 60-node call, 70.7 -> 64.5 us at 32768 keys)
         else hipLaunchKernelGGL((tree_attn_gqa_kernel<64, 4, 3>), dim3((unsigned)sl.n_wgs), dim3(768), 0, stream, sl);
-      } else if (d.head_dim == 128) {
-        launch_bf16<128>(pl, sl, stream);
       } else {
-        launch_bf16<64>(pl, sl, stream);
+        // keys and values of the call, read once each (one slab group per kv head)
+        const bool streamed = (size_t)total * (2 * kBlockKeys * 2) * d.head_dim > fspad_detail::kCacheBytes;
+        if (d.head_dim == 128) streamed ? launch_bf16<128, true>(pl, sl, stream) : launch_bf16<128, false>(pl, sl, stream);
+        else streamed ? launch_bf16<64, true>(pl, sl, stream) : launch_bf16<64, false>(pl, sl, stream);
       }
       if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       // the merge pass runs only if some unit was cut across workgroups

@@ -106,9 +106,9 @@ struct PartialGemmParams {
   Split plan;
 };
 
-template <int MT, bool PACKED>
+template <int MT, bool PACKED, bool STREAMED>
 __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void partial_gemm_kernel(const PartialGemmParams p) {
-  typedef StreamGemm<MT, PACKED> G;
+  typedef StreamGemm<MT, PACKED, STREAMED> G;
   __shared__ __attribute__((aligned(1024))) char lds[G::kLdsBytes];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, g = lane >> 4;
@@ -342,27 +342,28 @@ Split plan_split(int N, int K, int problems, int rows) {
 }
 size_t partial_floats(const Split& s, int rows) { return (size_t)(s.n_slices + s.n_wgs) * rows * kSliceRows; }
 
-template <bool PACKED>
+template <bool PACKED, bool STREAMED>
 void launch_partial(const PartialGemmParams& g, hipStream_t stream) {
   const dim3 grid((unsigned)g.plan.n_wgs), block(64 * fspad_detail::kStreamWaves);
-  if (g.rows <= 16) hipLaunchKernelGGL((partial_gemm_kernel<1, PACKED>), grid, block, 0, stream, g);
-  else if (g.rows <= 32) hipLaunchKernelGGL((partial_gemm_kernel<2, PACKED>), grid, block, 0, stream, g);
-  else if (g.rows <= 48) hipLaunchKernelGGL((partial_gemm_kernel<3, PACKED>), grid, block, 0, stream, g);
-  else if (g.rows <= 64) hipLaunchKernelGGL((partial_gemm_kernel<4, PACKED>), grid, block, 0, stream, g);
-  else hipLaunchKernelGGL((partial_gemm_kernel<8, PACKED>), grid, block, 0, stream, g);
+  if (g.rows <= 16) hipLaunchKernelGGL((partial_gemm_kernel<1, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (g.rows <= 32) hipLaunchKernelGGL((partial_gemm_kernel<2, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (g.rows <= 48) hipLaunchKernelGGL((partial_gemm_kernel<3, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (g.rows <= 64) hipLaunchKernelGGL((partial_gemm_kernel<4, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else hipLaunchKernelGGL((partial_gemm_kernel<8, PACKED, STREAMED>), grid, block, 0, stream, g);
 }
 
-// The partial sums of one projection (or of two that share x's shape and w's), on the stream.
+// The partial sums of one projection (or of two that share x's shape and w's), on the stream. `streamed`: the weights of
+// the whole call exceed the memory-side cache.
 fspad_status linear_partials(const void* x0, const void* x1, const void* w0, const void* w1, int rows, int N, int K,
-                             const Split& plan, float* part, bool packed, hipStream_t stream) {
+                             const Split& plan, float* part, bool packed, bool streamed, hipStream_t stream) {
   PartialGemmParams g{};
   g.x[0] = static_cast<const char*>(x0); g.x[1] = static_cast<const char*>(x1);
   g.w[0] = static_cast<const char*>(w0); g.w[1] = static_cast<const char*>(w1);
   g.part = part; g.rows = rows; g.N = N; g.K = K;
   g.split = w1 ? plan.n_slices / 2 : plan.n_slices;
   g.plan = plan;
-  if (packed) launch_partial<true>(g, stream);
-  else launch_partial<false>(g, stream);
+  if (packed) streamed ? launch_partial<true, true>(g, stream) : launch_partial<true, false>(g, stream);
+  else streamed ? launch_partial<false, true>(g, stream) : launch_partial<false, false>(g, stream);
   return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
 }
 
@@ -422,12 +423,14 @@ extern "C" fspad_status fspad_feature_sampler(int32_t rows, int32_t hidden_dim, 
   char* s_buf = static_cast<char*>(workspace);                       // SiLU(gate) * up, [rows][I] bf16
   float* part = reinterpret_cast<float*>(s_buf + pl.s_bytes);
 
+  const bool streamed = (size_t)3 * hidden_dim * intermediate_dim * 2 > fspad_detail::kCacheBytes;
+
   // up and gate projectors, one launch
   fspad_status st;
-  if ((st = linear_partials(f, e, w_up, w_gate, rows, intermediate_dim, hidden_dim, pl.up, part, packed, stream)) != FSPAD_OK) return st;
+  if ((st = linear_partials(f, e, w_up, w_gate, rows, intermediate_dim, hidden_dim, pl.up, part, packed, streamed, stream)) != FSPAD_OK) return st;
   if ((st = combine<0>(part, pl.up, nullptr, s_buf, nullptr, rows, intermediate_dim, stream)) != FSPAD_OK) return st;
   // down projector and residual
-  if ((st = linear_partials(s_buf, nullptr, w_down, nullptr, rows, hidden_dim, intermediate_dim, pl.down, part, packed, stream)) != FSPAD_OK)
+  if ((st = linear_partials(s_buf, nullptr, w_down, nullptr, rows, hidden_dim, intermediate_dim, pl.down, part, packed, streamed, stream)) != FSPAD_OK)
     return st;
   return combine<1>(part, pl.down, residual ? f : nullptr, eta, nullptr, rows, hidden_dim, stream);
 }
@@ -535,10 +538,12 @@ extern "C" fspad_status fspad_draft_layer(const fspad_draft_layer_desc* desc, co
   float* part = reinterpret_cast<float*>(at); at += pl.part_bytes;
   char* attn_ws = at;
 
+  const bool streamed = (size_t)pl.Hd * (pl.qkv_n + pl.attn_n + 4 * (size_t)pl.I) * 2 > fspad_detail::kCacheBytes;
+
   fspad_status st;
   // q, k, v = rotary(W_qkv rmsnorm(eta))
   if ((st = rms_norm(eta, w->gain_attn, xn, pl.rows, pl.Hd, desc->rms_eps, stream)) != FSPAD_OK) return st;
-  if ((st = linear_partials(xn, nullptr, w->w_qkv, nullptr, pl.rows, pl.qkv_n, pl.Hd, pl.qkv, part, packed, stream)) != FSPAD_OK)
+  if ((st = linear_partials(xn, nullptr, w->w_qkv, nullptr, pl.rows, pl.qkv_n, pl.Hd, pl.qkv, part, packed, streamed, stream)) != FSPAD_OK)
     return st;
   {
     QkvRopeParams r{};
@@ -554,7 +559,7 @@ extern "C" fspad_status fspad_draft_layer(const fspad_draft_layer_desc* desc, co
                        pl.attn_ws_bytes, hip_stream);
   if (st != FSPAD_OK) return st;
   // h = eta + W_o attn
-  if ((st = linear_partials(attn, nullptr, w->w_o, nullptr, pl.rows, pl.Hd, pl.attn_n, pl.o, part, packed, stream)) != FSPAD_OK)
+  if ((st = linear_partials(attn, nullptr, w->w_o, nullptr, pl.rows, pl.Hd, pl.attn_n, pl.o, part, packed, streamed, stream)) != FSPAD_OK)
     return st;
   // and its normalised form for the MLP (whose doubled down projection adds both halves to h)
   {
@@ -564,9 +569,9 @@ extern "C" fspad_status fspad_draft_layer(const fspad_draft_layer_desc* desc, co
     hipLaunchKernelGGL(combine_norm_kernel, dim3((unsigned)pl.rows), dim3(1024), 0, stream, c);
     if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   }
-  if ((st = linear_partials(xn, xn, w->w_up, w->w_gate, pl.rows, pl.I, pl.Hd, pl.up, part, packed, stream)) != FSPAD_OK) return st;
+  if ((st = linear_partials(xn, xn, w->w_up, w->w_gate, pl.rows, pl.I, pl.Hd, pl.up, part, packed, streamed, stream)) != FSPAD_OK) return st;
   if ((st = combine<0>(part, pl.up, nullptr, s, nullptr, pl.rows, pl.I, stream)) != FSPAD_OK) return st;
-  if ((st = linear_partials(s, nullptr, w->w_down, nullptr, pl.rows, 2 * pl.Hd, pl.I, pl.down, part, packed, stream)) != FSPAD_OK)
+  if ((st = linear_partials(s, nullptr, w->w_down, nullptr, pl.rows, 2 * pl.Hd, pl.I, pl.down, part, packed, streamed, stream)) != FSPAD_OK)
     return st;
   return combine<2>(part, pl.down, h, f_tilde, f, pl.rows, 2 * pl.Hd, stream);
 }

@@ -64,10 +64,10 @@ __device__ __forceinline__ unsigned long long pack_best(float v, int i) {
 // around (spread_phase).
 // MODE 0: per slice and row (max, first argmax) for the greedy walk. MODE 1: per slice and row
 // (max, sum of exponentials) and the logits of the draft tokens, for the sampling walk.
-template <int MT, int MODE, bool PACKED>
+template <int MT, int MODE, bool PACKED, bool STREAMED>
 __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_kernel(const LmHeadParams p) {
   using namespace fspad_detail;
-  typedef StreamGemm<MT, PACKED> G;
+  typedef StreamGemm<MT, PACKED, STREAMED> G;
   __shared__ __attribute__((aligned(1024))) char lds[G::kLdsBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
@@ -780,6 +780,16 @@ fspad_status check_lm_head_args(int32_t B, int32_t Nmax, int32_t V, int32_t hidd
   return FSPAD_OK;
 }
 
+template <int MODE, bool PACKED, bool STREAMED>
+void launch_rows(const LmHeadParams& g, dim3 grid, dim3 block, hipStream_t stream) {
+  const int r = g.rows_per_pass;
+  if (r <= 16) hipLaunchKernelGGL((lm_head_kernel<1, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (r <= 32) hipLaunchKernelGGL((lm_head_kernel<2, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (r <= 48) hipLaunchKernelGGL((lm_head_kernel<3, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (r <= 64) hipLaunchKernelGGL((lm_head_kernel<4, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else hipLaunchKernelGGL((lm_head_kernel<8, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+}
+
 // Fills in the launch shape and runs the GEMM in the given mode (0 greedy, 1 sampling).
 template <int MODE, bool PACKED>
 fspad_status launch_lm_head(LmHeadParams& g, int32_t hidden_dim, hipStream_t stream) {
@@ -793,11 +803,8 @@ fspad_status launch_lm_head(LmHeadParams& g, int32_t hidden_dim, hipStream_t str
   const int r = g.rows_per_pass;
   if (r <= 128) {
     const dim3 grid((unsigned)(g.n_slices < kComputeUnits ? g.n_slices : kComputeUnits), (unsigned)g.n_passes), block(512);
-    if (r <= 16) hipLaunchKernelGGL((lm_head_kernel<1, MODE, PACKED>), grid, block, 0, stream, g);
-    else if (r <= 32) hipLaunchKernelGGL((lm_head_kernel<2, MODE, PACKED>), grid, block, 0, stream, g);
-    else if (r <= 48) hipLaunchKernelGGL((lm_head_kernel<3, MODE, PACKED>), grid, block, 0, stream, g);
-    else if (r <= 64) hipLaunchKernelGGL((lm_head_kernel<4, MODE, PACKED>), grid, block, 0, stream, g);
-    else hipLaunchKernelGGL((lm_head_kernel<8, MODE, PACKED>), grid, block, 0, stream, g);
+    if ((size_t)g.V * g.K * 2 > fspad_detail::kCacheBytes) launch_rows<MODE, PACKED, true>(g, grid, block, stream);
+    else launch_rows<MODE, PACKED, false>(g, grid, block, stream);
     return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
   }
   const dim3 grid((unsigned)((g.n_slices + 7) / 8 * 8 * g.n_passes));

@@ -66,6 +66,13 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // matrix: 6.0 TB/s; with the phases of an XCD's workgroups 8 stages apart 2.9, all equal 4.6 TB/s.
 __device__ __forceinline__ unsigned spread_phase(int w, int C) { return (3u * ((unsigned)w / 8u + ((unsigned)w & 7u))) % (unsigned)C; }
 
+// The memory-side cache. What a call reads of more than that -- weights, keys and values, each byte once -- is gone before
+// the next call comes back to it, and is read with the non-temporal hint, which spares the caches the replacement: draft
+// step of 4 rows (4096 / 11008) 190 -> 180 us, of 40 rows 533 -> 500 us, 8B head 202 -> 197 us, attention of 33B layers
+// 1705 -> 1674 us. What may stay in the cache from one call to the next is slower with the hint: draft step at
+// hidden size 2048 88 -> 100 us, 2048 x 32000 head 28 -> 31 us, a 7B layer by itself 38.8 -> 40.9 us.
+constexpr size_t kCacheBytes = (size_t)256 << 20;
+
 constexpr int kStreamWaves = 8;
 constexpr int kSliceRows = 16 * kStreamWaves;   // rows of W per slice
 constexpr int kUnitK = 128;                     // k per unit of a wavefront's ring
@@ -74,7 +81,8 @@ constexpr int kUnitBytes = 16 * kUnitK * 2;
 // MT: 16-row tiles of X. PACKED: W is stored tile by tile instead of row by row -- the 16 rows x 32 k
 // of one operand are 1 KB in lane order (lane (n, g) at byte 16 * (n + 16 g)), the k-steps of a
 // 16-row tile follow one another, then the next 16 rows. The sums run in the same order either way.
-template <int MT, bool PACKED>
+// STREAMED: the copies of W carry the non-temporal hint (see kCacheBytes).
+template <int MT, bool PACKED, bool STREAMED = false>
 struct StreamGemm {
   static constexpr int kUnits = MT <= 4 ? 2 : 1;               // units per stage
   static constexpr int kStageK = kUnits * kUnitK;              // 256 or 128
@@ -162,7 +170,7 @@ struct StreamGemm {
       const char* b = wtile + (size_t)at.at * (PACKED ? 4096 : 256);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        __builtin_amdgcn_global_load_lds((StreamGlobalPtr)(b + woff[i]), (StreamLdsPtr)(ring + slot * kUnitBytes + i * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((StreamGlobalPtr)(b + woff[i]), (StreamLdsPtr)(ring + slot * kUnitBytes + i * 1024), 16, 0, STREAMED ? 2 : 0);
     };
     auto request_x = [&](const Cursor& at, int buf) {
       const char* b = (at.slice >= src.split ? src.x[1] : src.x[0]) + (size_t)at.at * kXRowBytes;
