@@ -1333,6 +1333,10 @@ int blocks_of(int kv_len, int n_nodes) {
   return (kv_len + kBlockKeys - 1) / kBlockKeys + (n_nodes + kBlockKeys - 1) / kBlockKeys;
 }
 
+// Wavefront sets that split a workgroup's keys: the two key groups of the shared-stage kernel, or
+// the wavefronts that do not take a row slab of their own.
+int key_waves(const Plan& pl) { return pl.shared_stage ? 2 : (pl.WS >= 4 ? 1 : 4 / pl.WS); }
+
 // Workgroup count for `total_blocks` flat blocks in `units` units: two resident workgroups per
 // compute unit for 16-row tiles, one otherwise, but no workgroup with fewer
 // than 2 blocks per key-splitting wave.
@@ -1348,9 +1352,7 @@ int blocks_of(int kv_len, int n_nodes) {
 // (32 heads, 8192 keys, 4 nodes: 34 us against 31). Units of a few blocks per wavefront stay whole when there
 // are enough of them: the merge costs more than the blocks (2 x 32 heads, 500 keys: 13.1 us against 14.2).
 int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool uniform, int forced) {
-  // wavefront sets that split a workgroup's keys: the two key groups of the shared-stage kernel, or
-  // the wavefronts that do not take a row slab of their own
-  const int KW = pl.shared_stage ? 2 : (pl.WS >= 4 ? 1 : 4 / pl.WS);
+  const int KW = key_waves(pl);
   // (the shared-stage kernel's eight wavefronts of up to 256 registers fill a compute unit by themselves)
   // (32-row tiles spill when two workgroups share a compute unit)
   const int64_t resident = pl.QT == 1 ? 2 * kComputeUnits : kComputeUnits;
@@ -1390,6 +1392,17 @@ int host_owner_of(int64_t x, int64_t T, int W) {
 int groups_of(const fspad_attn_desc& d, const Plan& pl, int n) {
   const int rows = n * (d.n_q_heads / d.n_kv_heads), slabs = (rows + 16 * pl.QT - 1) / (16 * pl.QT);
   return (slabs + pl.WS - 1) / pl.WS;
+}
+
+// Partial slots of a plan: one per (unit, workgroup) boundary at most. 32-row tiles get more than two workgroups per
+// compute unit only where each holds a whole unit, which leaves no partial results: not more slots then than a cut
+// batch of that size needs.
+int64_t slots_of(const Plan& pl, int64_t units, int64_t wgs, int64_t total_blocks, int forced) {
+  if (forced == 0 && pl.QT == 2 && !pl.shared_stage && wgs > 2 * kComputeUnits) {
+    wgs = 2 * kComputeUnits;
+    if (wgs > total_blocks / (2 * key_waves(pl))) wgs = total_blocks / (2 * key_waves(pl));
+  }
+  return units + wgs;
 }
 
 size_t slot_bytes(const fspad_attn_desc& d, const Plan& pl) {
@@ -1451,7 +1464,7 @@ extern "C" size_t fspad_tree_attn_workspace_bytes(const fspad_attn_desc* desc, i
     int64_t wgs = plan_wgs(pl, total, units, true, desc->workgroups);
     const int64_t wgs_cut = plan_wgs(pl, total, units, false, desc->workgroups);  // a ragged batch of the same size
     if (wgs_cut > wgs) wgs = wgs_cut;
-    const int64_t slots = units + wgs;
+    const int64_t slots = slots_of(pl, units, wgs, total, desc->workgroups);
     const size_t bytes = (size_t)slots * slot_bytes(*desc, pl);
     if (bytes > need) need = bytes;
   }
@@ -1546,7 +1559,8 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       // units of a sequence: the slab groups that its own tree fills, times the kv heads
       auto units_of = [&](int i) { return (int64_t)d.n_kv_heads * groups_of(d, pl, sl.n_nodes[i]); };
       const int64_t full_units = (int64_t)nb * d.n_kv_heads * pl.GY;   // (partial slots are numbered as if every tree were full)
-      const int64_t full_wgs = plan_wgs(pl, (int64_t)d.n_kv_heads * pl.GY * seq_blocks, full_units, uniform, d.workgroups);
+      const int64_t full_total = (int64_t)d.n_kv_heads * pl.GY * seq_blocks;
+      const int64_t full_wgs = plan_wgs(pl, full_total, full_units, uniform, d.workgroups);
       int64_t total = 0, units = 0;
       for (int i = 0; i < nb; ++i) {
         sl.bstart[i] = (int32_t)total;
@@ -1567,7 +1581,7 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       if (sl.n_wgs > full_wgs) sl.n_wgs = (int32_t)full_wgs;
       sl.wg_quot = (int32_t)(total / sl.n_wgs);
       sl.wg_rem = (int32_t)(total % sl.n_wgs);
-      const size_t need = (size_t)(full_units + full_wgs) * slot_bytes(d, pl);
+      const size_t need = (size_t)slots_of(pl, full_units, full_wgs, full_total, d.workgroups) * slot_bytes(d, pl);
       if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 15)) return FSPAD_ERR_WORKSPACE;
       if (pl.shared_stage) {
         if (d.head_dim == 128) hipLaunchKernelGGL((tree_attn_gqa_kernel<128, 4, 2>), dim3((unsigned)sl.n_wgs), dim3(512), 0, stream, sl);
