@@ -62,6 +62,7 @@ struct AttnParams {
   // one sequence (0 otherwise) and those two numbers, so that a workgroup finds its sequence and its
   // lengths by arithmetic instead of dependent loads from the arrays below
   int32_t seq_blocks, same_len, same_nodes;
+  int32_t setup;    // blocks that every unit counts for beyond its own in the flat list (ragged batches; setup_blocks)
   int32_t kv_len[kMaxBatchPerLaunch];
   int32_t bstart[kMaxBatchPerLaunch + 1];  // first flat block of each sequence; bstart[B] = total_blocks
   int32_t n_nodes[kMaxBatchPerLaunch];
@@ -88,11 +89,11 @@ struct AttnArgs {
   uint32_t g_magic, gy_magic;
   int32_t out_bf16;
   float scale;
-  int32_t seq_blocks, same_len, same_nodes;
+  int32_t seq_blocks, same_len, same_nodes, setup;
   KernargI32 kv_len, bstart, n_nodes;
 };
 static_assert(offsetof(AttnParams, stride_batch) == 64 && offsetof(AttnParams, B) == 88 && offsetof(AttnParams, total_blocks) == 128 &&
-              offsetof(AttnParams, scale) == 152 && offsetof(AttnParams, same_nodes) == 164 && offsetof(AttnParams, kv_len) == 168,
+              offsetof(AttnParams, scale) == 152 && offsetof(AttnParams, same_nodes) == 164 && offsetof(AttnParams, setup) == 168 && offsetof(AttnParams, kv_len) == 172,
               "fetch_args reads the scalars by their offsets");
 
 __device__ __forceinline__ AttnArgs fetch_args() {
@@ -122,7 +123,7 @@ __device__ __forceinline__ AttnArgs fetch_args() {
   r.out_bf16 = c[5];
   const int scale_bits = c[6];   // (a bit cast straight from the vector element reads element 0)
   r.scale = __builtin_bit_cast(float, scale_bits);
-  r.seq_blocks = c[7]; r.same_len = c[8]; r.same_nodes = c[9];
+  r.seq_blocks = c[7]; r.same_len = c[8]; r.same_nodes = c[9]; r.setup = c[10];
   r.kv_len = (KernargI32)(ka + offsetof(AttnParams, kv_len));
   r.bstart = (KernargI32)(ka + offsetof(AttnParams, bstart));
   r.n_nodes = (KernargI32)(ka + offsetof(AttnParams, n_nodes));
@@ -386,7 +387,9 @@ __device__ __forceinline__ void process_block(RowState<QT, D>& st, const bf16x8 
 // or a few *segments* (a run of blocks of one unit). A segment that is a whole unit is written
 // to `out` directly; otherwise its un-normalised (O, max, sum) goes to partial slot unit+w and the
 // merge kernel finishes the unit.
-template <int QT, int D, bool STREAMED>
+// RAGGED: units count for p.setup blocks more than they have (a form of its own: in the other one the bookkeeping
+// costs the 64-row tiles registers they do not have, 4 x 52 heads, 4096 keys: 83 -> 98 us).
+template <int QT, int D, bool STREAMED, bool RAGGED>
 __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(const AttnParams) {
   const AttnArgs p = fetch_args();
   constexpr int KS = D / 32;
@@ -435,9 +438,20 @@ __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
     const unsigned rel = r - seq_first_block(p, b);
-    const int ub = (int)(rel / (unsigned)n_blocks);              // unit within the sequence: (g, y)
-    const int seg_begin = (int)(rel - (unsigned)ub * (unsigned)n_blocks);
-    const int seg_count = min(n_blocks - seg_begin, (int)(r1 - r));
+    const int counted = RAGGED ? n_blocks + p.setup : n_blocks;  // what the unit counts for: its set-up first, then its blocks
+    const int ub = (int)(rel / (unsigned)counted);               // unit within the sequence: (g, y)
+    int seg_begin = (int)(rel - (unsigned)ub * (unsigned)counted);
+    int seg_count = min(counted - seg_begin, (int)(r1 - r));
+    const int count = seg_count;
+    if constexpr (RAGGED) {
+      const int end = seg_begin + count - p.setup;
+      seg_begin = max(seg_begin - p.setup, 0);
+      seg_count = end - seg_begin;
+      if (seg_count <= 0) {   // nothing but set-up
+        r += (unsigned)count;
+        continue;
+      }
+    }
     const int g = ub;   // one slab group per kv head in every plan of this kernel
     const int unit = b * p.Hkv + ub;
     const bool whole_unit = seg_count == n_blocks;
@@ -697,7 +711,7 @@ __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(
           write_quad(t, e0, o4, st.m[t], lsum[t]);
         }
     }
-    r += (unsigned)seg_count;
+    r += (unsigned)count;
     if (b + 1 < p.B && r >= seq_first_block(p, b + 1)) ++b;
     if ((KW > 1 || kQInLds) && r < r1) __syncthreads();  // the LDS buffers are reused by the next segment
   }
@@ -798,9 +812,14 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
     const unsigned rel = r - seq_first_block(p, b);
-    const int ub = (int)(rel / (unsigned)n_blocks);
-    const int seg_begin = (int)(rel - (unsigned)ub * (unsigned)n_blocks);
-    const int seg_count = min(n_blocks - seg_begin, (int)(r1 - r));
+    const int counted = n_blocks + p.setup;
+    const int ub = (int)(rel / (unsigned)counted);
+    const int from = (int)(rel - (unsigned)ub * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
+    const int seg_begin = max(from - p.setup, 0), seg_count = from + count - p.setup - seg_begin;
+    if (seg_count <= 0) {   // nothing but set-up
+      r += (unsigned)count;
+      continue;
+    }
     const int n_slabs = seq_slabs(p, n, ROWS), n_groups = seq_groups(p, n_slabs);
     const int g = head_of(p, ub, n_groups), y = ub - g * n_groups;
     const int unit = b * p.Hkv * p.GY + ub;
@@ -1067,7 +1086,7 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
         }
       }
     }
-    r += (unsigned)seg_count;
+    r += (unsigned)count;
     if (b + 1 < p.B && r >= seq_first_block(p, b + 1)) ++b;
     __syncthreads();  // every wavefront is done with the stages before the next segment refills them
   }
@@ -1094,7 +1113,7 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
   if (ub >= p.Hkv * n_groups) return;   // a tree smaller than the largest: no such unit
   const int g = head_of(p, ub, n_groups), y = ub - g * n_groups;
   const int n_blocks = (seq_len(p, b) + kBlockKeys - 1) / kBlockKeys + (seq_nodes(p, b) + kBlockKeys - 1) / kBlockKeys;
-  const unsigned fs = seq_first_block(p, b) + (unsigned)ub * (unsigned)n_blocks;
+  const unsigned fs = seq_first_block(p, b) + (unsigned)ub * (unsigned)(n_blocks + p.setup) + (unsigned)p.setup;
   const int w0 = owner_of(p, fs, inv_total), w1 = owner_of(p, fs + (unsigned)n_blocks - 1u, inv_total);
   if (w0 == w1) return;  // written directly by the one workgroup that held the whole unit
   const int rows_per_unit = p.WS * rows_per_slab;
@@ -1394,6 +1413,14 @@ int groups_of(const fspad_attn_desc& d, const Plan& pl, int n) {
   return (slabs + pl.WS - 1) / pl.WS;
 }
 
+// What a unit costs a workgroup beyond its blocks, in blocks: Q, the ramp of the stream, merge and output. In a ragged batch
+// the flat list counts every unit for that much more: an even split of the blocks alone gave the workgroups of the
+// short sequences a dozen units each, and the call lasted until they were done. Grouped heads, 16 sequences of 131 to
+// 6011 keys, 17 to 60 nodes: 98 us without, 77 / 72 / 78 us with 8 / 20 / 40; 64-row tiles, 2 x 32 heads, 100 to 5000 keys: 43,
+// 44 / 41 / 42; 32-row tiles, 8 x 32 heads, 200 to 3000 keys: 51, 44 / 46 / 52; 16-row tiles (two workgroups per
+// compute unit, which cover each other's set-up), 16 x 32 heads, 64 to 900 keys: 36, 39 / 40 / 39.
+int setup_blocks(const Plan& pl) { return pl.shared_stage || pl.QT >= 3 ? 20 : (pl.QT == 2 ? 8 : 0); }
+
 // Partial slots of a plan: one per (unit, workgroup) boundary at most. 32-row tiles get more than two workgroups per
 // compute unit only where each holds a whole unit, which leaves no partial results: not more slots then than a cut
 // batch of that size needs.
@@ -1422,15 +1449,20 @@ fspad_status check_desc(const fspad_attn_desc* d) {
   return FSPAD_OK;
 }
 
-template <int D, bool STREAMED>
+template <int D, bool STREAMED, bool RAGGED>
 void launch_bf16(const Plan& pl, const AttnParams& prm, hipStream_t stream) {
   const dim3 grid((unsigned)prm.n_wgs);
   switch (pl.QT) {
-    case 1: hipLaunchKernelGGL((tree_attn_bf16_kernel<1, D, STREAMED>), grid, dim3(256), 0, stream, prm); break;
-    case 2: hipLaunchKernelGGL((tree_attn_bf16_kernel<2, D, STREAMED>), grid, dim3(256), 0, stream, prm); break;
-    case 3: hipLaunchKernelGGL((tree_attn_bf16_kernel<3, D, STREAMED>), grid, dim3(256), 0, stream, prm); break;
-    default: hipLaunchKernelGGL((tree_attn_bf16_kernel<4, D, STREAMED>), grid, dim3(256), 0, stream, prm); break;
+    case 1: hipLaunchKernelGGL((tree_attn_bf16_kernel<1, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm); break;
+    case 2: hipLaunchKernelGGL((tree_attn_bf16_kernel<2, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm); break;
+    case 3: hipLaunchKernelGGL((tree_attn_bf16_kernel<3, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm); break;
+    default: hipLaunchKernelGGL((tree_attn_bf16_kernel<4, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm); break;
   }
+}
+template <int D>
+void launch_bf16(const Plan& pl, const AttnParams& prm, bool streamed, hipStream_t stream) {
+  if (prm.setup > 0) streamed ? launch_bf16<D, true, true>(pl, prm, stream) : launch_bf16<D, false, true>(pl, prm, stream);
+  else streamed ? launch_bf16<D, true, false>(pl, prm, stream) : launch_bf16<D, false, false>(pl, prm, stream);
 }
 
 // Nodes per workgroup of the fp32 kernel: a node of its own re-reads all of K and V through L2, which costs
@@ -1563,14 +1595,11 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       const int64_t full_wgs = plan_wgs(pl, full_total, full_units, uniform, d.workgroups);
       int64_t total = 0, units = 0;
       for (int i = 0; i < nb; ++i) {
-        sl.bstart[i] = (int32_t)total;
         total += units_of(i) * blocks_of(sl.kv_len[i], sl.n_nodes[i]);
         units += units_of(i);
         uniform = uniform && units_of(i) == units_of(0);
         if (total > kMaxFlatBlocks) return FSPAD_ERR_SHAPE;  // the kernels index blocks with 32 bits
       }
-      sl.bstart[nb] = (int32_t)total;
-      sl.total_blocks = (int32_t)total;
       bool same = true;
       for (int i = 1; i < nb; ++i) same = same && sl.kv_len[i] == sl.kv_len[0] && sl.n_nodes[i] == sl.n_nodes[0];
       sl.seq_blocks = same ? (int32_t)(units_of(0) * blocks_of(sl.kv_len[0], sl.n_nodes[0])) : 0;
@@ -1579,6 +1608,15 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       // never more workgroups than full trees would have: the workspace a call needs does not depend on the trees
       sl.n_wgs = plan_wgs(pl, total, units, uniform, d.workgroups);
       if (sl.n_wgs > full_wgs) sl.n_wgs = (int32_t)full_wgs;
+      sl.setup = uniform || total + units * setup_blocks(pl) > kMaxFlatBlocks ? 0 : setup_blocks(pl);
+      const int64_t kv_blocks = total;
+      total = 0;
+      for (int i = 0; i < nb; ++i) {
+        sl.bstart[i] = (int32_t)total;
+        total += units_of(i) * (blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup);
+      }
+      sl.bstart[nb] = (int32_t)total;
+      sl.total_blocks = (int32_t)total;
       sl.wg_quot = (int32_t)(total / sl.n_wgs);
       sl.wg_rem = (int32_t)(total % sl.n_wgs);
       const size_t need = (size_t)slots_of(pl, full_units, full_wgs, full_total, d.workgroups) * slot_bytes(d, pl);
@@ -1590,18 +1628,18 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         else hipLaunchKernelGGL((tree_attn_gqa_kernel<64, 4, 3>), dim3((unsigned)sl.n_wgs), dim3(768), 0, stream, sl);
       } else {
         // keys and values of the call, read once each (one slab group per kv head)
-        const bool streamed = (size_t)total * (2 * kBlockKeys * 2) * d.head_dim > fspad_detail::kCacheBytes;
-        if (d.head_dim == 128) streamed ? launch_bf16<128, true>(pl, sl, stream) : launch_bf16<128, false>(pl, sl, stream);
-        else streamed ? launch_bf16<64, true>(pl, sl, stream) : launch_bf16<64, false>(pl, sl, stream);
+        const bool streamed = (size_t)kv_blocks * (2 * kBlockKeys * 2) * d.head_dim > fspad_detail::kCacheBytes;
+        if (d.head_dim == 128) launch_bf16<128>(pl, sl, streamed, stream);
+        else launch_bf16<64>(pl, sl, streamed, stream);
       }
       if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       // the merge pass runs only if some unit was cut across workgroups
       bool any_cut = false;
       for (int i = 0; i < nb && !any_cut; ++i) {
-        const int64_t nblk = blocks_of(sl.kv_len[i], sl.n_nodes[i]);
+        const int64_t nblk = blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup;
         for (int64_t ub = 0; ub < units_of(i) && !any_cut; ++ub) {
           const int64_t fs = sl.bstart[i] + ub * nblk;
-          any_cut = host_owner_of(fs, total, sl.n_wgs) != host_owner_of(fs + nblk - 1, total, sl.n_wgs);
+          any_cut = host_owner_of(fs + sl.setup, total, sl.n_wgs) != host_owner_of(fs + nblk - 1, total, sl.n_wgs);
         }
       }
       if (any_cut) {

@@ -317,3 +317,14 @@ def test_bf16_workgroups_aligned_with_units(H, B, Hkv, G, N, L):
     two or three pieces of each, short units kept whole, and (4 x 39, 500 keys) just below the border."""
     case = H.AttnCase(700 + Hkv + N, B, N, Hkv * G, Hkv, 64, L, "bf16", n_nodes=[N] * B)
     _check(H, case, H.TOL["bf16"])
+
+
+@pytest.mark.parametrize("Hq,Hkv,N,D", [(4, 4, 60, 128), (4, 4, 26, 64), (4, 4, 9, 128), (16, 2, 40, 128), (28, 4, 33, 64)])
+@pytest.mark.parametrize("kv_len", [[2000, 0, 1, 33, 700, 5], [0, 31, 32, 0, 64, 1500], [3, 2, 1, 0, 0, 90]])
+@pytest.mark.parametrize("splits", [0, 5, 40, 4096])
+def test_bf16_ragged_batches_count_set_up(H, Hq, Hkv, N, D, kv_len, splits):
+    """Long and very short sequences in one batch: units count for more than their blocks in the flat split, so that
+    cuts fall inside a unit's set-up, workgroups get nothing but set-up, and units are cut anywhere."""
+    case = H.AttnCase(600 + N + len(kv_len), 6, N, Hq, Hkv, D, max(kv_len), "bf16", kv_len=kv_len,
+                      n_nodes=[N, 1, max(1, N // 2), N, 3, max(1, N // 3)])
+    _check(H, case, H.TOL["bf16"], **({"splits": splits} if splits else {}))
