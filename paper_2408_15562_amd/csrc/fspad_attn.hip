@@ -1423,9 +1423,9 @@ int setup_blocks(const Plan& pl) { return pl.shared_stage || pl.QT >= 3 ? 20 : (
 
 // Partial slots of a plan: one per (unit, workgroup) boundary at most. 32-row tiles get more than two workgroups per
 // compute unit only where each holds a whole unit, which leaves no partial results: not more slots then than a cut
-// batch of that size needs.
+// batch of that size needs. More units than a launch has workgroups (kMaxWorkgroups) do not stay whole.
 int64_t slots_of(const Plan& pl, int64_t units, int64_t wgs, int64_t total_blocks, int forced) {
-  if (forced == 0 && pl.QT == 2 && !pl.shared_stage && wgs > 2 * kComputeUnits) {
+  if (forced == 0 && pl.QT == 2 && !pl.shared_stage && wgs > 2 * kComputeUnits && wgs == units) {
     wgs = 2 * kComputeUnits;
     if (wgs > total_blocks / (2 * key_waves(pl))) wgs = total_blocks / (2 * key_waves(pl));
   }

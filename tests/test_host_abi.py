@@ -115,6 +115,33 @@ def test_attn_argument_checks_need_no_gpu(lib):
     assert binding.fspad_tree_attn_workspace_bytes(_desc(head_dim=96), 2048) == 0
 
 
+def _highest_partial_slot(units, blocks_per_unit, wgs):
+    """Highest partial slot (unit + workgroup) of equally long units cut over an even split of their blocks: every
+    workgroup that holds a part of a unit, but not all of it, writes one; -1 if every unit is whole."""
+    unit = np.arange(units, dtype=np.int64)
+    total = units * blocks_per_unit
+    first, last = unit * blocks_per_unit, (unit + 1) * blocks_per_unit - 1
+    w0, w1 = ((first + 1) * wgs - 1) // total, ((last + 1) * wgs - 1) // total   # the last w with w * total // wgs <= x
+    assert np.all(w0 * total // wgs <= first) and np.all((w1 + 1) * total // wgs > last)
+    cut = w0 != w1
+    return int((unit + w1)[cut].max()) if cut.any() else -1
+
+
+@pytest.mark.parametrize("B,Hkv", [(1, 400), (4, 150), (1, 512), (1, 513), (128, 255), (128, 256), (1, 32769), (128, 257),
+                                   (128, 300), (1, 40000)])
+@pytest.mark.parametrize("kv_len", [0, 20, 500])
+def test_attn_workspace_holds_every_partial_slot(B, Hkv, kv_len):
+    """32-row tiles with about as many units as a launch takes workgroups (one workgroup per whole unit up to 32768, fewer
+    than units beyond that), or cut over one workgroup per compute unit as a ragged batch would be."""
+    units, blocks = B * Hkv, (kv_len + 31) // 32 + 1
+    size = binding.fspad_tree_attn_workspace_bytes(_desc(batch=B, n_q_heads=Hkv, n_kv_heads=Hkv), kv_len)
+    slot = 32 * (128 + 2) * 4
+    whole = _highest_partial_slot(units, blocks, min(units, 32768))
+    assert (whole >= 0) == (units > 32768 and blocks > 1)   # (units of one block are never cut)
+    cut = _highest_partial_slot(units, blocks, max(1, min(256, units * blocks // 8)))
+    assert size >= (max(whole, cut) + 1) * slot
+
+
 def test_accept_argument_checks_need_no_gpu(lib):
     g, s = lib.fspad_tree_accept_greedy, lib.fspad_tree_accept_sample
     fake = ctypes.c_void_p(0x1000)
