@@ -310,6 +310,17 @@ def test_bf16_trees_smaller_than_the_largest(H, Hq, Hkv, D, N, n_nodes, splits):
     assert torch.equal(out, ref.to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(64, 8, 128), (12, 2, 64), (106, 53, 64)])
+@pytest.mark.parametrize("N,n_nodes", [(26, [26, 11, 16, 23]), (32, [3, 32, 1, 9]), (64, [3, 3, 5, 2])])
+@pytest.mark.parametrize("L", [0, 26, 300])
+def test_bf16_units_equally_long_in_trees_of_different_sizes(H, Hq, Hkv, D, N, n_nodes, L):
+    """Sequences of equally many key blocks whose trees fill different numbers of slab groups: units stay aligned with the
+    workgroups (whole, or the same number of pieces each, also where full trees would have had fewer workgroups)."""
+    kv_len = [L, max(0, L - 5), max(0, L - 9), max(0, L - 11)]
+    case = H.AttnCase(850 + N + L, 4, N, Hq, Hkv, D, L, "bf16", kv_len=kv_len, n_nodes=n_nodes, l_cap=L + 1)
+    _check(H, case, H.TOL["bf16"])
+
+
 @pytest.mark.parametrize("B,Hkv,G,N,L", [(4, 40, 1, 5, 130), (4, 52, 1, 26, 33), (2, 40, 1, 40, 700), (2, 52, 1, 9, 1100),
                                          (2, 32, 1, 60, 300), (3, 8, 4, 40, 900), (5, 8, 1, 3, 64), (4, 39, 1, 4, 500)])
 def test_bf16_workgroups_aligned_with_units(H, B, Hkv, G, N, L):
