@@ -1369,7 +1369,8 @@ int key_waves(const Plan& pl) { return pl.shared_stage ? 2 : (pl.WS >= 4 ? 1 : 4
 // unit, 200 of a whole one on fewer than three quarters of them), which straddling costs less than idle units do (4 x 40 heads, 8192 keys, 4 nodes: 129 us
 // against 120; 2 x 52 heads: 94 against 84), nor where 16-row tiles fill two workgroups per unit evenly
 // (32 heads, 8192 keys, 4 nodes: 34 us against 31). Units of a few blocks per wavefront stay whole when there
-// are enough of them: the merge costs more than the blocks (2 x 32 heads, 500 keys: 13.1 us against 14.2).
+// are enough of them (a quarter of the compute units, at most 5 blocks each): the merge costs more than the blocks
+// (D = 128, 60 nodes, 17 blocks: 104 units 18.1 us whole, 21.5 in two pieces each, 29.4 unaligned; 64 units 17.7, 19.4, 28.1).
 int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool uniform, int forced) {
   const int KW = key_waves(pl);
   // (the shared-stage kernel's eight wavefronts of up to 256 registers fill a compute unit by themselves)
@@ -1384,8 +1385,9 @@ int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool uniform, 
     if (units <= kComputeUnits) {
       int64_t pieces = (blocks_per_unit + 2 * KW - 1) / (2 * KW);
       if (pieces > kComputeUnits / units) pieces = kComputeUnits / units;
-      if (units >= kComputeUnits / 4 && blocks_per_unit <= 5 * KW) pieces = 1;
-      const bool is_short = blocks_per_unit <= 4 * KW * pieces;   // at most 4 blocks per wave
+      const bool few_blocks = units >= kComputeUnits / 4 && blocks_per_unit <= 5 * KW;
+      if (few_blocks) pieces = 1;
+      const bool is_short = few_blocks || blocks_per_unit <= 4 * KW * pieces;   // at most 4 (5 in whole units) blocks per wave
       const bool fills = 5 * units * pieces >= 3 * (wgs < kComputeUnits ? wgs : kComputeUnits);
       const bool even_anyway = pl.QT == 1 && (2 * kComputeUnits) % units == 0;
       const int64_t longest = pieces > 1 ? 100 * pieces : (4 * units >= 3 * kComputeUnits ? total_blocks : 200);
