@@ -389,8 +389,9 @@ __device__ __forceinline__ void process_block(RowState<QT, D>& st, const bf16x8 
 // merge kernel finishes the unit.
 // RAGGED: units count for p.setup blocks more than they have (a form of its own: in the other one the bookkeeping
 // costs the 64-row tiles registers they do not have, 4 x 52 heads, 4096 keys: 83 -> 98 us).
-template <int QT, int D, bool STREAMED, bool RAGGED>
-__global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(const AttnParams) {
+// PAIR: two workgroups per compute unit, for launches of more workgroups than compute units (launch_bf16).
+template <int QT, int D, bool STREAMED, bool RAGGED, bool PAIR = false>
+__global__ __launch_bounds__(256, (QT == 1 || PAIR ? 2 : 1)) void tree_attn_bf16_kernel(const AttnParams) {
   const AttnArgs p = fetch_args();
   constexpr int KS = D / 32;
   constexpr int DT = D / 16;
@@ -398,10 +399,10 @@ __global__ __launch_bounds__(256, (QT == 1 ? 2 : 1)) void tree_attn_bf16_kernel(
   // merge buffers: 4 wavefronts x (QT*DT accumulators + QT stats) x 64 lanes. With large row tiles
   // the Q fragments of the 4 wavefronts live in lane-private LDS slots instead of registers; they are
   // dead once a segment's stream is done, so they share the space of the merge buffers.
-  constexpr bool kQInLds = QT >= 3;
+  constexpr bool kQInLds = QT >= 3 || PAIR;
   // Tiles done in several passes run one wavefront per SIMD: they hide the memory latency by
   // themselves, keeping K and V of the next block in flight for a whole block
-  constexpr bool kDeep = QT >= 3;
+  constexpr bool kDeep = QT >= 3 && !PAIR;
   constexpr int kMergeBytes = 4 * QT * DT * 64 * 16;
   constexpr int kQBytes = kQInLds ? 4 * QT * KS * 64 * 16 : 0;
   __shared__ __attribute__((aligned(16))) char lds_raw[kMergeBytes > kQBytes ? kMergeBytes : kQBytes];
@@ -1451,20 +1452,38 @@ fspad_status check_desc(const fspad_attn_desc* d) {
   return FSPAD_OK;
 }
 
-template <int D, bool STREAMED, bool RAGGED>
-void launch_bf16(const Plan& pl, const AttnParams& prm, hipStream_t stream) {
+// The row tiles whose kernel has a form that leaves room for a second workgroup on every compute unit (Q in LDS and, of
+// 48-row tiles, one K block in registers: 256 and 243 registers, no spills), for launches of more workgroups than compute
+// units: each is a whole unit then, and one's set-up and merge run beside another's stream. 16 x 52 heads, 26 nodes, D = 128:
+// 150 keys 27.5 us (one workgroup per compute unit: 37.7), 600 keys 57.3 (68.3), 1400 keys 113 (126); D = 64, 40 nodes:
+// 150 keys 19.7 (30.5), 1200 keys 56.5 (66.9). 16-row tiles and D = 64 with 32-row tiles have the room anyway; 64-row
+// tiles do not fit twice.
+constexpr bool has_pair_form(int QT, int D) { return (QT == 2 && D == 128) || (QT == 3 && D == 64); }
+
+template <int QT, int D, bool STREAMED, bool RAGGED>
+void launch_bf16(const AttnParams& prm, hipStream_t stream) {
   const dim3 grid((unsigned)prm.n_wgs);
+  if constexpr (has_pair_form(QT, D) && !RAGGED) {
+    if (prm.n_wgs > kComputeUnits) {
+      hipLaunchKernelGGL((tree_attn_bf16_kernel<QT, D, STREAMED, RAGGED, true>), grid, dim3(256), 0, stream, prm);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((tree_attn_bf16_kernel<QT, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm);
+}
+template <int D, bool STREAMED>
+void launch_bf16(const Plan& pl, const AttnParams& prm, hipStream_t stream) {
+  const bool ragged = prm.setup > 0;   // (never with 16-row tiles: setup_blocks)
   switch (pl.QT) {
-    case 1: hipLaunchKernelGGL((tree_attn_bf16_kernel<1, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm); break;
-    case 2: hipLaunchKernelGGL((tree_attn_bf16_kernel<2, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm); break;
-    case 3: hipLaunchKernelGGL((tree_attn_bf16_kernel<3, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm); break;
-    default: hipLaunchKernelGGL((tree_attn_bf16_kernel<4, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm); break;
+    case 1: launch_bf16<1, D, STREAMED, false>(prm, stream); break;
+    case 2: ragged ? launch_bf16<2, D, STREAMED, true>(prm, stream) : launch_bf16<2, D, STREAMED, false>(prm, stream); break;
+    case 3: ragged ? launch_bf16<3, D, STREAMED, true>(prm, stream) : launch_bf16<3, D, STREAMED, false>(prm, stream); break;
+    default: ragged ? launch_bf16<4, D, STREAMED, true>(prm, stream) : launch_bf16<4, D, STREAMED, false>(prm, stream); break;
   }
 }
 template <int D>
 void launch_bf16(const Plan& pl, const AttnParams& prm, bool streamed, hipStream_t stream) {
-  if (prm.setup > 0) streamed ? launch_bf16<D, true, true>(pl, prm, stream) : launch_bf16<D, false, true>(pl, prm, stream);
-  else streamed ? launch_bf16<D, true, false>(pl, prm, stream) : launch_bf16<D, false, false>(pl, prm, stream);
+  streamed ? launch_bf16<D, true>(pl, prm, stream) : launch_bf16<D, false>(pl, prm, stream);
 }
 
 // Nodes per workgroup of the fp32 kernel: a node of its own re-reads all of K and V through L2, which costs

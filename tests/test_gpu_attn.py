@@ -332,6 +332,28 @@ def test_bf16_workgroups_aligned_with_units(H, B, Hkv, G, N, L):
     _check(H, case, H.TOL["bf16"])
 
 
+@pytest.mark.parametrize("B,Hkv,G,N,D", [(8, 48, 1, 17, 128), (2, 200, 1, 32, 128), (8, 50, 2, 13, 128), (3, 128, 1, 33, 64),
+                                         (10, 40, 3, 16, 64)])
+@pytest.mark.parametrize("L", [0, 33, 300])
+def test_bf16_more_whole_units_than_compute_units(H, B, Hkv, G, N, D, L):
+    """The forms of the 32- and 48-row tiles that share a compute unit, one whole unit per workgroup: trees of different
+    sizes (of equally many blocks), both output types.
+
+    The error of an output is at most 2^-8 of the weighted mean of |V| it is formed from (every weight is rounded to
+    bf16, 2^-9, and the sum runs over the rounded ones). Among the 10^6 outputs of these cases are rows that few keys
+    dominate, of ten times the RMS: each is held to the bar relative to its own value, where that is larger than the RMS."""
+    n_nodes = [(N - 1) // 32 * 32 + 1 if b % 2 else N for b in range(B)]
+    case = H.AttnCase(650 + B + N + L, B, N, Hkv * G, Hkv, D, L, "bf16", n_nodes=n_nodes, topk=4)
+    out, ref = case.run_gpu(), case.run_oracle()
+    got = out.double().cpu().numpy()
+    for b in range(B):
+        rms = np.sqrt(np.mean(ref[b, :n_nodes[b]] ** 2))
+        assert np.all(np.abs(got[b] - ref[b]) <= H.TOL["bf16"] * np.maximum(rms, np.abs(ref[b])))
+        assert np.sqrt(np.mean((got[b] - ref[b]) ** 2)) <= 2.0 ** -8 * rms
+        assert np.all(got[b, n_nodes[b]:] == 0)
+    assert torch.equal(case.run_gpu(out_dtype=torch.bfloat16), out.to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("Hq,Hkv,N,D", [(4, 4, 60, 128), (4, 4, 26, 64), (4, 4, 9, 128), (16, 2, 40, 128), (28, 4, 33, 64)])
 @pytest.mark.parametrize("kv_len", [[2000, 0, 1, 33, 700, 5], [0, 31, 32, 0, 64, 1500], [3, 2, 1, 0, 0, 90]])
 @pytest.mark.parametrize("splits", [0, 5, 40, 4096])
