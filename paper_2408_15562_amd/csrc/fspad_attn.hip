@@ -1649,8 +1649,12 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         // 64/8-head, 16384-key, 60-node call, 70.7 -> 64.5 us at 32768 keys)
         else hipLaunchKernelGGL((tree_attn_gqa_kernel<64, 4, 3>), dim3((unsigned)sl.n_wgs), dim3(768), 0, stream, sl);
       } else {
-        // keys and values of the call, read once each (one slab group per kv head)
-        const bool streamed = (size_t)kv_blocks * (2 * kBlockKeys * 2) * d.head_dim > fspad_detail::kCacheBytes;
+        // keys and values of the call, read once each (one slab group per kv head). Not the 48- and 64-row tiles of
+        // D = 128 where a compute unit takes more than two workgroups in turn: 16 x 40 heads, 60 nodes, 2500 keys 172 us
+        // without the hint and 178 with it, 32 x 32 heads, 1200 keys 144 and 148 (one or two in turn: 16 x 32 heads, 76 and
+        // 74 us; D = 64: 160 and 156; 16-row tiles 107 and 98)
+        const bool in_turn = d.head_dim == 128 && pl.QT >= 3 && sl.n_wgs > 2 * kComputeUnits;
+        const bool streamed = !in_turn && (size_t)kv_blocks * (2 * kBlockKeys * 2) * d.head_dim > fspad_detail::kCacheBytes;
         if (d.head_dim == 128) launch_bf16<128>(pl, sl, streamed, stream);
         else launch_bf16<64>(pl, sl, streamed, stream);
       }
