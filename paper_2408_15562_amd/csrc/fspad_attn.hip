@@ -1305,7 +1305,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void tree_attn_f32_kernel(const Att
 struct Plan {
   bool shared_stage;   // the kernel whose wavefronts share K/V blocks through LDS (WS = 4 or 8 slabs of 32 rows)
   bool short_stream;   // few blocks per workgroup: one workgroup per compute unit, so that fewer partials are written
-  int QT, NS, WS, GY;
+  int QT, NS, WS, GY, D;
   int rows_per_unit;
   int n_wgs;           // workgroups for the largest slice of sequences
   int64_t total_blocks;
@@ -1333,6 +1333,7 @@ void plan_rows(const fspad_attn_desc& d, Plan& pl, int max_ws = 4) {
     if (cost < best_cost) { best_cost = cost; pl.QT = qt; pl.NS = ns; pl.WS = ws; pl.GY = gy; }
   }
   pl.rows_per_unit = pl.WS * 16 * pl.QT;
+  pl.D = d.head_dim;
 }
 
 // The shared-stage kernel's plan: 32-row slabs, one per wavefront, four per workgroup.
@@ -1347,6 +1348,7 @@ void plan_rows_gqa(const fspad_attn_desc& d, Plan& pl) {
   pl.WS = 4;
   pl.GY = (pl.NS + pl.WS - 1) / pl.WS;
   pl.rows_per_unit = 32 * pl.WS;
+  pl.D = d.head_dim;
 }
 
 int blocks_of(int kv_len, int n_nodes) {
@@ -1396,6 +1398,9 @@ int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool uniform, 
         wgs = units * pieces;
     }
     if (4 * units >= 3 * rounds * resident) wgs = units;   // whole units fill the chip
+    // D = 64, 32-row tiles: two workgroups fit on a compute unit, and share it with profit where the units would leave
+    // more than two turns unevenly filled (13 x 40 heads, 26 nodes: 300 keys 19.6 us, one workgroup each 22.4; 3000 keys 78, 83)
+    else if (units > 2 * kComputeUnits && pl.QT == 2 && !pl.shared_stage && pl.D == 64) wgs = cap < 2 * kComputeUnits ? cap : 2 * kComputeUnits;
   }
   if (forced > 0) wgs = forced < kMaxForcedWorkgroups ? forced : kMaxForcedWorkgroups;
   if (wgs > kMaxWorkgroups) wgs = kMaxWorkgroups;  // the kernels form w * (T mod W) in 32 bits

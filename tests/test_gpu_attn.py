@@ -323,11 +323,12 @@ def test_bf16_units_equally_long_in_trees_of_different_sizes(H, Hq, Hkv, D, N, n
 
 @pytest.mark.parametrize("B,Hkv,G,N,L", [(4, 40, 1, 5, 130), (4, 52, 1, 26, 33), (2, 40, 1, 40, 700), (2, 52, 1, 9, 1100),
                                          (2, 32, 1, 60, 300), (3, 8, 4, 40, 900), (5, 8, 1, 3, 64), (4, 39, 1, 4, 500),
-                                         (3, 40, 1, 60, 476), (2, 60, 1, 10, 600), (1, 64, 1, 26, 500), (4, 8, 4, 60, 220)])
+                                         (13, 40, 1, 26, 70), (3, 40, 1, 60, 476), (2, 60, 1, 10, 600), (1, 64, 1, 26, 500),
+                                         (4, 8, 4, 60, 220)])
 def test_bf16_workgroups_aligned_with_units(H, B, Hkv, G, N, L):
     """Equally long units whose number does not divide the compute units: whole units on part of the chip,
-    two or three pieces of each, short units kept whole (the last four: of 4 to 5 blocks per wavefront), and
-    (4 x 39, 500 keys) just below the border."""
+    two or three pieces of each, short units kept whole (the last four: of 4 to 5 blocks per wavefront), (4 x 39,
+    500 keys) just below the border, and (13 x 40) two workgroups per compute unit over more units than that."""
     case = H.AttnCase(700 + Hkv + N, B, N, Hkv * G, Hkv, 64, L, "bf16", n_nodes=[N] * B)
     _check(H, case, H.TOL["bf16"])
 
