@@ -1180,6 +1180,8 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
 // lanes that hold the key's V entries: no exchange between the two products. The wavefronts' (max, sum,
 // output) meet in LDS once, at the end. 8 heads, D = 64, 256 keys, 26 nodes: 6.1 us (one wavefront per node, a
 // lane per key, the weights exchanged key by key for the second product: 60.6 us).
+// WAVES = 1: short prefixes under many rows (launch_f32), where most of the eight would find no key. One wavefront per
+// node, which reads only the tree keys that its node sees.
 constexpr int kF32Waves = 8;
 constexpr int kF32Loads = 8;   // K (and V) rows a lane has in flight per tile
 
@@ -1197,21 +1199,23 @@ __device__ __forceinline__ float key_sum(float v) {
   return v;
 }
 
-template <int D, int QN>
-__global__ __launch_bounds__(64 * kF32Waves) void tree_attn_f32_kernel(const AttnParams p) {
+template <int D, int QN, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void tree_attn_f32_kernel(const AttnParams p) {
+  static_assert(WAVES > 1 || QN == 1, "the list of tree keys is one node's");
   constexpr int LPK = D / 4, KPL = 64 / LPK;       // lanes per key, keys per load instruction
   constexpr int kTile = kF32Loads * KPL;           // keys per wavefront and turn
-  __shared__ __attribute__((aligned(16))) float sh_o[kF32Waves][QN][D];
-  __shared__ float sh_m[kF32Waves][QN], sh_l[kF32Waves][QN];
+  __shared__ __attribute__((aligned(16))) float sh_o[WAVES][QN][D];
+  __shared__ float sh_m[WAVES][QN], sh_l[WAVES][QN];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x, b = blockIdx.z, node0 = blockIdx.y * QN;
   const int g = h / p.G;
-  const int n = p.n_nodes[b], L = p.kv_len[b], total = L + n;
+  const int n = p.n_nodes[b], L = p.kv_len[b];
+  int total = L + n;
   const int64_t row0 = ((int64_t)b * p.Nmax + node0) * p.Hq + h;   // (b, node0, h); the next node is Hq rows further
   float* const out0 = reinterpret_cast<float*>(p.out) + row0 * D;
   const int64_t node_stride = (int64_t)p.Hq * D;
   if (node0 >= n) {
-    for (int i = tid; i < QN * D; i += 64 * kF32Waves)
+    for (int i = tid; i < QN * D; i += 64 * WAVES)
       if (node0 + i / D < p.Nmax) out0[(i / D) * node_stride + i % D] = 0.f;
     return;
   }
@@ -1235,13 +1239,22 @@ __global__ __launch_bounds__(64 * kF32Waves) void tree_attn_f32_kernel(const Att
     m[t] = -INFINITY;
     l[t] = 0.f;
   }
-  for (int base = wave * kTile; base < total; base += kF32Waves * kTile) {
+  int nth = 0;   // WAVES = 1: lane r holds the r-th tree node that this one sees
+  if constexpr (WAVES == 1) {
+    const uint64_t own = word[0] & (~0ull >> (64 - n));
+    const int n_seen = __popcll(own), below = __popcll(own & ((1ull << lane) - 1));
+    nth = __builtin_amdgcn_ds_permute(4 * ((own >> lane) & 1 ? below : n_seen + lane - below), lane);
+    total = L + n_seen;
+  }
+  for (int base = wave * kTile; base < total; base += WAVES * kTile) {
     f32x4 k[kF32Loads], v[kF32Loads];
 #pragma unroll
     for (int i = 0; i < kF32Loads; ++i) {   // (keys past the end re-read the last one; they are masked below)
       const int j = min(base + i * KPL + grp, total - 1);
       const bool prefix = j < L;
-      const int64_t at = prefix ? j * p.stride_token : (j - L) * tree_stride;
+      int node = j - L;
+      if constexpr (WAVES == 1) node = __shfl(nth, max(node, 0));
+      const int64_t at = prefix ? j * p.stride_token : node * tree_stride;
       k[i] = *reinterpret_cast<const f32x4*>((prefix ? kc : ktr) + at + 4 * sub);
       v[i] = *reinterpret_cast<const f32x4*>((prefix ? vc : vtr) + at + 4 * sub);
     }
@@ -1252,7 +1265,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void tree_attn_f32_kernel(const Att
       for (int i = 0; i < kF32Loads; ++i) {
         const float dot = key_sum<LPK>(fmaf(q[t][3], k[i][3], fmaf(q[t][2], k[i][2], fmaf(q[t][1], k[i][1], q[t][0] * k[i][0]))));
         const int j = base + i * KPL + grp;
-        const bool seen = j < L || (j < total && ((word[t] >> (j - L)) & 1ull));
+        const bool seen = j < L || (j < total && (WAVES == 1 || ((word[t] >> (j - L)) & 1ull)));
         s[i] = seen ? dot * p.scale : -INFINITY;
         mx = fmaxf(mx, s[i]);
       }
@@ -1285,14 +1298,14 @@ __global__ __launch_bounds__(64 * kF32Waves) void tree_attn_f32_kernel(const Att
     if (lane == 0) { sh_m[wave][t] = m[t]; sh_l[wave][t] = l[t]; }
   }
   __syncthreads();
-  for (int i = tid; i < QN * D; i += 64 * kF32Waves) {
+  for (int i = tid; i < QN * D; i += 64 * WAVES) {
     const int t = i / D, d = i % D, node = node0 + t;
     if (node >= p.Nmax) break;
     float M = sh_m[0][t], num = 0.f, den = 0.f;
 #pragma unroll
-    for (int w = 1; w < kF32Waves; ++w) M = fmaxf(M, sh_m[w][t]);
+    for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sh_m[w][t]);
 #pragma unroll
-    for (int w = 0; w < kF32Waves; ++w) {   // in wavefront order: deterministic
+    for (int w = 0; w < WAVES; ++w) {   // in wavefront order: deterministic
       const float a = sh_m[w][t] > -INFINITY ? expf(sh_m[w][t] - M) : 0.f;
       den += a * sh_l[w][t];
       num += a * sh_o[w][t][d];
@@ -1495,12 +1508,23 @@ void launch_bf16(const Plan& pl, const AttnParams& prm, bool streamed, hipStream
 // nothing while the chip has room (one node against two: 6.1 / 8.3 us with 8 heads x 26 nodes, 256 keys, D = 64;
 // 8.1 / 8.2 us with 8 x 60; 16.9 / 18.5 us with 16 x 48, 600 keys) and is what bounds the call beyond that
 // (13.3 / 11.5 us with 16 x 60, 300 keys; 89 / 73 us with 2 x 16 x 64, 700 keys, D = 128; four nodes: 77 us).
+// Beyond that, prefixes of up to two tiles of a wavefront's keys (64 at D = 64, 32 at D = 128) leave most of the eight
+// wavefronts without one: a single wavefront per node. 16 x 32 / 8 heads, 26 nodes, D = 64: no prefix 14.4 us (58.0 with eight
+// wavefronts), 20 keys 14.6 (60.8), 50 keys 23.9 (59.2); 8 x 32 heads, 60 nodes, D = 128, 20 keys 27.6 us (88). With fewer rows
+// the eight cost a launch of many workgroups only where a single one has the keys in half a tile (4 x 16 / 4 heads, 10 nodes,
+// no prefix: 4.3 us, 6.5; 20 keys 4.3 against 4.4 with 2 x 16 heads, 100 keys 8.7 against 4.5).
 template <int D>
 void launch_f32(const AttnParams& prm, hipStream_t stream) {
-  const bool one = (int64_t)prm.B * prm.Hq * prm.Nmax <= 768;
+  constexpr int kTile = kF32Loads * 64 / (D / 4);
+  const bool few = (int64_t)prm.B * prm.Hq * prm.Nmax <= 768;
+  int longest = 0;
+  for (int b = 0; b < prm.B; ++b) longest = prm.kv_len[b] > longest ? prm.kv_len[b] : longest;
+  const bool single = longest <= (few ? kTile / 2 : 2 * kTile);
+  const bool one = few || single;
   const dim3 grid((unsigned)prm.Hq, (unsigned)(one ? prm.Nmax : (prm.Nmax + 1) / 2), (unsigned)prm.B), block(64 * kF32Waves);
-  if (one) hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1>), grid, block, 0, stream, prm);
-  else hipLaunchKernelGGL((tree_attn_f32_kernel<D, 2>), grid, block, 0, stream, prm);
+  if (single) hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1, 1>), grid, dim3(64), 0, stream, prm);
+  else if (one) hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1, kF32Waves>), grid, block, 0, stream, prm);
+  else hipLaunchKernelGGL((tree_attn_f32_kernel<D, 2, kF32Waves>), grid, block, 0, stream, prm);
 }
 
 }  // namespace
