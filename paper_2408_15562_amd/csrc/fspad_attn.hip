@@ -1317,7 +1317,6 @@ __global__ __launch_bounds__(64 * WAVES) void tree_attn_f32_kernel(const AttnPar
 // ---------------------------------------------------------------------------------------------
 struct Plan {
   bool shared_stage;   // the kernel whose wavefronts share K/V blocks through LDS (WS = 4 or 8 slabs of 32 rows)
-  bool short_stream;   // few blocks per workgroup: one workgroup per compute unit, so that fewer partials are written
   int QT, NS, WS, GY, D;
   int rows_per_unit;
   int n_wgs;           // workgroups for the largest slice of sequences
@@ -1326,42 +1325,31 @@ struct Plan {
 
 constexpr int64_t kComputeUnits = 256;
 constexpr int64_t kMaxWorkgroups = 32768;
-constexpr int64_t kShortStreamBlocks = 16;  // blocks per workgroup below which a stream counts as short
 constexpr int kMaxQT = 4;                   // 16-row tiles per wavefront at most
 constexpr int kMaxForcedWorkgroups = 4096;  // upper limit of fspad_attn_desc.workgroups
 
-// Row tiling of one kv head's N*G query rows: slabs of 16*QT rows, WS slabs per workgroup.
-void plan_rows(const fspad_attn_desc& d, Plan& pl, int max_ws = 4) {
-  pl.shared_stage = false;
-  pl.short_stream = false;
-  const int G = d.n_q_heads / d.n_kv_heads;
-  const int rows = d.n_nodes_max * G;
-  int best_cost = 1 << 30;
-  for (int qt = kMaxQT; qt >= 1; --qt) {  // ties go to the larger tile: fewer re-reads of K/V
-    const int ns = (rows + 16 * qt - 1) / (16 * qt);
-    int ws = ns == 1 ? 1 : (ns == 2 ? 2 : 4);
-    if (ws > max_ws) ws = max_ws;
-    const int gy = (ns + ws - 1) / ws;
-    const int cost = gy * ws * qt;
-    if (cost < best_cost) { best_cost = cost; pl.QT = qt; pl.NS = ns; pl.WS = ws; pl.GY = gy; }
+// Row tiling of one kv head's N*G query rows: up to 128 rows one or two slabs of 16*QT rows, one workgroup's. More:
+// the shared-stage kernel's slabs of 32 rows, one per wavefront, four per workgroup (32/8 heads, 4096 keys, 60 nodes: 24.9 us
+// against 29.9 us for 64-row tiles with two slabs).
+void plan_rows(const fspad_attn_desc& d, Plan& pl) {
+  const int rows = d.n_nodes_max * (d.n_q_heads / d.n_kv_heads);
+  pl.D = d.head_dim;
+  pl.shared_stage = rows > 4 * 32;
+  if (pl.shared_stage) {
+    pl.QT = 2;
+    pl.NS = (rows + 31) / 32;
+    pl.WS = 4;
+    pl.GY = (pl.NS + pl.WS - 1) / pl.WS;
+  } else {
+    int best_cost = 1 << 30;
+    for (int qt = kMaxQT; qt >= 1; --qt) {  // ties go to the larger tile: fewer re-reads of K/V
+      const int ns = (rows + 16 * qt - 1) / (16 * qt);
+      if (ns > 2) break;
+      if (ns * qt < best_cost) { best_cost = ns * qt; pl.QT = qt; pl.NS = pl.WS = ns; }
+    }
+    pl.GY = 1;
   }
   pl.rows_per_unit = pl.WS * 16 * pl.QT;
-  pl.D = d.head_dim;
-}
-
-// The shared-stage kernel's plan: 32-row slabs, one per wavefront, four per workgroup.
-bool gqa_plan_applies(const fspad_attn_desc& d) {
-  return d.n_nodes_max * (d.n_q_heads / d.n_kv_heads) > 4 * 32;
-}
-void plan_rows_gqa(const fspad_attn_desc& d, Plan& pl) {
-  pl.shared_stage = true;
-  pl.short_stream = false;
-  pl.QT = 2;
-  pl.NS = (d.n_nodes_max * (d.n_q_heads / d.n_kv_heads) + 31) / 32;
-  pl.WS = 4;
-  pl.GY = (pl.NS + pl.WS - 1) / pl.WS;
-  pl.rows_per_unit = 32 * pl.WS;
-  pl.D = d.head_dim;
 }
 
 int blocks_of(int kv_len, int n_nodes) {
@@ -1370,7 +1358,7 @@ int blocks_of(int kv_len, int n_nodes) {
 
 // Wavefront sets that split a workgroup's keys: the two key groups of the shared-stage kernel, or
 // the wavefronts that do not take a row slab of their own.
-int key_waves(const Plan& pl) { return pl.shared_stage ? 2 : (pl.WS >= 4 ? 1 : 4 / pl.WS); }
+int key_waves(const Plan& pl) { return pl.shared_stage ? 2 : 4 / pl.WS; }
 
 // Workgroup count for `total_blocks` flat blocks in `units` units: two resident workgroups per
 // compute unit for 16-row tiles, one otherwise, but no workgroup with fewer
@@ -1532,25 +1520,16 @@ void launch_f32(const AttnParams& prm, hipStream_t stream) {
 extern "C" size_t fspad_tree_attn_workspace_bytes(const fspad_attn_desc* desc, int32_t max_kv_len) {
   if (check_desc(desc) != FSPAD_OK || max_kv_len < 0) return 0;
   if (desc->io_dtype == FSPAD_F32) return 16;
-  // one partial slot per (unit, workgroup) boundary at most: units + workgroups of the largest slice;
-  // the call may settle on either slab count (see kShortStreamBlocks), so both are sized
-  size_t need = 0;
-  for (int variant = 0; variant < 3; ++variant) {   // four slabs, two slabs, the shared-stage plan
-    Plan pl{};
-    if (variant < 2) plan_rows(*desc, pl, variant == 0 ? 4 : 2);
-    else if (gqa_plan_applies(*desc)) plan_rows_gqa(*desc, pl);
-    else break;
-    const int nb = desc->batch < kMaxBatchPerLaunch ? desc->batch : kMaxBatchPerLaunch;
-    const int64_t units = (int64_t)nb * desc->n_kv_heads * pl.GY;
-    const int64_t total = units * blocks_of(max_kv_len, desc->n_nodes_max);
-    int64_t wgs = plan_wgs(pl, total, units, true, desc->workgroups);
-    const int64_t wgs_cut = plan_wgs(pl, total, units, false, desc->workgroups);  // a ragged batch of the same size
-    if (wgs_cut > wgs) wgs = wgs_cut;
-    const int64_t slots = slots_of(pl, units, wgs, total, desc->workgroups);
-    const size_t bytes = (size_t)slots * slot_bytes(*desc, pl);
-    if (bytes > need) need = bytes;
-  }
-  return need;
+  // one partial slot per (unit, workgroup) boundary at most: units + workgroups of the largest slice
+  Plan pl{};
+  plan_rows(*desc, pl);
+  const int nb = desc->batch < kMaxBatchPerLaunch ? desc->batch : kMaxBatchPerLaunch;
+  const int64_t units = (int64_t)nb * desc->n_kv_heads * pl.GY;
+  const int64_t total = units * blocks_of(max_kv_len, desc->n_nodes_max);
+  int64_t wgs = plan_wgs(pl, total, units, true, desc->workgroups);
+  const int64_t wgs_cut = plan_wgs(pl, total, units, false, desc->workgroups);  // a ragged batch of the same size
+  if (wgs_cut > wgs) wgs = wgs_cut;
+  return (size_t)slots_of(pl, units, wgs, total, desc->workgroups) * slot_bytes(*desc, pl);
 }
 
 extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void* q, const void* k_tree,
@@ -1616,25 +1595,8 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         uniform = uniform && blocks_of(sl.kv_len[i], sl.n_nodes[i]) == blocks_of(sl.kv_len[0], sl.n_nodes[0]);
         seq_blocks += blocks_of(sl.kv_len[i], sl.n_nodes[i]);
       }
-      // Four row slabs per workgroup share every K/V block between its four wavefronts, but the
-      // partial results of a cut unit grow with the rows a workgroup holds. With short streams
-      // (few blocks per workgroup) those partials outweigh the K/V bytes: two slabs then.
       Plan pl{};
       plan_rows(d, pl);
-      if (pl.WS == 4) {
-        const int64_t units4 = (int64_t)nb * d.n_kv_heads * pl.GY;
-        const int64_t total4 = (int64_t)d.n_kv_heads * pl.GY * seq_blocks;
-        const bool short_stream = total4 < kShortStreamBlocks * plan_wgs(pl, total4, units4, uniform, d.workgroups);
-        if (gqa_plan_applies(d)) {
-          // more than four 32-row slabs per kv head: wavefronts of 32 rows that share every K/V
-          // block through LDS (measured on a 32/8-head layer, 4096 keys, 60 nodes: 24.9 us against
-          // 29.9 us for 64-row tiles with two slabs); with short streams one workgroup per compute unit
-          plan_rows_gqa(d, pl);
-          pl.short_stream = short_stream;
-        } else if (short_stream) {
-          plan_rows(d, pl, 2);
-        }
-      }
       sl.WS = pl.WS; sl.NS = pl.NS; sl.GY = pl.GY;
       sl.ws_shift = pl.WS == 4 ? 2 : (pl.WS == 2 ? 1 : 0);
       sl.gy_magic = pl.GY > 1 ? (uint32_t)(((1ull << 32) + pl.GY - 1) / pl.GY) : 0u;
