@@ -1601,19 +1601,20 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       sl.ws_shift = pl.WS == 4 ? 2 : (pl.WS == 2 ? 1 : 0);
       sl.gy_magic = pl.GY > 1 ? (uint32_t)(((1ull << 32) + pl.GY - 1) / pl.GY) : 0u;
       // units of a sequence: the slab groups that its own tree fills, times the kv heads
-      auto units_of = [&](int i) { return (int64_t)d.n_kv_heads * groups_of(d, pl, sl.n_nodes[i]); };
+      int64_t seq_units[kMaxBatchPerLaunch];
       const int64_t full_units = (int64_t)nb * d.n_kv_heads * pl.GY;   // (partial slots are numbered as if every tree were full)
       const int64_t full_total = (int64_t)d.n_kv_heads * pl.GY * seq_blocks;
       const int64_t full_wgs = plan_wgs(pl, full_total, full_units, uniform, d.workgroups);
       int64_t total = 0, units = 0;
       for (int i = 0; i < nb; ++i) {
-        total += units_of(i) * blocks_of(sl.kv_len[i], sl.n_nodes[i]);
-        units += units_of(i);
+        seq_units[i] = (int64_t)d.n_kv_heads * groups_of(d, pl, sl.n_nodes[i]);
+        total += seq_units[i] * blocks_of(sl.kv_len[i], sl.n_nodes[i]);
+        units += seq_units[i];
         if (total > kMaxFlatBlocks) return FSPAD_ERR_SHAPE;  // the kernels index blocks with 32 bits
       }
       bool same = true;
       for (int i = 1; i < nb; ++i) same = same && sl.kv_len[i] == sl.kv_len[0] && sl.n_nodes[i] == sl.n_nodes[0];
-      sl.seq_blocks = same ? (int32_t)(units_of(0) * blocks_of(sl.kv_len[0], sl.n_nodes[0])) : 0;
+      sl.seq_blocks = same ? (int32_t)(seq_units[0] * blocks_of(sl.kv_len[0], sl.n_nodes[0])) : 0;
       sl.same_len = sl.kv_len[0];
       sl.same_nodes = sl.n_nodes[0];
       // never more workgroups than full trees would have: the workspace a call needs does not depend on the trees
@@ -1626,7 +1627,7 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       total = 0;
       for (int i = 0; i < nb; ++i) {
         sl.bstart[i] = (int32_t)total;
-        total += units_of(i) * (blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup);
+        total += seq_units[i] * (blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup);
       }
       sl.bstart[nb] = (int32_t)total;
       sl.total_blocks = (int32_t)total;
@@ -1654,7 +1655,7 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       bool any_cut = false;
       for (int i = 0; i < nb && !any_cut; ++i) {
         const int64_t nblk = blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup;
-        for (int64_t ub = 0; ub < units_of(i) && !any_cut; ++ub) {
+        for (int64_t ub = 0; ub < seq_units[i] && !any_cut; ++ub) {
           const int64_t fs = sl.bstart[i] + ub * nblk;
           any_cut = host_owner_of(fs + sl.setup, total, sl.n_wgs) != host_owner_of(fs + nblk - 1, total, sl.n_wgs);
         }
