@@ -118,7 +118,7 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void partial_ge
   const int t0 = range_begin(p.plan, w), t1 = range_begin(p.plan, w + 1);
   typename G::Source src;
   src.x[0] = p.x[0]; src.x[1] = p.x[1]; src.w[0] = p.w[0]; src.w[1] = p.w[1];
-  src.split = p.split; src.n_xrows = p.rows; src.n_wrows = p.N; src.row0 = 0; src.K = p.K;
+  src.split = p.split; src.n_xrows = p.rows; src.n_wrows = p.N; src.K = p.K;
   const int slice = t0 / p.plan.stages;
   // every slice is walked from a stage of its own on: the ranges of an XCD would otherwise be at the same
   // stage of k, or at few different ones, wherever the length of a range and a slice's stages have a common

@@ -43,7 +43,8 @@ struct LmHeadParams {
   const int32_t* draft_tokens;   // sampling: the tree, to know which logits the walk will ask for
   const int32_t* parent;
   const int32_t* n_nodes;
-  int32_t M, V, K, n_slices, n_passes, rows_per_pass;
+  int32_t M, V, K, n_slices;
+  int32_t n_passes, rows_per_pass;   // lm_head_wide_kernel
   int32_t Nmax;
   float inv_t_log2e;    // sampling: log2(e) / T
 };
@@ -58,7 +59,7 @@ __device__ __forceinline__ unsigned long long pack_best(float v, int i) {
   return ((unsigned long long)(unsigned)i << 32) | __float_as_uint(v);
 }
 
-// The LM head over the rows of one pass (blockIdx.y): a workgroup takes a contiguous run of 128-token
+// The LM head over up to 128 rows: a workgroup takes a contiguous run of 128-token
 // slices, whole ones, and streams their weights without a pause -- the copies of the next slice are in
 // flight while the statistics of the last one are formed. It starts `c0` stages into every slice and wraps
 // around (spread_phase).
@@ -71,26 +72,25 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_ke
   __shared__ __attribute__((aligned(1024))) char lds[G::kLdsBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
-  const int w = blockIdx.x, row0 = blockIdx.y * p.rows_per_pass;
+  const int w = blockIdx.x;
   const int s0 = (int)((unsigned)w * (unsigned)p.n_slices / gridDim.x), s1 = (int)((unsigned)(w + 1) * (unsigned)p.n_slices / gridDim.x);
   const int C = p.K / G::kStageK;
   const int c0 = (int)fspad_detail::spread_phase(w, C);
 
-  // sampling: the row of thread tid's node's parent and the node's token (-1: none), for nodes below 512
+  // sampling: the row of thread tid's node's parent and the node's token (-1: none); M <= 128, a thread per node
   int my_row = -1, my_tok = -1;
-  auto node_of = [&](int cnode, int& r, int& tok) {
-    const int b = cnode / p.Nmax, i = cnode - b * p.Nmax;
-    r = -1;
-    if (i == 0 || i >= p.n_nodes[b]) return;
-    const int par = p.parent[cnode];
-    tok = p.draft_tokens[cnode];
-    if (par >= 0 && par < i && tok >= 0 && tok < p.V) r = b * p.Nmax + par - row0;
-  };
-  if (MODE == 1 && tid < p.M) node_of(tid, my_row, my_tok);
+  if (MODE == 1 && tid < p.M) {
+    const int b = tid / p.Nmax, i = tid - b * p.Nmax;
+    if (i > 0 && i < p.n_nodes[b]) {
+      const int par = p.parent[tid];
+      my_tok = p.draft_tokens[tid];
+      if (par >= 0 && par < i && my_tok >= 0 && my_tok < p.V) my_row = b * p.Nmax + par;
+    }
+  }
 
   typename G::Source src;
   src.x[0] = src.x[1] = p.hidden; src.w[0] = src.w[1] = p.weights; src.split = 0x7fffffff;
-  src.n_xrows = p.M; src.n_wrows = p.V; src.row0 = row0; src.K = p.K;
+  src.n_xrows = p.M; src.n_wrows = p.V; src.K = p.K;
   G::run(lds, src, s0, c0, c0, 0, (s1 - s0) * C, [&](int slice, const f32x4 (&acc)[MT], unsigned spare) {
     const int slice0 = slice * kVocabPerWg;
     if constexpr (MODE == 1) {
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_ke
           double dsum = (sub & 3) == 0 ? (double)half[0] + (double)half[1] : 0.0;
 #pragma unroll
           for (int d = 4; d < 16; d <<= 1) dsum += __shfl_xor(dsum, d);
-          const int row = row0 + t0 * 16 + r;
+          const int row = t0 * 16 + r;
           if (row < p.M) {
             const size_t slot = (size_t)row * p.n_slices + slice;
             if ((sub & 3) == 0) {
@@ -150,22 +150,14 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_ke
             }
           }
         }
-        // the logits the walk will test: a node's token under the row of its parent
-        auto set_aside = [&](int cnode, int r, int tok) {
-          r -= t0 * 16;
-          const int vl = tok - slice0;
-          if (r < 0 || r >= kTiles * 16 || vl < 0 || vl >= kVocabPerWg) return;
+        // the logit the walk will test: this thread's node's token under the row of its parent
+        const int at = my_row - t0 * 16, vl = my_tok - slice0;
+        if (my_row >= 0 && at >= 0 && at < kTiles * 16 && vl >= 0 && vl < kVocabPerWg) {
           float x;
-          lds_read4(x, spare + (unsigned)r * 512u + ((((unsigned)(vl >> 2) ^ (unsigned)(r & 15)) << 4) | (unsigned)(vl & 3) << 2));
+          lds_read4(x, spare + (unsigned)at * 512u + ((((unsigned)(vl >> 2) ^ (unsigned)(at & 15)) << 4) | (unsigned)(vl & 3) << 2));
           wait_lds<0>();
           settled(x);
-          p.node_logit[cnode] = x;
-        };
-        set_aside(tid, my_row, my_tok);
-        for (int cnode = tid + 64 * kStreamWaves; cnode < p.M; cnode += 64 * kStreamWaves) {
-          int r, tok = -1;
-          node_of(cnode, r, tok);
-          set_aside(cnode, r, tok);
+          p.node_logit[tid] = x;
         }
       }
     } else {
@@ -191,7 +183,7 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_ke
         if (g == 0) lds_write8(spare + (unsigned)(wave * MT * 16 + t * 16 + n) * 8u, pack_best(best, idx));
       }
       lds_barrier();
-      if (tid < MT * 16 && row0 + tid < p.M) {
+      if (tid < MT * 16 && tid < p.M) {
         unsigned long long part[kStreamWaves];
 #pragma unroll
         for (int w8 = 0; w8 < kStreamWaves; ++w8) lds_read8(part[w8], spare + (unsigned)(w8 * MT * 16 + tid) * 8u);
@@ -203,7 +195,7 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void lm_head_ke
           settled(part[w8]);
           take_better(best, idx, __uint_as_float((unsigned)part[w8]), (int)(part[w8] >> 32));
         }
-        const size_t slot = (size_t)slice * p.M + row0 + tid;
+        const size_t slot = (size_t)slice * p.M + tid;
         p.part_max[slot] = best;
         p.part_idx[slot] = idx;
       }
@@ -782,34 +774,29 @@ fspad_status check_lm_head_args(int32_t B, int32_t Nmax, int32_t V, int32_t hidd
 
 template <int MODE, bool PACKED, bool STREAMED>
 void launch_rows(const LmHeadParams& g, dim3 grid, dim3 block, hipStream_t stream) {
-  const int r = g.rows_per_pass;
-  if (r <= 16) hipLaunchKernelGGL((lm_head_kernel<1, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
-  else if (r <= 32) hipLaunchKernelGGL((lm_head_kernel<2, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
-  else if (r <= 48) hipLaunchKernelGGL((lm_head_kernel<3, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
-  else if (r <= 64) hipLaunchKernelGGL((lm_head_kernel<4, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+  if (g.M <= 16) hipLaunchKernelGGL((lm_head_kernel<1, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (g.M <= 32) hipLaunchKernelGGL((lm_head_kernel<2, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (g.M <= 48) hipLaunchKernelGGL((lm_head_kernel<3, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
+  else if (g.M <= 64) hipLaunchKernelGGL((lm_head_kernel<4, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
   else hipLaunchKernelGGL((lm_head_kernel<8, MODE, PACKED, STREAMED>), grid, block, 0, stream, g);
 }
 
 // Fills in the launch shape and runs the GEMM in the given mode (0 greedy, 1 sampling).
 template <int MODE, bool PACKED>
-fspad_status launch_lm_head(LmHeadParams& g, int32_t hidden_dim, hipStream_t stream) {
-  // rows per workgroup: everything up to 128 rows in one pass of the eight-wavefront shape, more in
-  // passes of up to 256 rows (each pass streams the weights again)
-  g.rows_per_pass = g.M <= 128 ? g.M : 256;
-  g.n_passes = (g.M + g.rows_per_pass - 1) / g.rows_per_pass;
-  const int pass_rows = g.n_passes > 1 ? (g.M + g.n_passes - 1) / g.n_passes : g.M;   // passes of equal size
-  if (g.n_passes > 1) g.rows_per_pass = (pass_rows + 15) / 16 * 16;
-  if (((int64_t)g.n_slices + 7) * g.n_passes > 0x7fffffff) return FSPAD_ERR_SHAPE;
-  const int r = g.rows_per_pass;
-  if (r <= 128) {
-    const dim3 grid((unsigned)(g.n_slices < kComputeUnits ? g.n_slices : kComputeUnits), (unsigned)g.n_passes), block(512);
+fspad_status launch_lm_head(LmHeadParams& g, hipStream_t stream) {
+  if (g.M <= 128) {
+    const dim3 grid((unsigned)(g.n_slices < kComputeUnits ? g.n_slices : kComputeUnits)), block(64 * fspad_detail::kStreamWaves);
     if ((size_t)g.V * g.K * 2 > fspad_detail::kCacheBytes) launch_rows<MODE, PACKED, true>(g, grid, block, stream);
     else launch_rows<MODE, PACKED, false>(g, grid, block, stream);
     return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
   }
-  const dim3 grid((unsigned)((g.n_slices + 7) / 8 * 8 * g.n_passes));
-  if (r <= 192) hipLaunchKernelGGL((lm_head_wide_kernel<3, MODE, PACKED>), grid, dim3(512), 0, stream, g);
-  else hipLaunchKernelGGL((lm_head_wide_kernel<4, MODE, PACKED>), grid, dim3(512), 0, stream, g);
+  // up to 256 rows in one pass, more in passes of equal size (each pass streams the weights again)
+  g.n_passes = (g.M + 255) / 256;
+  g.rows_per_pass = g.n_passes == 1 ? 256 : ((g.M + g.n_passes - 1) / g.n_passes + 15) / 16 * 16;
+  if (((int64_t)g.n_slices + 7) * g.n_passes > 0x7fffffff) return FSPAD_ERR_SHAPE;
+  const dim3 grid((unsigned)((g.n_slices + 7) / 8 * 8 * g.n_passes)), block(64 * fspad_detail::kStreamWaves);
+  if (g.rows_per_pass <= 192) hipLaunchKernelGGL((lm_head_wide_kernel<3, MODE, PACKED>), grid, block, 0, stream, g);
+  else hipLaunchKernelGGL((lm_head_wide_kernel<4, MODE, PACKED>), grid, block, 0, stream, g);
   return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
 }
 
@@ -844,8 +831,8 @@ extern "C" fspad_status fspad_tree_accept_greedy_lm_head(int32_t B, int32_t Nmax
   const size_t slots = (size_t)g.M * g.n_slices;
   g.part_max = static_cast<float*>(workspace);
   g.part_idx = reinterpret_cast<int32_t*>(g.part_max + slots);
-  const fspad_status gs = (flags & FSPAD_WEIGHTS_PACKED) ? launch_lm_head<0, true>(g, hidden_dim, stream)
-                                                         : launch_lm_head<0, false>(g, hidden_dim, stream);
+  const fspad_status gs = (flags & FSPAD_WEIGHTS_PACKED) ? launch_lm_head<0, true>(g, stream)
+                                                         : launch_lm_head<0, false>(g, stream);
   if (gs != FSPAD_OK) return gs;
 
   LmWalkParams w{};
@@ -888,8 +875,8 @@ extern "C" fspad_status fspad_tree_accept_sample_lm_head(int32_t B, int32_t Nmax
   float* row_max = g.node_logit + g.M;
   g.draft_tokens = draft_tokens; g.parent = parent; g.n_nodes = n_nodes;
   g.inv_t_log2e = (float)(1.4426950408889634 / (double)temperature);
-  const fspad_status gs = (flags & FSPAD_WEIGHTS_PACKED) ? launch_lm_head<1, true>(g, hidden_dim, stream)
-                                                         : launch_lm_head<1, false>(g, hidden_dim, stream);
+  const fspad_status gs = (flags & FSPAD_WEIGHTS_PACKED) ? launch_lm_head<1, true>(g, stream)
+                                                         : launch_lm_head<1, false>(g, stream);
   if (gs != FSPAD_OK) return gs;
 
   LmSampleWalkParams w{};

@@ -99,14 +99,14 @@ struct StreamGemm {
     const char* x[2];      // [n_xrows][K] bf16; slices below `split` multiply x[0] / w[0], the others x[1] / w[1]
     const char* w[2];      // [n_wrows][K] bf16
     int split;             // slices of the first problem (0x7fffffff: there is only one)
-    int n_xrows, n_wrows, row0, K;
+    int n_xrows, n_wrows, K;
   };
 
   // Walks `n_stages` stages. A slice is walked from stage `border` of its C = K / kStageK on, around the
   // end of k, back to `border`; then the next slice follows, whose border lies `rot` stages further. The
   // walk begins at stage `at` of `slice`.
   // At a slice's end `slice_end(slice, acc, spare)` takes the sums: acc[t] of lane (n, g) is row
-  // row0 + 16 t + n of X against rows 128 slice + 16 wave + 4 g .. + 3 of W. `spare` is the LDS address of
+  // 16 t + n of X against rows 128 slice + 16 wave + 4 g .. + 3 of W. `spare` is the LDS address of
   // kXStageBytes that are free from a barrier inside `slice_end` on (plain LDS accesses there would
   // wait for the copies in flight). The range's last sums are handed over too, whole or not.
   template <typename SliceEnd>
@@ -123,7 +123,7 @@ struct StreamGemm {
 #pragma unroll
     for (int i = 0; i < kXCopies; ++i) {
       const int piece = (wave * kXCopies + i) * 64 + lane, r = piece / kXChunks, s = piece % kXChunks;
-      xoff[i] = (unsigned)min(src.row0 + r, src.n_xrows - 1) * (unsigned)row_bytes + (unsigned)(s ^ (r & 15)) * 16u;
+      xoff[i] = (unsigned)min(r, src.n_xrows - 1) * (unsigned)row_bytes + (unsigned)(s ^ (r & 15)) * 16u;
     }
     // operand reads: chunk 4 kk + g of row n, kept at slot (4 kk + g) ^ n = (4 kk) ^ (g ^ n)
     const unsigned xread = xs + (unsigned)n * kXRowBytes + ((unsigned)(g ^ n) << 4);
