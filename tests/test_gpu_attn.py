@@ -233,6 +233,32 @@ def test_config3_one_layer_four_sequences_sampled_heads(H):
     assert torch.isfinite(out).all()
 
 
+@pytest.mark.parametrize("N,D,Hkv,kv_len", [
+    (9, 128, 16, [8300] * 4), (26, 128, 16, [8300] * 4), (26, 128, 100, [1340] * 4), (40, 128, 16, [8300] * 4),
+    (60, 64, 32, [8300] * 4), (26, 64, 32, [8300] * 4), (40, 64, 100, [2700] * 4), (9, 64, 32, [8300] * 4),
+    (9, 128, 16, [16400, 3000, 14001, 2]), (26, 128, 16, [16400, 3000, 14001, 2]), (40, 128, 16, [16400, 3000, 14001, 2]),
+    (60, 128, 16, [16400, 3000, 14001, 2]), (26, 64, 32, [16400, 3000, 14001, 2]), (60, 64, 32, [16400, 3000, 14001, 2])])
+def test_keys_and_values_beyond_the_memory_side_cache(H, N, D, Hkv, kv_len):
+    """More than 256 MB of keys and values in a call: the forms that read them with the non-temporal hint, for every row
+    tile, of equally long and of ragged batches, and of whole units beyond the compute units. All kv heads share the
+    keys and values of one (a head stride of zero), which the oracle sees for three of them."""
+    import oracle
+    B, L = 4, max(kv_len)
+    assert sum(-(-x // 32) + -(-N // 32) for x in kv_len) * Hkv * 32 * D * 4 > 256 << 20
+    case = H.AttnCase(510 + N + D, B, N, Hkv, Hkv, D, 1, "bf16", kv_len=[0] * B, n_nodes=[N, N, (N - 1) // 32 * 32 + 1, N], topk=4)
+    rng = np.random.default_rng(N + D)
+    kc, vc = [H.to_dev(rng.standard_normal((B, 1, L, D), dtype=np.float32), "bf16") for _ in range(2)]
+    case.k_cache, case.v_cache, case.kv_len = kc.expand(B, Hkv, L, D), vc.expand(B, Hkv, L, D), np.asarray(kv_len, np.int32)
+    assert case.k_cache.stride(1) == 0
+    out = case.run_gpu()
+    assert torch.isfinite(out).all()
+    heads, h = [0, Hkv // 2, Hkv - 1], case.host
+    kc3, vc3 = [np.repeat(t.float().cpu().numpy(), 3, axis=1) for t in (kc, vc)]
+    ref = oracle.tree_attn(h["q"][:, :, heads], h["k_tree"][:, :, heads], h["v_tree"][:, :, heads], kc3, vc3, case.kv_len,
+                           case.n_nodes, case.parent, packed_mask=case.mask, nthreads=16)
+    assert H.rel_err(out[:, :, heads], ref) <= H.TOL["bf16"]
+
+
 def test_config4_one_layer_long_context_sampled_heads(H):
     """One layer of the LLaMA3-70B-shaped stack (64/8 GQA, L=16384, N=60); oracle on 4 sampled heads."""
     c = CONFIGS["c4"]
