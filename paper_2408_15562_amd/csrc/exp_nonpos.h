@@ -39,7 +39,8 @@ __device__ __forceinline__ double exp_nonpos(double x) {
   return vanishes ? 0.0 : p * scale;
 }
 
-// The same for a loop over many arguments, with a table of 2^(j/32) in LDS: x = (32 n + j) ln2/32 + r,
+// The same for a loop over many arguments, with a table of 2^(j/32) in LDS (table-driven exponential after Tang, the argument
+// reduced with ln2 in two parts after Cody and Waite, as above): x = (32 n + j) ln2/32 + r,
 // |r| <= ln2/64, degree-5 Taylor polynomial (truncation below 2.3e-15 relative): 20 fp64 instructions per
 // weight of a sum instead of 25. 32 entries of 8 bytes fill the 64 banks: lanes that read different entries
 // meet no conflict. x is finite or -infinity; below -708 the result is that of -708 (3e-308, which moves no sum
@@ -58,7 +59,7 @@ __device__ __forceinline__ double exp_nonpos_table(double x, const double* table
   const double shift = 6755399441055744.0;  // 1.5 * 2^52
   const double t = fma(x, 46.166241308446828384, shift);   // 32 / ln2
   const double k = t - shift;
-  const int ki = (int)__double2loint(t);    // 32 n + j in [-32684, 0]
+  const int ki = (int)__double2loint(t);    // 32 n + j in [-32686, 0]: n >= -1022, root * 2^n is a normal number
   double r = fma(-k, 6.93147180369123816490e-01 / 32.0, x);   // (ln2's leading 32 bits: the product is exact)
   r = fma(-k, 1.90821492927058770002e-10 / 32.0, r);
   double p = 1.0 / 120.0;

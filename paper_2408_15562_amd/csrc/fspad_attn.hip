@@ -1365,20 +1365,20 @@ int key_waves(const Plan& pl) { return pl.shared_stage ? 2 : 4 / pl.WS; }
 // than 2 blocks per key-splitting wave.
 // When all units are equally long, the count is a multiple of the unit count where that pays: every unit is then cut
 // into the same number of pieces, or not at all, and no workgroup straddles two units (a second segment costs a
-// workgroup as much as 20 to 30 blocks do). Measured with 4 x 52 heads, 4096 keys, 26 nodes: 208 workgroups 83 us, 512
-// unaligned ones 103 us; 4 x 40 heads, 60 nodes: 500 keys 19 us (160) against 34 (256), 4096 keys 70 against 83; 2 x 40
-// heads, 2048 keys, 60 nodes: 33 us (240) against 40 (256). One workgroup per compute unit at most: a second one
-// shares its instruction issue and finishes last (32 heads, 4096 keys, 26 nodes: 25 us against 28 with 512).
+// workgroup as much as 20 to 30 blocks do). Measured with 4 x 52 heads, 26 nodes: 1500 keys 28 us (208 workgroups) against
+// 34 (256 unaligned ones), 4096 keys 77 against 79 (85 with 512); 4 x 40 heads, 60 nodes: 500 keys 19 us (160) against 33 (256),
+// 4096 keys 78 against 80; 2 x 40 heads, 2048 keys, 60 nodes: 28 us (240) against 35 (256). One workgroup per compute unit
+// at most: a second one shares its instruction issue and finishes last (32 heads, 4096 keys, 26 nodes: 19 us against 21 with 512).
 // Not where it leaves more than two fifths of the compute units idle, nor for long streams (100 blocks of a cut
-// unit, 200 of a whole one on fewer than three quarters of them), which straddling costs less than idle units do (4 x 40 heads, 8192 keys, 4 nodes: 129 us
-// against 120; 2 x 52 heads: 94 against 84), nor where 16-row tiles fill two workgroups per unit evenly
+// unit, 200 of a whole one on fewer than three quarters of them), which straddling costs less than idle units do (4 x 40 heads, 8192 keys, 4 nodes: whole
+// units 134 us, cut ones 107; 2 x 52 heads: two pieces each 76, cut anywhere 72), nor where 16-row tiles fill two workgroups per unit evenly
 // (32 heads, 8192 keys, 4 nodes: 34 us against 31). Units of a few blocks per wavefront stay whole when there
 // are enough of them (a quarter of the compute units, at most 5 blocks each): the merge costs more than the blocks
 // (D = 128, 60 nodes, 17 blocks: 104 units 18.1 us whole, 21.5 in two pieces each, 29.4 unaligned; 64 units 17.7, 19.4, 28.1).
 int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool uniform, int forced) {
   const int KW = key_waves(pl);
   // (the shared-stage kernel's eight wavefronts of up to 256 registers fill a compute unit by themselves)
-  // (32-row tiles spill when two workgroups share a compute unit)
+  // (32-row tiles spill when two workgroups share a compute unit, in the form for cut units)
   const int64_t resident = pl.QT == 1 ? 2 * kComputeUnits : kComputeUnits;
   int64_t wgs = resident;
   const int64_t cap = total_blocks / (2 * KW);

@@ -68,9 +68,11 @@ __device__ __forceinline__ unsigned spread_phase(int w, int C) { return (3u * ((
 
 // The memory-side cache. What a call reads of more than that -- weights, keys and values, each byte once -- is gone before
 // the next call comes back to it, and is read with the non-temporal hint, which spares the caches the replacement: draft
-// step of 4 rows (4096 / 11008) 190 -> 180 us, of 40 rows 533 -> 500 us, 8B head 202 -> 197 us, attention of 33B layers
-// 1705 -> 1674 us. What may stay in the cache from one call to the next is slower with the hint: draft step at
-// hidden size 2048 88 -> 100 us, 2048 x 32000 head 28 -> 31 us, a 7B layer by itself 38.8 -> 40.9 us.
+// step of 4 rows (4096 / 11008) 190 -> 180 us, of 40 rows 530 -> 492 us, 20 attention layers of a 33B model 1705 -> 1679 us
+// (an 8B head 202 -> 201). What may stay in the cache from one call to the next is slower with the hint: draft step at
+// hidden size 2048 88 -> 100 us, 2048 x 32000 head 28 -> 31 us, an attention call over 134 MB repeated by itself 38.8 -> 40.9 us.
+// Just above the line both are true: a sampler of 270 MB (60 rows, 4096 / 11008) repeated by itself 60 -> 68 us, with four
+// sets of weights in turn, as between two draft steps, 71 -> 68; from 350 MB on the hint is faster either way (70 -> 64 us).
 constexpr size_t kCacheBytes = (size_t)256 << 20;
 
 constexpr int kStreamWaves = 8;
