@@ -82,7 +82,7 @@ def parse_args():
                          "to bf16 logits, widened to fp32, then fspad_tree_accept_{greedy,sample} (the comparison)")
     ap.add_argument("--packed-weights", action="store_true",
                     help="with --feature-sampler fused / --draft-layer fused / --lm-head fused: the weight matrices are repacked once into "
-                         "the tile order of fspad_pack_weight (same results, faster streaming)")
+                         "the tile order of fspad_pack_weight (same results)")
     ap.add_argument("--hidden-dim", type=int, default=None, help="hidden size for --lm-head (default: the workload's model)")
     ap.add_argument("--probe-overlap", action="store_true",
                     help="instead of a workload: time what one SIMD runs at the same time (a matrix instruction and vector "

@@ -272,7 +272,7 @@ fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, int32_t V,
  *   lm_head      dev [V,hidden_dim] bf16, contiguous, 16-byte aligned (the weight matrix as the
  *                models store it: one row per token)
  *   flags        0, or FSPAD_WEIGHTS_PACKED (defined below): lm_head went through
- *                fspad_pack_weight(V, hidden_dim, ...) and is in tile order (same results, faster)
+ *                fspad_pack_weight(V, hidden_dim, ...) and is in tile order (same results)
  *   hidden_dim   multiple of 256, 256..65536
  *   draft_tokens, parent, n_nodes, path, path_len, tokens, n_tokens: as for fspad_tree_accept_greedy
  *   node_target  dev [B,Nmax] i32 out, may be NULL: target[b,i] (-1 in unused slots)
@@ -362,8 +362,8 @@ fspad_status fspad_kv_commit(const fspad_attn_desc* desc, const void* k_tree, co
  * along k; the 1 KB of a tile holds, at byte 16 * (n + 16 g), the eight values
  * w[16 t + n][32 s + 8 g .. + 7] (t: tile row, s: tile along k, n in 0..15, g in 0..3). Rows past
  * n_rows in the last tile row are zeros. A wavefront then streams contiguous kilobytes instead of
- * sixteen 64-byte pieces a row pitch apart, which HBM serves faster (Feature Sampler at
- * 4096 / 11008: 60 instead of 74 us); results are bit-identical to those from row-major weights.
+ * four rows x 256 bytes per request, at the same rate on gfx950 (Feature Sampler at 4096 / 11008: 55 and
+ * 54 us); results are bit-identical to those from row-major weights.
  *
  *   n_rows >= 1; k a multiple of 32; w dev [n_rows][k] bf16; packed dev,
  *   fspad_packed_weight_bytes(n_rows, k) = ceil(n_rows / 16) * 16 * k * 2 bytes (0 = bad shape);
