@@ -389,9 +389,14 @@ __device__ __forceinline__ void process_block(RowState<QT, D>& st, const bf16x8 
 // merge kernel finishes the unit.
 // RAGGED: units count for p.setup blocks more than they have (a form of its own: in the other one the bookkeeping
 // costs the 64-row tiles registers they do not have, 4 x 52 heads, 4096 keys: 83 -> 98 us).
-// PAIR: two workgroups per compute unit, for launches of more workgroups than compute units (launch_bf16).
-template <int QT, int D, bool STREAMED, bool RAGGED, bool PAIR = false>
-__global__ __launch_bounds__(256, (QT == 1 || PAIR ? 2 : 1)) void tree_attn_bf16_kernel(const AttnParams) {
+// Two workgroups fit on a compute unit except of 64-row tiles and of 48-row tiles at D = 128 (and of 32-row tiles at D = 128 in
+// ragged batches, where 256 registers made it spill): launches of more whole units than compute units need that, so that one's
+// set-up and merge run beside another's stream. 16 x 52 heads, 26 nodes, D = 128: 150 keys 25.0 us, with one workgroup per
+// compute unit 37.7, 600 keys 55.9 (68.3), 1400 keys 112 (126); D = 64, 40 nodes: 150 keys 19.4 (30.5), 1200 keys 54.4 (66.9). The limit
+// stands where the compiler would pass it: asked for it everywhere, D = 64 with 32-row tiles lost up to 13 % in ragged batches
+// (184 registers without) and D = 64 with 48-row tiles 1 % (239 without).
+template <int QT, int D, bool STREAMED, bool RAGGED>
+__global__ __launch_bounds__(256, (QT == 1 || (QT == 2 && D == 128 && !RAGGED) ? 2 : 1)) void tree_attn_bf16_kernel(const AttnParams) {
   const AttnArgs p = fetch_args();
   constexpr int KS = D / 32;
   constexpr int DT = D / 16;
@@ -399,10 +404,10 @@ __global__ __launch_bounds__(256, (QT == 1 || PAIR ? 2 : 1)) void tree_attn_bf16
   // merge buffers: 4 wavefronts x (QT*DT accumulators + QT stats) x 64 lanes. With large row tiles
   // the Q fragments of the 4 wavefronts live in lane-private LDS slots instead of registers; they are
   // dead once a segment's stream is done, so they share the space of the merge buffers.
-  constexpr bool kQInLds = QT >= 3 || PAIR;
+  constexpr bool kQInLds = QT >= 3;
   // Tiles done in several passes run one wavefront per SIMD: they hide the memory latency by
   // themselves, keeping K and V of the next block in flight for a whole block
-  constexpr bool kDeep = QT >= 3 && !PAIR;
+  constexpr bool kDeep = QT >= 3;
   constexpr int kMergeBytes = 4 * QT * DT * 64 * 16;
   constexpr int kQBytes = kQInLds ? 4 * QT * KS * 64 * 16 : 0;
   __shared__ __attribute__((aligned(16))) char lds_raw[kMergeBytes > kQBytes ? kMergeBytes : kQBytes];
@@ -672,10 +677,12 @@ __global__ __launch_bounds__(256, (QT == 1 || PAIR ? 2 : 1)) void tree_attn_bf16
       }
     };
 
-    if (KW > 1) {
-      // The key-splitting wavefronts of a slab leave their states in lane-private LDS slots; after one
-      // barrier each of them reduces and writes its own share of the (row tile, 4 d-tiles) quads, so
-      // the tail of a short-lived workgroup is spread over all its wavefronts.
+    // The key-splitting wavefronts of a slab leave their states in lane-private LDS slots; after one
+    // barrier each of them reduces and writes its own share of the (row tile, 4 d-tiles) quads, so
+    // the tail of a short-lived workgroup is spread over all its wavefronts.
+    // (KW is 2 or 4. The test stands for the large tiles, whose merge the compiler otherwise mixes with the end of the
+    // stream: 20 layers of 4 x 52 heads, 4096 keys, 60 nodes 1665 us with it, 1703 without; smaller tiles are faster without)
+    if (!kQInLds || KW > 1) {
       if (kQInLds) __syncthreads();  // every wavefront is done with its Q slots before they are overwritten
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
@@ -703,18 +710,10 @@ __global__ __launch_bounds__(256, (QT == 1 || PAIR ? 2 : 1)) void tree_attn_bf16
         }
         write_quad(t, e0, o4, mm, l_row);
       }
-    } else {
-#pragma unroll
-      for (int t = 0; t < QT; ++t)
-#pragma unroll
-        for (int e0 = 0; e0 < DT; e0 += 4) {
-          const f32x4 o4[4] = {st.o[t][e0], st.o[t][e0 + 1], st.o[t][e0 + 2], st.o[t][e0 + 3]};
-          write_quad(t, e0, o4, st.m[t], lsum[t]);
-        }
     }
     r += (unsigned)count;
     if (b + 1 < p.B && r >= seq_first_block(p, b + 1)) ++b;
-    if ((KW > 1 || kQInLds) && r < r1) __syncthreads();  // the LDS buffers are reused by the next segment
+    if (r < r1) __syncthreads();  // the LDS buffers are reused by the next segment
   }
 }
 
@@ -1378,7 +1377,7 @@ int key_waves(const Plan& pl) { return pl.shared_stage ? 2 : 4 / pl.WS; }
 int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool uniform, int forced) {
   const int KW = key_waves(pl);
   // (the shared-stage kernel's eight wavefronts of up to 256 registers fill a compute unit by themselves)
-  // (32-row tiles spill when two workgroups share a compute unit, in the form for cut units)
+  // (a second resident workgroup of 32-row tiles pays where whole units outnumber the compute units, not for cut ones)
   const int64_t resident = pl.QT == 1 ? 2 * kComputeUnits : kComputeUnits;
   int64_t wgs = resident;
   const int64_t cap = total_blocks / (2 * KW);
@@ -1458,24 +1457,9 @@ fspad_status check_desc(const fspad_attn_desc* d) {
   return FSPAD_OK;
 }
 
-// The row tiles whose kernel has a form that leaves room for a second workgroup on every compute unit (Q in LDS and, of
-// 48-row tiles, one K block in registers: 256 and 243 registers, no spills), for launches of more workgroups than compute
-// units: each is a whole unit then, and one's set-up and merge run beside another's stream. 16 x 52 heads, 26 nodes, D = 128:
-// 150 keys 27.5 us (one workgroup per compute unit: 37.7), 600 keys 57.3 (68.3), 1400 keys 113 (126); D = 64, 40 nodes:
-// 150 keys 19.7 (30.5), 1200 keys 56.5 (66.9). 16-row tiles and D = 64 with 32-row tiles have the room anyway; 64-row
-// tiles do not fit twice.
-constexpr bool has_pair_form(int QT, int D) { return (QT == 2 && D == 128) || (QT == 3 && D == 64); }
-
 template <int QT, int D, bool STREAMED, bool RAGGED>
 void launch_bf16(const AttnParams& prm, hipStream_t stream) {
-  const dim3 grid((unsigned)prm.n_wgs);
-  if constexpr (has_pair_form(QT, D) && !RAGGED) {
-    if (prm.n_wgs > kComputeUnits) {
-      hipLaunchKernelGGL((tree_attn_bf16_kernel<QT, D, STREAMED, RAGGED, true>), grid, dim3(256), 0, stream, prm);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((tree_attn_bf16_kernel<QT, D, STREAMED, RAGGED>), grid, dim3(256), 0, stream, prm);
+  hipLaunchKernelGGL((tree_attn_bf16_kernel<QT, D, STREAMED, RAGGED>), dim3((unsigned)prm.n_wgs), dim3(256), 0, stream, prm);
 }
 template <int D, bool STREAMED>
 void launch_bf16(const Plan& pl, const AttnParams& prm, hipStream_t stream) {
