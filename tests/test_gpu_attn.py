@@ -364,7 +364,7 @@ def test_bf16_workgroups_aligned_with_units(H, B, Hkv, G, N, L):
                                          (10, 40, 3, 16, 64)])
 @pytest.mark.parametrize("L", [0, 33, 300])
 def test_bf16_more_whole_units_than_compute_units(H, B, Hkv, G, N, D, L):
-    """The forms of the 32- and 48-row tiles that share a compute unit, one whole unit per workgroup: trees of different
+    """32- and 48-row tiles, one whole unit per workgroup and two workgroups on a compute unit: trees of different
     sizes (of equally many blocks), both output types.
 
     The error of an output is at most 2^-8 of the weighted mean of |V| it is formed from (every weight is rounded to
