@@ -45,7 +45,7 @@ struct AttnParams {
   const void* v_cache;
   const uint64_t* anc_mask;
   void* out;
-  float* part;     // partial slots: [slot][rows_per_unit][D] un-normalised outputs, then [rows_per_unit][2] (shift, sum)
+  float* part;     // partial slots: [slot][rows_per_unit * D] un-normalised outputs (rows, or partial_index), then [rows_per_unit][2] (shift, sum)
   int64_t stride_batch, stride_head, stride_token;  // cache strides, elements
   int32_t B, Nmax, Hq, Hkv, G;
   int32_t WS;       // row slabs per workgroup: 1, 2 or 4 (4/WS wavefronts share a slab and split its keys)
@@ -182,6 +182,25 @@ __device__ __forceinline__ void zero_rows(const AttnArgs& p, int b, int g, int f
 // the accumulator layout of two 16-key S^T tiles puts keys 4*g4+i (tile 0) and
 // 16+4*g4+i (tile 1) in lane group g4.
 __device__ __forceinline__ int key_of(int g4, int j) { return (j < 4) ? 4 * g4 + j : 16 + 4 * g4 + (j - 4); }
+
+// Partial results of the shared-stage kernel lie in their slots as its lanes hold them, [16-row tile][store instruction][lane]
+// pieces of four dims: a store instruction writes a kilobyte in a row and a merging workgroup, eight rows by all pieces, reads
+// whole lines. They are written through to memory (device scope), where the merge kernel, mostly on another die, finds them
+// anyway: left dirty in the L2 caches, 17 MB of them were written back when the kernel ended, with nothing else to do. Row by
+// row, in 16-byte pieces, each would cost the write of a part of a line. A call with 32 / 8 heads, 60 nodes, 4096 keys:
+// 21.2 us row by row, 20.8 in lane order, 19.9 written through; 1000 keys 16.5, 16.0, 15.1; D = 64, 3000 keys 15.9, 14.3, 13.8.
+// (The wavefronts that split keys of few rows gain nothing and keep rows: 32 heads, 4 nodes 13.2 us, in lane order 13.7.)
+// Offset in floats of piece `piece` (dims 4 * piece .. + 3) of row lr.
+template <int D>
+__device__ __forceinline__ int partial_index(int lr, int piece) {
+  // D = 128: accumulator e of a lane holds dims 16 * e + 4 * g4 .. + 3; D = 64: dims 4 * (4 * g4 + i) .. + 3 are stored i-th
+  const int nth = D == 128 ? piece >> 2 : piece & 3, g4 = D == 128 ? piece & 3 : piece >> 2;
+  return 4 * (((lr >> 4) * (D / 16) + nth) * 64 + g4 * 16 + (lr & 15));
+}
+// (the store reads its data behind its issue: one slot before anything may write those registers)
+__device__ __forceinline__ void store_through(float* p, const f32x4& v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"((__attribute__((address_space(1))) float*)p), "v"(v) : "memory");
+}
 
 // Where one 32-key block lives and how it is masked.
 struct BlockSrc {
@@ -1048,7 +1067,7 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
                     f32x4{vals[0], vals[1], vals[2], vals[3]};
               }
             } else if (ri.valid) {
-              *reinterpret_cast<f32x4*>(slot + (int64_t)lr * D + d0) = st.o[t][e];
+              store_through(slot + partial_index<D>(lr, 4 * e + g4), st.o[t][e]);
             }
           }
           continue;
@@ -1080,8 +1099,7 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
             if (g4 == 0 && e0 == 0) *reinterpret_cast<float2*>(slot + (int64_t)rows_per_unit * D + 2 * lr) = make_float2(st.m[t], l_row);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-              *reinterpret_cast<f32x4*>(slot + (int64_t)lr * D + DT * (4 * g4 + i) + e0) =
-                  f32x4{st.o[t][e0][i], st.o[t][e0 + 1][i], st.o[t][e0 + 2][i], st.o[t][e0 + 3][i]};
+              store_through(slot + partial_index<D>(lr, (DT * (4 * g4 + i) + e0) / 4), f32x4{st.o[t][e0][i], st.o[t][e0 + 1][i], st.o[t][e0 + 2][i], st.o[t][e0 + 3][i]});
           }
         }
       }
@@ -1102,7 +1120,7 @@ __device__ __forceinline__ int owner_of(const AttnArgs& p, unsigned x, double in
 // Finishes every unit that was cut into several segments:
 // out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s over the unit's partial slots.
 // One thread per 4 output dims; rows of nodes past n_nodes are written as zeros.
-template <int D>
+template <int D, bool SHARED>
 __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams, int rows_per_slab, double inv_total) {
   const AttnArgs p = fetch_args();
   constexpr int TPR = D / 4;  // threads per row
@@ -1117,9 +1135,10 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
   const int w0 = owner_of(p, fs, inv_total), w1 = owner_of(p, fs + (unsigned)n_blocks - 1u, inv_total);
   if (w0 == w1) return;  // written directly by the one workgroup that held the whole unit
   const int rows_per_unit = p.WS * rows_per_slab;
-  const int lr = blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
+  constexpr int RPW = 256 / TPR;   // rows of this workgroup: in lane order (partial_index) the faster index of its threads
+  const int lr = blockIdx.x * RPW + (SHARED ? threadIdx.x % RPW : threadIdx.x / TPR);
   if (lr >= rows_per_unit) return;
-  const int d0 = (threadIdx.x % TPR) * 4;
+  const int piece = SHARED ? threadIdx.x / RPW : threadIdx.x % TPR, d0 = 4 * piece;
   const int slab_local = lr / rows_per_slab;
   const int rr = (y * p.WS + slab_local) * rows_per_slab + (lr - slab_local * rows_per_slab);
   if (rr >= p.Nmax * p.G) return;
@@ -1128,7 +1147,7 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   if (node < seq_nodes(p, b)) {
     const int64_t slot_floats = (int64_t)rows_per_unit * (D + 2);
-    const float* o_base = p.part + (int64_t)(unit + w0) * slot_floats + (int64_t)lr * D + d0;
+    const float* o_base = p.part + (int64_t)(unit + w0) * slot_floats + (SHARED ? partial_index<D>(lr, piece) : lr * D + d0);
     const float* ml_base = p.part + (int64_t)(unit + w0) * slot_floats + (int64_t)rows_per_unit * D + 2 * lr;
     // slots in index order (deterministic), eight at a time so that their loads are in flight together
     float M = kNegBig, denom = 0.f;
@@ -1476,6 +1495,13 @@ void launch_bf16(const Plan& pl, const AttnParams& prm, bool streamed, hipStream
   streamed ? launch_bf16<D, true>(pl, prm, stream) : launch_bf16<D, false>(pl, prm, stream);
 }
 
+template <int D>
+void launch_combine(const Plan& pl, dim3 grid, const AttnParams& prm, int rows_per_slab, int64_t total, hipStream_t stream) {
+  const double inv_total = 1.0 / (double)total;
+  if (pl.shared_stage) hipLaunchKernelGGL((tree_attn_combine_kernel<D, true>), grid, dim3(256), 0, stream, prm, rows_per_slab, inv_total);
+  else hipLaunchKernelGGL((tree_attn_combine_kernel<D, false>), grid, dim3(256), 0, stream, prm, rows_per_slab, inv_total);
+}
+
 // Nodes per workgroup of the fp32 kernel: a node of its own re-reads all of K and V through L2, which costs
 // nothing while the chip has room (one node against two: 6.1 / 8.3 us with 8 heads x 26 nodes, 256 keys, D = 64;
 // 8.1 / 8.2 us with 8 x 60; 16.9 / 18.5 us with 16 x 48, 600 keys) and is what bounds the call beyond that
@@ -1648,8 +1674,8 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         const int rows_per_slab = 16 * pl.QT;
         const int rpb = 256 / (d.head_dim / 4);
         dim3 cgrid((unsigned)((pl.rows_per_unit + rpb - 1) / rpb), (unsigned)full_units);
-        if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_combine_kernel<128>, cgrid, dim3(256), 0, stream, sl, rows_per_slab, 1.0 / (double)total);
-        else hipLaunchKernelGGL(tree_attn_combine_kernel<64>, cgrid, dim3(256), 0, stream, sl, rows_per_slab, 1.0 / (double)total);
+        if (d.head_dim == 128) launch_combine<128>(pl, cgrid, sl, rows_per_slab, total, stream);
+        else launch_combine<64>(pl, cgrid, sl, rows_per_slab, total, stream);
         if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       }
     } else {
