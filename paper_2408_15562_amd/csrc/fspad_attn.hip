@@ -30,6 +30,7 @@ using fspad_detail::bf16x8;
 using fspad_detail::f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int kMaxBatchPerLaunch = 128;
 constexpr int64_t kMaxFlatBlocks = 1ll << 30;  // 32-key blocks of one launch, summed over its units
@@ -183,7 +184,7 @@ __device__ __forceinline__ void zero_rows(const AttnArgs& p, int b, int g, int f
 // 16+4*g4+i (tile 1) in lane group g4.
 __device__ __forceinline__ int key_of(int g4, int j) { return (j < 4) ? 4 * g4 + j : 16 + 4 * g4 + (j - 4); }
 
-// Partial results of the shared-stage kernel lie in their slots as its lanes hold them, [16-row tile][store instruction][lane]
+// Partial results of the shared-stage kernel lie in their slots as its lanes hold them, [row tile][store instruction][lane]
 // pieces of four dims: a store instruction writes a kilobyte in a row and a merging workgroup, eight rows by all pieces, reads
 // whole lines. They are written through to memory (device scope), where the merge kernel, mostly on another die, finds them
 // anyway: left dirty in the L2 caches, 17 MB of them were written back when the kernel ended, with nothing else to do. Row by
@@ -193,9 +194,9 @@ __device__ __forceinline__ int key_of(int g4, int j) { return (j < 4) ? 4 * g4 +
 // Offset in floats of piece `piece` (dims 4 * piece .. + 3) of row lr.
 template <int D>
 __device__ __forceinline__ int partial_index(int lr, int piece) {
-  // D = 128: accumulator e of a lane holds dims 16 * e + 4 * g4 .. + 3; D = 64: dims 4 * (4 * g4 + i) .. + 3 are stored i-th
-  const int nth = D == 128 ? piece >> 2 : piece & 3, g4 = D == 128 ? piece & 3 : piece >> 2;
-  return 4 * (((lr >> 4) * (D / 16) + nth) * 64 + g4 * 16 + (lr & 15));
+  // D = 128: a lane holds dims 8 * x + 4 * h .. + 3 of its row; D = 64: dims 4 * (4 * g4 + i) .. + 3 are stored i-th
+  if constexpr (D == 128) return 4 * (((lr >> 5) * 16 + (piece >> 1)) * 64 + (piece & 1) * 32 + (lr & 31));
+  else return 4 * (((lr >> 4) * 4 + (piece & 3)) * 64 + (piece >> 2) * 16 + (lr & 15));
 }
 // (the store reads its data behind its issue: one slot before anything may write those registers)
 __device__ __forceinline__ void store_through(float* p, const f32x4& v) {
@@ -283,9 +284,7 @@ constexpr float kLazyLog2 = 8.0f;
 // the next block's K there when it keeps a single K buffer). `after_transpose()` runs, for tiles
 // done in several passes, once v has been transposed and is dead (the caller requests the next
 // block's V into the same registers there: a whole block of lead time at no register cost).
-// kVReady: `v` already holds the DT transposed operands (operand e = dwords 4e .. 4e+3 of the
-// array, d = 16e + col) instead of the lane's raw 16-byte slices of 8 V rows.
-template <int QT, int D, bool kVReady = false, typename QFn, typename MaskFn, typename AfterFn, typename AfterVFn>
+template <int QT, int D, typename QFn, typename MaskFn, typename AfterFn, typename AfterVFn>
 __device__ __forceinline__ void process_block(RowState<QT, D>& st, const bf16x8 (&k)[2][D / 32],
                                               const unsigned (&v)[8][D / 32], QFn&& q_frag, const BlockSrc& src,
                                               MaskFn&& mask_of_tile, float c, int g4, AfterFn&& after_scores,
@@ -367,10 +366,6 @@ __device__ __forceinline__ void process_block(RowState<QT, D>& st, const bf16x8 
       for (int j = 0; j < 8; ++j) pf[tt][j] = (__bf16)__builtin_amdgcn_exp2f(tv[tt][j]);
     }
     auto transposed = [&](int e) {  // A operand of d-tile e from the lane's 8 x DT slice of V
-      if constexpr (kVReady) {
-        const unsigned* flat = &v[0][0];
-        return __builtin_bit_cast(bf16x8, u32x4{flat[4 * e], flat[4 * e + 1], flat[4 * e + 2], flat[4 * e + 3]});
-      }
       const unsigned sel = (e & 1) ? 0x07060302u : 0x05040100u;
       u32x4 w;
 #pragma unroll
@@ -737,58 +732,41 @@ __global__ __launch_bounds__(256, (QT == 1 || (QT == 2 && D == 128 && !RAGGED) ?
 }
 
 // ---------------------------------------------------------------------------------------------
-// GQA with many query rows per kv head: four wavefronts per workgroup, 32 rows each (128 rows of
-// one kv head), two such sets per compute unit, i.e. two wavefronts per SIMD, so that the matrix
-// work of one can run beside the vector work and the waits of the other (vector instructions behind a
-// matrix instruction of the same wavefront do not overlap it on this machine). At 32 rows a wavefront
-// cannot afford to fetch every K/V block for itself (four to eight copies of each block through the
-// texture path is what would bound the kernel): the workgroup fetches each block once, every
-// wavefront copying a quarter of it into an LDS stage with the global-to-LDS load (row-contiguous
-// requests, no registers), and all of them pick their operands out of the stage. K is kept swizzled
-// (16-byte chunk c of row r at slot c ^ f(r)) so that a fragment read, 16 rows by one chunk, touches
-// 16 different bank groups; V (D = 128) is read with the transposing LDS load of gfx950, which hands
-// every lane the four keys of one dim -- the A operand of V^T P^T as it is, without byte permutes
-// (its 32-byte pieces are swizzled too). Three stages of one block each: stage i is read while i+1
-// and i+2 are in flight. (WAVES and the blocks per stage are template parameters; only the
-// four-wavefront, one-block form is instantiated.)
-template <int D, int WAVES>
+// GQA with many query rows per kv head (more than 128): wavefronts of 32 rows, four to a set that holds 128 rows of one kv head.
+// At 32 rows a wavefront cannot afford to fetch every K/V block for itself (four to eight copies of each block through the
+// texture path is what would bound the kernel): the set fetches each block once, every wavefront copying a quarter of it into
+// LDS with the global-to-LDS load (row-contiguous requests, no registers), and all of them pick their operands out of there.
+// A workgroup is two sets (three for head dim 64), its key groups, on the same rows: they take alternate blocks of the
+// workgroup's segment and merge their states through LDS at the segment's end. One workgroup of eight (twelve) wavefronts per
+// compute unit holds as many wavefronts as two of four, but a cut unit leaves one partial result per workgroup.
+// Head dim 64: three stages of one block per key group: stage i is read while i+1 and i+2 are in flight. K is kept swizzled
+// (16-byte chunk c of row r at slot c ^ f(r)) so that a fragment read, 16 rows by one chunk, touches 16 different bank groups.
 struct Stage {
+  static constexpr int D = 64, WAVES = 4;
   static constexpr int kChunks = D / 8;                      // 16-byte chunks per row
   static constexpr int kRowsPerLoad = 64 / kChunks;          // rows one copy instruction covers
   static constexpr int kLoads = kBlockKeys / kRowsPerLoad;   // copy instructions per tensor and block
   static constexpr int kTensorBytes = kBlockKeys * D * 2;
   static constexpr int kBytes = 2 * kTensorBytes;            // K then V
   static constexpr int kPerWave = 2 * kLoads / WAVES;        // copy instructions per wavefront and block
-  __device__ static __forceinline__ int swizzle(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
-  // V, D = 128: read with the transposing LDS load, 16 lanes x 8 bytes = 4 keys x 32 bytes at a time;
-  // 32-byte piece e of key r sits at piece e ^ (r & 7), so that the 16 keys one instruction touches
-  // spread over all banks. D = 64: row-major, read as rows.
-  __device__ static __forceinline__ int v_swizzle(int r) { return D == 128 ? 2 * (r & 7) : 0; }
+  __device__ static __forceinline__ int swizzle(int r) { return (r >> 1) & 7; }
 };
 typedef const __attribute__((address_space(1))) void* GlobalPtr;
 typedef __attribute__((address_space(3))) void* LdsPtr;
 
-// KG key groups: with KG = 2 (3 for head dim 64) a workgroup is two (three) such sets of four wavefronts on the same 128 rows;
-// the sets take alternate blocks of the workgroup's segment, each through three stages of its own,
-// and merge their states through LDS at the segment's end. One workgroup of eight wavefronts per
-// compute unit holds as many wavefronts as two of four, but a cut unit leaves one partial result
-// per workgroup: half as many partial bytes are written and read back.
-template <int D, int WAVES, int KG>
-__global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_gqa_kernel(const AttnParams) {
+__global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) {
   const AttnArgs p = fetch_args();
-  typedef Stage<D, WAVES> S;
-  constexpr int QT = 2, KS = D / 32, DT = D / 16, ROWS = 32, kWaves = WAVES, kStages = 3;
-  constexpr int kGroup = 1;   // blocks per stage
-  constexpr int kStageBytes = kGroup * S::kBytes;
-  constexpr int kGroupBytes = kStages * kStageBytes;
-  // the merge of two key groups needs (DT + 1) 16-byte slots per lane, tile and wavefront of one group
+  typedef Stage S;
+  constexpr int D = S::D, KG = 3, QT = 2, KS = D / 32, DT = D / 16, ROWS = 32, kWaves = S::WAVES, kStages = 3;
+  constexpr int kGroupBytes = kStages * S::kBytes;
+  // the merge needs (DT + 1) 16-byte slots per lane, tile and wavefront of every key group but the first
   constexpr int kMergeBytes = (KG - 1) * kWaves * QT * (DT + 1) * 64 * 16;
   constexpr int kLdsBytes = KG * kGroupBytes > kMergeBytes ? KG * kGroupBytes : kMergeBytes;
   __shared__ __attribute__((aligned(16))) char lds_all[kLdsBytes];
 
   const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int kg = KG == 1 ? 0 : wave_all / kWaves;          // key group of this wavefront
-  const int wave = KG == 1 ? wave_all : wave_all % kWaves; // its row slab within the workgroup
+  const int kg = wave_all / kWaves;     // key group of this wavefront
+  const int wave = wave_all % kWaves;   // its row slab within the workgroup
   char* const stages = lds_all + kg * kGroupBytes;
   const int col = lane & 15, g4 = lane >> 4;
   const float c = p.scale * kLog2e;
@@ -805,7 +783,7 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
     dma_tensor[i] = x / S::kLoads;
     dma_row[i] = n * S::kRowsPerLoad + lane / S::kChunks;
     const int chunk = lane & (S::kChunks - 1);
-    dma_chunk[i] = dma_tensor[i] == 0 ? (chunk ^ S::swizzle(dma_row[i])) : (chunk ^ S::v_swizzle(dma_row[i]));
+    dma_chunk[i] = dma_tensor[i] == 0 ? (chunk ^ S::swizzle(dma_row[i])) : chunk;
     dma_dst[i] = dma_tensor[i] * S::kTensorBytes + n * 1024;
   }
   // this lane's operand reads: K fragments (key tile 0; tile 1 is 16 rows further), V rows
@@ -814,10 +792,6 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
   for (int ks = 0; ks < KS; ++ks) kfrag[ks] = (unsigned)col * (D * 2) + 16u * ((4 * ks + g4) ^ S::swizzle(col));
 #pragma unroll
   for (int j = 0; j < 8; ++j) vrow[j] = S::kTensorBytes + (unsigned)key_of(g4, j) * (D * 2) + (unsigned)(D / 8) * col;
-  // transposing read (D = 128): lane (col, g4) points at key 4*g4 + col/4 (+16 for the second half),
-  // dims 16e + 4*(col%4) .. +3, and receives dims 16e + col of the group's four keys
-  const unsigned vtr_off = S::kTensorBytes + (unsigned)(4 * g4 + (col >> 2)) * (D * 2) + 8u * (col & 3) +
-                       ((unsigned)((4 * g4 + (col >> 2)) & 7) << 5);
 
   const unsigned w = blockIdx.x;
   const unsigned wr = w * (unsigned)p.wg_rem, wq = wr / (unsigned)p.n_wgs;
@@ -848,7 +822,7 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
     const bool slab_works = slab < n_slabs;      // has rows of the tree
     if (seg_begin == 0 && y == 0) {
       const int covered = n_groups * rows_per_unit;
-      if (covered < p.Nmax * p.G) zero_rows<D, 64 * WAVES * KG>(p, b, g, covered);
+      if (covered < p.Nmax * p.G) zero_rows<D, 64 * kWaves * KG>(p, b, g, covered);
     }
 
     const char* kc = reinterpret_cast<const char*>(p.k_cache) + (b * p.stride_batch + g * p.stride_head) * 2;
@@ -878,21 +852,20 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
       }
       return src;
     };
-    // request this wavefront's share of a block into slot u of a stage (rows past the end are clamped; masked later)
-    auto request_block = [&](const BlockSrc& s, int stage, int u) {
+    // request this wavefront's share of a block into a stage (rows past the end are clamped; masked later)
+    auto request_block = [&](const BlockSrc& s, int stage) {
 #pragma unroll
       for (int i = 0; i < S::kPerWave; ++i) {
         const unsigned off = (unsigned)min(dma_row[i], s.nvalid - 1) * s.row_bytes + 16u * dma_chunk[i];
         const char* src = (dma_tensor[i] == 0 ? s.k : s.v) + off;
-        __builtin_amdgcn_global_load_lds((GlobalPtr)src, (LdsPtr)(stages + stage * kStageBytes + u * S::kBytes + dma_dst[i]), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((GlobalPtr)src, (LdsPtr)(stages + stage * S::kBytes + dma_dst[i]), 16, 0, 0);
       }
     };
     // key group kg takes blocks kg, kg + KG, ... of the segment
     const int blk_begin = seg_begin + kg, blk_end = seg_begin + seg_count;
     auto request_group = [&](int first, int stage) {
-      if (first < blk_end) request_block(locate(first), stage, 0);
+      if (first < blk_end) request_block(locate(first), stage);
     };
-    auto group_size = [&](int first) { return first < blk_end ? 1 : 0; };
 
     request_group(blk_begin, 0);
     request_group(blk_begin + KG, 1);
@@ -948,78 +921,49 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
       // this turn's copies have landed (the next turn's, requested after them, may still be in
       // flight); the barrier makes every wavefront's share visible and retires the stage that the
       // turn after the next is about to overwrite
-      const int next_size = group_size(first + KG);
-      if (next_size == 1) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(S::kPerWave) : "memory");
+      if (first + KG < blk_end) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(S::kPerWave) : "memory");
       else asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
       __syncthreads();
       request_group(first + 2 * KG, stage == 0 ? 2 : stage - 1);
       if (slab_works && first < blk_end) {
-        {
-          const BlockSrc cur = locate(first);
-          const char* sbase = stages + stage * kStageBytes;
-          bf16x8 kf[2][KS];
-          unsigned vr[8][D / 32];
+        const BlockSrc cur = locate(first);
+        const char* sbase = stages + stage * S::kBytes;
+        bf16x8 kf[2][KS];
+        unsigned vr[8][D / 32];
 #pragma unroll
-          for (int kt = 0; kt < 2; ++kt)
+        for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-              kf[kt][ks] = *reinterpret_cast<const bf16x8*>(sbase + kt * 16 * (D * 2) + kfrag[ks]);
-          if constexpr (D == 128) {
-            // The transposing reads are written out as instructions: through the builtin the compiler
-            // cannot tell them from the stages that the copies requested above are still filling, and
-            // waits for every copy in flight (vmcnt(0)) before the first of them, which serialises the
-            // prefetch. This stage's copies have landed (the wait and the barrier above).
-            const unsigned sb = (unsigned)(uintptr_t)(LdsPtr)(sbase);
-            u32x2 tr[2 * DT];
+          for (int ks = 0; ks < KS; ++ks)
+            kf[kt][ks] = *reinterpret_cast<const bf16x8*>(sbase + kt * 16 * (D * 2) + kfrag[ks]);
 #pragma unroll
-            for (int e = 0; e < DT; ++e) {
-              const unsigned a0 = sb + (vtr_off ^ ((unsigned)e << 5));
-              asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(tr[2 * e]) : "v"(a0));
-              asm volatile("ds_read_b64_tr_b16 %0, %1 offset:4096" : "=v"(tr[2 * e + 1]) : "v"(a0));
-            }
-            static_assert(16 * (D * 2) == 4096, "second half of the keys: 16 rows further");
-            asm volatile("s_waitcnt lgkmcnt(0)"
-                         : "+v"(tr[0]), "+v"(tr[1]), "+v"(tr[2]), "+v"(tr[3]), "+v"(tr[4]), "+v"(tr[5]), "+v"(tr[6]), "+v"(tr[7]),
-                           "+v"(tr[8]), "+v"(tr[9]), "+v"(tr[10]), "+v"(tr[11]), "+v"(tr[12]), "+v"(tr[13]), "+v"(tr[14]), "+v"(tr[15]));
-            unsigned* flat = &vr[0][0];
-#pragma unroll
-            for (int e = 0; e < DT; ++e) {
-              flat[4 * e] = tr[2 * e][0]; flat[4 * e + 1] = tr[2 * e][1]; flat[4 * e + 2] = tr[2 * e + 1][0]; flat[4 * e + 3] = tr[2 * e + 1][1];
-            }
-            process_block<QT, D, true>(st, kf, vr, q_frag, cur, mask_of_tile, c, g4, [] {}, [] {});
-          } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const u32x2 x = *reinterpret_cast<const u32x2*>(sbase + vrow[j]);
-              vr[j][0] = x[0]; vr[j][1] = x[1];
-            }
-            process_block<QT, D>(st, kf, vr, q_frag, cur, mask_of_tile, c, g4, [] {}, [] {});
-          }
+        for (int j = 0; j < 8; ++j) {
+          const u32x2 x = *reinterpret_cast<const u32x2*>(sbase + vrow[j]);
+          vr[j][0] = x[0]; vr[j][1] = x[1];
         }
+        process_block<QT, D>(st, kf, vr, q_frag, cur, mask_of_tile, c, g4, [] {}, [] {});
       }
       stage = stage == 2 ? 0 : stage + 1;
     }
 
-    if constexpr (KG >= 2) {
-      // the other key groups hand their states over in lane-private LDS slots (the stages are free
-      // once every wavefront has left the loop); wavefront w of the first group and wavefront w of the
-      // second hold the same rows in the same lanes, so the merge is lane by lane and in a fixed order
-      __syncthreads();
-      constexpr int kGroupSlots = kWaves * QT * (DT + 1) * 64;   // 16-byte slots one group hands over
-      f32x4* const mbuf0 = reinterpret_cast<f32x4*>(lds_all) + (wave * QT * (DT + 1)) * 64 + lane;
-      if (kg >= 1 && slab_live) {
-        f32x4* mbuf = mbuf0 + (kg - 1) * kGroupSlots;
+    // the other key groups hand their states over in lane-private LDS slots (the stages are free
+    // once every wavefront has left the loop); wavefront w of the first group and wavefront w of the
+    // second hold the same rows in the same lanes, so the merge is lane by lane and in a fixed order
+    __syncthreads();
+    constexpr int kGroupSlots = kWaves * QT * (DT + 1) * 64;   // 16-byte slots one group hands over
+    f32x4* const mbuf0 = reinterpret_cast<f32x4*>(lds_all) + (wave * QT * (DT + 1)) * 64 + lane;
+    if (kg >= 1 && slab_live) {
+      f32x4* mbuf = mbuf0 + (kg - 1) * kGroupSlots;
 #pragma unroll
-        for (int t = 0; t < QT; ++t) {
+      for (int t = 0; t < QT; ++t) {
 #pragma unroll
-          for (int e = 0; e < DT; ++e) mbuf[(t * (DT + 1) + e) * 64] = st.o[t][e];
-          mbuf[(t * (DT + 1) + DT) * 64] = f32x4{st.m[t], st.l[t][0], 0.f, 0.f};
-        }
+        for (int e = 0; e < DT; ++e) mbuf[(t * (DT + 1) + e) * 64] = st.o[t][e];
+        mbuf[(t * (DT + 1) + DT) * 64] = f32x4{st.m[t], st.l[t][0], 0.f, 0.f};
       }
-      __syncthreads();
-      if (kg == 0 && slab_live) {
+    }
+    __syncthreads();
+    if (kg == 0 && slab_live) {
 #pragma unroll
-        for (int other = 1; other < KG; ++other) {   // in group order: deterministic
+      for (int other = 1; other < KG; ++other) {   // in group order: deterministic
         const f32x4* mbuf = mbuf0 + (other - 1) * kGroupSlots;
 #pragma unroll
         for (int t = 0; t < QT; ++t) {
@@ -1031,7 +975,6 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
 #pragma unroll
           for (int e = 0; e < DT; ++e) st.o[t][e] = st.o[t][e] * a0 + mbuf[(t * (DT + 1) + e) * 64] * a1;
         }
-        }
       }
     }
 
@@ -1042,36 +985,6 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
         const RowInfo ri = row_info(t);
         if (!ri.exists) continue;
         const float l_row = st.l[t][0];
-        if constexpr (D == 128) {
-          // operands from the transposing read: accumulator e holds dims 16e + 4*g4 .. +3
-          const float inv = ri.valid ? 1.0f / l_row : 0.f;
-          float* slot = p.part + (int64_t)(unit + w) * rows_per_unit * (D + 2);
-          const int lr = wave * ROWS + 16 * t + col;
-          if (!whole_unit && ri.valid && g4 == 0)
-            *reinterpret_cast<float2*>(slot + (int64_t)rows_per_unit * D + 2 * lr) = make_float2(st.m[t], l_row);
-#pragma unroll
-          for (int e = 0; e < DT; ++e) {
-            const int d0 = 16 * e + 4 * g4;
-            if (whole_unit) {
-              float vals[4];
-#pragma unroll
-              for (int i = 0; i < 4; ++i) vals[i] = ri.valid ? st.o[t][e][i] * inv : 0.f;
-              if (p.out_bf16) {
-                typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-                bf16x4 pk;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) pk[i] = (__bf16)vals[i];
-                *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + ri.out * D + d0) = pk;
-              } else {
-                *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + ri.out * D + d0) =
-                    f32x4{vals[0], vals[1], vals[2], vals[3]};
-              }
-            } else if (ri.valid) {
-              store_through(slot + partial_index<D>(lr, 4 * e + g4), st.o[t][e]);
-            }
-          }
-          continue;
-        }
 #pragma unroll
         for (int e0 = 0; e0 < DT; e0 += 4) {
           if (whole_unit) {
@@ -1107,6 +1020,372 @@ __global__ __launch_bounds__(64 * WAVES * KG, (KG == 1 ? 2 : 1)) void tree_attn_
     r += (unsigned)count;
     if (b + 1 < p.B && r >= seq_first_block(p, b + 1)) ++b;
     __syncthreads();  // every wavefront is done with the stages before the next segment refills them
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same decomposition for head dim 128 (four wavefronts of 32 rows, two key groups, K/V blocks shared through LDS), with
+// the matrix products as 32x32x16 tiles and every operand read issued half a turn ahead of its products.
+//
+// A turn is one 32-key block per wavefront. Its parts bound it about alike (64 / 8 heads, 60 nodes, us per 16384 keys: the
+// products alone 15.0, with weights and operand reads 21.6, the copies alone 20.0, all of it 28), so it is written as three
+// parts that hide each other:
+//   pv      O^T += V^T P^T of block i           under it the K operands of block i + 1 are read from LDS
+//   qk      S^T = K Q^T of block i + 1          under it the V operands of block i + 1
+//   weights p = 2^(S c - m), row sums           vector work only, no LDS
+// Vector and LDS instructions issue beside a 32x32x16 product at their own rate, of the same wavefront and of the SIMD's other
+// one (17 products with 48 vector instructions among them 564 clocks, the products alone 548; beside 16x16x32 products the
+// vector instructions take 525 instead of 399). The two key groups stand half a turn apart: the turn's one barrier comes
+// after `weights` in group 0 and before it in group 1, so that the vector part of one runs beside the products of the other.
+// The copies stand behind the products: issued among them they stalled the wavefront (28 -> 37). Rings of five blocks: as four.
+// Against 16x16x32 tiles with the reads in front of their products: 64 / 8 heads, 16384 keys 53.9 -> 52.0 us a call, 32 / 8
+// heads, 1000 keys 15.0 -> 14.7, 4096 keys 20.3 -> 20.4.
+//
+// Blocks lie in LDS row by row as they are copied (whole rows per request: as 64-byte pieces a 32 / 8-head call over 4096 keys
+// took a microsecond more), with the 16-byte chunks of a K row exchanged by key (c at c ^ (key & 15)) and the 64-byte pieces of
+// a V row (d at d ^ (key & 3)): reads then touch every bank once a pass.
+constexpr int kWideRing = 4;                        // K and V blocks that a key group holds
+constexpr int kWideTensor = kBlockKeys * 128 * 2;  // bytes of one tensor's block
+constexpr int kWideGroup = 2 * kWideRing * kWideTensor;
+// Weights stay below 2: a score that would go above moves its row's shift to 2^7 times the largest weight so far (the test is
+// the exponent's top bit of the packed weights). As with kLazyLog2, shifts move almost never after the first blocks.
+constexpr float kWideHeadroom = 7.0f;
+
+// O^T += V^T P^T of a block (v[s][dt]: 16 keys, 32 dims), and the K operands of the next block out of LDS.
+__device__ __forceinline__ void pv_reading_k(f32x16 (&o)[4], const bf16x8 (&v)[2][4], const bf16x8 (&w)[2], bf16x8 (&k)[8], unsigned ka) {
+  unsigned a0, a1;
+  asm volatile(
+      "ds_read_b128 %[k0], %[ka]\n\tv_xor_b32 %[a1], 32, %[ka]\n\tds_read_b128 %[k1], %[a1]\n\ts_nop 1\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[o0], %[v00], %[w0], %[o0]\n\tv_xor_b32 %[a0], 64, %[ka]\n\tds_read_b128 %[k2], %[a0]\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[o1], %[v01], %[w0], %[o1]\n\tv_xor_b32 %[a1], 0x60, %[ka]\n\tds_read_b128 %[k3], %[a1]\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[o2], %[v02], %[w0], %[o2]\n\tv_xor_b32 %[a0], 0x80, %[ka]\n\tds_read_b128 %[k4], %[a0]\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[o3], %[v03], %[w0], %[o3]\n\tv_xor_b32 %[a1], 0xa0, %[ka]\n\tds_read_b128 %[k5], %[a1]\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[o0], %[v10], %[w1], %[o0]\n\tv_xor_b32 %[a0], 0xc0, %[ka]\n\tds_read_b128 %[k6], %[a0]\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[o1], %[v11], %[w1], %[o1]\n\tv_xor_b32 %[a1], 0xe0, %[ka]\n\tds_read_b128 %[k7], %[a1]\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[o2], %[v12], %[w1], %[o2]\n\tv_mfma_f32_32x32x16_bf16 %[o3], %[v13], %[w1], %[o3]\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : [o0] "+v"(o[0]), [o1] "+v"(o[1]), [o2] "+v"(o[2]), [o3] "+v"(o[3]), [k0] "=&v"(k[0]), [k1] "=&v"(k[1]), [k2] "=&v"(k[2]),
+        [k3] "=&v"(k[3]), [k4] "=&v"(k[4]), [k5] "=&v"(k[5]), [k6] "=&v"(k[6]), [k7] "=&v"(k[7]), [a0] "=&v"(a0), [a1] "=&v"(a1)
+      : [v00] "v"(v[0][0]), [v01] "v"(v[0][1]), [v02] "v"(v[0][2]), [v03] "v"(v[0][3]), [v10] "v"(v[1][0]), [v11] "v"(v[1][1]),
+        [v12] "v"(v[1][2]), [v13] "v"(v[1][3]), [w0] "v"(w[0]), [w1] "v"(w[1]), [ka] "v"(ka)
+      : "memory");
+}
+// K operands alone (a segment's first block)
+__device__ __forceinline__ void read_k(bf16x8 (&k)[8], unsigned ka) {
+  unsigned a0, a1;
+  asm volatile(
+      "ds_read_b128 %[k0], %[ka]\n\tv_xor_b32 %[a0], 32, %[ka]\n\tds_read_b128 %[k1], %[a0]\n\tv_xor_b32 %[a1], 64, %[ka]\n\t"
+      "ds_read_b128 %[k2], %[a1]\n\tv_xor_b32 %[a0], 0x60, %[ka]\n\tds_read_b128 %[k3], %[a0]\n\tv_xor_b32 %[a1], 0x80, %[ka]\n\t"
+      "ds_read_b128 %[k4], %[a1]\n\tv_xor_b32 %[a0], 0xa0, %[ka]\n\tds_read_b128 %[k5], %[a0]\n\tv_xor_b32 %[a1], 0xc0, %[ka]\n\t"
+      "ds_read_b128 %[k6], %[a1]\n\tv_xor_b32 %[a0], 0xe0, %[ka]\n\tds_read_b128 %[k7], %[a0]\n\ts_waitcnt lgkmcnt(0)"
+      : [k0] "=&v"(k[0]), [k1] "=&v"(k[1]), [k2] "=&v"(k[2]), [k3] "=&v"(k[3]), [k4] "=&v"(k[4]), [k5] "=&v"(k[5]), [k6] "=&v"(k[6]), [k7] "=&v"(k[7]),
+        [a0] "=&v"(a0), [a1] "=&v"(a1)
+      : [ka] "v"(ka)
+      : "memory");
+}
+// S^T = K Q^T of a block, and its V operands out of LDS (r: halves of v[s][dt], four keys each). The wait states at the end are
+// those between a matrix instruction and a vector instruction that reads its result.
+__device__ __forceinline__ void qk_reading_v(f32x16& s, const bf16x8 (&k)[8], const bf16x8 (&q)[8], u32x2 (&r)[16], unsigned va) {
+  unsigned a0, a1;
+  asm volatile(
+      "v_mfma_f32_32x32x16_bf16 %[s], %[k0], %[q0], 0\n\tds_read_b64_tr_b16 %[r0], %[va]\n\t"
+      "ds_read_b64_tr_b16 %[r1], %[va] offset:2048\n\tv_mfma_f32_32x32x16_bf16 %[s], %[k1], %[q1], %[s]\n\t"
+      "ds_read_b64_tr_b16 %[r8], %[va] offset:4096\n\tds_read_b64_tr_b16 %[r9], %[va] offset:6144\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[s], %[k2], %[q2], %[s]\n\tv_xor_b32 %[a1], 0x40, %[va]\n\tds_read_b64_tr_b16 %[r2], %[a1]\n\t"
+      "ds_read_b64_tr_b16 %[r3], %[a1] offset:2048\n\tv_mfma_f32_32x32x16_bf16 %[s], %[k3], %[q3], %[s]\n\t"
+      "ds_read_b64_tr_b16 %[r10], %[a1] offset:4096\n\tds_read_b64_tr_b16 %[r11], %[a1] offset:6144\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[s], %[k4], %[q4], %[s]\n\tv_xor_b32 %[a0], 0x80, %[va]\n\tds_read_b64_tr_b16 %[r4], %[a0]\n\t"
+      "ds_read_b64_tr_b16 %[r5], %[a0] offset:2048\n\tv_mfma_f32_32x32x16_bf16 %[s], %[k5], %[q5], %[s]\n\t"
+      "ds_read_b64_tr_b16 %[r12], %[a0] offset:4096\n\tds_read_b64_tr_b16 %[r13], %[a0] offset:6144\n\t"
+      "v_mfma_f32_32x32x16_bf16 %[s], %[k6], %[q6], %[s]\n\tv_xor_b32 %[a1], 0xc0, %[va]\n\tds_read_b64_tr_b16 %[r6], %[a1]\n\t"
+      "ds_read_b64_tr_b16 %[r7], %[a1] offset:2048\n\tv_mfma_f32_32x32x16_bf16 %[s], %[k7], %[q7], %[s]\n\t"
+      "ds_read_b64_tr_b16 %[r14], %[a1] offset:4096\n\tds_read_b64_tr_b16 %[r15], %[a1] offset:6144\n\ts_waitcnt lgkmcnt(0)\n\t"
+      "s_nop 13"
+      : [s] "=&v"(s), [a0] "=&v"(a0), [a1] "=&v"(a1), [r0] "=&v"(r[0]), [r1] "=&v"(r[1]), [r2] "=&v"(r[2]), [r3] "=&v"(r[3]), [r4] "=&v"(r[4]), [r5] "=&v"(r[5]),
+        [r6] "=&v"(r[6]), [r7] "=&v"(r[7]), [r8] "=&v"(r[8]), [r9] "=&v"(r[9]), [r10] "=&v"(r[10]), [r11] "=&v"(r[11]),
+        [r12] "=&v"(r[12]), [r13] "=&v"(r[13]), [r14] "=&v"(r[14]), [r15] "=&v"(r[15])
+      : [k0] "v"(k[0]), [k1] "v"(k[1]), [k2] "v"(k[2]), [k3] "v"(k[3]), [k4] "v"(k[4]), [k5] "v"(k[5]), [k6] "v"(k[6]),
+        [k7] "v"(k[7]), [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [q4] "v"(q[4]), [q5] "v"(q[5]),
+        [q6] "v"(q[6]), [q7] "v"(q[7]), [va] "v"(va)
+      : "memory");
+}
+
+// Weights p = 2^(s c - m) of a row's 16 keys in bf16, and their sum added to l. `grow`: lanes with a weight of 2 or more.
+__device__ __forceinline__ void weights_of(const f32x16& s, float c, float m, unsigned (&p)[8], float& l, uint64_t& grow) {
+  float t[16];
+  unsigned x;
+  asm volatile(
+      "v_fma_f32 %[t0], %[s0], %[c], -%[m]\n\tv_fma_f32 %[t1], %[s1], %[c], -%[m]\n\tv_fma_f32 %[t2], %[s2], %[c], -%[m]\n\t"
+      "v_fma_f32 %[t3], %[s3], %[c], -%[m]\n\tv_exp_f32 %[t0], %[t0]\n\tv_fma_f32 %[t4], %[s4], %[c], -%[m]\n\t"
+      "v_exp_f32 %[t1], %[t1]\n\tv_fma_f32 %[t5], %[s5], %[c], -%[m]\n\tv_exp_f32 %[t2], %[t2]\n\t"
+      "v_fma_f32 %[t6], %[s6], %[c], -%[m]\n\tv_exp_f32 %[t3], %[t3]\n\tv_fma_f32 %[t7], %[s7], %[c], -%[m]\n\t"
+      "v_exp_f32 %[t4], %[t4]\n\tv_fma_f32 %[t8], %[s8], %[c], -%[m]\n\tv_exp_f32 %[t5], %[t5]\n\t"
+      "v_fma_f32 %[t9], %[s9], %[c], -%[m]\n\tv_exp_f32 %[t6], %[t6]\n\tv_fma_f32 %[t10], %[s10], %[c], -%[m]\n\t"
+      "v_exp_f32 %[t7], %[t7]\n\tv_fma_f32 %[t11], %[s11], %[c], -%[m]\n\tv_exp_f32 %[t8], %[t8]\n\t"
+      "v_fma_f32 %[t12], %[s12], %[c], -%[m]\n\tv_exp_f32 %[t9], %[t9]\n\tv_fma_f32 %[t13], %[s13], %[c], -%[m]\n\t"
+      "v_exp_f32 %[t10], %[t10]\n\tv_fma_f32 %[t14], %[s14], %[c], -%[m]\n\tv_exp_f32 %[t11], %[t11]\n\t"
+      "v_fma_f32 %[t15], %[s15], %[c], -%[m]\n\tv_exp_f32 %[t12], %[t12]\n\tv_cvt_pk_bf16_f32 %[p0], %[t0], %[t1]\n\t"
+      "v_cvt_pk_bf16_f32 %[p1], %[t2], %[t3]\n\tv_exp_f32 %[t13], %[t13]\n\tv_dot2c_f32_bf16 %[l], 0x3f803f80, %[p0]\n\t"
+      "v_cvt_pk_bf16_f32 %[p2], %[t4], %[t5]\n\tv_exp_f32 %[t14], %[t14]\n\tv_dot2c_f32_bf16 %[l], 0x3f803f80, %[p1]\n\t"
+      "v_cvt_pk_bf16_f32 %[p3], %[t6], %[t7]\n\tv_exp_f32 %[t15], %[t15]\n\tv_dot2c_f32_bf16 %[l], 0x3f803f80, %[p2]\n\t"
+      "v_cvt_pk_bf16_f32 %[p4], %[t8], %[t9]\n\tv_dot2c_f32_bf16 %[l], 0x3f803f80, %[p3]\n\t"
+      "v_cvt_pk_bf16_f32 %[p5], %[t10], %[t11]\n\tv_dot2c_f32_bf16 %[l], 0x3f803f80, %[p4]\n\t"
+      "v_or3_b32 %[x], %[p0], %[p1], %[p2]\n\tv_cvt_pk_bf16_f32 %[p6], %[t12], %[t13]\n\t"
+      "v_dot2c_f32_bf16 %[l], 0x3f803f80, %[p5]\n\tv_or3_b32 %[x], %[x], %[p3], %[p4]\n\t"
+      "v_cvt_pk_bf16_f32 %[p7], %[t14], %[t15]\n\tv_dot2c_f32_bf16 %[l], 0x3f803f80, %[p6]\n\t"
+      "v_or3_b32 %[x], %[x], %[p5], %[p6]\n\tv_dot2c_f32_bf16 %[l], 0x3f803f80, %[p7]\n\tv_or_b32 %[x], %[x], %[p7]\n\t"
+      "v_and_b32 %[x], 0x40004000, %[x]\n\tv_cmp_ne_u32_e64 %[g], 0, %[x]"
+      : [p0] "=&v"(p[0]), [p1] "=&v"(p[1]), [p2] "=&v"(p[2]), [p3] "=&v"(p[3]), [p4] "=&v"(p[4]), [p5] "=&v"(p[5]),
+        [p6] "=&v"(p[6]), [p7] "=&v"(p[7]), [t0] "=&v"(t[0]), [t1] "=&v"(t[1]), [t2] "=&v"(t[2]), [t3] "=&v"(t[3]),
+        [t4] "=&v"(t[4]), [t5] "=&v"(t[5]), [t6] "=&v"(t[6]), [t7] "=&v"(t[7]), [t8] "=&v"(t[8]), [t9] "=&v"(t[9]),
+        [t10] "=&v"(t[10]), [t11] "=&v"(t[11]), [t12] "=&v"(t[12]), [t13] "=&v"(t[13]), [t14] "=&v"(t[14]), [t15] "=&v"(t[15]),
+        [x] "=&v"(x), [l] "+v"(l), [g] "=&s"(grow)
+      : [s0] "v"(s[0]), [s1] "v"(s[1]), [s2] "v"(s[2]), [s3] "v"(s[3]), [s4] "v"(s[4]), [s5] "v"(s[5]), [s6] "v"(s[6]),
+        [s7] "v"(s[7]), [s8] "v"(s[8]), [s9] "v"(s[9]), [s10] "v"(s[10]), [s11] "v"(s[11]), [s12] "v"(s[12]), [s13] "v"(s[13]),
+        [s14] "v"(s[14]), [s15] "v"(s[15]), [c] "v"(c), [m] "v"(m));
+}
+
+__global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams) {
+  const AttnArgs p = fetch_args();
+  constexpr int D = 128, KG = 2, WAVES = 4, ROWS = 32, rows_per_unit = WAVES * ROWS;
+  __shared__ __attribute__((aligned(1024))) char lds_all[KG * kWideGroup];
+
+  const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kg = wave_all >> 2, wave = wave_all & 3;   // key group, row slab within the workgroup
+  char* const ring = lds_all + kg * kWideGroup;        // K blocks, then V blocks
+  const int row = lane & 31, h = lane >> 5;
+  const float c = p.scale * kLog2e;
+  const unsigned tree_row_bytes = (unsigned)p.Hkv * D * 2u;
+  const unsigned cache_row_bytes = (unsigned)p.stride_token * 2u;
+
+  // this wavefront's copies: eight keys of each tensor, four per instruction (this lane: key copy_key, and copy_key + 4)
+  const int copy_key = 8 * wave + (lane >> 4);
+  const unsigned chunk = lane & 15;
+  const unsigned k_chunk[2] = {16u * (chunk ^ (copy_key & 15)), 16u * (chunk ^ ((copy_key + 4) & 15))}, v_chunk = 16u * (chunk ^ (4 * (copy_key & 3)));
+  const unsigned copy_dst = 2048u * wave;
+  // this lane's operand reads of a block in slot 0
+  const unsigned lds0 = (unsigned)(uintptr_t)(LdsPtr)ring;
+  const unsigned k_at = lds0 + 256u * row + 16u * (h ^ (row & 15));
+  const unsigned v_at = lds0 + kWideRing * kWideTensor + 256u * (4 * h + ((lane >> 2) & 3)) + 64u * ((lane >> 2) & 3) + 32u * ((lane >> 4) & 1) + 8u * (lane & 3);
+
+  const unsigned w = blockIdx.x;
+  const unsigned wr = w * (unsigned)p.wg_rem, wq = wr / (unsigned)p.n_wgs;
+  const unsigned r0 = w * (unsigned)p.wg_quot + wq;
+  const unsigned r1 = r0 + (unsigned)p.wg_quot + ((wr - wq * (unsigned)p.n_wgs) + (unsigned)p.wg_rem >= (unsigned)p.n_wgs ? 1u : 0u);
+  int b = seq_of_block(p, r0);
+
+  for (unsigned r = r0; r < r1;) {
+    const int n = seq_nodes(p, b);
+    const int L = seq_len(p, b);
+    const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
+    const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
+    const unsigned rel = r - seq_first_block(p, b);
+    const int counted = n_blocks + p.setup;
+    const int ub = (int)(rel / (unsigned)counted);
+    const int from = (int)(rel - (unsigned)ub * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
+    const int seg_begin = max(from - p.setup, 0), seg_count = from + count - p.setup - seg_begin;
+    if (seg_count <= 0) {   // nothing but set-up
+      r += (unsigned)count;
+      continue;
+    }
+    const int n_slabs = seq_slabs(p, n, ROWS), n_groups = seq_groups(p, n_slabs);
+    const int g = head_of(p, ub, n_groups), y = ub - g * n_groups;
+    const int unit = b * p.Hkv * p.GY + ub;
+    const bool whole_unit = seg_count == n_blocks;
+    const int slab = y * WAVES + wave;
+
+    const char* kc = reinterpret_cast<const char*>(p.k_cache) + (b * p.stride_batch + g * p.stride_head) * 2;
+    const char* vc = reinterpret_cast<const char*>(p.v_cache) + (b * p.stride_batch + g * p.stride_head) * 2;
+    const int64_t tree0 = ((int64_t)b * p.Nmax * p.Hkv + g) * (D * 2);
+
+    // blocks of this key group: kg, kg + 2, ... of the segment; those before n_full are whole prefix blocks
+    const int blk_begin = seg_begin + kg;
+    const int n_own = (seg_count - kg + KG - 1) / KG;
+    const int n_full = (min(seg_begin + seg_count, L / kBlockKeys) - blk_begin + KG - 1) >> 1;   // (not positive: none)
+    const int64_t first_byte = (int64_t)blk_begin * kBlockKeys * cache_row_bytes;
+    const int64_t step = (int64_t)(KG * kBlockKeys) * cache_row_bytes;
+
+    // Where this wavefront's copies of block i of its key group come from. Every turn copies four pieces, so that the count of
+    // copies in flight tells what has landed; past the last block it is the segment's first row.
+    const char *k_src = kc + first_byte, *v_src = vc + first_byte;
+    unsigned row_at[2] = {(unsigned)copy_key * cache_row_bytes, (unsigned)(copy_key + 4) * cache_row_bytes};
+    auto locate_rest = [&](int i) {   // not a whole prefix block
+      const int blk = i < n_own ? blk_begin + KG * i : seg_begin;
+      const bool tree = blk >= n_prefix_blocks;
+      const int key0 = (tree ? blk - n_prefix_blocks : blk) * kBlockKeys, left = i < n_own ? (tree ? n : L) - key0 : 1;
+      const unsigned rb = tree ? tree_row_bytes : cache_row_bytes;
+      const int64_t at = (int64_t)key0 * rb;
+      k_src = (tree ? reinterpret_cast<const char*>(p.k_tree) + tree0 : kc) + at;
+      v_src = (tree ? reinterpret_cast<const char*>(p.v_tree) + tree0 : vc) + at;
+      row_at[0] = (unsigned)min(copy_key, left - 1) * rb;   // (rows past the end are masked later)
+      row_at[1] = (unsigned)min(copy_key + 4, left - 1) * rb;
+    };
+    auto locate = [&](int i) {   // blocks in order
+      if (i >= n_full) locate_rest(i);
+      else if (i > 0) { k_src += step; v_src += step; }
+    };
+    auto copy_block = [&](unsigned at) {
+      char* dst = ring + at + copy_dst;
+#pragma unroll
+      for (int x = 0; x < 2; ++x) __builtin_amdgcn_global_load_lds((GlobalPtr)(k_src + (row_at[x] + k_chunk[x])), (LdsPtr)(dst + 1024 * x), 16, 0, 0);
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+        __builtin_amdgcn_global_load_lds((GlobalPtr)(v_src + (row_at[x] + v_chunk)), (LdsPtr)(dst + kWideRing * kWideTensor + 1024 * x), 16, 0, 0);
+    };
+    locate(0);
+    copy_block(0);
+
+    // this lane's row: row rr of the kv head's N*G rows = (node, head within group)
+    const int rr = slab * ROWS + row;
+    const int node = (int)div_magic((unsigned)rr, p.G, p.g_magic);
+    const bool exists = rr < p.Nmax * p.G, valid = exists && node < n;
+    const int64_t out_row = ((int64_t)b * p.Nmax + node) * p.Hq + g * p.G + (rr - node * p.G);
+    bf16x8 q[8];
+    uint64_t tree_mask = 0;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) q[ks] = bf16x8{};
+    if (valid) {
+      const __bf16* qrow = reinterpret_cast<const __bf16*>(p.q) + out_row * D + 8 * h;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) q[ks] = *reinterpret_cast<const bf16x8*>(qrow + 16 * ks);
+      tree_mask = p.anc_mask[b * p.Nmax + node];
+    }
+#pragma unroll 1
+    for (int i = 1; i < kWideRing; ++i) {
+      locate(i);
+      copy_block(i * kWideTensor);
+    }
+    if (seg_begin == 0 && y == 0) {
+      const int covered = n_groups * rows_per_unit;
+      if (covered < p.Nmax * p.G) zero_rows<D, 64 * WAVES * KG>(p, b, g, covered);
+    }
+
+    f32x16 o[4], s;
+    float m = kNegBig, l = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+    bf16x8 k[8], v[2][4], wt[2];
+    u32x2 vr[16];
+
+    auto barrier = [] {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (kWideRing - 1)) : "memory");   // block 0 (and Q, requested behind it)
+    barrier();
+    read_k(k, k_at);
+    unsigned slot = 0;
+    for (int i = 0; i < n_own; ++i) {
+      const unsigned slot_next = slot + kWideTensor == kWideRing * kWideTensor ? 0u : slot + kWideTensor;
+      qk_reading_v(s, k, q, vr, v_at + slot);
+      if (kg == 1) {
+        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (kWideRing - 2)) : "memory");
+        barrier();
+      }
+      if (i >= n_full) {   // ragged tail or tree block
+        const int blk = blk_begin + KG * i;
+        const bool tree = blk >= n_prefix_blocks;
+        const int key0 = (tree ? blk - n_prefix_blocks : blk) * kBlockKeys, left = (tree ? n : L) - key0;
+        unsigned vis = left >= kBlockKeys ? ~0u : ((1u << left) - 1u);
+        if (tree) vis &= (unsigned)(tree_mask >> key0);
+        vis >>= 4 * h;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = ((vis >> (8 * (e >> 2) + (e & 3))) & 1u) ? s[e] : -INFINITY;
+      }
+      unsigned pk[8];
+      uint64_t grow;
+      const float l_before = l;
+      weights_of(s, c, m, pk, l, grow);
+      if (grow != 0) {   // rare: move the rows' shifts
+        float mx = s[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mnew = fmaxf(m, fmaf(mx, c, kWideHeadroom));
+        const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+        m = mnew;
+        l = l_before * alpha;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
+        weights_of(s, c, m, pk, l, grow);
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) wt[t] = __builtin_bit_cast(bf16x8, u32x4{pk[4 * t], pk[4 * t + 1], pk[4 * t + 2], pk[4 * t + 3]});
+      if (kg == 0) {
+        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (kWideRing - 2)) : "memory");
+        barrier();
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) {
+          const int x = 2 * (4 * t + dt);
+          v[t][dt] = __builtin_bit_cast(bf16x8, u32x4{vr[x][0], vr[x][1], vr[x + 1][0], vr[x + 1][1]});
+        }
+      pv_reading_k(o, v, wt, k, k_at + slot_next);
+      // block i is read by all four wavefronts: its place in the ring takes a later one
+      locate(i + kWideRing);
+      copy_block(slot);
+      slot = slot_next;
+    }
+    if (kg == 1 && (seg_count & 1)) barrier();   // group 0 has a block more
+
+    // The two key groups hold the same rows in the same lanes. Group 0 finishes dims 0..63 and group 1 dims 64..127: each hands
+    // the other half over in lane-private LDS slots (the rings are free), so that all eight wavefronts merge and write.
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 7" ::: "memory");   // (products of the last block, issued in assembly, before the first vector read)
+    __syncthreads();
+    f32x4* const mbuf = reinterpret_cast<f32x4*>(lds_all) + wave * (2 * 8 * 64) + lane;
+    float2* const ml = reinterpret_cast<float2*>(lds_all + 65536) + wave * 128 + lane;
+    l += __shfl_xor(l, 32);
+    ml[kg * 64] = make_float2(m, l);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const int e = 4 * (x & 3);
+      const f32x16 give = kg == 0 ? o[2 + (x >> 2)] : o[x >> 2];
+      mbuf[(kg * 8 + x) * 64] = f32x4{give[e], give[e + 1], give[e + 2], give[e + 3]};
+    }
+    __syncthreads();
+    if (exists) {
+      const float2 a = ml[0], bb = ml[64];
+      const float mm = fmaxf(a.x, bb.x);
+      const float f0 = __builtin_amdgcn_exp2f(a.x - mm), f1 = __builtin_amdgcn_exp2f(bb.x - mm);
+      const float l_row = a.y * f0 + bb.y * f1;
+      const float own = kg == 0 ? f0 : f1, other = kg == 0 ? f1 : f0;
+      const float inv = whole_unit ? (valid ? 1.0f / l_row : 0.f) : 1.0f;
+      float* const slot = p.part + (int64_t)(unit + w) * rows_per_unit * (D + 2);
+      const int lr = wave * ROWS + row;
+      if (!whole_unit && valid && lane < 32 && kg == 0) *reinterpret_cast<float2*>(slot + (int64_t)rows_per_unit * D + 2 * lr) = make_float2(mm, l_row);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int e = 4 * (x & 3), d0 = 64 * kg + 32 * (x >> 2) + 8 * (x & 3) + 4 * h;
+        const f32x16 keep = kg == 0 ? o[x >> 2] : o[2 + (x >> 2)];
+        const f32x4 got = mbuf[((kg ^ 1) * 8 + x) * 64];
+        f32x4 val;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) val[j] = keep[e + j] * own + got[j] * other;
+        if (!whole_unit) {
+          if (valid) store_through(slot + partial_index<D>(lr, d0 / 4), val);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) val[j] = valid ? val[j] * inv : 0.f;
+          if (p.out_bf16) {
+            typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+            bf16x4 o4;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o4[j] = (__bf16)val[j];
+            *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + out_row * D + d0) = o4;
+          } else {
+            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + out_row * D + d0) = val;
+          }
+        }
+      }
+    }
+    r += (unsigned)count;
+    if (b + 1 < p.B && r >= seq_first_block(p, b + 1)) ++b;
+    __syncthreads();  // every wavefront is done with the merge buffers before the next segment fills the rings
   }
 }
 
@@ -1646,10 +1925,10 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       const size_t need = (size_t)slots_of(pl, full_units, full_wgs, full_total, d.workgroups) * slot_bytes(d, pl);
       if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 15)) return FSPAD_ERR_WORKSPACE;
       if (pl.shared_stage) {
-        if (d.head_dim == 128) hipLaunchKernelGGL((tree_attn_gqa_kernel<128, 4, 2>), dim3((unsigned)sl.n_wgs), dim3(512), 0, stream, sl);
+        if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_gqa128_kernel, dim3((unsigned)sl.n_wgs), dim3(512), 0, stream, sl);
         // (head dim 64 leaves registers for three wavefronts per SIMD: three key groups; 43.1 -> 40.6 us on a
         // 64/8-head, 16384-key, 60-node call, 70.7 -> 64.5 us at 32768 keys)
-        else hipLaunchKernelGGL((tree_attn_gqa_kernel<64, 4, 3>), dim3((unsigned)sl.n_wgs), dim3(768), 0, stream, sl);
+        else hipLaunchKernelGGL(tree_attn_gqa64_kernel, dim3((unsigned)sl.n_wgs), dim3(768), 0, stream, sl);
       } else {
         // keys and values of the call, read once each (one slab group per kv head). Not the 48- and 64-row tiles of
         // D = 128 where a compute unit takes more than two workgroups in turn: 16 x 40 heads, 60 nodes, 2500 keys 172 us

@@ -391,3 +391,14 @@ def test_bf16_ragged_batches_count_set_up(H, Hq, Hkv, N, D, kv_len, splits):
     case = H.AttnCase(600 + N + len(kv_len), 6, N, Hq, Hkv, D, max(kv_len), "bf16", kv_len=kv_len,
                       n_nodes=[N, 1, max(1, N // 2), N, 3, max(1, N // 3)])
     _check(H, case, H.TOL["bf16"], **({"splits": splits} if splits else {}))
+
+
+@pytest.mark.parametrize("L,splits", [(0, 1), (5, 3), (64, 1), (95, 2), (160, 1), (256, 1), (289, 5), (1000, 1), (1000, 9), (1031, 40)])
+@pytest.mark.parametrize("N,Hq,Hkv,scale", [(33, 4, 1, 0.0), (60, 8, 2, 1.0), (17, 8, 1, 0.3)])
+def test_bf16_shared_stage_rings_and_segments(H, N, Hq, Hkv, scale, L, splits):
+    """Segments of one to sixty blocks, odd and even, one or several to a workgroup: each length wraps the rings of K/V blocks
+    elsewhere and ends the two key groups differently. Scale 1.0 spreads the scores over tens of powers of two, so that the
+    shifts of the softmax keep moving along the stream. A tree smaller than the batch's largest leaves slabs without rows."""
+    case = H.AttnCase(77 * N + L + splits, 2, N, Hq, Hkv, 128, L, "bf16", l_cap=L + 3, n_nodes=[N, (N + 1) // 2])
+    out, _, _ = _check(H, case, H.TOL["bf16"], splits=splits, **({"scale": scale} if scale else {}))
+    assert torch.equal(out, case.run_gpu(splits=splits, **({"scale": scale} if scale else {})))
