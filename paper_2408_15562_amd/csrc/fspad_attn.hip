@@ -64,6 +64,7 @@ struct AttnParams {
   // lengths by arithmetic instead of dependent loads from the arrays below
   int32_t seq_blocks, same_len, same_nodes;
   int32_t setup;    // blocks that every unit counts for beyond its own in the flat list (ragged batches; setup_blocks)
+  uint32_t wgs_rcp, seq_rcp, unit_rcp;  // reciprocals (div_rcp) of n_wgs and, with seq_blocks > 0, of that and of the blocks a unit counts for
   int32_t kv_len[kMaxBatchPerLaunch];
   int32_t bstart[kMaxBatchPerLaunch + 1];  // first flat block of each sequence; bstart[B] = total_blocks
   int32_t n_nodes[kMaxBatchPerLaunch];
@@ -91,10 +92,11 @@ struct AttnArgs {
   int32_t out_bf16;
   float scale;
   int32_t seq_blocks, same_len, same_nodes, setup;
+  uint32_t wgs_rcp, seq_rcp, unit_rcp;
   KernargI32 kv_len, bstart, n_nodes;
 };
 static_assert(offsetof(AttnParams, stride_batch) == 64 && offsetof(AttnParams, B) == 88 && offsetof(AttnParams, total_blocks) == 128 &&
-              offsetof(AttnParams, scale) == 152 && offsetof(AttnParams, same_nodes) == 164 && offsetof(AttnParams, setup) == 168 && offsetof(AttnParams, kv_len) == 172,
+              offsetof(AttnParams, scale) == 152 && offsetof(AttnParams, same_nodes) == 164 && offsetof(AttnParams, setup) == 168 && offsetof(AttnParams, unit_rcp) == 180 && offsetof(AttnParams, kv_len) == 184,
               "fetch_args reads the scalars by their offsets");
 
 __device__ __forceinline__ AttnArgs fetch_args() {
@@ -125,14 +127,23 @@ __device__ __forceinline__ AttnArgs fetch_args() {
   const int scale_bits = c[6];   // (a bit cast straight from the vector element reads element 0)
   r.scale = __builtin_bit_cast(float, scale_bits);
   r.seq_blocks = c[7]; r.same_len = c[8]; r.same_nodes = c[9]; r.setup = c[10];
+  r.wgs_rcp = (uint32_t)c[11]; r.seq_rcp = (uint32_t)c[12]; r.unit_rcp = (uint32_t)c[13];
   r.kv_len = (KernargI32)(ka + offsetof(AttnParams, kv_len));
   r.bstart = (KernargI32)(ka + offsetof(AttnParams, bstart));
   r.n_nodes = (KernargI32)(ka + offsetof(AttnParams, n_nodes));
   return r;
 }
+// x / d with rcp = floor(2^32 / d) from the host (2^32 - 1 for d = 1): the product's high half is the quotient or one less.
+// A division whose divisor the compiler does not know is some 22 instructions with a trip through the vector unit and back, and
+// a workgroup made three of them, a merging one too, before its first request: 32 / 8 heads, 60 nodes, 1000 keys 14.76 -> 14.50 us a
+// call, 32 heads, 26 nodes, 2048 keys 16.08 -> 15.94.
+__device__ __forceinline__ unsigned div_rcp(unsigned x, unsigned d, unsigned rcp) {
+  const unsigned q = __umulhi(x, rcp);
+  return q + (x - q * d >= d ? 1u : 0u);
+}
 // sequence that flat block r0 belongs to, and the first flat block / lengths of a sequence
 __device__ __forceinline__ int seq_of_block(const AttnArgs& p, unsigned r0) {
-  if (p.seq_blocks > 0) return (int)(r0 / (unsigned)p.seq_blocks);
+  if (p.seq_blocks > 0) return (int)div_rcp(r0, (unsigned)p.seq_blocks, p.seq_rcp);
   int b = 0;
   while (b + 1 < p.B && r0 >= (unsigned)p.bstart[b + 1]) ++b;
   return b;
@@ -142,6 +153,17 @@ __device__ __forceinline__ unsigned seq_first_block(const AttnArgs& p, int b) {
 }
 __device__ __forceinline__ int seq_nodes(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_nodes : p.n_nodes[b]; }
 __device__ __forceinline__ int seq_len(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_len : p.kv_len[b]; }
+
+// flat blocks [r0, r1) of workgroup w: [floor(w*T/W), floor((w+1)*T/W)) with T = wg_quot*W + wg_rem
+__device__ __forceinline__ void workgroup_blocks(const AttnArgs& p, unsigned w, unsigned& r0, unsigned& r1) {
+  const unsigned wr = w * (unsigned)p.wg_rem, wq = div_rcp(wr, (unsigned)p.n_wgs, p.wgs_rcp);
+  r0 = w * (unsigned)p.wg_quot + wq;
+  r1 = r0 + (unsigned)p.wg_quot + ((wr - wq * (unsigned)p.n_wgs) + (unsigned)p.wg_rem >= (unsigned)p.n_wgs ? 1u : 0u);
+}
+// unit that flat block `rel` of a sequence belongs to, its units counting for `counted` blocks each
+__device__ __forceinline__ int unit_of_block(const AttnArgs& p, unsigned rel, int counted) {
+  return (int)(p.seq_blocks > 0 ? div_rcp(rel, (unsigned)counted, p.unit_rcp) : rel / (unsigned)counted);
+}
 
 // x / d for x*d < 2^32, with magic = ceil(2^32 / d) (d >= 2) from the host
 __device__ __forceinline__ unsigned div_magic(unsigned x, int d, unsigned magic) {
@@ -446,10 +468,8 @@ __global__ __launch_bounds__(256, (QT == 1 || (QT == 2 && D == 128 && !RAGGED) ?
   // index arithmetic up to the first loads is 32-bit, and divisions by the launch's constants
   // are multiplications.
   const unsigned w = blockIdx.x;
-  // [r0, r1) = [floor(w*T/W), floor((w+1)*T/W)) with T = wg_quot*W + wg_rem, from one division
-  const unsigned wr = w * (unsigned)p.wg_rem, wq = wr / (unsigned)p.n_wgs;
-  const unsigned r0 = w * (unsigned)p.wg_quot + wq;
-  const unsigned r1 = r0 + (unsigned)p.wg_quot + ((wr - wq * (unsigned)p.n_wgs) + (unsigned)p.wg_rem >= (unsigned)p.n_wgs ? 1u : 0u);
+  unsigned r0, r1;
+  workgroup_blocks(p, w, r0, r1);
   int b = seq_of_block(p, r0);
 
   for (unsigned r = r0; r < r1;) {
@@ -459,7 +479,7 @@ __global__ __launch_bounds__(256, (QT == 1 || (QT == 2 && D == 128 && !RAGGED) ?
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
     const unsigned rel = r - seq_first_block(p, b);
     const int counted = RAGGED ? n_blocks + p.setup : n_blocks;  // what the unit counts for: its set-up first, then its blocks
-    const int ub = (int)(rel / (unsigned)counted);               // unit within the sequence: (g, y)
+    const int ub = unit_of_block(p, rel, counted);                // unit within the sequence: (g, y)
     int seg_begin = (int)(rel - (unsigned)ub * (unsigned)counted);
     int seg_count = min(counted - seg_begin, (int)(r1 - r));
     const int count = seg_count;
@@ -794,9 +814,8 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) 
   for (int j = 0; j < 8; ++j) vrow[j] = S::kTensorBytes + (unsigned)key_of(g4, j) * (D * 2) + (unsigned)(D / 8) * col;
 
   const unsigned w = blockIdx.x;
-  const unsigned wr = w * (unsigned)p.wg_rem, wq = wr / (unsigned)p.n_wgs;
-  const unsigned r0 = w * (unsigned)p.wg_quot + wq;
-  const unsigned r1 = r0 + (unsigned)p.wg_quot + ((wr - wq * (unsigned)p.n_wgs) + (unsigned)p.wg_rem >= (unsigned)p.n_wgs ? 1u : 0u);
+  unsigned r0, r1;
+  workgroup_blocks(p, w, r0, r1);
   int b = seq_of_block(p, r0);
 
   for (unsigned r = r0; r < r1;) {
@@ -806,7 +825,7 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) 
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
     const unsigned rel = r - seq_first_block(p, b);
     const int counted = n_blocks + p.setup;
-    const int ub = (int)(rel / (unsigned)counted);
+    const int ub = unit_of_block(p, rel, counted);
     const int from = (int)(rel - (unsigned)ub * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
     const int seg_begin = max(from - p.setup, 0), seg_count = from + count - p.setup - seg_begin;
     if (seg_count <= 0) {   // nothing but set-up
@@ -1169,9 +1188,8 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams)
   const unsigned v_at = lds0 + kWideRing * kWideTensor + 256u * (4 * h + ((lane >> 2) & 3)) + 64u * ((lane >> 2) & 3) + 32u * ((lane >> 4) & 1) + 8u * (lane & 3);
 
   const unsigned w = blockIdx.x;
-  const unsigned wr = w * (unsigned)p.wg_rem, wq = wr / (unsigned)p.n_wgs;
-  const unsigned r0 = w * (unsigned)p.wg_quot + wq;
-  const unsigned r1 = r0 + (unsigned)p.wg_quot + ((wr - wq * (unsigned)p.n_wgs) + (unsigned)p.wg_rem >= (unsigned)p.n_wgs ? 1u : 0u);
+  unsigned r0, r1;
+  workgroup_blocks(p, w, r0, r1);
   int b = seq_of_block(p, r0);
 
   for (unsigned r = r0; r < r1;) {
@@ -1181,7 +1199,7 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams)
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
     const unsigned rel = r - seq_first_block(p, b);
     const int counted = n_blocks + p.setup;
-    const int ub = (int)(rel / (unsigned)counted);
+    const int ub = unit_of_block(p, rel, counted);
     const int from = (int)(rel - (unsigned)ub * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
     const int seg_begin = max(from - p.setup, 0), seg_count = from + count - p.setup - seg_begin;
     if (seg_count <= 0) {   // nothing but set-up
@@ -1399,38 +1417,43 @@ __device__ __forceinline__ int owner_of(const AttnArgs& p, unsigned x, double in
 // Finishes every unit that was cut into several segments:
 // out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s over the unit's partial slots.
 // One thread per 4 output dims; rows of nodes past n_nodes are written as zeros.
+// pieces: workgroups per unit where every unit of the launch is cut into that many and no workgroup holds parts of two (0 where
+// that is not so).
 template <int D, bool SHARED>
-__global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams, int rows_per_slab, double inv_total) {
+__global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams, int rows_per_unit, int pieces, double inv_total) {
   const AttnArgs p = fetch_args();
   constexpr int TPR = D / 4;  // threads per row
-  const int unit = blockIdx.y;
-  const int units_per_seq = p.Hkv * p.GY;
-  const int b = unit / units_per_seq, ub = unit - b * units_per_seq;
-  const int n_groups = p.GY == 1 ? 1 : seq_groups(p, seq_slabs(p, seq_nodes(p, b), rows_per_slab));
-  if (ub >= p.Hkv * n_groups) return;   // a tree smaller than the largest: no such unit
-  const int g = head_of(p, ub, n_groups), y = ub - g * n_groups;
-  const int n_blocks = (seq_len(p, b) + kBlockKeys - 1) / kBlockKeys + (seq_nodes(p, b) + kBlockKeys - 1) / kBlockKeys;
-  const unsigned fs = seq_first_block(p, b) + (unsigned)ub * (unsigned)(n_blocks + p.setup) + (unsigned)p.setup;
-  const int w0 = owner_of(p, fs, inv_total), w1 = owner_of(p, fs + (unsigned)n_blocks - 1u, inv_total);
-  if (w0 == w1) return;  // written directly by the one workgroup that held the whole unit
-  const int rows_per_unit = p.WS * rows_per_slab;
+  const int b = blockIdx.z, ub = blockIdx.y, unit = b * gridDim.y + ub;
+  const int n = seq_nodes(p, b);
+  const int n_groups = SHARED ? seq_groups(p, seq_slabs(p, n, 32)) : 1;
+  if (SHARED && ub >= p.Hkv * n_groups) return;   // a tree smaller than the largest: no such unit
+  const int g = SHARED ? head_of(p, ub, n_groups) : ub, y = SHARED ? ub - g * n_groups : 0;
+  int w0, n_seg;
+  if (pieces > 0) {   // (every tree fills as many groups)
+    w0 = (b * p.Hkv * n_groups + ub) * pieces;
+    n_seg = pieces;
+  } else {
+    const int n_blocks = (seq_len(p, b) + kBlockKeys - 1) / kBlockKeys + (n + kBlockKeys - 1) / kBlockKeys;
+    const unsigned fs = seq_first_block(p, b) + (unsigned)ub * (unsigned)(n_blocks + p.setup) + (unsigned)p.setup;
+    w0 = owner_of(p, fs, inv_total);
+    n_seg = owner_of(p, fs + (unsigned)n_blocks - 1u, inv_total) - w0 + 1;
+    if (n_seg == 1) return;  // written directly by the one workgroup that held the whole unit
+  }
   constexpr int RPW = 256 / TPR;   // rows of this workgroup: in lane order (partial_index) the faster index of its threads
   const int lr = blockIdx.x * RPW + (SHARED ? threadIdx.x % RPW : threadIdx.x / TPR);
   if (lr >= rows_per_unit) return;
   const int piece = SHARED ? threadIdx.x / RPW : threadIdx.x % TPR, d0 = 4 * piece;
-  const int slab_local = lr / rows_per_slab;
-  const int rr = (y * p.WS + slab_local) * rows_per_slab + (lr - slab_local * rows_per_slab);
+  const int rr = y * rows_per_unit + lr;
   if (rr >= p.Nmax * p.G) return;
   const int node = (int)div_magic((unsigned)rr, p.G, p.g_magic), hl = rr - node * p.G;
   const int64_t row = ((int64_t)b * p.Nmax + node) * p.Hq + g * p.G + hl;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (node < seq_nodes(p, b)) {
+  if (node < n) {
     const int64_t slot_floats = (int64_t)rows_per_unit * (D + 2);
     const float* o_base = p.part + (int64_t)(unit + w0) * slot_floats + (SHARED ? partial_index<D>(lr, piece) : lr * D + d0);
     const float* ml_base = p.part + (int64_t)(unit + w0) * slot_floats + (int64_t)rows_per_unit * D + 2 * lr;
     // slots in index order (deterministic), eight at a time so that their loads are in flight together
     float M = kNegBig, denom = 0.f;
-    const int n_seg = w1 - w0 + 1;
     for (int s0 = 0; s0 < n_seg; s0 += 8) {
       float2 ml[8];
       f32x4 o[8];
@@ -1775,11 +1798,14 @@ void launch_bf16(const Plan& pl, const AttnParams& prm, bool streamed, hipStream
 }
 
 template <int D>
-void launch_combine(const Plan& pl, dim3 grid, const AttnParams& prm, int rows_per_slab, int64_t total, hipStream_t stream) {
+void launch_combine(const Plan& pl, const AttnParams& prm, int pieces, int64_t total, hipStream_t stream) {
+  const int rows_per_wg = 1024 / D;
+  const dim3 grid((unsigned)((pl.rows_per_unit + rows_per_wg - 1) / rows_per_wg), (unsigned)(prm.Hkv * pl.GY), (unsigned)prm.B);
   const double inv_total = 1.0 / (double)total;
-  if (pl.shared_stage) hipLaunchKernelGGL((tree_attn_combine_kernel<D, true>), grid, dim3(256), 0, stream, prm, rows_per_slab, inv_total);
-  else hipLaunchKernelGGL((tree_attn_combine_kernel<D, false>), grid, dim3(256), 0, stream, prm, rows_per_slab, inv_total);
+  if (pl.shared_stage) hipLaunchKernelGGL((tree_attn_combine_kernel<D, true>), grid, dim3(256), 0, stream, prm, pl.rows_per_unit, pieces, inv_total);
+  else hipLaunchKernelGGL((tree_attn_combine_kernel<D, false>), grid, dim3(256), 0, stream, prm, pl.rows_per_unit, pieces, inv_total);
 }
+uint32_t reciprocal(int64_t d) { return d <= 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint64_t)d); }
 
 // Nodes per workgroup of the fp32 kernel: a node of its own re-reads all of K and V through L2, which costs
 // nothing while the chip has room (one node against two: 6.1 / 8.3 us with 8 heads x 26 nodes, 256 keys, D = 64;
@@ -1922,6 +1948,9 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       sl.total_blocks = (int32_t)total;
       sl.wg_quot = (int32_t)(total / sl.n_wgs);
       sl.wg_rem = (int32_t)(total % sl.n_wgs);
+      sl.wgs_rcp = reciprocal(sl.n_wgs);
+      sl.seq_rcp = reciprocal(sl.seq_blocks);
+      sl.unit_rcp = reciprocal(blocks_of(sl.kv_len[0], sl.n_nodes[0]) + sl.setup);
       const size_t need = (size_t)slots_of(pl, full_units, full_wgs, full_total, d.workgroups) * slot_bytes(d, pl);
       if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 15)) return FSPAD_ERR_WORKSPACE;
       if (pl.shared_stage) {
@@ -1950,11 +1979,11 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         }
       }
       if (any_cut) {
-        const int rows_per_slab = 16 * pl.QT;
-        const int rpb = 256 / (d.head_dim / 4);
-        dim3 cgrid((unsigned)((pl.rows_per_unit + rpb - 1) / rpb), (unsigned)full_units);
-        if (d.head_dim == 128) launch_combine<128>(pl, cgrid, sl, rows_per_slab, total, stream);
-        else launch_combine<64>(pl, cgrid, sl, rows_per_slab, total, stream);
+        // aligned: as many groups for every tree, units of one length, a whole number of workgroups each
+        const bool aligned = sl.seq_blocks > 0 && sl.n_wgs % units == 0;
+        const int pieces = aligned ? (int)(sl.n_wgs / units) : 0;
+        if (d.head_dim == 128) launch_combine<128>(pl, sl, pieces, total, stream);
+        else launch_combine<64>(pl, sl, pieces, total, stream);
         if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       }
     } else {
