@@ -27,6 +27,8 @@
 namespace {
 
 using fspad_detail::bf16x8;
+using fspad_detail::div_rcp;
+using fspad_detail::reciprocal;
 using fspad_detail::f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
@@ -132,14 +134,6 @@ __device__ __forceinline__ AttnArgs fetch_args() {
   r.bstart = (KernargI32)(ka + offsetof(AttnParams, bstart));
   r.n_nodes = (KernargI32)(ka + offsetof(AttnParams, n_nodes));
   return r;
-}
-// x / d with rcp = floor(2^32 / d) from the host (2^32 - 1 for d = 1): the product's high half is the quotient or one less.
-// A division whose divisor the compiler does not know is some 22 instructions with a trip through the vector unit and back, and
-// a workgroup made three of them, a merging one too, before its first request: 32 / 8 heads, 60 nodes, 1000 keys 14.76 -> 14.50 us a
-// call, 32 heads, 26 nodes, 2048 keys 16.08 -> 15.94.
-__device__ __forceinline__ unsigned div_rcp(unsigned x, unsigned d, unsigned rcp) {
-  const unsigned q = __umulhi(x, rcp);
-  return q + (x - q * d >= d ? 1u : 0u);
 }
 // sequence that flat block r0 belongs to, and the first flat block / lengths of a sequence
 __device__ __forceinline__ int seq_of_block(const AttnArgs& p, unsigned r0) {
@@ -1805,7 +1799,7 @@ void launch_combine(const Plan& pl, const AttnParams& prm, int pieces, int64_t t
   if (pl.shared_stage) hipLaunchKernelGGL((tree_attn_combine_kernel<D, true>), grid, dim3(256), 0, stream, prm, pl.rows_per_unit, pieces, inv_total);
   else hipLaunchKernelGGL((tree_attn_combine_kernel<D, false>), grid, dim3(256), 0, stream, prm, pl.rows_per_unit, pieces, inv_total);
 }
-uint32_t reciprocal(int64_t d) { return d <= 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint64_t)d); }
+
 
 // Nodes per workgroup of the fp32 kernel: a node of its own re-reads all of K and V through L2, which costs
 // nothing while the chip has room (one node against two: 6.1 / 8.3 us with 8 heads x 26 nodes, 256 keys, D = 64;

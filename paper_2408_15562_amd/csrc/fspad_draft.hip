@@ -31,6 +31,8 @@
 namespace {
 
 using fspad_detail::bf16x8;
+using fspad_detail::div_rcp;
+using fspad_detail::reciprocal;
 using fspad_detail::f32x4;
 using fspad_detail::StreamGemm;
 
@@ -38,6 +40,7 @@ constexpr int kSliceRows = fspad_detail::kSliceRows;   // weight rows per slice
 constexpr int kChunkK = 256;         // every k extent is a multiple of this
 constexpr int kMaxRows = 128;        // rows of X per call
 
+constexpr int kRot = 3;
 // How a projection is spread: its slices (of all problems that share the launch) and their stages
 // along k form one flat list, and workgroup w streams the contiguous range
 // [floor(w T / W), floor((w + 1) T / W)) of it, so that every compute unit fetches the same number of
@@ -47,10 +50,12 @@ struct Split {
   int32_t stages;     // per slice
   int32_t total;      // n_slices * stages
   int32_t n_wgs;
+  int32_t rot;        // stages of k by which the start of a slice is further than that of the slice before
+  uint32_t wgs_rcp, total_rcp, stages_rcp;   // reciprocals (div_rcp)
 };
-__device__ __forceinline__ int range_begin(const Split& s, int w) { return (int)((unsigned)w * (unsigned)s.total / (unsigned)s.n_wgs); }
+__device__ __forceinline__ int range_begin(const Split& s, int w) { return (int)div_rcp((unsigned)w * (unsigned)s.total, (unsigned)s.n_wgs, s.wgs_rcp); }
 // the workgroup whose range holds stage x (32 bits do: at most 2^21 stages and 256 workgroups)
-__device__ __forceinline__ int owner_of(const Split& s, int x) { return (int)((((unsigned)x + 1u) * (unsigned)s.n_wgs - 1u) / (unsigned)s.total); }
+__device__ __forceinline__ int owner_of(const Split& s, int x) { return (int)div_rcp(((unsigned)x + 1u) * (unsigned)s.n_wgs - 1u, (unsigned)s.total, s.total_rcp); }
 
 // Partial sums of a launch: slot (slice + w) holds [rows][128] fp32 for the stages of the slice that
 // workgroup w summed.
@@ -119,15 +124,15 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void partial_ge
   typename G::Source src;
   src.x[0] = p.x[0]; src.x[1] = p.x[1]; src.w[0] = p.w[0]; src.w[1] = p.w[1];
   src.split = p.split; src.n_xrows = p.rows; src.n_wrows = p.N; src.K = p.K;
-  const int slice = t0 / p.plan.stages;
+  const int slice = (int)div_rcp((unsigned)t0, (unsigned)p.plan.stages, p.plan.stages_rcp);
   // every slice is walked from a stage of its own on: the ranges of an XCD would otherwise be at the same
   // stage of k, or at few different ones, wherever the length of a range and a slice's stages have a common
   // divisor (4096-wide rows: six stages of 16), and rows a power-of-two pitch apart then crowd a few L2 channels
-  constexpr int kRot = 3;
-  const int border = (int)((unsigned)slice * kRot % (unsigned)p.plan.stages);
+  const unsigned turned = (unsigned)slice * kRot;
+  const int border = (int)(turned - (unsigned)p.plan.stages * div_rcp(turned, (unsigned)p.plan.stages, p.plan.stages_rcp));
   int at = t0 - slice * p.plan.stages + border;
   at -= at >= p.plan.stages ? p.plan.stages : 0;
-  G::run(lds, src, slice, at, border, kRot % p.plan.stages, t1 - t0, [&](int s, const f32x4 (&acc)[MT], unsigned) {
+  G::run(lds, src, slice, at, border, p.plan.rot, t1 - t0, [&](int s, const f32x4 (&acc)[MT], unsigned) {
     // lane (n, g) holds columns 16 wave + 4g .. +3 of row 16t + n
     float* out = p.part + (size_t)(s + w) * p.rows * kSliceRows + wave * 16 + 4 * g;
 #pragma unroll
@@ -152,10 +157,9 @@ struct CombineParams {
 template <int MODE>
 __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-  const unsigned quads_per_row = (unsigned)p.N / 4;
-  const unsigned q = blockIdx.x * 256 + threadIdx.x;
-  if (q >= (unsigned)p.rows * quads_per_row) return;
-  const int row = (int)(q / quads_per_row), col = 4 * (int)(q - (unsigned)row * quads_per_row);
+  const int row = blockIdx.y, col = 4 * (int)(blockIdx.x * 256 + threadIdx.x);
+  if (col >= p.N) return;
+  const size_t q = ((size_t)row * p.N + col) / 4;
   f32x4 a, b;
   if (MODE == 0) {
     f32x4 both[2];
@@ -171,7 +175,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
     for (int i = 0; i < 4; ++i) o[i] = (__bf16)(b[i] / (1.0f + __expf(-b[i])) * a[i]);   // a: up, b: gate
   } else if (MODE == 1) {
     if (p.residual) {
-      const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.f + 8 * (size_t)q);
+      const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.f + 8 * q);
 #pragma unroll
       for (int i = 0; i < 4; ++i) a[i] += (float)r[i];
     }
@@ -187,7 +191,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
     *reinterpret_cast<bf16x4*>((second ? p.out2 : p.out) + at) = o;
     return;
   }
-  *reinterpret_cast<bf16x4*>(p.out + 8 * (size_t)q) = o;
+  *reinterpret_cast<bf16x4*>(p.out + 8 * q) = o;
 }
 
 // RMSNorm of one row per workgroup: out = x / sqrt(mean(x^2) + eps) * gain, fp32 arithmetic, one
@@ -282,7 +286,8 @@ __global__ __launch_bounds__(1024) void combine_norm_kernel(const CombineNormPar
 // row and the four partner columns of the second half: entry i of the first half and entry i of
 // the second half turn by position * theta^(-2i/D). Angles and their sine / cosine are formed in
 // fp64 (a position of some thousands times a frequency rounded to fp32 would already be off by
-// more than the result's bf16 rounding).
+// more than the result's bf16 rounding), once per workgroup (a row's heads share them): one angle for each of its first D/2
+// threads instead of four for every thread.
 struct QkvRopeParams {
   Partials part;
   const int32_t* positions;  // [rows]
@@ -294,14 +299,18 @@ struct QkvRopeParams {
 };
 __global__ __launch_bounds__(256) void qkv_rope_kernel(const QkvRopeParams p) {
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-  const int quads_per_head = p.D / 8, heads = p.Hq + 2 * p.Hkv;
-  const size_t total = (size_t)p.rows * heads * quads_per_head;
-  const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= total) return;
-  const int j = (int)(t % quads_per_head);
-  const int head = (int)((t / quads_per_head) % heads);
-  const int row = (int)(t / ((size_t)quads_per_head * heads));
-  const int half = p.D / 2;
+  __shared__ float2 turn[64];   // cosine and sine of entry i
+  const int quad_shift = p.D == 128 ? 4 : 3, heads = p.Hq + 2 * p.Hkv, half = p.D / 2;
+  const int row = blockIdx.y, t = (int)(blockIdx.x * 256 + threadIdx.x);
+  if ((int)threadIdx.x < half) {
+    const double ang = (double)p.positions[row] * exp2((double)threadIdx.x * p.neg_log2_theta_2_over_d);
+    double sn, cs;
+    sincos(ang, &sn, &cs);
+    turn[threadIdx.x] = make_float2((float)cs, (float)sn);
+  }
+  __syncthreads();
+  const int j = t & ((1 << quad_shift) - 1), head = t >> quad_shift;
+  if (head >= heads) return;
   f32x4 ab[2];
   p.part.sum<2>({0, 0}, row, {head * p.D + 4 * j, head * p.D + 4 * j + half}, ab);
   const f32x4 a = ab[0], b = ab[1];
@@ -311,13 +320,9 @@ __global__ __launch_bounds__(256) void qkv_rope_kernel(const QkvRopeParams p) {
   else dst = p.v + ((size_t)row * p.Hkv + (head - p.Hq - p.Hkv)) * p.D * 2;
   bf16x4 oa, ob;
   if (head < p.Hq + p.Hkv) {
-    const double pos = (double)p.positions[row];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const double ang = pos * exp2((double)(4 * j + i) * p.neg_log2_theta_2_over_d);
-      double sn, cs;
-      sincos(ang, &sn, &cs);
-      const float c = (float)cs, s = (float)sn;
+      const float c = turn[4 * j + i].x, s = turn[4 * j + i].y;
       oa[i] = (__bf16)(a[i] * c - b[i] * s);
       ob[i] = (__bf16)(b[i] * c + a[i] * s);
     }
@@ -338,6 +343,8 @@ Split plan_split(int N, int K, int problems, int rows) {
   s.stages = K / (rows <= 64 ? 256 : 128);
   s.total = s.n_slices * s.stages;
   s.n_wgs = s.total / 2 < kComputeUnits ? (s.total + 1) / 2 : kComputeUnits;
+  s.rot = kRot % s.stages;
+  s.wgs_rcp = reciprocal(s.n_wgs); s.total_rcp = reciprocal(s.total); s.stages_rcp = reciprocal(s.stages);
   return s;
 }
 size_t partial_floats(const Split& s, int rows) { return (size_t)(s.n_slices + s.n_wgs) * rows * kSliceRows; }
@@ -374,8 +381,7 @@ fspad_status combine(const float* part, const Split& plan, const void* residual,
   c.part = Partials{part, plan, rows};
   c.f = static_cast<const char*>(residual); c.out = static_cast<char*>(out);
   c.out2 = static_cast<char*>(out2); c.rows = rows; c.N = N; c.residual = residual != nullptr;
-  const size_t quads = (size_t)rows * N / 4;
-  hipLaunchKernelGGL(combine_kernel<MODE>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, c);
+  hipLaunchKernelGGL(combine_kernel<MODE>, dim3((unsigned)((N / 4 + 255) / 256), (unsigned)rows), dim3(256), 0, stream, c);
   return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
 }
 
@@ -550,8 +556,8 @@ extern "C" fspad_status fspad_draft_layer(const fspad_draft_layer_desc* desc, co
     r.part = Partials{part, pl.qkv, pl.rows}; r.positions = positions; r.q = q; r.k = static_cast<char*>(k_tree); r.v = static_cast<char*>(v_tree);
     r.rows = pl.rows; r.Hq = a.n_q_heads; r.Hkv = a.n_kv_heads; r.D = a.head_dim;
     r.neg_log2_theta_2_over_d = -2.0 * log2((double)desc->rope_theta) / (double)a.head_dim;
-    const size_t threads = (size_t)pl.rows * (a.n_q_heads + 2 * a.n_kv_heads) * (a.head_dim / 8);
-    hipLaunchKernelGGL(qkv_rope_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, r);
+    const int threads = (a.n_q_heads + 2 * a.n_kv_heads) * (a.head_dim / 8);   // per row
+    hipLaunchKernelGGL(qkv_rope_kernel, dim3((unsigned)((threads + 255) / 256), (unsigned)pl.rows), dim3(256), 0, stream, r);
     if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   }
   // tree attention over the draft's own cache
