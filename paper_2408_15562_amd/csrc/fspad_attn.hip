@@ -37,6 +37,20 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 constexpr int kMaxBatchPerLaunch = 128;
 constexpr int64_t kMaxFlatBlocks = 1ll << 30;  // 32-key blocks of one launch, summed over its units
 constexpr int kBlockKeys = 32;          // keys per streamed block
+constexpr int kMaxClasses = 4;          // classes of sequences (shared-stage kernels)
+
+// Sequences whose trees fill equally many slab groups, of the shared-stage kernels. The kv heads of a class form one flat list of
+// blocks; a *cluster* takes a contiguous range of it (every cluster of the class the same number of blocks) with one workgroup
+// per slab group, all of them on the same keys at the same time and on the same die (workgroups eight apart), so that K and V come
+// from memory once for all slab groups. With the slab groups one after another in the list, as units of their own, each fetched
+// them for itself wherever the pieces of a unit were not a multiple of eight: 16 sequences of 131 to 6011 keys, 17 to 60 nodes,
+// 32 / 8 heads 98.5 -> 95.5 us a call; 4 equal ones of 4096 keys, 60 nodes 36.5 -> 34.5, 40 / 8 heads 23.2 -> 22.0.
+struct SeqClass {
+  int32_t wg_begin, groups, clusters, quot, rem;   // cluster p starts at block p * quot + p * rem / clusters of the class
+  uint32_t clusters_rcp, tile_rcp;                 // reciprocals (div_rcp) of clusters and of 8 * groups
+  int32_t first_seq, slot0, units;                 // units: (sequence, kv head) pairs
+  double inv_total;                                // 1 / blocks of the class
+};
 constexpr float kNegBig = -1.0e30f;     // finite stand-in for "no key seen yet"
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -54,11 +68,12 @@ struct AttnParams {
   int32_t WS;       // row slabs per workgroup: 1, 2 or 4 (4/WS wavefronts share a slab and split its keys)
   int32_t ws_shift; // log2(WS)
   int32_t NS;       // row slabs per kv head
-  int32_t GY;       // slab groups per kv head of a full tree: a (sequence, kv head, slab group) is one unit of work
-  int32_t n_wgs;    // workgroups of the flat decomposition
+  int32_t GY;       // slab groups per kv head (of the launch's only class)
+  int32_t n_wgs;    // workgroups of the flat decomposition (clusters of the only class)
   int32_t total_blocks;  // 32-key blocks summed over all units (T)
   int32_t wg_quot, wg_rem;  // T = wg_quot * n_wgs + wg_rem: workgroup w starts at w*wg_quot + w*wg_rem/n_wgs
-  uint32_t g_magic, gy_magic;  // ceil(2^32 / G), ceil(2^32 / GY): division by multiplication (unused when the divisor is 1)
+  uint32_t g_magic;   // ceil(2^32 / G): division by multiplication (unused when the divisor is 1)
+  uint32_t tile_rcp;  // reciprocal of 8 * GY
   int32_t out_bf16;
   float scale;      // softmax scale
   // when every sequence of the launch has the same prefix length and node count: the flat blocks of
@@ -67,9 +82,13 @@ struct AttnParams {
   int32_t seq_blocks, same_len, same_nodes;
   int32_t setup;    // blocks that every unit counts for beyond its own in the flat list (ragged batches; setup_blocks)
   uint32_t wgs_rcp, seq_rcp, unit_rcp;  // reciprocals (div_rcp) of n_wgs and, with seq_blocks > 0, of that and of the blocks a unit counts for
+  int32_t n_classes;
+  SeqClass classes[kMaxClasses];           // where there is more than one
+  // sequences in the order of their classes
   int32_t kv_len[kMaxBatchPerLaunch];
   int32_t bstart[kMaxBatchPerLaunch + 1];  // first flat block of each sequence; bstart[B] = total_blocks
   int32_t n_nodes[kMaxBatchPerLaunch];
+  int32_t order[kMaxBatchPerLaunch];       // their places in the batch
 };
 
 // The scalar part of AttnParams as the kernels use it, fetched from the kernel-argument segment in
@@ -90,16 +109,28 @@ struct AttnArgs {
   float* part;
   int64_t stride_batch, stride_head, stride_token;
   int32_t B, Nmax, Hq, Hkv, G, WS, ws_shift, NS, GY, n_wgs, total_blocks, wg_quot, wg_rem;
-  uint32_t g_magic, gy_magic;
+  uint32_t g_magic, tile_rcp;
   int32_t out_bf16;
   float scale;
   int32_t seq_blocks, same_len, same_nodes, setup;
   uint32_t wgs_rcp, seq_rcp, unit_rcp;
-  KernargI32 kv_len, bstart, n_nodes;
+  int32_t n_classes;
 };
 static_assert(offsetof(AttnParams, stride_batch) == 64 && offsetof(AttnParams, B) == 88 && offsetof(AttnParams, total_blocks) == 128 &&
-              offsetof(AttnParams, scale) == 152 && offsetof(AttnParams, same_nodes) == 164 && offsetof(AttnParams, setup) == 168 && offsetof(AttnParams, unit_rcp) == 180 && offsetof(AttnParams, kv_len) == 184,
+              offsetof(AttnParams, scale) == 152 && offsetof(AttnParams, same_nodes) == 164 && offsetof(AttnParams, setup) == 168 && offsetof(AttnParams, n_classes) == 184 && offsetof(AttnParams, classes) == 192,
               "fetch_args reads the scalars by their offsets");
+
+// Arguments that are read where they are used: the arrays, and in the shared-stage kernels what only a segment's end needs
+// (kept in scalar registers for the length of a stream they displaced what the stream needs).
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* arg_at(size_t offset) {
+  return (const __attribute__((address_space(4))) T*)((KernargPtr)__builtin_amdgcn_kernarg_segment_ptr() + offset);
+}
+__device__ __forceinline__ KernargI32 arg_kv_len() { return arg_at<int32_t>(offsetof(AttnParams, kv_len)); }
+__device__ __forceinline__ KernargI32 arg_bstart() { return arg_at<int32_t>(offsetof(AttnParams, bstart)); }
+__device__ __forceinline__ KernargI32 arg_n_nodes() { return arg_at<int32_t>(offsetof(AttnParams, n_nodes)); }
+__device__ __forceinline__ KernargI32 arg_order() { return arg_at<int32_t>(offsetof(AttnParams, order)); }
+__device__ __forceinline__ const __attribute__((address_space(4))) SeqClass* arg_classes() { return arg_at<SeqClass>(offsetof(AttnParams, classes)); }
 
 __device__ __forceinline__ AttnArgs fetch_args() {
   typedef int v16i __attribute__((ext_vector_type(16)));
@@ -124,35 +155,70 @@ __device__ __forceinline__ AttnArgs fetch_args() {
   r.stride_token = (int64_t)u64(b[4], b[5]);
   r.B = b[6]; r.Nmax = b[7]; r.Hq = b[8]; r.Hkv = b[9]; r.G = b[10]; r.WS = b[11]; r.ws_shift = b[12]; r.NS = b[13];
   r.GY = b[14]; r.n_wgs = b[15];
-  r.total_blocks = c[0]; r.wg_quot = c[1]; r.wg_rem = c[2]; r.g_magic = (uint32_t)c[3]; r.gy_magic = (uint32_t)c[4];
+  r.total_blocks = c[0]; r.wg_quot = c[1]; r.wg_rem = c[2]; r.g_magic = (uint32_t)c[3]; r.tile_rcp = (uint32_t)c[4];
   r.out_bf16 = c[5];
   const int scale_bits = c[6];   // (a bit cast straight from the vector element reads element 0)
   r.scale = __builtin_bit_cast(float, scale_bits);
   r.seq_blocks = c[7]; r.same_len = c[8]; r.same_nodes = c[9]; r.setup = c[10];
-  r.wgs_rcp = (uint32_t)c[11]; r.seq_rcp = (uint32_t)c[12]; r.unit_rcp = (uint32_t)c[13];
-  r.kv_len = (KernargI32)(ka + offsetof(AttnParams, kv_len));
-  r.bstart = (KernargI32)(ka + offsetof(AttnParams, bstart));
-  r.n_nodes = (KernargI32)(ka + offsetof(AttnParams, n_nodes));
+  r.wgs_rcp = (uint32_t)c[11]; r.seq_rcp = (uint32_t)c[12]; r.unit_rcp = (uint32_t)c[13]; r.n_classes = c[14];
   return r;
 }
 // sequence that flat block r0 belongs to, and the first flat block / lengths of a sequence
-__device__ __forceinline__ int seq_of_block(const AttnArgs& p, unsigned r0) {
+__device__ __forceinline__ int seq_of_block(const AttnArgs& p, unsigned r0, int first = 0) {
   if (p.seq_blocks > 0) return (int)div_rcp(r0, (unsigned)p.seq_blocks, p.seq_rcp);
-  int b = 0;
-  while (b + 1 < p.B && r0 >= (unsigned)p.bstart[b + 1]) ++b;
+  int b = first;
+  while (b + 1 < p.B && r0 >= (unsigned)arg_bstart()[b + 1]) ++b;
   return b;
 }
 __device__ __forceinline__ unsigned seq_first_block(const AttnArgs& p, int b) {
-  return p.seq_blocks > 0 ? (unsigned)b * (unsigned)p.seq_blocks : (unsigned)p.bstart[b];
+  return p.seq_blocks > 0 ? (unsigned)b * (unsigned)p.seq_blocks : (unsigned)arg_bstart()[b];
 }
-__device__ __forceinline__ int seq_nodes(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_nodes : p.n_nodes[b]; }
-__device__ __forceinline__ int seq_len(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_len : p.kv_len[b]; }
+__device__ __forceinline__ int seq_nodes(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_nodes : arg_n_nodes()[b]; }
+__device__ __forceinline__ int seq_len(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_len : arg_kv_len()[b]; }
 
 // flat blocks [r0, r1) of workgroup w: [floor(w*T/W), floor((w+1)*T/W)) with T = wg_quot*W + wg_rem
 __device__ __forceinline__ void workgroup_blocks(const AttnArgs& p, unsigned w, unsigned& r0, unsigned& r1) {
   const unsigned wr = w * (unsigned)p.wg_rem, wq = div_rcp(wr, (unsigned)p.n_wgs, p.wgs_rcp);
   r0 = w * (unsigned)p.wg_quot + wq;
   r1 = r0 + (unsigned)p.wg_quot + ((wr - wq * (unsigned)p.n_wgs) + (unsigned)p.wg_rem >= (unsigned)p.n_wgs ? 1u : 0u);
+}
+// What a workgroup of a shared-stage kernel does: blocks [r0, r1) of the flat list for slab group y. The partial result of the
+// unit-th (sequence, kv head) pair of the class goes to slot `slot` + unit.
+struct Share {
+  unsigned r0, r1;
+  int y, first_seq, slot;
+};
+__device__ __forceinline__ Share share_of(const AttnArgs& p, unsigned w) {
+  SeqClass c;
+  c.wg_begin = 0; c.groups = p.GY; c.clusters = p.n_wgs; c.quot = p.wg_quot; c.rem = p.wg_rem; c.clusters_rcp = p.wgs_rcp;
+  c.tile_rcp = p.tile_rcp; c.first_seq = 0; c.slot0 = 0; c.units = p.B * p.Hkv;
+  unsigned flat0 = 0;
+  if (p.n_classes > 1) {
+    int k = 0;
+    while (k + 1 < p.n_classes && (int)w >= arg_classes()[k + 1].wg_begin) ++k;
+    const __attribute__((address_space(4))) SeqClass& from = arg_classes()[k];
+    c.wg_begin = from.wg_begin; c.groups = from.groups; c.clusters = from.clusters; c.quot = from.quot; c.rem = from.rem;
+    c.clusters_rcp = from.clusters_rcp; c.tile_rcp = from.tile_rcp; c.first_seq = from.first_seq; c.slot0 = from.slot0; c.units = from.units;
+    flat0 = (unsigned)arg_bstart()[c.first_seq];
+  }
+  // eight clusters at a time: their workgroups for the first slab group, then those for the second, ...
+  const unsigned local = w - (unsigned)c.wg_begin, tile = div_rcp(local, 8u * c.groups, c.tile_rcp);
+  unsigned in_tile = local - tile * 8u * c.groups;
+  const unsigned width = min(8u, (unsigned)c.clusters - 8u * tile);
+  Share s;
+  s.y = 0;
+  if (width == 8u) {
+    s.y = (int)(in_tile >> 3);
+    in_tile &= 7u;
+  } else {
+    for (; in_tile >= width; in_tile -= width) ++s.y;
+  }
+  const unsigned at = 8u * tile + in_tile, ar = at * (unsigned)c.rem, aq = div_rcp(ar, (unsigned)c.clusters, c.clusters_rcp);
+  s.r0 = flat0 + at * (unsigned)c.quot + aq;
+  s.r1 = s.r0 + (unsigned)c.quot + ((ar - aq * (unsigned)c.clusters) + (unsigned)c.rem >= (unsigned)c.clusters ? 1u : 0u);
+  s.first_seq = c.first_seq;
+  s.slot = c.slot0 + s.y * (c.units + c.clusters) + (int)at;
+  return s;
 }
 // unit that flat block `rel` of a sequence belongs to, its units counting for `counted` blocks each
 __device__ __forceinline__ int unit_of_block(const AttnArgs& p, unsigned rel, int counted) {
@@ -164,7 +230,7 @@ __device__ __forceinline__ unsigned div_magic(unsigned x, int d, unsigned magic)
   return d == 1 ? x : __umulhi(x, magic);
 }
 
-// Row slabs a sequence's tree fills, and the slab groups (units per kv head) that hold them: a tree smaller
+// Row slabs a sequence's tree fills, and the slab groups that hold them: a tree smaller
 // than the batch's largest has no work beyond them. The rows past its last group are zeroed by the workgroup
 // that holds the first block of its first group (zero_rows). 16 sequences of 17 to 60 nodes, 32 / 8 heads: 98 -> 86 us.
 __device__ __forceinline__ int seq_slabs(const AttnArgs& p, int n, int rows_per_slab) { return (int)((unsigned)(n * p.G + rows_per_slab - 1) / (unsigned)rows_per_slab); }
@@ -174,12 +240,6 @@ __device__ __forceinline__ float wave_xor_max_16_32(float v) {
   v = fmaxf(v, __shfl_xor(v, 16));
   v = fmaxf(v, __shfl_xor(v, 32));
   return v;
-}
-
-// kv head of unit ub of a sequence that has n_groups units per head
-__device__ __forceinline__ int head_of(const AttnArgs& p, int ub, int n_groups) {
-  if (n_groups == p.GY) return (int)div_magic((unsigned)ub, p.GY, p.gy_magic);
-  return n_groups == 1 ? ub : (int)((unsigned)ub / (unsigned)n_groups);
 }
 
 // Zeros for the output rows of (sequence b, kv head g) from row `first` of its Nmax * G rows on.
@@ -807,28 +867,29 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) 
 #pragma unroll
   for (int j = 0; j < 8; ++j) vrow[j] = S::kTensorBytes + (unsigned)key_of(g4, j) * (D * 2) + (unsigned)(D / 8) * col;
 
-  const unsigned w = blockIdx.x;
-  unsigned r0, r1;
-  workgroup_blocks(p, w, r0, r1);
-  int b = seq_of_block(p, r0);
+  const Share share = share_of(p, blockIdx.x);
+  const unsigned r1 = share.r1;
+  const int y = share.y;
+  int at_seq = seq_of_block(p, share.r0, share.first_seq);   // place in the launch's order of sequences
 
-  for (unsigned r = r0; r < r1;) {
-    const int n = seq_nodes(p, b);
-    const int L = seq_len(p, b);
+  for (unsigned r = share.r0; r < r1;) {
+    const int n = seq_nodes(p, at_seq);
+    const int L = seq_len(p, at_seq);
+    const int b = p.seq_blocks > 0 ? at_seq : arg_order()[at_seq];
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
-    const unsigned rel = r - seq_first_block(p, b);
+    const unsigned rel = r - seq_first_block(p, at_seq);
     const int counted = n_blocks + p.setup;
-    const int ub = unit_of_block(p, rel, counted);
-    const int from = (int)(rel - (unsigned)ub * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
+    const int g = unit_of_block(p, rel, counted);
+    const int from = (int)(rel - (unsigned)g * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
     const int seg_begin = max(from - p.setup, 0), seg_count = from + count - p.setup - seg_begin;
-    if (seg_count <= 0) {   // nothing but set-up
+    const int n_slabs = seq_slabs(p, n, ROWS), n_groups = seq_groups(p, n_slabs);
+    if (seg_count <= 0 || y >= n_groups) {   // nothing but set-up, or no rows for this slab group (classes put together)
       r += (unsigned)count;
+      if (at_seq + 1 < p.B && r >= seq_first_block(p, at_seq + 1)) ++at_seq;
       continue;
     }
-    const int n_slabs = seq_slabs(p, n, ROWS), n_groups = seq_groups(p, n_slabs);
-    const int g = head_of(p, ub, n_groups), y = ub - g * n_groups;
-    const int unit = b * p.Hkv * p.GY + ub;
+    const int unit = share.slot + (at_seq - share.first_seq) * p.Hkv + g;   // partial slot
     const bool whole_unit = seg_count == n_blocks;
     const int slab = y * kWaves + wave;
     const bool slab_live = slab < p.NS;          // has output rows
@@ -1020,7 +1081,7 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) 
               }
             }
           } else if (ri.valid) {
-            float* slot = p.part + (int64_t)(unit + w) * rows_per_unit * (D + 2);
+            float* slot = p.part + (int64_t)unit * rows_per_unit * (D + 2);
             const int lr = wave * ROWS + 16 * t + col;
             if (g4 == 0 && e0 == 0) *reinterpret_cast<float2*>(slot + (int64_t)rows_per_unit * D + 2 * lr) = make_float2(st.m[t], l_row);
 #pragma unroll
@@ -1031,7 +1092,7 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) 
       }
     }
     r += (unsigned)count;
-    if (b + 1 < p.B && r >= seq_first_block(p, b + 1)) ++b;
+    if (at_seq + 1 < p.B && r >= seq_first_block(p, at_seq + 1)) ++at_seq;
     __syncthreads();  // every wavefront is done with the stages before the next segment refills them
   }
 }
@@ -1181,28 +1242,29 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams)
   const unsigned k_at = lds0 + 256u * row + 16u * (h ^ (row & 15));
   const unsigned v_at = lds0 + kWideRing * kWideTensor + 256u * (4 * h + ((lane >> 2) & 3)) + 64u * ((lane >> 2) & 3) + 32u * ((lane >> 4) & 1) + 8u * (lane & 3);
 
-  const unsigned w = blockIdx.x;
-  unsigned r0, r1;
-  workgroup_blocks(p, w, r0, r1);
-  int b = seq_of_block(p, r0);
+  const Share share = share_of(p, blockIdx.x);
+  const unsigned r1 = share.r1;
+  const int y = share.y;
+  int at_seq = seq_of_block(p, share.r0, share.first_seq);   // place in the launch's order of sequences
 
-  for (unsigned r = r0; r < r1;) {
-    const int n = seq_nodes(p, b);
-    const int L = seq_len(p, b);
+  for (unsigned r = share.r0; r < r1;) {
+    const int n = seq_nodes(p, at_seq);
+    const int L = seq_len(p, at_seq);
+    const int b = p.seq_blocks > 0 ? at_seq : arg_order()[at_seq];
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
-    const unsigned rel = r - seq_first_block(p, b);
+    const unsigned rel = r - seq_first_block(p, at_seq);
     const int counted = n_blocks + p.setup;
-    const int ub = unit_of_block(p, rel, counted);
-    const int from = (int)(rel - (unsigned)ub * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
+    const int g = unit_of_block(p, rel, counted);
+    const int from = (int)(rel - (unsigned)g * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
     const int seg_begin = max(from - p.setup, 0), seg_count = from + count - p.setup - seg_begin;
-    if (seg_count <= 0) {   // nothing but set-up
+    const int n_slabs = seq_slabs(p, n, ROWS), n_groups = seq_groups(p, n_slabs);
+    if (seg_count <= 0 || y >= n_groups) {   // nothing but set-up, or no rows for this slab group (classes put together)
       r += (unsigned)count;
+      if (at_seq + 1 < p.B && r >= seq_first_block(p, at_seq + 1)) ++at_seq;
       continue;
     }
-    const int n_slabs = seq_slabs(p, n, ROWS), n_groups = seq_groups(p, n_slabs);
-    const int g = head_of(p, ub, n_groups), y = ub - g * n_groups;
-    const int unit = b * p.Hkv * p.GY + ub;
+    const int unit = share.slot + (at_seq - share.first_seq) * p.Hkv + g;   // partial slot
     const bool whole_unit = seg_count == n_blocks;
     const int slab = y * WAVES + wave;
 
@@ -1367,7 +1429,8 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams)
       const float l_row = a.y * f0 + bb.y * f1;
       const float own = kg == 0 ? f0 : f1, other = kg == 0 ? f1 : f0;
       const float inv = whole_unit ? (valid ? 1.0f / l_row : 0.f) : 1.0f;
-      float* const slot = p.part + (int64_t)(unit + w) * rows_per_unit * (D + 2);
+      float* const slot = (float*)*arg_at<__attribute__((address_space(1))) float*>(offsetof(AttnParams, part)) + (int64_t)unit * rows_per_unit * (D + 2);
+      void* const out_ptr = (void*)*arg_at<__attribute__((address_space(1))) void*>(offsetof(AttnParams, out));
       const int lr = wave * ROWS + row;
       if (!whole_unit && valid && lane < 32 && kg == 0) *reinterpret_cast<float2*>(slot + (int64_t)rows_per_unit * D + 2 * lr) = make_float2(mm, l_row);
 #pragma unroll
@@ -1383,29 +1446,29 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams)
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j) val[j] = valid ? val[j] * inv : 0.f;
-          if (p.out_bf16) {
+          if (*arg_at<int32_t>(offsetof(AttnParams, out_bf16))) {
             typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
             bf16x4 o4;
 #pragma unroll
             for (int j = 0; j < 4; ++j) o4[j] = (__bf16)val[j];
-            *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(p.out) + out_row * D + d0) = o4;
+            *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(out_ptr) + out_row * D + d0) = o4;
           } else {
-            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.out) + out_row * D + d0) = val;
+            *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out_ptr) + out_row * D + d0) = val;
           }
         }
       }
     }
     r += (unsigned)count;
-    if (b + 1 < p.B && r >= seq_first_block(p, b + 1)) ++b;
+    if (at_seq + 1 < p.B && r >= seq_first_block(p, at_seq + 1)) ++at_seq;
     __syncthreads();  // every wavefront is done with the merge buffers before the next segment fills the rings
   }
 }
 
-// Workgroup that owns flat block x under the even split: the last w with floor(w T / W) <= x, i.e.
-// floor(((x + 1) W - 1) / T). The numerator is below 2^45 and the quotient below 2^15: half a unit up, the product
+// Workgroup (cluster) of n that owns flat block x under the even split: the last w with floor(w T / n) <= x, i.e.
+// floor(((x + 1) n - 1) / T). The numerator is below 2^45 and the quotient below 2^15: half a unit up, the product
 // with 1/T in fp64 is further from the next integer than its rounding can carry it.
-__device__ __forceinline__ int owner_of(const AttnArgs& p, unsigned x, double inv_total) {
-  return (int)(((double)(x + 1u) * (double)p.n_wgs - 0.5) * inv_total);
+__device__ __forceinline__ int owner_of(unsigned x, int n, double inv_total) {
+  return (int)(((double)(x + 1u) * (double)n - 0.5) * inv_total);
 }
 
 // Finishes every unit that was cut into several segments:
@@ -1417,24 +1480,32 @@ template <int D, bool SHARED>
 __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams, int rows_per_unit, int pieces, double inv_total) {
   const AttnArgs p = fetch_args();
   constexpr int TPR = D / 4;  // threads per row
-  const int b = blockIdx.z, ub = blockIdx.y, unit = b * gridDim.y + ub;
-  const int n = seq_nodes(p, b);
-  const int n_groups = SHARED ? seq_groups(p, seq_slabs(p, n, 32)) : 1;
-  if (SHARED && ub >= p.Hkv * n_groups) return;   // a tree smaller than the largest: no such unit
-  const int g = SHARED ? head_of(p, ub, n_groups) : ub, y = SHARED ? ub - g * n_groups : 0;
+  constexpr int RPW = 256 / TPR;   // rows of this workgroup: in lane order (partial_index) the faster index of its threads
+  const int at_seq = blockIdx.z, g = blockIdx.y;
+  const int n = seq_nodes(p, at_seq), b = p.seq_blocks > 0 ? at_seq : arg_order()[at_seq];
+  const int y = SHARED ? (int)(blockIdx.x * RPW) / 128 : 0;   // (128 rows per slab group)
+  if (SHARED && y >= seq_groups(p, seq_slabs(p, n, 32))) return;   // a tree smaller than the largest: no such rows of it
+  int clusters = p.n_wgs, units = p.B * p.Hkv, first_seq = 0, slot0 = 0;
+  if (SHARED && p.n_classes > 1) {
+    int k = 0;
+    while (k + 1 < p.n_classes && at_seq >= arg_classes()[k + 1].first_seq) ++k;
+    clusters = arg_classes()[k].clusters; units = arg_classes()[k].units; first_seq = arg_classes()[k].first_seq; slot0 = arg_classes()[k].slot0;
+    inv_total = arg_classes()[k].inv_total;
+  }
+  const int unit = (at_seq - first_seq) * p.Hkv + g;
   int w0, n_seg;
-  if (pieces > 0) {   // (every tree fills as many groups)
-    w0 = (b * p.Hkv * n_groups + ub) * pieces;
+  if (pieces > 0) {
+    w0 = unit * pieces;
     n_seg = pieces;
   } else {
-    const int n_blocks = (seq_len(p, b) + kBlockKeys - 1) / kBlockKeys + (n + kBlockKeys - 1) / kBlockKeys;
-    const unsigned fs = seq_first_block(p, b) + (unsigned)ub * (unsigned)(n_blocks + p.setup) + (unsigned)p.setup;
-    w0 = owner_of(p, fs, inv_total);
-    n_seg = owner_of(p, fs + (unsigned)n_blocks - 1u, inv_total) - w0 + 1;
+    const int n_blocks = (seq_len(p, at_seq) + kBlockKeys - 1) / kBlockKeys + (n + kBlockKeys - 1) / kBlockKeys;
+    const unsigned fs = seq_first_block(p, at_seq) - seq_first_block(p, first_seq) + (unsigned)g * (unsigned)(n_blocks + p.setup) + (unsigned)p.setup;
+    w0 = owner_of(fs, clusters, inv_total);
+    n_seg = owner_of(fs + (unsigned)n_blocks - 1u, clusters, inv_total) - w0 + 1;
     if (n_seg == 1) return;  // written directly by the one workgroup that held the whole unit
   }
-  constexpr int RPW = 256 / TPR;   // rows of this workgroup: in lane order (partial_index) the faster index of its threads
-  const int lr = blockIdx.x * RPW + (SHARED ? threadIdx.x % RPW : threadIdx.x / TPR);
+  const int slot = slot0 + y * (units + clusters) + unit + w0;
+  const int lr = (int)(blockIdx.x * RPW) - y * 128 + (int)(SHARED ? threadIdx.x % RPW : threadIdx.x / TPR);
   if (lr >= rows_per_unit) return;
   const int piece = SHARED ? threadIdx.x / RPW : threadIdx.x % TPR, d0 = 4 * piece;
   const int rr = y * rows_per_unit + lr;
@@ -1444,8 +1515,8 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   if (node < n) {
     const int64_t slot_floats = (int64_t)rows_per_unit * (D + 2);
-    const float* o_base = p.part + (int64_t)(unit + w0) * slot_floats + (SHARED ? partial_index<D>(lr, piece) : lr * D + d0);
-    const float* ml_base = p.part + (int64_t)(unit + w0) * slot_floats + (int64_t)rows_per_unit * D + 2 * lr;
+    const float* o_base = p.part + (int64_t)slot * slot_floats + (SHARED ? partial_index<D>(lr, piece) : lr * D + d0);
+    const float* ml_base = p.part + (int64_t)slot * slot_floats + (int64_t)rows_per_unit * D + 2 * lr;
     // slots in index order (deterministic), eight at a time so that their loads are in flight together
     float M = kNegBig, denom = 0.f;
     for (int s0 = 0; s0 < n_seg; s0 += 8) {
@@ -1736,6 +1807,101 @@ int groups_of(const fspad_attn_desc& d, const Plan& pl, int n) {
   return (slabs + pl.WS - 1) / pl.WS;
 }
 
+constexpr int kWholeSetup = 4096;   // more than the blocks of a launch's units can differ from an even division by
+
+// The flat list of blocks and its division among workgroups: sequences in the order of their classes (see SeqClass), `wgs`
+// workgroups shared among the classes by their blocks. Returns the workgroups of the launch (at most wgs, but one per class and
+// slab group at least); `any_cut`: some unit is cut among several.
+int plan_classes(const fspad_attn_desc& d, const Plan& pl, const int* groups, int64_t wgs, AttnParams& sl, bool& any_cut) {
+  const int nb = sl.B;
+  // the kernels of one slab group per kv head: one class. More different numbers of slab groups than a launch has classes
+  // (1024 rows per kv head): rounded up, with workgroups that pass over the sequences without rows for them
+  int used[kMaxBatchPerLaunch], n_classes = 0, class_groups[kMaxBatchPerLaunch];
+  for (int unit = 1;; unit *= 2) {
+    n_classes = 0;
+    for (int i = 0; i < nb; ++i) {
+      used[i] = (groups[i] + unit - 1) / unit * unit;
+      if (used[i] > pl.GY) used[i] = pl.GY;
+      bool known = false;
+      for (int k = 0; k < n_classes; ++k) known = known || class_groups[k] == used[i];
+      if (!known) class_groups[n_classes++] = used[i];
+    }
+    if (n_classes <= kMaxClasses) break;
+  }
+  const AttnParams in = sl;
+  // whole units (kWholeSetup): the shorter ones first, so that a workgroup's range ends behind its own unit, in the next one's set-up
+  int by[kMaxBatchPerLaunch];
+  for (int i = 0; i < nb; ++i) {
+    int at = i;
+    if (sl.setup == kWholeSetup)
+      for (; at > 0 && blocks_of(in.kv_len[by[at - 1]], in.n_nodes[by[at - 1]]) > blocks_of(in.kv_len[i], in.n_nodes[i]); --at) by[at] = by[at - 1];
+    by[at] = i;
+  }
+  SeqClass* cls = sl.classes;
+  int64_t blocks[kMaxClasses], work = 0, flat = 0, left = wgs;
+  for (int k = 0, at = 0; k < n_classes; ++k) {
+    cls[k] = SeqClass{};
+    cls[k].groups = class_groups[k];
+    cls[k].first_seq = at;
+    const int64_t flat0 = flat;
+    for (int j = 0; j < nb; ++j) {
+      const int i = by[j];
+      if (used[i] != class_groups[k]) continue;
+      sl.order[at] = i; sl.kv_len[at] = in.kv_len[i]; sl.n_nodes[at] = in.n_nodes[i]; sl.bstart[at] = (int32_t)flat;
+      flat += (int64_t)d.n_kv_heads * (blocks_of(in.kv_len[i], in.n_nodes[i]) + sl.setup);
+      ++at;
+    }
+    cls[k].units = (at - cls[k].first_seq) * d.n_kv_heads;
+    blocks[k] = flat - flat0;
+    work += blocks[k] * class_groups[k];
+  }
+  sl.bstart[nb] = (int32_t)flat;
+  for (int k = 0; k < n_classes; ++k) {
+    const int64_t n = wgs * blocks[k] / work;   // (= its share of the workgroups over its slab groups)
+    cls[k].clusters = (int32_t)(n < 1 ? 1 : n);
+    left -= (int64_t)cls[k].groups * cls[k].clusters;
+  }
+  for (;;) {   // what the rounding left goes to the class with the longest ranges, where there are classes
+    int longest = -1;
+    for (int k = 0; n_classes > 1 && k < n_classes; ++k)
+      if (cls[k].groups <= left && cls[k].clusters < blocks[k] &&
+          (longest < 0 || blocks[k] * cls[longest].clusters > blocks[longest] * cls[k].clusters))
+        longest = k;
+    if (longest < 0) break;
+    cls[longest].clusters += 1;
+    left -= cls[longest].groups;
+  }
+  int grid = 0;
+  int64_t slot = 0;
+  any_cut = false;
+  for (int k = 0; k < n_classes; ++k) {
+    SeqClass& c = cls[k];
+    c.wg_begin = grid;
+    grid += c.groups * c.clusters;
+    c.quot = (int32_t)(blocks[k] / c.clusters);
+    c.rem = (int32_t)(blocks[k] % c.clusters);
+    c.clusters_rcp = reciprocal(c.clusters);
+    c.tile_rcp = reciprocal(8 * c.groups);
+    c.inv_total = 1.0 / (double)blocks[k];
+    c.slot0 = (int32_t)slot;
+    bool cut = false;
+    for (int i = c.first_seq; i < c.first_seq + c.units / d.n_kv_heads && !cut; ++i) {
+      const int64_t nblk = blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup;
+      for (int g = 0; g < d.n_kv_heads && !cut; ++g) {
+        const int64_t fs = sl.bstart[i] - sl.bstart[c.first_seq] + g * nblk;
+        cut = host_owner_of(fs + sl.setup, blocks[k], c.clusters) != host_owner_of(fs + nblk - 1, blocks[k], c.clusters);
+      }
+    }
+    any_cut = any_cut || cut;
+    if (cut) slot += (int64_t)c.groups * (c.units + c.clusters);   // (at most units + workgroups altogether)
+  }
+  sl.n_classes = n_classes;
+  sl.total_blocks = (int32_t)flat;
+  sl.GY = cls[0].groups; sl.n_wgs = cls[0].clusters; sl.wg_quot = cls[0].quot; sl.wg_rem = cls[0].rem;
+  sl.wgs_rcp = cls[0].clusters_rcp; sl.tile_rcp = cls[0].tile_rcp;
+  return grid;
+}
+
 // What a unit costs a workgroup beyond its blocks, in blocks: Q, the ramp of the stream, merge and output. In a ragged batch
 // the flat list counts every unit for that much more: an even split of the blocks alone gave the workgroups of the
 // short sequences a dozen units each, and the call lasted until they were done. Grouped heads, 16 sequences of 131 to
@@ -1792,10 +1958,10 @@ void launch_bf16(const Plan& pl, const AttnParams& prm, bool streamed, hipStream
 }
 
 template <int D>
-void launch_combine(const Plan& pl, const AttnParams& prm, int pieces, int64_t total, hipStream_t stream) {
+void launch_combine(const Plan& pl, const AttnParams& prm, int pieces, hipStream_t stream) {
   const int rows_per_wg = 1024 / D;
-  const dim3 grid((unsigned)((pl.rows_per_unit + rows_per_wg - 1) / rows_per_wg), (unsigned)(prm.Hkv * pl.GY), (unsigned)prm.B);
-  const double inv_total = 1.0 / (double)total;
+  const dim3 grid((unsigned)((pl.rows_per_unit + rows_per_wg - 1) / rows_per_wg * pl.GY), (unsigned)prm.Hkv, (unsigned)prm.B);
+  const double inv_total = 1.0 / (double)prm.total_blocks;
   if (pl.shared_stage) hipLaunchKernelGGL((tree_attn_combine_kernel<D, true>), grid, dim3(256), 0, stream, prm, pl.rows_per_unit, pieces, inv_total);
   else hipLaunchKernelGGL((tree_attn_combine_kernel<D, false>), grid, dim3(256), 0, stream, prm, pl.rows_per_unit, pieces, inv_total);
 }
@@ -1908,50 +2074,50 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       plan_rows(d, pl);
       sl.WS = pl.WS; sl.NS = pl.NS; sl.GY = pl.GY;
       sl.ws_shift = pl.WS == 4 ? 2 : (pl.WS == 2 ? 1 : 0);
-      sl.gy_magic = pl.GY > 1 ? (uint32_t)(((1ull << 32) + pl.GY - 1) / pl.GY) : 0u;
       // units of a sequence: the slab groups that its own tree fills, times the kv heads
-      int64_t seq_units[kMaxBatchPerLaunch];
-      const int64_t full_units = (int64_t)nb * d.n_kv_heads * pl.GY;   // (partial slots are numbered as if every tree were full)
+      int groups[kMaxBatchPerLaunch];
+      const int64_t full_units = (int64_t)nb * d.n_kv_heads * pl.GY;   // (partial slots: as many as if every tree were full)
       const int64_t full_total = (int64_t)d.n_kv_heads * pl.GY * seq_blocks;
       const int64_t full_wgs = plan_wgs(pl, full_total, full_units, uniform, d.workgroups);
       int64_t total = 0, units = 0;
+      int longest = 0;
       for (int i = 0; i < nb; ++i) {
-        seq_units[i] = (int64_t)d.n_kv_heads * groups_of(d, pl, sl.n_nodes[i]);
-        total += seq_units[i] * blocks_of(sl.kv_len[i], sl.n_nodes[i]);
-        units += seq_units[i];
+        groups[i] = groups_of(d, pl, sl.n_nodes[i]);
+        total += (int64_t)d.n_kv_heads * groups[i] * blocks_of(sl.kv_len[i], sl.n_nodes[i]);
+        units += (int64_t)d.n_kv_heads * groups[i];
         if (total > kMaxFlatBlocks) return FSPAD_ERR_SHAPE;  // the kernels index blocks with 32 bits
+        if (blocks_of(sl.kv_len[i], sl.n_nodes[i]) > longest) longest = blocks_of(sl.kv_len[i], sl.n_nodes[i]);
       }
       bool same = true;
       for (int i = 1; i < nb; ++i) same = same && sl.kv_len[i] == sl.kv_len[0] && sl.n_nodes[i] == sl.n_nodes[0];
-      sl.seq_blocks = same ? (int32_t)(seq_units[0] * blocks_of(sl.kv_len[0], sl.n_nodes[0])) : 0;
-      sl.same_len = sl.kv_len[0];
-      sl.same_nodes = sl.n_nodes[0];
       // never more workgroups than full trees would have: the workspace a call needs does not depend on the trees
       // (units of equally many blocks stay aligned with the workgroups, however many of them a sequence has: 4 x 64 / 8 heads,
       // 16 to 26 keys, trees of 11 to 26 nodes 10.2 us, planned as a ragged batch 17.4)
-      sl.n_wgs = plan_wgs(pl, total, units, uniform, d.workgroups);
-      if (sl.n_wgs > full_wgs) sl.n_wgs = (int32_t)(uniform && full_wgs >= units ? full_wgs / units * units : full_wgs);
+      int64_t wgs = plan_wgs(pl, total, units, uniform, d.workgroups);
+      if (wgs > full_wgs) wgs = uniform && full_wgs >= units ? full_wgs / units * units : full_wgs;
       sl.setup = uniform || total + units * setup_blocks(pl) > kMaxFlatBlocks ? 0 : setup_blocks(pl);
-      const int64_t kv_blocks = total;
-      total = 0;
-      for (int i = 0; i < nb; ++i) {
-        sl.bstart[i] = (int32_t)total;
-        total += seq_units[i] * (blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup);
+      // short units of a ragged batch that fit the chip stay whole, as those of an equal one do (plan_wgs): a workgroup each, and
+      // so much set-up that the even division falls into it (12 x 40 / 8 heads, 3 to 8 blocks, 26 nodes: 18.3 -> 13.5 us)
+      if (!uniform && pl.shared_stage && d.workgroups == 0 && 4 * units >= kComputeUnits && units <= kComputeUnits && units <= full_wgs &&
+          longest <= 5 * key_waves(pl)) {
+        wgs = units;
+        sl.setup = kWholeSetup;
       }
-      sl.bstart[nb] = (int32_t)total;
-      sl.total_blocks = (int32_t)total;
-      sl.wg_quot = (int32_t)(total / sl.n_wgs);
-      sl.wg_rem = (int32_t)(total % sl.n_wgs);
-      sl.wgs_rcp = reciprocal(sl.n_wgs);
+      const int64_t kv_blocks = total;
+      bool any_cut = false;
+      const int grid = plan_classes(d, pl, groups, wgs, sl, any_cut);
+      sl.seq_blocks = same ? d.n_kv_heads * blocks_of(sl.kv_len[0], sl.n_nodes[0]) : 0;
+      sl.same_len = sl.kv_len[0];
+      sl.same_nodes = sl.n_nodes[0];
       sl.seq_rcp = reciprocal(sl.seq_blocks);
       sl.unit_rcp = reciprocal(blocks_of(sl.kv_len[0], sl.n_nodes[0]) + sl.setup);
       const size_t need = (size_t)slots_of(pl, full_units, full_wgs, full_total, d.workgroups) * slot_bytes(d, pl);
       if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 15)) return FSPAD_ERR_WORKSPACE;
       if (pl.shared_stage) {
-        if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_gqa128_kernel, dim3((unsigned)sl.n_wgs), dim3(512), 0, stream, sl);
+        if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_gqa128_kernel, dim3((unsigned)grid), dim3(512), 0, stream, sl);
         // (head dim 64 leaves registers for three wavefronts per SIMD: three key groups; 43.1 -> 40.6 us on a
         // 64/8-head, 16384-key, 60-node call, 70.7 -> 64.5 us at 32768 keys)
-        else hipLaunchKernelGGL(tree_attn_gqa64_kernel, dim3((unsigned)sl.n_wgs), dim3(768), 0, stream, sl);
+        else hipLaunchKernelGGL(tree_attn_gqa64_kernel, dim3((unsigned)grid), dim3(768), 0, stream, sl);
       } else {
         // keys and values of the call, read once each (one slab group per kv head). Not the 48- and 64-row tiles of
         // D = 128 where a compute unit takes more than two workgroups in turn: 16 x 40 heads, 60 nodes, 2500 keys 172 us
@@ -1964,20 +2130,12 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       }
       if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       // the merge pass runs only if some unit was cut across workgroups
-      bool any_cut = false;
-      for (int i = 0; i < nb && !any_cut; ++i) {
-        const int64_t nblk = blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup;
-        for (int64_t ub = 0; ub < seq_units[i] && !any_cut; ++ub) {
-          const int64_t fs = sl.bstart[i] + ub * nblk;
-          any_cut = host_owner_of(fs + sl.setup, total, sl.n_wgs) != host_owner_of(fs + nblk - 1, total, sl.n_wgs);
-        }
-      }
       if (any_cut) {
-        // aligned: as many groups for every tree, units of one length, a whole number of workgroups each
-        const bool aligned = sl.seq_blocks > 0 && sl.n_wgs % units == 0;
-        const int pieces = aligned ? (int)(sl.n_wgs / units) : 0;
-        if (d.head_dim == 128) launch_combine<128>(pl, sl, pieces, total, stream);
-        else launch_combine<64>(pl, sl, pieces, total, stream);
+        // every unit of the launch cut into as many pieces, no workgroup with parts of two (0 where that is not so)
+        const int64_t pairs = (int64_t)nb * d.n_kv_heads;
+        const int pieces = sl.seq_blocks > 0 && sl.n_wgs % pairs == 0 ? (int)(sl.n_wgs / pairs) : 0;
+        if (d.head_dim == 128) launch_combine<128>(pl, sl, pieces, stream);
+        else launch_combine<64>(pl, sl, pieces, stream);
         if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       }
     } else {

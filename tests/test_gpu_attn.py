@@ -402,3 +402,31 @@ def test_bf16_shared_stage_rings_and_segments(H, N, Hq, Hkv, scale, L, splits):
     case = H.AttnCase(77 * N + L + splits, 2, N, Hq, Hkv, 128, L, "bf16", l_cap=L + 3, n_nodes=[N, (N + 1) // 2])
     out, _, _ = _check(H, case, H.TOL["bf16"], splits=splits, **({"scale": scale} if scale else {}))
     assert torch.equal(out, case.run_gpu(splits=splits, **({"scale": scale} if scale else {})))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,N,Hq,Hkv,lens,nodes", [
+    (3, 60, 8, 2, (400, 90, 777), (60, 17, 33)),             # two classes of sequences, cut units
+    (5, 64, 12, 1, (500, 3, 90, 301, 33), (64, 5, 22, 43, 11)),   # groups of 1 to 6: more than a launch has classes
+    (9, 33, 32, 8, (90, 3, 40, 66, 0, 31, 64, 5, 77), (33, 9, 20, 33, 1, 16, 17, 30, 25)),   # short units, whole
+    (40, 40, 8, 2, tuple(7 * i % 83 for i in range(40)), tuple(1 + 11 * i % 40 for i in range(40))),
+    (4, 60, 8, 1, (2100, 1900, 2050, 2000), (60, 60, 60, 60)),   # four slab groups, equal classes
+])
+def test_bf16_shared_stage_classes(H, D, B, N, Hq, Hkv, lens, nodes):
+    """Ragged batches of grouped heads: sequences whose trees fill different numbers of slab groups are planned in classes, short
+    units stay whole; every output row is written exactly once either way, rows of unused nodes as zeros, at any
+    number of workgroups."""
+    case = H.AttnCase(900 + B + N + D, B, N, Hq, Hkv, D, max(lens), "bf16", l_cap=max(lens) + 2, kv_len=list(lens), n_nodes=list(nodes), topk=4)
+    # The weights are rounded to bf16 (2^-9 of each) in numerator and sum alike: an output is off by at most 2^-9 (sum of
+    # p |v| + |output|), under 2^-8 times the same attention over |v|; the rest is fp32. (A bar in terms of the whole batch's
+    # RMS does not fit sequences of 3 and of 500 keys side by side: their outputs differ in size by a factor of ten.)
+    import oracle
+    h = case.host
+    ref = case.run_oracle()
+    bound = 1.05 * 2.0 ** -8 * oracle.tree_attn(h["q"], h["k_tree"], np.abs(h["v_tree"]), h["k_cache"], np.abs(h["v_cache"]), case.kv_len,
+                                                case.n_nodes, case.parent, packed_mask=case.mask, nthreads=16) + 1e-5
+    for splits in (0, 1, 5, 37):
+        out = case.run_gpu(splits=splits)
+        assert np.all(np.abs(out.double().cpu().numpy() - ref) <= bound), f"workgroups {splits}"
+        for b, n in enumerate(case.n_nodes):
+            assert torch.all(out[b, int(n):] == 0)
