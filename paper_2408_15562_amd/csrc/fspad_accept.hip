@@ -57,7 +57,16 @@ struct AcceptParams {
   const float* logits2;
   float* part_max2;
   double* part_sum2;
+  // rows of leaves: of the first array the maximum alone, of the second nothing (the chip-wide walk of sampled drafts
+  // tests no child there: it draws from weights that it forms itself, and the draft's row is not looked at)
+  int32_t spare_leaves;
 };
+
+// Has a node a child among the n nodes of its tree? (n <= 64; one lane each, the same answer in every lane)
+__device__ __forceinline__ bool has_child(const int32_t* parent, int n, int node) {
+  const int lane = threadIdx.x & 63;
+  return __any(lane > node && lane < n && parent[lane] == node);
+}
 
 // Inclusive running sum over the 64 lanes of a wavefront, lane order, with data-parallel-primitive moves
 // (no LDS round trips): four shifts inside each row of 16 lanes (a lane without a source adds 0), then the
@@ -103,6 +112,11 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
     for (int i = threadIdx.x; i < p.clear_count; i += kThreads) p.clear_words[i] = 0u;
   if (node >= p.n_nodes[b]) return;  // rows of unused tree slots are never read
   const bool second = blockIdx.z != 0;
+  bool max_only = false;
+  if (MODE == 1 && p.spare_leaves) {
+    max_only = !has_child(p.parent + (int64_t)b * p.Nmax, min(p.n_nodes[b], p.Nmax), node);
+    if (max_only && second) return;
+  }
   const float* rp = (second ? p.logits2 : p.logits) + (int64_t)row * p.row_stride;
   float* const part_max = second ? p.part_max2 : p.part_max;
   double* const part_sum = second ? p.part_sum2 : p.part_sum;
@@ -147,7 +161,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
 #pragma unroll
     for (int k = 1; k < kPerThread; ++k) mt = fmaxf(mt, x[k]);
     double st = 0.0;
-    if (mt > -INFINITY) {
+    if (mt > -INFINITY && !max_only) {
       const double mtd = (double)mt;
 #pragma unroll
       for (int k = 0; k < kPerThread; ++k) st += exp_nonpos_table(((double)x[k] - mtd) * p.inv_temperature, exp2_table);
@@ -158,7 +172,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
     if (lane == 0) sh_max[wave] = mw;
     __syncthreads();
     const float mc = fmaxf(fmaxf(sh_max[0], sh_max[1]), fmaxf(sh_max[2], sh_max[3]));
-    double sum = mt > -INFINITY ? st * exp_nonpos(((double)mt - (double)mc) * p.inv_temperature) : 0.0;
+    double sum = mt > -INFINITY && !max_only ? st * exp_nonpos(((double)mt - (double)mc) * p.inv_temperature) : 0.0;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
     if (lane == 0) sh_sum[wave] = sum;
@@ -997,6 +1011,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_row_merge_kernel(const Dr
   const int row = blockIdx.x, arr = blockIdx.y, tid = threadIdx.x;
   const int b = row / p.Nmax, node = row - b * p.Nmax;
   if (node >= p.n_nodes[b]) return;   // rows of unused tree slots have no chunk statistics
+  if (arr && !has_child(p.parent + (int64_t)b * p.Nmax, min(p.n_nodes[b], p.Nmax), node)) return;   // (nor leaves of the draft's)
   const float* pm = (arr ? p.part_max_q : p.part_max_p) + (int64_t)row * p.n_chunks;
   const double* ps = (arr ? p.part_sum_q : p.part_sum_p) + (int64_t)row * p.n_chunks;
   float m = -INFINITY;
@@ -1068,7 +1083,8 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
   for (;;) {
     const float* lrow = p.logits + (o + cur) * p.row_stride;
     const float* qrow = p.draft_logits + (o + cur) * p.row_stride;
-    // (rows of nodes beyond the tree are never walked: their entries hold no statistics)
+    // (rows of nodes beyond the tree are never walked: their entries hold no statistics; a leaf has the maximum of its target row
+    // only, which is all that the draw below takes: the rest is for tests of children)
     const double mp = t_stats[0][cur][0], zp = t_stats[0][cur][1], mq = t_stats[1][cur][0], zq = t_stats[1][cur][1];
     double sp = zp > 0.0 ? 1.0 / zp : 0.0, sq = zq > 0.0 ? 1.0 / zq : 0.0;
     auto weight_p = [&](int v) {
@@ -1419,6 +1435,15 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
   AcceptParams both = pa;
   both.logits2 = draft_logits; both.part_max2 = pb.part_max; both.part_sum2 = pb.part_sum;
   both.clear_words = pb.clear_words; both.clear_count = pb.clear_count;
+  // The chip-wide walk needs less of the leaves' rows, which are more than half of a tree's: 60 nodes,
+  // V = 128256: 70.4 -> 67.7 us a call.
+  // (The one-workgroup form needs all: also where it takes over from a cooperative launch that a capture refuses.)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    capture = hipStreamCaptureStatusActive;
+  }
+  both.spare_leaves = plan.E != 0 && capture == hipStreamCaptureStatusNone;
   launch_rows<1>(both, rows_vectorisable(logits, row_stride) && rows_vectorisable(draft_logits, row_stride), stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   if (plan.E != 0) {
@@ -1446,6 +1471,11 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
     }
     if (err == hipSuccess) return FSPAD_OK;
     (void)hipGetLastError();   // the launch was refused (a capture in progress, say): the one-workgroup form below
+    if (both.spare_leaves) {
+      both.spare_leaves = 0;
+      launch_rows<1>(both, rows_vectorisable(logits, row_stride) && rows_vectorisable(draft_logits, row_stride), stream);
+      if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
+    }
   }
   DraftAcceptParams p{};
   p.logits = logits; p.draft_logits = draft_logits; p.row_stride = row_stride;
