@@ -87,8 +87,7 @@ struct AttnParams {
   // sequences in the order of their classes
   int32_t kv_len[kMaxBatchPerLaunch];
   int32_t bstart[kMaxBatchPerLaunch + 1];  // first flat block of each sequence; bstart[B] = total_blocks
-  int32_t n_nodes[kMaxBatchPerLaunch];
-  int32_t order[kMaxBatchPerLaunch];       // their places in the batch
+  int32_t n_nodes[kMaxBatchPerLaunch];     // and, from bit 8 on, their places in the batch (plan_classes)
 };
 
 // The scalar part of AttnParams as the kernels use it, fetched from the kernel-argument segment in
@@ -129,7 +128,6 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* arg_at(siz
 __device__ __forceinline__ KernargI32 arg_kv_len() { return arg_at<int32_t>(offsetof(AttnParams, kv_len)); }
 __device__ __forceinline__ KernargI32 arg_bstart() { return arg_at<int32_t>(offsetof(AttnParams, bstart)); }
 __device__ __forceinline__ KernargI32 arg_n_nodes() { return arg_at<int32_t>(offsetof(AttnParams, n_nodes)); }
-__device__ __forceinline__ KernargI32 arg_order() { return arg_at<int32_t>(offsetof(AttnParams, order)); }
 __device__ __forceinline__ const __attribute__((address_space(4))) SeqClass* arg_classes() { return arg_at<SeqClass>(offsetof(AttnParams, classes)); }
 
 __device__ __forceinline__ AttnArgs fetch_args() {
@@ -173,7 +171,8 @@ __device__ __forceinline__ int seq_of_block(const AttnArgs& p, unsigned r0, int 
 __device__ __forceinline__ unsigned seq_first_block(const AttnArgs& p, int b) {
   return p.seq_blocks > 0 ? (unsigned)b * (unsigned)p.seq_blocks : (unsigned)arg_bstart()[b];
 }
-__device__ __forceinline__ int seq_nodes(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_nodes : arg_n_nodes()[b]; }
+__device__ __forceinline__ int seq_nodes(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_nodes : arg_n_nodes()[b] & 0xff; }
+__device__ __forceinline__ int seq_place(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? b : arg_n_nodes()[b] >> 8; }
 __device__ __forceinline__ int seq_len(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_len : arg_kv_len()[b]; }
 
 // flat blocks [r0, r1) of workgroup w: [floor(w*T/W), floor((w+1)*T/W)) with T = wg_quot*W + wg_rem
@@ -875,7 +874,7 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) 
   for (unsigned r = share.r0; r < r1;) {
     const int n = seq_nodes(p, at_seq);
     const int L = seq_len(p, at_seq);
-    const int b = p.seq_blocks > 0 ? at_seq : arg_order()[at_seq];
+    const int b = seq_place(p, at_seq);
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
     const unsigned rel = r - seq_first_block(p, at_seq);
@@ -1250,7 +1249,7 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams)
   for (unsigned r = share.r0; r < r1;) {
     const int n = seq_nodes(p, at_seq);
     const int L = seq_len(p, at_seq);
-    const int b = p.seq_blocks > 0 ? at_seq : arg_order()[at_seq];
+    const int b = seq_place(p, at_seq);
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
     const unsigned rel = r - seq_first_block(p, at_seq);
@@ -1482,7 +1481,7 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
   constexpr int TPR = D / 4;  // threads per row
   constexpr int RPW = 256 / TPR;   // rows of this workgroup: in lane order (partial_index) the faster index of its threads
   const int at_seq = blockIdx.z, g = blockIdx.y;
-  const int n = seq_nodes(p, at_seq), b = p.seq_blocks > 0 ? at_seq : arg_order()[at_seq];
+  const int n = seq_nodes(p, at_seq), b = seq_place(p, at_seq);
   const int y = SHARED ? (int)(blockIdx.x * RPW) / 128 : 0;   // (128 rows per slab group)
   if (SHARED && y >= seq_groups(p, seq_slabs(p, n, 32))) return;   // a tree smaller than the largest: no such rows of it
   int clusters = p.n_wgs, units = p.B * p.Hkv, first_seq = 0, slot0 = 0;
@@ -1828,7 +1827,9 @@ int plan_classes(const fspad_attn_desc& d, const Plan& pl, const int* groups, in
     }
     if (n_classes <= kMaxClasses) break;
   }
-  const AttnParams in = sl;
+  struct { int32_t kv_len[kMaxBatchPerLaunch], n_nodes[kMaxBatchPerLaunch]; } in;   // in the batch's order
+  for (int i = 0; i < nb; ++i) { in.kv_len[i] = sl.kv_len[i]; in.n_nodes[i] = sl.n_nodes[i]; }
+  int place[kMaxBatchPerLaunch];
   // whole units (kWholeSetup): the shorter ones first, so that a workgroup's range ends behind its own unit, in the next one's set-up
   int by[kMaxBatchPerLaunch];
   for (int i = 0; i < nb; ++i) {
@@ -1847,7 +1848,7 @@ int plan_classes(const fspad_attn_desc& d, const Plan& pl, const int* groups, in
     for (int j = 0; j < nb; ++j) {
       const int i = by[j];
       if (used[i] != class_groups[k]) continue;
-      sl.order[at] = i; sl.kv_len[at] = in.kv_len[i]; sl.n_nodes[at] = in.n_nodes[i]; sl.bstart[at] = (int32_t)flat;
+      place[at] = i; sl.kv_len[at] = in.kv_len[i]; sl.n_nodes[at] = in.n_nodes[i]; sl.bstart[at] = (int32_t)flat;
       flat += (int64_t)d.n_kv_heads * (blocks_of(in.kv_len[i], in.n_nodes[i]) + sl.setup);
       ++at;
     }
@@ -1895,6 +1896,7 @@ int plan_classes(const fspad_attn_desc& d, const Plan& pl, const int* groups, in
     any_cut = any_cut || cut;
     if (cut) slot += (int64_t)c.groups * (c.units + c.clusters);   // (at most units + workgroups altogether)
   }
+  for (int i = 0; i < nb; ++i) sl.n_nodes[i] |= place[i] << 8;
   sl.n_classes = n_classes;
   sl.total_blocks = (int32_t)flat;
   sl.GY = cls[0].groups; sl.n_wgs = cls[0].clusters; sl.wg_quot = cls[0].quot; sl.wg_rem = cls[0].rem;
@@ -2106,11 +2108,12 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       const int64_t kv_blocks = total;
       bool any_cut = false;
       const int grid = plan_classes(d, pl, groups, wgs, sl, any_cut);
-      sl.seq_blocks = same ? d.n_kv_heads * blocks_of(sl.kv_len[0], sl.n_nodes[0]) : 0;
-      sl.same_len = sl.kv_len[0];
-      sl.same_nodes = sl.n_nodes[0];
+      sl.same_len = kv_len[b0];
+      sl.same_nodes = n_nodes[b0];
+      const int same_blocks = blocks_of(sl.same_len, sl.same_nodes);
+      sl.seq_blocks = same ? d.n_kv_heads * same_blocks : 0;
       sl.seq_rcp = reciprocal(sl.seq_blocks);
-      sl.unit_rcp = reciprocal(blocks_of(sl.kv_len[0], sl.n_nodes[0]) + sl.setup);
+      sl.unit_rcp = reciprocal(same_blocks + sl.setup);
       const size_t need = (size_t)slots_of(pl, full_units, full_wgs, full_total, d.workgroups) * slot_bytes(d, pl);
       if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 15)) return FSPAD_ERR_WORKSPACE;
       if (pl.shared_stage) {
