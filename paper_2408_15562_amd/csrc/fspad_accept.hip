@@ -10,7 +10,7 @@
 // exp((l-max)/T)) for sampling. The second, one workgroup per sequence, merges the
 // chunk statistics of every row at once, walks the tree with wavefront ballots
 // out of LDS and, for sampling, draws the last token by an inverse-CDF search that
-// descends chunk -> thread segment -> element.
+// descends chunk -> thread segment -> element. (Large sampling calls: four kernels, see kInnerFirst.)
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <atomic>
@@ -57,15 +57,21 @@ struct AcceptParams {
   const float* logits2;
   float* part_max2;
   double* part_sum2;
-  // rows of leaves: of the first array the maximum alone, of the second nothing (the chip-wide walk of sampled drafts
-  // tests no child there: it draws from weights that it forms itself, and the draft's row is not looked at)
-  int32_t spare_leaves;
+  int32_t rows;        // kAllRows, ...: which rows' statistics this launch forms (sampling)
 };
 
-// Has a node a child among the n nodes of its tree? (n <= 64; one lane each, the same answer in every lane)
+constexpr int32_t kAllRows = 0;
+// rows of leaves: of the first array the maximum alone, of the second nothing (the chip-wide walk of sampled drafts
+// tests no child there: it draws from weights that it forms itself, and the draft's row is not looked at)
+constexpr int32_t kSpareLeaves = 1;
+constexpr int32_t kInnerRows = 2;   // nodes that have children
+constexpr int32_t kStopRows = 3;    // one node a sequence: where the walk stopped (part_idx[b]), if it is a leaf
+
+// Has a node a child among the n nodes of its tree, as the walk would test it? (n <= 64; one lane each, the same answer in
+// every lane)
 __device__ __forceinline__ bool has_child(const int32_t* parent, int n, int node) {
   const int lane = threadIdx.x & 63;
-  return __any(lane > node && lane < n && parent[lane] == node);
+  return __any(lane > 0 && lane < n && parent[lane] == node);
 }
 
 // Inclusive running sum over the 64 lanes of a wavefront, lane order, with data-parallel-primitive moves
@@ -106,16 +112,26 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
   __shared__ int sh_idx[4];
   __shared__ double sh_sum[4];
   __shared__ double exp2_table[32];
-  const int row = blockIdx.y, chunk = blockIdx.x;
-  const int b = row / p.Nmax, node = row - b * p.Nmax;
+  int row = blockIdx.y;
+  const int chunk = blockIdx.x;
+  int b, node;
+  if (MODE == 1 && p.rows == kStopRows) {
+    b = row;
+    node = p.part_idx[b];
+    row = b * p.Nmax + node;
+  } else {
+    b = row / p.Nmax;
+    node = row - b * p.Nmax;
+  }
   if (row == 0 && chunk == 0)
     for (int i = threadIdx.x; i < p.clear_count; i += kThreads) p.clear_words[i] = 0u;
   if (node >= p.n_nodes[b]) return;  // rows of unused tree slots are never read
   const bool second = blockIdx.z != 0;
   bool max_only = false;
-  if (MODE == 1 && p.spare_leaves) {
-    max_only = !has_child(p.parent + (int64_t)b * p.Nmax, min(p.n_nodes[b], p.Nmax), node);
-    if (max_only && second) return;
+  if (MODE == 1 && p.rows != kAllRows) {
+    const bool leaf = !has_child(p.parent + (int64_t)b * p.Nmax, min(p.n_nodes[b], p.Nmax), node);
+    if (leaf ? second || p.rows == kInnerRows : p.rows == kStopRows) return;
+    max_only = leaf && p.rows == kSpareLeaves;
   }
   const float* rp = (second ? p.logits2 : p.logits) + (int64_t)row * p.row_stride;
   float* const part_max = second ? p.part_max2 : p.part_max;
@@ -371,6 +387,8 @@ __device__ __forceinline__ void draw_in_chunk(const DrawArgs& a) {
 // already proposed weighs nothing, because it has left the residual by the time it is tested);
 // (3) wavefront 0 walks the tree out of LDS, testing the children of the current node in index
 // order against the running residual; (4) the workgroup draws the last token.
+// Without DRAW it leaves the node where the walk stops in part_idx[b], nothing else: no leaf's statistics are looked at.
+template <bool DRAW>
 __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const AcceptParams p) {
   __shared__ int rej_tok[FSPAD_MAX_NODES];
   __shared__ double rej_w[FSPAD_MAX_NODES];
@@ -491,6 +509,10 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
       cur = accepted;
       ++len;
     }
+    if constexpr (!DRAW) {
+      if (lane == 0) p.part_idx[b] = cur;
+      return;
+    }
     if (lane < nrej) { rej_tok[lane] = my_rej; rej_w[lane] = my_rej_w; }
     __builtin_amdgcn_wave_barrier();
     if (lane < p.Nmax) { p.path[o + lane] = my_path; if (lane != len - 1) p.tokens[o + lane] = my_out; }
@@ -534,6 +556,7 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
       sh_d[2] = found >= 0 ? t - before : INFINITY;
     }
   }
+  if constexpr (!DRAW) return;
   __syncthreads();
 
   // bonus, stage 2: inside the chunk, thread k owns chunk/1024 consecutive entries
@@ -607,7 +630,7 @@ bool rows_vectorisable(const float* logits, int64_t row_stride) {
 
 template <int MODE>
 void launch_rows(const AcceptParams& p, bool vec, hipStream_t stream) {
-  const dim3 grid((unsigned)p.n_chunks, (unsigned)(p.B * p.Nmax), p.logits2 ? 2u : 1u);
+  const dim3 grid((unsigned)p.n_chunks, (unsigned)(p.rows == kStopRows ? p.B : p.B * p.Nmax), p.logits2 ? 2u : 1u);
 #define FSPAD_ROWS(PT)                                                                                         \
   do {                                                                                                           \
     if (vec) hipLaunchKernelGGL((accept_rows_kernel<MODE, true, PT>), grid, dim3(kThreads), 0, stream, p);      \
@@ -1372,6 +1395,15 @@ extern "C" fspad_status fspad_tree_accept_greedy_static(int32_t B, int32_t Nmax,
                                   n_tokens, ptr, FSPAD_STATIC_SCRATCH_BYTES, hip_stream);
 }
 
+// Sampling, large calls: the rows of leaves are looked at only where the walk ends, for the last draw, and leaves are more than
+// half of a tree. From so many logits on, the first pass leaves them out, the walk runs without its draw, and a second pass adds
+// the one leaf a sequence that it stopped at. The two more launches cost about 7 us. Trees with half of their nodes leaves,
+// V = 128256, us a call: 16 x 60 nodes 133 -> 92, 16 x 20..60 nodes 94 -> 74, 6 x 60 63 -> 57, 4 x 60 49 -> 47, 3 x 60 42 -> 43,
+// 1 x 60 22 -> 26; 64 x 60 nodes, V = 32000: 132 -> 95. Drafts without branches have one leaf and lose the 7 us (64 x 6 nodes
+// 66 -> 76), whence the least number of nodes: below it most drafts are such, and trees gain little (16 x 16 50.5 -> 50.5).
+constexpr int64_t kInnerFirst = (int64_t)40 << 20;
+constexpr int32_t kInnerFirstNodes = 24;
+
 extern "C" fspad_status fspad_tree_accept_sample(int32_t B, int32_t Nmax, int32_t V, const float* logits,
                                                  int64_t row_stride, const int32_t* draft_tokens,
                                                  const int32_t* parent, const int32_t* n_nodes, float temperature,
@@ -1388,9 +1420,18 @@ extern "C" fspad_status fspad_tree_accept_sample(int32_t B, int32_t Nmax, int32_
   p.uniforms = uniforms;
   p.inv_temperature = 1.0 / (double)temperature;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-  launch_rows<1>(p, rows_vectorisable(logits, row_stride), stream);
+  const bool vec = rows_vectorisable(logits, row_stride);
+  if (Nmax >= kInnerFirstNodes && (int64_t)B * Nmax * V >= kInnerFirst) {
+    p.rows = kInnerRows;
+    launch_rows<1>(p, vec, stream);
+    if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
+    hipLaunchKernelGGL((accept_sample_walk_kernel<false>), dim3((unsigned)B), dim3(kWalkThreads), 0, stream, p);
+    if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
+    p.rows = kStopRows;
+  }
+  launch_rows<1>(p, vec, stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-  hipLaunchKernelGGL(accept_sample_walk_kernel, dim3((unsigned)B), dim3(kWalkThreads), 0, stream, p);
+  hipLaunchKernelGGL((accept_sample_walk_kernel<true>), dim3((unsigned)B), dim3(kWalkThreads), 0, stream, p);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   return FSPAD_OK;
 }
@@ -1443,7 +1484,7 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
     (void)hipGetLastError();
     capture = hipStreamCaptureStatusActive;
   }
-  both.spare_leaves = plan.E != 0 && capture == hipStreamCaptureStatusNone;
+  both.rows = plan.E != 0 && capture == hipStreamCaptureStatusNone ? kSpareLeaves : kAllRows;
   launch_rows<1>(both, rows_vectorisable(logits, row_stride) && rows_vectorisable(draft_logits, row_stride), stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   if (plan.E != 0) {
@@ -1471,8 +1512,8 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
     }
     if (err == hipSuccess) return FSPAD_OK;
     (void)hipGetLastError();   // the launch was refused (a capture in progress, say): the one-workgroup form below
-    if (both.spare_leaves) {
-      both.spare_leaves = 0;
+    if (both.rows != kAllRows) {
+      both.rows = kAllRows;
       launch_rows<1>(both, rows_vectorisable(logits, row_stride) && rows_vectorisable(draft_logits, row_stride), stream);
       if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
     }

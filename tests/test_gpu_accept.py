@@ -59,6 +59,22 @@ def test_ragged_n_nodes_and_padded_rows(H):
     H.assert_accept_equal(gpu, cpu, cpu[4] >= H.MARGIN)
 
 
+@pytest.mark.parametrize("B,N,V,row_pad,n_nodes,chain",
+                         [(5, 64, 131072, 0, None, False),                       # 40 * 2^20 logits: the first size that leaves leaves out
+                          (5, 64, 131071, 1, None, False),                       # the last that does not
+                          (13, 33, 100003, 2, [33, 1, 2, 17] * 3 + [5], False),  # ragged, a tree that is its root alone, rows not aligned
+                          (8, 24, 220000, 0, None, True)])                       # the fewest nodes; one leaf each
+def test_large_sampling_calls(H, B, N, V, row_pad, n_nodes, chain):
+    parent = np.broadcast_to(np.arange(-1, N - 1, dtype=np.int32), (B, N)) if chain else None
+    case = H.AcceptCase(2700 + B, B, N, V, "sample", peak=1.5, row_pad=row_pad, n_nodes=n_nodes, parent=parent)
+    first = case.gpu_sample(1.0)
+    cpu = case.cpu_sample(1.0)
+    keep = cpu[4] >= H.MARGIN
+    assert keep.sum() >= B - 1
+    H.assert_accept_equal(first, cpu, keep)
+    H.assert_accept_equal(case.gpu_sample(1.0), first)
+
+
 def test_argmax_ties_nan_and_signed_zero(H):
     parent = np.array([[-1, 0, 0]], np.int32)
     V = 9000
