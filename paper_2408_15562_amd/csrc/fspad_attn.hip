@@ -1408,7 +1408,9 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams)
 
     // The two key groups hold the same rows in the same lanes. Group 0 finishes dims 0..63 and group 1 dims 64..127: each hands
     // the other half over in lane-private LDS slots (the rings are free), so that all eight wavefronts merge and write.
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 7" ::: "memory");   // (products of the last block, issued in assembly, before the first vector read)
+    // (the compiler does not know that o comes from matrix instructions: the wait states behind the last of them own it, so that
+    // no read of it can be placed in front of them)
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 7" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]) : : "memory");
     __syncthreads();
     f32x4* const mbuf = reinterpret_cast<f32x4*>(lds_all) + wave * (2 * 8 * 64) + lane;
     float2* const ml = reinterpret_cast<float2*>(lds_all + 65536) + wave * 128 + lane;

@@ -1,0 +1,37 @@
+"""CPU-only checks of the device sources themselves, for mistakes that no result shows on the machine at hand."""
+import glob
+import os
+import re
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2408_15562_amd", "csrc")
+
+
+def _asm_statements(text):
+    """(line, text) of every asm statement, its parentheses balanced outside string literals."""
+    for m in re.finditer(r"\basm volatile\s*\(", text):
+        depth, i, quoted = 1, m.end(), False
+        while depth:
+            c = text[i]
+            if quoted:
+                i += c == "\\"
+                quoted = c != '"'
+            elif c == '"':
+                quoted = True
+            else:
+                depth += (c == "(") - (c == ")")
+            i += 1
+        yield text.count("\n", 0, m.start()) + 1, text[m.start():i]
+
+
+def test_wait_states_own_what_they_protect():
+    """Wait states (s_nop) order nothing for the compiler by themselves: they stand in one statement with the instruction they
+    belong to, or they name the registers that it wrote as operands ("+v"). Products issued in assembly are not known to the
+    compiler as matrix instructions, so nothing else keeps a read of their results behind the wait."""
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.h"))):
+        for line, stmt in _asm_statements(open(path).read()):
+            if "s_nop" not in stmt:
+                continue
+            seen += 1
+            assert re.search(r'v_mfma|global_store|"\+v"\(', stmt), f"{os.path.basename(path)}:{line}: {stmt}"
+    assert seen >= 4
