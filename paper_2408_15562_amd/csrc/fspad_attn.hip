@@ -49,8 +49,11 @@ struct SeqClass {
   int32_t wg_begin, groups, clusters, quot, rem;   // cluster p starts at block p * quot + p * rem / clusters of the class
   uint32_t clusters_rcp, tile_rcp;                 // reciprocals (div_rcp) of clusters and of 8 * groups
   int32_t first_seq, slot0, units;                 // units: (sequence, kv head) pairs
+  int32_t first_block;                             // in the launch's flat list
   double inv_total;                                // 1 / blocks of the class
 };
+// A sequence's prefix length and node count; from bit 8 of `nodes` on its place in the batch, from bit 16 on its class.
+struct SeqInfo { int32_t kv_len, nodes; };
 constexpr float kNegBig = -1.0e30f;     // finite stand-in for "no key seen yet"
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -83,11 +86,18 @@ struct AttnParams {
   int32_t setup;    // blocks that every unit counts for beyond its own in the flat list (ragged batches; setup_blocks)
   uint32_t wgs_rcp, seq_rcp, unit_rcp;  // reciprocals (div_rcp) of n_wgs and, with seq_blocks > 0, of that and of the blocks a unit counts for
   int32_t n_classes;
-  SeqClass classes[kMaxClasses];           // where there is more than one
-  // sequences in the order of their classes
-  int32_t kv_len[kMaxBatchPerLaunch];
+  // Sequences in the order of their classes. A workgroup that knows its sequence reads both entries at once, in one trip: fetched
+  // one number after the other, and the merge kernel's own arguments behind them, a ragged call took over half a microsecond more
+  // (2 x 40 heads, 91 to 729 keys, 48 nodes 19.8 -> 18.9 us, 4 x 32 heads, D = 64, 1 to 102 keys, 48 nodes 18.1 -> 17.4).
   int32_t bstart[kMaxBatchPerLaunch + 1];  // first flat block of each sequence; bstart[B] = total_blocks
-  int32_t n_nodes[kMaxBatchPerLaunch];     // and, from bit 8 on, their places in the batch (plan_classes)
+  SeqInfo seq[kMaxBatchPerLaunch];
+};
+// The arguments of the shared-stage kernels, which the other ones do without: with 200 bytes more, and a sequence's lengths further
+// from the scalars, fp32 calls of 4 to 10 us took 0.15 to 0.2 us longer.
+struct SharedParams {
+  AttnParams a;
+  int32_t class_wg[kMaxClasses];   // first workgroup of each class (of those that the launch does not have: none, INT32_MAX)
+  SeqClass classes[kMaxClasses];   // where there is more than one
 };
 
 // The scalar part of AttnParams as the kernels use it, fetched from the kernel-argument segment in
@@ -115,8 +125,9 @@ struct AttnArgs {
   uint32_t wgs_rcp, seq_rcp, unit_rcp;
   int32_t n_classes;
 };
+static_assert(sizeof(AttnParams) <= 1728, "a longer argument block costs every launch");
 static_assert(offsetof(AttnParams, stride_batch) == 64 && offsetof(AttnParams, B) == 88 && offsetof(AttnParams, total_blocks) == 128 &&
-              offsetof(AttnParams, scale) == 152 && offsetof(AttnParams, same_nodes) == 164 && offsetof(AttnParams, setup) == 168 && offsetof(AttnParams, n_classes) == 184 && offsetof(AttnParams, classes) == 192,
+              offsetof(AttnParams, scale) == 152 && offsetof(AttnParams, same_nodes) == 164 && offsetof(AttnParams, setup) == 168 && offsetof(AttnParams, n_classes) == 184 && sizeof(AttnParams) % 8 == 0 && sizeof(SharedParams) % 8 == 0,
               "fetch_args reads the scalars by their offsets");
 
 // Arguments that are read where they are used: the arrays, and in the shared-stage kernels what only a segment's end needs
@@ -125,17 +136,14 @@ template <typename T>
 __device__ __forceinline__ const __attribute__((address_space(4))) T* arg_at(size_t offset) {
   return (const __attribute__((address_space(4))) T*)((KernargPtr)__builtin_amdgcn_kernarg_segment_ptr() + offset);
 }
-__device__ __forceinline__ KernargI32 arg_kv_len() { return arg_at<int32_t>(offsetof(AttnParams, kv_len)); }
 __device__ __forceinline__ KernargI32 arg_bstart() { return arg_at<int32_t>(offsetof(AttnParams, bstart)); }
-__device__ __forceinline__ KernargI32 arg_n_nodes() { return arg_at<int32_t>(offsetof(AttnParams, n_nodes)); }
-__device__ __forceinline__ const __attribute__((address_space(4))) SeqClass* arg_classes() { return arg_at<SeqClass>(offsetof(AttnParams, classes)); }
+__device__ __forceinline__ const __attribute__((address_space(4))) SeqClass* arg_classes() { return arg_at<SeqClass>(offsetof(SharedParams, classes)); }
 
-__device__ __forceinline__ AttnArgs fetch_args() {
-  typedef int v16i __attribute__((ext_vector_type(16)));
-  KernargPtr ka = (KernargPtr)__builtin_amdgcn_kernarg_segment_ptr();   // AttnParams is the first argument
-  v16i a, b, c;
-  asm volatile("s_load_dwordx16 %0, %3, 0x0\n\ts_load_dwordx16 %1, %3, 0x40\n\ts_load_dwordx16 %2, %3, 0x80\n\ts_waitcnt lgkmcnt(0)"
-               : "=&s"(a), "=&s"(b), "=&s"(c) : "s"(ka));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ AttnArgs args_from(const i32x16& a, const i32x16& b, const i32x16& c) {
   auto u64 = [](int lo, int hi) { return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo; };
   // (a pointer formed from an integer is a generic one: its accesses become flat instructions, which count as LDS accesses
   // too and may return in any order, so that every wait for one is a wait for all that is in flight)
@@ -161,6 +169,44 @@ __device__ __forceinline__ AttnArgs fetch_args() {
   r.wgs_rcp = (uint32_t)c[11]; r.seq_rcp = (uint32_t)c[12]; r.unit_rcp = (uint32_t)c[13]; r.n_classes = c[14];
   return r;
 }
+__device__ __forceinline__ AttnArgs fetch_args() {
+  KernargPtr ka = (KernargPtr)__builtin_amdgcn_kernarg_segment_ptr();   // AttnParams is the first argument
+  i32x16 a, b, c;
+  asm volatile("s_load_dwordx16 %0, %3, 0x0\n\ts_load_dwordx16 %1, %3, 0x40\n\ts_load_dwordx16 %2, %3, 0x80\n\ts_waitcnt lgkmcnt(0)"
+               : "=&s"(a), "=&s"(b), "=&s"(c) : "s"(ka));
+  AttnArgs r = args_from(a, b, c);
+  // Registers of their own for what is read throughout: left in the sixteen of their load they are spilled, and fetched back, all
+  // sixteen at a time (moves from spilled registers in the code of the 48-row tiles at D = 64: 201, now 43; 4 x 52 heads of it,
+  // 497 keys, 42 to 48 nodes 11.3 -> 10.9 us). Loads of four or two words
+  // instead cost more than they spare: 10 x 8 heads, 70 keys, 64 nodes 12.6 us, in loads of four 13.2, of two 13.9.
+  asm volatile("" : "+s"(r.seq_blocks), "+s"(r.same_len), "+s"(r.same_nodes), "+s"(r.setup), "+s"(r.unit_rcp), "+s"(r.g_magic), "+s"(r.out_bf16), "+s"(r.n_classes), "+s"(r.wgs_rcp), "+s"(r.seq_rcp), "+s"(r.scale));
+  return r;
+}
+// The same with what the merge needs of a sequence and the merge kernel's own arguments, which lie `tail` bytes into the segment.
+struct MergeArgs {
+  AttnArgs p;
+  int first_block, kv_len, nodes;   // of the sequence (SeqInfo)
+  int rows_per_unit, pieces;
+  double inv_total;
+};
+__device__ __forceinline__ MergeArgs fetch_merge_args(int at_seq, size_t tail) {
+  KernargPtr ka = (KernargPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  i32x16 a, b, c;
+  i32x4 own;
+  i32x2 seq;
+  int first;
+  asm volatile("s_load_dwordx16 %0, %6, 0x0\n\ts_load_dwordx16 %1, %6, 0x40\n\ts_load_dwordx16 %2, %6, 0x80\n\t"
+               "s_load_dwordx4 %3, %7, 0x0\n\ts_load_dwordx2 %4, %8, 0x0\n\ts_load_dword %5, %9, 0x0\n\ts_waitcnt lgkmcnt(0)"
+               : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(own), "=&s"(seq), "=&s"(first)
+               : "s"(ka), "s"(ka + tail), "s"(ka + offsetof(AttnParams, seq) + (unsigned)at_seq * sizeof(SeqInfo)),
+                 "s"(ka + offsetof(AttnParams, bstart) + (unsigned)at_seq * sizeof(int32_t)));
+  MergeArgs m;
+  m.p = args_from(a, b, c);
+  m.first_block = first; m.kv_len = seq[0]; m.nodes = seq[1];
+  m.rows_per_unit = own[0]; m.pieces = own[1];
+  m.inv_total = __builtin_bit_cast(double, i32x2{own[2], own[3]});
+  return m;
+}
 // sequence that flat block r0 belongs to, and the first flat block / lengths of a sequence
 __device__ __forceinline__ int seq_of_block(const AttnArgs& p, unsigned r0, int first = 0) {
   if (p.seq_blocks > 0) return (int)div_rcp(r0, (unsigned)p.seq_blocks, p.seq_rcp);
@@ -171,9 +217,23 @@ __device__ __forceinline__ int seq_of_block(const AttnArgs& p, unsigned r0, int 
 __device__ __forceinline__ unsigned seq_first_block(const AttnArgs& p, int b) {
   return p.seq_blocks > 0 ? (unsigned)b * (unsigned)p.seq_blocks : (unsigned)arg_bstart()[b];
 }
-__device__ __forceinline__ int seq_nodes(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_nodes : arg_n_nodes()[b] & 0xff; }
-__device__ __forceinline__ int seq_place(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? b : arg_n_nodes()[b] >> 8; }
-__device__ __forceinline__ int seq_len(const AttnArgs& p, int b) { return p.seq_blocks > 0 ? p.same_len : arg_kv_len()[b]; }
+// what a workgroup needs to know of a sequence of the launch's order
+struct Seq {
+  int n, len, place;   // nodes, prefix keys, place in the batch
+  unsigned first;      // first flat block
+};
+__device__ __forceinline__ Seq seq_at(const AttnArgs& p, int b) {
+  Seq s{p.same_nodes, p.same_len, b, (unsigned)b * (unsigned)p.seq_blocks};
+  if (p.seq_blocks <= 0) {
+    KernargPtr ka = (KernargPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    i32x2 info;
+    int first;
+    asm volatile("s_load_dwordx2 %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=&s"(info), "=&s"(first)
+                 : "s"(ka + offsetof(AttnParams, seq) + (unsigned)b * sizeof(SeqInfo)), "s"(ka + offsetof(AttnParams, bstart) + (unsigned)b * sizeof(int32_t)));
+    s = Seq{info[1] & 0xff, info[0], (info[1] >> 8) & 0xff, (unsigned)first};
+  }
+  return s;
+}
 
 // flat blocks [r0, r1) of workgroup w: [floor(w*T/W), floor((w+1)*T/W)) with T = wg_quot*W + wg_rem
 __device__ __forceinline__ void workgroup_blocks(const AttnArgs& p, unsigned w, unsigned& r0, unsigned& r1) {
@@ -193,12 +253,12 @@ __device__ __forceinline__ Share share_of(const AttnArgs& p, unsigned w) {
   c.tile_rcp = p.tile_rcp; c.first_seq = 0; c.slot0 = 0; c.units = p.B * p.Hkv;
   unsigned flat0 = 0;
   if (p.n_classes > 1) {
-    int k = 0;
-    while (k + 1 < p.n_classes && (int)w >= arg_classes()[k + 1].wg_begin) ++k;
+    const __attribute__((address_space(4))) int32_t* begin = arg_at<int32_t>(offsetof(SharedParams, class_wg));
+    const int k = ((int)w >= begin[1] ? 1 : 0) + ((int)w >= begin[2] ? 1 : 0) + ((int)w >= begin[3] ? 1 : 0);
     const __attribute__((address_space(4))) SeqClass& from = arg_classes()[k];
     c.wg_begin = from.wg_begin; c.groups = from.groups; c.clusters = from.clusters; c.quot = from.quot; c.rem = from.rem;
     c.clusters_rcp = from.clusters_rcp; c.tile_rcp = from.tile_rcp; c.first_seq = from.first_seq; c.slot0 = from.slot0; c.units = from.units;
-    flat0 = (unsigned)arg_bstart()[c.first_seq];
+    flat0 = (unsigned)from.first_block;
   }
   // eight clusters at a time: their workgroups for the first slab group, then those for the second, ...
   const unsigned local = w - (unsigned)c.wg_begin, tile = div_rcp(local, 8u * c.groups, c.tile_rcp);
@@ -526,11 +586,11 @@ __global__ __launch_bounds__(256, (QT == 1 || (QT == 2 && D == 128 && !RAGGED) ?
   int b = seq_of_block(p, r0);
 
   for (unsigned r = r0; r < r1;) {
-    const int n = seq_nodes(p, b);
-    const int L = seq_len(p, b);
+    const Seq seq = seq_at(p, b);
+    const int n = seq.n, L = seq.len;
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
-    const unsigned rel = r - seq_first_block(p, b);
+    const unsigned rel = r - seq.first;
     const int counted = RAGGED ? n_blocks + p.setup : n_blocks;  // what the unit counts for: its set-up first, then its blocks
     const int ub = unit_of_block(p, rel, counted);                // unit within the sequence: (g, y)
     int seg_begin = (int)(rel - (unsigned)ub * (unsigned)counted);
@@ -827,7 +887,7 @@ struct Stage {
 typedef const __attribute__((address_space(1))) void* GlobalPtr;
 typedef __attribute__((address_space(3))) void* LdsPtr;
 
-__global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) {
+__global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const SharedParams) {
   const AttnArgs p = fetch_args();
   typedef Stage S;
   constexpr int D = S::D, KG = 3, QT = 2, KS = D / 32, DT = D / 16, ROWS = 32, kWaves = S::WAVES, kStages = 3;
@@ -872,12 +932,11 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const AttnParams) 
   int at_seq = seq_of_block(p, share.r0, share.first_seq);   // place in the launch's order of sequences
 
   for (unsigned r = share.r0; r < r1;) {
-    const int n = seq_nodes(p, at_seq);
-    const int L = seq_len(p, at_seq);
-    const int b = seq_place(p, at_seq);
+    const Seq seq = seq_at(p, at_seq);
+    const int n = seq.n, L = seq.len, b = seq.place;
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
-    const unsigned rel = r - seq_first_block(p, at_seq);
+    const unsigned rel = r - seq.first;
     const int counted = n_blocks + p.setup;
     const int g = unit_of_block(p, rel, counted);
     const int from = (int)(rel - (unsigned)g * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
@@ -1218,7 +1277,7 @@ __device__ __forceinline__ void weights_of(const f32x16& s, float c, float m, un
         [s14] "v"(s[14]), [s15] "v"(s[15]), [c] "v"(c), [m] "v"(m));
 }
 
-__global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams) {
+__global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParams) {
   const AttnArgs p = fetch_args();
   constexpr int D = 128, KG = 2, WAVES = 4, ROWS = 32, rows_per_unit = WAVES * ROWS;
   __shared__ __attribute__((aligned(1024))) char lds_all[KG * kWideGroup];
@@ -1247,12 +1306,11 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const AttnParams)
   int at_seq = seq_of_block(p, share.r0, share.first_seq);   // place in the launch's order of sequences
 
   for (unsigned r = share.r0; r < r1;) {
-    const int n = seq_nodes(p, at_seq);
-    const int L = seq_len(p, at_seq);
-    const int b = seq_place(p, at_seq);
+    const Seq seq = seq_at(p, at_seq);
+    const int n = seq.n, L = seq.len, b = seq.place;
     const int n_prefix_blocks = (L + kBlockKeys - 1) / kBlockKeys;
     const int n_blocks = n_prefix_blocks + (n + kBlockKeys - 1) / kBlockKeys;
-    const unsigned rel = r - seq_first_block(p, at_seq);
+    const unsigned rel = r - seq.first;
     const int counted = n_blocks + p.setup;
     const int g = unit_of_block(p, rel, counted);
     const int from = (int)(rel - (unsigned)g * (unsigned)counted), count = min(counted - from, (int)(r1 - r));
@@ -1477,21 +1535,25 @@ __device__ __forceinline__ int owner_of(unsigned x, int n, double inv_total) {
 // One thread per 4 output dims; rows of nodes past n_nodes are written as zeros.
 // pieces: workgroups per unit where every unit of the launch is cut into that many and no workgroup holds parts of two (0 where
 // that is not so).
+template <bool SHARED>
+using MergeParams = std::conditional_t<SHARED, SharedParams, AttnParams>;
 template <int D, bool SHARED>
-__global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams, int rows_per_unit, int pieces, double inv_total) {
-  const AttnArgs p = fetch_args();
+__global__ __launch_bounds__(256) void tree_attn_combine_kernel(const MergeParams<SHARED>, int, int, double) {
+  const int at_seq = blockIdx.z, g = blockIdx.y;
+  const MergeArgs m = fetch_merge_args(at_seq, sizeof(MergeParams<SHARED>));
+  const AttnArgs& p = m.p;
+  const int rows_per_unit = m.rows_per_unit, pieces = m.pieces;
   constexpr int TPR = D / 4;  // threads per row
   constexpr int RPW = 256 / TPR;   // rows of this workgroup: in lane order (partial_index) the faster index of its threads
-  const int at_seq = blockIdx.z, g = blockIdx.y;
-  const int n = seq_nodes(p, at_seq), b = seq_place(p, at_seq);
+  const int n = m.nodes & 0xff, b = (m.nodes >> 8) & 0xff;
   const int y = SHARED ? (int)(blockIdx.x * RPW) / 128 : 0;   // (128 rows per slab group)
   if (SHARED && y >= seq_groups(p, seq_slabs(p, n, 32))) return;   // a tree smaller than the largest: no such rows of it
-  int clusters = p.n_wgs, units = p.B * p.Hkv, first_seq = 0, slot0 = 0;
+  int clusters = p.n_wgs, units = p.B * p.Hkv, first_seq = 0, slot0 = 0, first_block = 0;
+  double inv_total = m.inv_total;
   if (SHARED && p.n_classes > 1) {
-    int k = 0;
-    while (k + 1 < p.n_classes && at_seq >= arg_classes()[k + 1].first_seq) ++k;
-    clusters = arg_classes()[k].clusters; units = arg_classes()[k].units; first_seq = arg_classes()[k].first_seq; slot0 = arg_classes()[k].slot0;
-    inv_total = arg_classes()[k].inv_total;
+    const __attribute__((address_space(4))) SeqClass& from = arg_classes()[m.nodes >> 16];
+    clusters = from.clusters; units = from.units; first_seq = from.first_seq; slot0 = from.slot0; first_block = from.first_block;
+    inv_total = from.inv_total;
   }
   const int unit = (at_seq - first_seq) * p.Hkv + g;
   int w0, n_seg;
@@ -1499,8 +1561,8 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const AttnParams
     w0 = unit * pieces;
     n_seg = pieces;
   } else {
-    const int n_blocks = (seq_len(p, at_seq) + kBlockKeys - 1) / kBlockKeys + (n + kBlockKeys - 1) / kBlockKeys;
-    const unsigned fs = seq_first_block(p, at_seq) - seq_first_block(p, first_seq) + (unsigned)g * (unsigned)(n_blocks + p.setup) + (unsigned)p.setup;
+    const int n_blocks = (m.kv_len + kBlockKeys - 1) / kBlockKeys + (n + kBlockKeys - 1) / kBlockKeys;
+    const unsigned fs = (unsigned)(m.first_block - first_block) + (unsigned)g * (unsigned)(n_blocks + p.setup) + (unsigned)p.setup;
     w0 = owner_of(fs, clusters, inv_total);
     n_seg = owner_of(fs + (unsigned)n_blocks - 1u, clusters, inv_total) - w0 + 1;
     if (n_seg == 1) return;  // written directly by the one workgroup that held the whole unit
@@ -1595,7 +1657,7 @@ __global__ __launch_bounds__(64 * WAVES) void tree_attn_f32_kernel(const AttnPar
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x, b = blockIdx.z, node0 = blockIdx.y * QN;
   const int g = h / p.G;
-  const int n = p.n_nodes[b], L = p.kv_len[b];
+  const int n = p.seq[b].nodes, L = p.seq[b].kv_len;
   int total = L + n;
   const int64_t row0 = ((int64_t)b * p.Nmax + node0) * p.Hq + h;   // (b, node0, h); the next node is Hq rows further
   float* const out0 = reinterpret_cast<float*>(p.out) + row0 * D;
@@ -1813,7 +1875,8 @@ constexpr int kWholeSetup = 4096;   // more than the blocks of a launch's units 
 // The flat list of blocks and its division among workgroups: sequences in the order of their classes (see SeqClass), `wgs`
 // workgroups shared among the classes by their blocks. Returns the workgroups of the launch (at most wgs, but one per class and
 // slab group at least); `any_cut`: some unit is cut among several.
-int plan_classes(const fspad_attn_desc& d, const Plan& pl, const int* groups, int64_t wgs, AttnParams& sl, bool& any_cut) {
+int plan_classes(const fspad_attn_desc& d, const Plan& pl, const int* groups, int64_t wgs, SharedParams& sp, bool& any_cut) {
+  AttnParams& sl = sp.a;
   const int nb = sl.B;
   // the kernels of one slab group per kv head: one class. More different numbers of slab groups than a launch has classes
   // (1024 rows per kv head): rounded up, with workgroups that pass over the sequences without rows for them
@@ -1829,29 +1892,34 @@ int plan_classes(const fspad_attn_desc& d, const Plan& pl, const int* groups, in
     }
     if (n_classes <= kMaxClasses) break;
   }
-  struct { int32_t kv_len[kMaxBatchPerLaunch], n_nodes[kMaxBatchPerLaunch]; } in;   // in the batch's order
-  for (int i = 0; i < nb; ++i) { in.kv_len[i] = sl.kv_len[i]; in.n_nodes[i] = sl.n_nodes[i]; }
-  int place[kMaxBatchPerLaunch];
+  SeqInfo in[kMaxBatchPerLaunch];   // in the batch's order
+  int len[kMaxBatchPerLaunch];      // blocks of each
+  for (int i = 0; i < nb; ++i) {
+    in[i] = sl.seq[i];
+    len[i] = blocks_of(in[i].kv_len, in[i].nodes);
+  }
   // whole units (kWholeSetup): the shorter ones first, so that a workgroup's range ends behind its own unit, in the next one's set-up
   int by[kMaxBatchPerLaunch];
   for (int i = 0; i < nb; ++i) {
     int at = i;
     if (sl.setup == kWholeSetup)
-      for (; at > 0 && blocks_of(in.kv_len[by[at - 1]], in.n_nodes[by[at - 1]]) > blocks_of(in.kv_len[i], in.n_nodes[i]); --at) by[at] = by[at - 1];
+      for (; at > 0 && len[by[at - 1]] > len[i]; --at) by[at] = by[at - 1];
     by[at] = i;
   }
-  SeqClass* cls = sl.classes;
+  SeqClass* cls = sp.classes;
   int64_t blocks[kMaxClasses], work = 0, flat = 0, left = wgs;
   for (int k = 0, at = 0; k < n_classes; ++k) {
     cls[k] = SeqClass{};
     cls[k].groups = class_groups[k];
     cls[k].first_seq = at;
     const int64_t flat0 = flat;
+    cls[k].first_block = (int32_t)flat0;
     for (int j = 0; j < nb; ++j) {
       const int i = by[j];
       if (used[i] != class_groups[k]) continue;
-      place[at] = i; sl.kv_len[at] = in.kv_len[i]; sl.n_nodes[at] = in.n_nodes[i]; sl.bstart[at] = (int32_t)flat;
-      flat += (int64_t)d.n_kv_heads * (blocks_of(in.kv_len[i], in.n_nodes[i]) + sl.setup);
+      sl.seq[at] = SeqInfo{in[i].kv_len, in[i].nodes | i << 8 | k << 16};
+      sl.bstart[at] = (int32_t)flat;
+      flat += (int64_t)d.n_kv_heads * (len[i] + sl.setup);
       ++at;
     }
     cls[k].units = (at - cls[k].first_seq) * d.n_kv_heads;
@@ -1889,16 +1957,16 @@ int plan_classes(const fspad_attn_desc& d, const Plan& pl, const int* groups, in
     c.slot0 = (int32_t)slot;
     bool cut = false;
     for (int i = c.first_seq; i < c.first_seq + c.units / d.n_kv_heads && !cut; ++i) {
-      const int64_t nblk = blocks_of(sl.kv_len[i], sl.n_nodes[i]) + sl.setup;
+      const int64_t nblk = len[sl.seq[i].nodes >> 8 & 0xff] + sl.setup;
       for (int g = 0; g < d.n_kv_heads && !cut; ++g) {
-        const int64_t fs = sl.bstart[i] - sl.bstart[c.first_seq] + g * nblk;
+        const int64_t fs = sl.bstart[i] - c.first_block + g * nblk;
         cut = host_owner_of(fs + sl.setup, blocks[k], c.clusters) != host_owner_of(fs + nblk - 1, blocks[k], c.clusters);
       }
     }
     any_cut = any_cut || cut;
     if (cut) slot += (int64_t)c.groups * (c.units + c.clusters);   // (at most units + workgroups altogether)
   }
-  for (int i = 0; i < nb; ++i) sl.n_nodes[i] |= place[i] << 8;
+  for (int k = 0; k < kMaxClasses; ++k) sp.class_wg[k] = k < n_classes ? cls[k].wg_begin : INT32_MAX;
   sl.n_classes = n_classes;
   sl.total_blocks = (int32_t)flat;
   sl.GY = cls[0].groups; sl.n_wgs = cls[0].clusters; sl.wg_quot = cls[0].quot; sl.wg_rem = cls[0].rem;
@@ -1962,11 +2030,12 @@ void launch_bf16(const Plan& pl, const AttnParams& prm, bool streamed, hipStream
 }
 
 template <int D>
-void launch_combine(const Plan& pl, const AttnParams& prm, int pieces, hipStream_t stream) {
+void launch_combine(const Plan& pl, const SharedParams& sp, int pieces, hipStream_t stream) {
+  const AttnParams& prm = sp.a;
   const int rows_per_wg = 1024 / D;
   const dim3 grid((unsigned)((pl.rows_per_unit + rows_per_wg - 1) / rows_per_wg * pl.GY), (unsigned)prm.Hkv, (unsigned)prm.B);
   const double inv_total = 1.0 / (double)prm.total_blocks;
-  if (pl.shared_stage) hipLaunchKernelGGL((tree_attn_combine_kernel<D, true>), grid, dim3(256), 0, stream, prm, pl.rows_per_unit, pieces, inv_total);
+  if (pl.shared_stage) hipLaunchKernelGGL((tree_attn_combine_kernel<D, true>), grid, dim3(256), 0, stream, sp, pl.rows_per_unit, pieces, inv_total);
   else hipLaunchKernelGGL((tree_attn_combine_kernel<D, false>), grid, dim3(256), 0, stream, prm, pl.rows_per_unit, pieces, inv_total);
 }
 
@@ -1985,7 +2054,7 @@ void launch_f32(const AttnParams& prm, hipStream_t stream) {
   constexpr int kTile = kF32Loads * 64 / (D / 4);
   const bool few = (int64_t)prm.B * prm.Hq * prm.Nmax <= 768;
   int longest = 0;
-  for (int b = 0; b < prm.B; ++b) longest = prm.kv_len[b] > longest ? prm.kv_len[b] : longest;
+  for (int b = 0; b < prm.B; ++b) longest = prm.seq[b].kv_len > longest ? prm.seq[b].kv_len : longest;
   const bool single = longest <= (few ? kTile / 2 : 2 * kTile);
   const bool one = few || single;
   const dim3 grid((unsigned)prm.Hq, (unsigned)(one ? prm.Nmax : (prm.Nmax + 1) / 2), (unsigned)prm.B), block(64 * kF32Waves);
@@ -2053,7 +2122,9 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
   // per-sequence lengths travel as kernel arguments), each slice reusing the workspace in stream order
   for (int b0 = 0; b0 < d.batch; b0 += kMaxBatchPerLaunch) {
     const int nb = d.batch - b0 < kMaxBatchPerLaunch ? d.batch - b0 : kMaxBatchPerLaunch;
-    AttnParams sl = prm;
+    SharedParams sp;   // (its classes: plan_classes, for the kernels that take them)
+    AttnParams& sl = sp.a;
+    sl = prm;
     sl.B = nb;
     const size_t q_rows = (size_t)b0 * d.n_nodes_max * d.n_q_heads * d.head_dim;
     const size_t kv_rows = (size_t)b0 * d.n_nodes_max * d.n_kv_heads * d.head_dim;
@@ -2066,13 +2137,13 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
     }
     sl.anc_mask = anc_mask + (size_t)b0 * d.n_nodes_max;
     sl.out = static_cast<char*>(out) + q_rows * (d.out_dtype == FSPAD_BF16 ? 2 : 4);
-    for (int i = 0; i < nb; ++i) { sl.kv_len[i] = kv_len[b0 + i]; sl.n_nodes[i] = n_nodes[b0 + i]; }
+    for (int i = 0; i < nb; ++i) sl.seq[i] = SeqInfo{kv_len[b0 + i], n_nodes[b0 + i]};
     if (d.io_dtype == FSPAD_BF16) {
       bool uniform = true;
       int64_t seq_blocks = 0;
       for (int i = 0; i < nb; ++i) {
-        uniform = uniform && blocks_of(sl.kv_len[i], sl.n_nodes[i]) == blocks_of(sl.kv_len[0], sl.n_nodes[0]);
-        seq_blocks += blocks_of(sl.kv_len[i], sl.n_nodes[i]);
+        uniform = uniform && blocks_of(sl.seq[i].kv_len, sl.seq[i].nodes) == blocks_of(sl.seq[0].kv_len, sl.seq[0].nodes);
+        seq_blocks += blocks_of(sl.seq[i].kv_len, sl.seq[i].nodes);
       }
       Plan pl{};
       plan_rows(d, pl);
@@ -2086,14 +2157,15 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       int64_t total = 0, units = 0;
       int longest = 0;
       for (int i = 0; i < nb; ++i) {
-        groups[i] = groups_of(d, pl, sl.n_nodes[i]);
-        total += (int64_t)d.n_kv_heads * groups[i] * blocks_of(sl.kv_len[i], sl.n_nodes[i]);
+        const int blocks = blocks_of(sl.seq[i].kv_len, sl.seq[i].nodes);
+        groups[i] = groups_of(d, pl, sl.seq[i].nodes);
+        total += (int64_t)d.n_kv_heads * groups[i] * blocks;
         units += (int64_t)d.n_kv_heads * groups[i];
         if (total > kMaxFlatBlocks) return FSPAD_ERR_SHAPE;  // the kernels index blocks with 32 bits
-        if (blocks_of(sl.kv_len[i], sl.n_nodes[i]) > longest) longest = blocks_of(sl.kv_len[i], sl.n_nodes[i]);
+        if (blocks > longest) longest = blocks;
       }
       bool same = true;
-      for (int i = 1; i < nb; ++i) same = same && sl.kv_len[i] == sl.kv_len[0] && sl.n_nodes[i] == sl.n_nodes[0];
+      for (int i = 1; i < nb; ++i) same = same && sl.seq[i].kv_len == sl.seq[0].kv_len && sl.seq[i].nodes == sl.seq[0].nodes;
       // never more workgroups than full trees would have: the workspace a call needs does not depend on the trees
       // (units of equally many blocks stay aligned with the workgroups, however many of them a sequence has: 4 x 64 / 8 heads,
       // 16 to 26 keys, trees of 11 to 26 nodes 10.2 us, planned as a ragged batch 17.4)
@@ -2109,7 +2181,7 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       }
       const int64_t kv_blocks = total;
       bool any_cut = false;
-      const int grid = plan_classes(d, pl, groups, wgs, sl, any_cut);
+      const int grid = plan_classes(d, pl, groups, wgs, sp, any_cut);
       sl.same_len = kv_len[b0];
       sl.same_nodes = n_nodes[b0];
       const int same_blocks = blocks_of(sl.same_len, sl.same_nodes);
@@ -2119,10 +2191,10 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       const size_t need = (size_t)slots_of(pl, full_units, full_wgs, full_total, d.workgroups) * slot_bytes(d, pl);
       if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 15)) return FSPAD_ERR_WORKSPACE;
       if (pl.shared_stage) {
-        if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_gqa128_kernel, dim3((unsigned)grid), dim3(512), 0, stream, sl);
+        if (d.head_dim == 128) hipLaunchKernelGGL(tree_attn_gqa128_kernel, dim3((unsigned)grid), dim3(512), 0, stream, sp);
         // (head dim 64 leaves registers for three wavefronts per SIMD: three key groups; 43.1 -> 40.6 us on a
         // 64/8-head, 16384-key, 60-node call, 70.7 -> 64.5 us at 32768 keys)
-        else hipLaunchKernelGGL(tree_attn_gqa64_kernel, dim3((unsigned)grid), dim3(768), 0, stream, sl);
+        else hipLaunchKernelGGL(tree_attn_gqa64_kernel, dim3((unsigned)grid), dim3(768), 0, stream, sp);
       } else {
         // keys and values of the call, read once each (one slab group per kv head). Not the 48- and 64-row tiles of
         // D = 128 where a compute unit takes more than two workgroups in turn: 16 x 40 heads, 60 nodes, 2500 keys 172 us
@@ -2139,8 +2211,8 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
         // every unit of the launch cut into as many pieces, no workgroup with parts of two (0 where that is not so)
         const int64_t pairs = (int64_t)nb * d.n_kv_heads;
         const int pieces = sl.seq_blocks > 0 && sl.n_wgs % pairs == 0 ? (int)(sl.n_wgs / pairs) : 0;
-        if (d.head_dim == 128) launch_combine<128>(pl, sl, pieces, stream);
-        else launch_combine<64>(pl, sl, pieces, stream);
+        if (d.head_dim == 128) launch_combine<128>(pl, sp, pieces, stream);
+        else launch_combine<64>(pl, sp, pieces, stream);
         if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
       }
     } else {
