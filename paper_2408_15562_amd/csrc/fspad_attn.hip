@@ -2172,10 +2172,12 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       int64_t wgs = plan_wgs(pl, total, units, uniform, d.workgroups);
       if (wgs > full_wgs) wgs = uniform && full_wgs >= units ? full_wgs / units * units : full_wgs;
       sl.setup = uniform || total + units * setup_blocks(pl) > kMaxFlatBlocks ? 0 : setup_blocks(pl);
-      // short units of a ragged batch that fit the chip stay whole, as those of an equal one do (plan_wgs): a workgroup each, and
-      // so much set-up that the even division falls into it (12 x 40 / 8 heads, 3 to 8 blocks, 26 nodes: 18.3 -> 13.5 us)
-      if (!uniform && pl.shared_stage && d.workgroups == 0 && 4 * units >= kComputeUnits && units <= kComputeUnits && units <= full_wgs &&
-          longest <= 5 * key_waves(pl)) {
+      // Short units of a ragged batch that fit the chip stay whole, as those of an equal one do (plan_wgs): a workgroup each, and
+      // so much set-up that the even division falls into it. Whole units leave no partial results, so the workspace does not bound
+      // their number. 12 x 40 / 8 heads, 3 to 8 blocks, 26 nodes: 18.3 -> 13.5 us; few units, which an even split of their blocks
+      // puts several to a workgroup: 6 x 12 / 2 heads, D = 64, 2 or 3 blocks 21.7 -> 8.9, 4 x 16 / 1 heads, D = 64, 2 to 8 blocks
+      // 16.7 -> 10.0, 2 x 12 / 2 heads, 3 to 5 blocks 19.5 -> 11.2.
+      if (!uniform && pl.shared_stage && d.workgroups == 0 && units <= kComputeUnits && longest <= 5 * key_waves(pl)) {
         wgs = units;
         sl.setup = kWholeSetup;
       }

@@ -430,3 +430,26 @@ def test_bf16_shared_stage_classes(H, D, B, N, Hq, Hkv, lens, nodes):
         assert np.all(np.abs(out.double().cpu().numpy() - ref) <= bound), f"workgroups {splits}"
         for b, n in enumerate(case.n_nodes):
             assert torch.all(out[b, int(n):] == 0)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,Hq,Hkv,lens,nodes", [
+    (26, 12, 2, (36, 19, 4, 4, 9, 32), (26,) * 6),                  # few units of 2 or 3 blocks
+    (31, 16, 1, (219, 27, 100, 64), (31, 31, 9, 20)),               # up to 8 blocks, one to four slab groups
+    (44, 12, 2, (91, 11), (44, 44)),
+    (30, 16, 2, (287, 1, 150), (30, 30, 30)),                       # 10 blocks: the most that stay whole
+    (20, 28, 4, tuple(6 + 2 * i for i in range(24)), (20,) * 24),   # more units than an even split of their blocks has workgroups
+])
+def test_bf16_short_ragged_units_stay_whole(H, D, N, Hq, Hkv, lens, nodes):
+    """Units of up to five blocks per key group, of different lengths, that fit the chip are a workgroup's each: nothing is left
+    in the workspace, and every output row is written."""
+    import paper_2408_15562_amd as fspad
+    case = H.AttnCase(960 + N + D, len(lens), N, Hq, Hkv, D, max(lens), "bf16", l_cap=max(lens) + 1, kv_len=list(lens), n_nodes=list(nodes), topk=4)
+    desc = fspad.make_attn_desc(case.q, case.k_tree, case.k_cache)
+    ws = torch.full((fspad.fspad_tree_attn_workspace_bytes(desc, max(lens)),), 0xA5, dtype=torch.uint8, device=H.DEV)
+    out = torch.full(case.q.shape, float("nan"), dtype=torch.bfloat16, device=H.DEV)
+    fspad.fspad_tree_attn(case.q, case.k_tree, case.v_tree, case.k_cache, case.v_cache, case.kv_len, case.n_nodes, case.mask_dev,
+                          out=out, workspace=ws)
+    assert torch.all(ws == 0xA5)
+    ref, _, _ = _check(H, case, H.TOL["bf16"])
+    assert torch.equal(out, ref.to(torch.bfloat16))
