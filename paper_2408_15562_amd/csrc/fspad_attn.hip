@@ -169,18 +169,32 @@ __device__ __forceinline__ AttnArgs args_from(const i32x16& a, const i32x16& b, 
   r.wgs_rcp = (uint32_t)c[11]; r.seq_rcp = (uint32_t)c[12]; r.unit_rcp = (uint32_t)c[13]; r.n_classes = c[14];
   return r;
 }
+// Registers of their own for what is read throughout: left in the sixteen of their load they are spilled, and fetched back, all
+// sixteen at a time (moves from spilled registers in the code of the 48-row tiles at D = 64: 201, now 43; 4 x 52 heads of it,
+// 497 keys, 42 to 48 nodes 11.3 -> 10.9 us). Loads of four or two words instead cost more than they spare: 10 x 8 heads, 70 keys,
+// 64 nodes 12.6 us, in loads of four 13.2, of two 13.9.
+__device__ __forceinline__ AttnArgs args_apart(const i32x16& a, const i32x16& b, const i32x16& c) {
+  AttnArgs r = args_from(a, b, c);
+  asm volatile("" : "+s"(r.seq_blocks), "+s"(r.same_len), "+s"(r.same_nodes), "+s"(r.setup), "+s"(r.unit_rcp), "+s"(r.g_magic), "+s"(r.out_bf16),
+                    "+s"(r.n_classes), "+s"(r.wgs_rcp), "+s"(r.seq_rcp), "+s"(r.scale));
+  return r;
+}
 __device__ __forceinline__ AttnArgs fetch_args() {
   KernargPtr ka = (KernargPtr)__builtin_amdgcn_kernarg_segment_ptr();   // AttnParams is the first argument
   i32x16 a, b, c;
   asm volatile("s_load_dwordx16 %0, %3, 0x0\n\ts_load_dwordx16 %1, %3, 0x40\n\ts_load_dwordx16 %2, %3, 0x80\n\ts_waitcnt lgkmcnt(0)"
                : "=&s"(a), "=&s"(b), "=&s"(c) : "s"(ka));
-  AttnArgs r = args_from(a, b, c);
-  // Registers of their own for what is read throughout: left in the sixteen of their load they are spilled, and fetched back, all
-  // sixteen at a time (moves from spilled registers in the code of the 48-row tiles at D = 64: 201, now 43; 4 x 52 heads of it,
-  // 497 keys, 42 to 48 nodes 11.3 -> 10.9 us). Loads of four or two words
-  // instead cost more than they spare: 10 x 8 heads, 70 keys, 64 nodes 12.6 us, in loads of four 13.2, of two 13.9.
-  asm volatile("" : "+s"(r.seq_blocks), "+s"(r.same_len), "+s"(r.same_nodes), "+s"(r.setup), "+s"(r.unit_rcp), "+s"(r.g_magic), "+s"(r.out_bf16), "+s"(r.n_classes), "+s"(r.wgs_rcp), "+s"(r.seq_rcp), "+s"(r.scale));
-  return r;
+  return args_apart(a, b, c);
+}
+// The same with the first workgroups of the classes, for the shared-stage kernels (a trip of their own: two classes, 2 x 12 / 2
+// heads, D = 64, 3 and 26 keys 8.6 -> 8.4 us; with one class the load beside the others costs nothing measurable).
+__device__ __forceinline__ AttnArgs fetch_args(i32x4& class_wg) {
+  KernargPtr ka = (KernargPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  i32x16 a, b, c;
+  asm volatile("s_load_dwordx16 %0, %4, 0x0\n\ts_load_dwordx16 %1, %4, 0x40\n\ts_load_dwordx16 %2, %4, 0x80\n\ts_load_dwordx4 %3, %4, %5\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(class_wg) : "s"(ka), "n"(offsetof(SharedParams, class_wg)));
+  return args_apart(a, b, c);
 }
 // The same with what the merge needs of a sequence and the merge kernel's own arguments, which lie `tail` bytes into the segment.
 struct MergeArgs {
@@ -247,14 +261,13 @@ struct Share {
   unsigned r0, r1;
   int y, first_seq, slot;
 };
-__device__ __forceinline__ Share share_of(const AttnArgs& p, unsigned w) {
+__device__ __forceinline__ Share share_of(const AttnArgs& p, const i32x4& class_wg, unsigned w) {
   SeqClass c;
   c.wg_begin = 0; c.groups = p.GY; c.clusters = p.n_wgs; c.quot = p.wg_quot; c.rem = p.wg_rem; c.clusters_rcp = p.wgs_rcp;
   c.tile_rcp = p.tile_rcp; c.first_seq = 0; c.slot0 = 0; c.units = p.B * p.Hkv;
   unsigned flat0 = 0;
   if (p.n_classes > 1) {
-    const __attribute__((address_space(4))) int32_t* begin = arg_at<int32_t>(offsetof(SharedParams, class_wg));
-    const int k = ((int)w >= begin[1] ? 1 : 0) + ((int)w >= begin[2] ? 1 : 0) + ((int)w >= begin[3] ? 1 : 0);
+    const int k = ((int)w >= class_wg[1] ? 1 : 0) + ((int)w >= class_wg[2] ? 1 : 0) + ((int)w >= class_wg[3] ? 1 : 0);
     const __attribute__((address_space(4))) SeqClass& from = arg_classes()[k];
     c.wg_begin = from.wg_begin; c.groups = from.groups; c.clusters = from.clusters; c.quot = from.quot; c.rem = from.rem;
     c.clusters_rcp = from.clusters_rcp; c.tile_rcp = from.tile_rcp; c.first_seq = from.first_seq; c.slot0 = from.slot0; c.units = from.units;
@@ -888,7 +901,8 @@ typedef const __attribute__((address_space(1))) void* GlobalPtr;
 typedef __attribute__((address_space(3))) void* LdsPtr;
 
 __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const SharedParams) {
-  const AttnArgs p = fetch_args();
+  i32x4 class_wg;
+  const AttnArgs p = fetch_args(class_wg);
   typedef Stage S;
   constexpr int D = S::D, KG = 3, QT = 2, KS = D / 32, DT = D / 16, ROWS = 32, kWaves = S::WAVES, kStages = 3;
   constexpr int kGroupBytes = kStages * S::kBytes;
@@ -926,7 +940,7 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const SharedParams
 #pragma unroll
   for (int j = 0; j < 8; ++j) vrow[j] = S::kTensorBytes + (unsigned)key_of(g4, j) * (D * 2) + (unsigned)(D / 8) * col;
 
-  const Share share = share_of(p, blockIdx.x);
+  const Share share = share_of(p, class_wg, blockIdx.x);
   const unsigned r1 = share.r1;
   const int y = share.y;
   int at_seq = seq_of_block(p, share.r0, share.first_seq);   // place in the launch's order of sequences
@@ -1278,7 +1292,8 @@ __device__ __forceinline__ void weights_of(const f32x16& s, float c, float m, un
 }
 
 __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParams) {
-  const AttnArgs p = fetch_args();
+  i32x4 class_wg;
+  const AttnArgs p = fetch_args(class_wg);
   constexpr int D = 128, KG = 2, WAVES = 4, ROWS = 32, rows_per_unit = WAVES * ROWS;
   __shared__ __attribute__((aligned(1024))) char lds_all[KG * kWideGroup];
 
@@ -1300,7 +1315,7 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
   const unsigned k_at = lds0 + 256u * row + 16u * (h ^ (row & 15));
   const unsigned v_at = lds0 + kWideRing * kWideTensor + 256u * (4 * h + ((lane >> 2) & 3)) + 64u * ((lane >> 2) & 3) + 32u * ((lane >> 4) & 1) + 8u * (lane & 3);
 
-  const Share share = share_of(p, blockIdx.x);
+  const Share share = share_of(p, class_wg, blockIdx.x);
   const unsigned r1 = share.r1;
   const int y = share.y;
   int at_seq = seq_of_block(p, share.r0, share.first_seq);   // place in the launch's order of sequences
