@@ -10,7 +10,7 @@
 // exp((l-max)/T)) for sampling. The second, one workgroup per sequence, merges the
 // chunk statistics of every row at once, walks the tree with wavefront ballots
 // out of LDS and, for sampling, draws the last token by an inverse-CDF search that
-// descends chunk -> thread segment -> element. (Large sampling calls: four kernels, see kInnerFirst.)
+// descends chunk -> thread segment -> element. (Large sampling calls: see kInnerFirst.)
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <atomic>
@@ -65,13 +65,13 @@ constexpr int32_t kAllRows = 0;
 // tests no child there: it draws from weights that it forms itself, and the draft's row is not looked at)
 constexpr int32_t kSpareLeaves = 1;
 constexpr int32_t kInnerRows = 2;   // nodes that have children
-constexpr int32_t kStopRows = 3;    // one node a sequence: where the walk stopped (part_idx[b]), if it is a leaf
 
-// Has a node a child among the n nodes of its tree, as the walk would test it? (n <= 64; one lane each, the same answer in
-// every lane)
-__device__ __forceinline__ bool has_child(const int32_t* parent, int n, int node) {
+// Has a node a child among the n nodes of its tree (n <= Nmax), as the walk would test it? my_parent: of the node that is this
+// lane's number. (the same answer in every lane)
+__device__ __forceinline__ int lane_parent(const int32_t* parent, int Nmax) { return parent[min((int)(threadIdx.x & 63), Nmax - 1)]; }
+__device__ __forceinline__ bool has_child(int my_parent, int n, int node) {
   const int lane = threadIdx.x & 63;
-  return __any(lane > 0 && lane < n && parent[lane] == node);
+  return __ballot(my_parent == node && lane > 0 && lane < n) != 0ull;
 }
 
 // Inclusive running sum over the 64 lanes of a wavefront, lane order, with data-parallel-primitive moves
@@ -112,25 +112,19 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
   __shared__ int sh_idx[4];
   __shared__ double sh_sum[4];
   __shared__ double exp2_table[32];
-  int row = blockIdx.y;
-  const int chunk = blockIdx.x;
-  int b, node;
-  if (MODE == 1 && p.rows == kStopRows) {
-    b = row;
-    node = p.part_idx[b];
-    row = b * p.Nmax + node;
-  } else {
-    b = row / p.Nmax;
-    node = row - b * p.Nmax;
-  }
+  const int row = blockIdx.y, chunk = blockIdx.x;
+  const int b = row / p.Nmax, node = row - b * p.Nmax;
+  // (asked for together with the tree's size: behind it the first logits were a trip later)
+  const int my_parent = MODE == 1 ? lane_parent(p.parent + (int64_t)b * p.Nmax, p.Nmax) : -1;
   if (row == 0 && chunk == 0)
     for (int i = threadIdx.x; i < p.clear_count; i += kThreads) p.clear_words[i] = 0u;
-  if (node >= p.n_nodes[b]) return;  // rows of unused tree slots are never read
+  const int n = p.n_nodes[b];
+  if (node >= n) return;  // rows of unused tree slots are never read
   const bool second = blockIdx.z != 0;
   bool max_only = false;
   if (MODE == 1 && p.rows != kAllRows) {
-    const bool leaf = !has_child(p.parent + (int64_t)b * p.Nmax, min(p.n_nodes[b], p.Nmax), node);
-    if (leaf ? second || p.rows == kInnerRows : p.rows == kStopRows) return;
+    const bool leaf = !has_child(my_parent, min(n, p.Nmax), node);
+    if (leaf && (second || p.rows == kInnerRows)) return;
     max_only = leaf && p.rows == kSpareLeaves;
   }
   const float* rp = (second ? p.logits2 : p.logits) + (int64_t)row * p.row_stride;
@@ -380,6 +374,57 @@ __device__ __forceinline__ void draw_in_chunk(const DrawArgs& a) {
   }
 }
 
+// A chunk's statistics by the walk's workgroup, as the first pass forms them but for the order of the sum. wave_max, wave_sum: LDS,
+// one slot a wavefront.
+template <bool VEC>
+__device__ __forceinline__ void form_chunk(const float* rp, int base, int V, double inv_temperature, const double* exp2_table,
+                                           float* wave_max, double* wave_sum, float* out_max, double* out_sum) {
+  constexpr int E = kMaxChunk / kWalkThreads;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float x[E];
+#pragma unroll
+  for (int k = 0; k < E / 4; ++k) {
+    const int e0 = base + (k * kWalkThreads + tid) * 4;
+    if (VEC && e0 + 3 < V) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(rp + e0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[4 * k + j] = v[j];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[4 * k + j] = rp[min(e0 + j, V - 1)];
+    }
+  }
+  float mt = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    x[k] = base + ((k >> 2) * kWalkThreads + tid) * 4 + (k & 3) < V ? clean(x[k]) : -INFINITY;
+    mt = fmaxf(mt, x[k]);
+  }
+  float mc = mt;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mc = fmaxf(mc, __shfl_xor(mc, off));
+  if (lane == 0) wave_max[wave] = mc;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWalkWaves; ++w) mc = fmaxf(mc, wave_max[w]);
+  double sum = 0.0;
+  if (mc > -INFINITY) {
+#pragma unroll
+    for (int k = 0; k < E; ++k) sum += exp_nonpos_table(((double)x[k] - (double)mc) * inv_temperature, exp2_table);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane == 0) wave_sum[wave] = sum;
+  __syncthreads();
+  if (tid == 0) {
+    double total = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWalkWaves; ++w) total += wave_sum[w];
+    *out_max = mc;
+    *out_sum = total;
+  }
+}
+
 // Sampling. Everything the walk can need is fetched up front, in parallel, so that the walk itself
 // touches no memory: (1) the chunk statistics of every row are merged into the row's max M and
 // normaliser Z (four threads per row); (2) every node fetches the weight of its own draft token
@@ -387,8 +432,10 @@ __device__ __forceinline__ void draw_in_chunk(const DrawArgs& a) {
 // already proposed weighs nothing, because it has left the residual by the time it is tested);
 // (3) wavefront 0 walks the tree out of LDS, testing the children of the current node in index
 // order against the running residual; (4) the workgroup draws the last token.
-// Without DRAW it leaves the node where the walk stops in part_idx[b], nothing else: no leaf's statistics are looked at.
-template <bool DRAW>
+// LARGE (kInnerFirst): leaves have no statistics, and the walk looks at none of theirs. If it ends at one, that row's are formed
+// now: every one of the sequence's gridDim.x workgroups walks the tree, to the same end, and takes its share of the chunks; the
+// last to finish (an arrival counter, part_idx[b]) draws. Where the walk ends at an inner node the first one goes on alone.
+template <bool LARGE, bool VEC>
 __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const AcceptParams p) {
   __shared__ int rej_tok[FSPAD_MAX_NODES];
   __shared__ double rej_w[FSPAD_MAX_NODES];
@@ -399,7 +446,7 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
   __shared__ double row_M[FSPAD_MAX_NODES], row_Z[FSPAD_MAX_NODES], node_w[FSPAD_MAX_NODES];
   __shared__ int node_par[FSPAD_MAX_NODES], node_tok[FSPAD_MAX_NODES];
   __shared__ float node_u[2][FSPAD_MAX_NODES];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = LARGE ? blockIdx.y : blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t o = (int64_t)b * p.Nmax;
   const float* u_acc = p.uniforms + (int64_t)b * 2 * p.Nmax;
 
@@ -407,8 +454,7 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
   // two chunks in flight at a time, keeping a running (max, sum); the sixteen parts of a row are then
   // merged with lane exchanges. Nothing here waits for the tree size: rows past it hold unused numbers.
   const int n_raw = p.n_nodes[b];
-  {
-    const int row = tid >> 4, q = tid & 15;
+  auto merge_row = [&](int row, int q) {   // sixteen threads, q = 0 .. 15
     const bool in_range = row < p.Nmax;
     const float* pm = p.part_max + (o + (in_range ? row : 0)) * p.n_chunks;
     const double* ps = p.part_sum + (o + (in_range ? row : 0)) * p.n_chunks;
@@ -441,13 +487,14 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) z += __shfl_xor(z, off);
     if (in_range && q == 0) { row_M[row] = (double)mx; row_Z[row] = z; }
-    if (tid < FSPAD_MAX_NODES) {
-      const bool ok = tid < p.Nmax;
-      node_par[tid] = ok ? p.parent[o + tid] : -2;
-      node_tok[tid] = ok ? p.draft_tokens[o + tid] : -1;
-      node_u[0][tid] = ok ? u_acc[tid] : 0.f;
-      node_u[1][tid] = ok ? u_acc[p.Nmax + tid] : 0.f;
-    }
+  };
+  merge_row(tid >> 4, tid & 15);
+  if (tid < FSPAD_MAX_NODES) {
+    const bool ok = tid < p.Nmax;
+    node_par[tid] = ok ? p.parent[o + tid] : -2;
+    node_tok[tid] = ok ? p.draft_tokens[o + tid] : -1;
+    node_u[0][tid] = ok ? u_acc[tid] : 0.f;
+    node_u[1][tid] = ok ? u_acc[p.Nmax + tid] : 0.f;
   }
   const int n = n_raw;
   __syncthreads();
@@ -466,15 +513,15 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
   }
   __syncthreads();
 
-  if (wave == 0) {
+  int my_path = lane == 0 ? 0 : -1, my_out = -1;
+  int cur = 0, len = 1, nrej = 0;
+  int my_rej = -1;       // lane k keeps the k-th token rejected at the current node, and its weight
+  double my_rej_w = 0.0;
+  double M = 0.0, Z = 0.0;
+  auto walk = [&] {      // (3), wavefront 0
     const int my_par = node_par[lane], my_tok = node_tok[lane];
     const double my_w = node_w[lane];
     const float my_u = node_u[0][lane];
-    int my_path = lane == 0 ? 0 : -1, my_out = -1;
-    int cur = 0, len = 1, nrej = 0;
-    int my_rej = -1;       // lane k keeps the k-th token rejected at the current node, and its weight
-    double my_rej_w = 0.0;
-    double M = 0.0, Z = 0.0;
     auto lane_value = [](double v, int src) {   // src is the same in every lane: scalar reads, no LDS exchange
       const unsigned long long bits = __builtin_bit_cast(unsigned long long, v);
       const unsigned lo = __builtin_amdgcn_readlane((unsigned)bits, src);
@@ -509,10 +556,12 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
       cur = accepted;
       ++len;
     }
-    if constexpr (!DRAW) {
-      if (lane == 0) p.part_idx[b] = cur;
-      return;
+    if constexpr (LARGE) {
+      const bool leaf = __ballot(lane > 0 && lane < n && my_par == cur) == 0ull;
+      if (lane == 0) { sh_i[5] = cur; sh_i[6] = leaf; }
     }
+  };
+  auto settle = [&] {    // the results but for the last token, and the chunk that holds it; wavefront 0
     if (lane < nrej) { rej_tok[lane] = my_rej; rej_w[lane] = my_rej_w; }
     __builtin_amdgcn_wave_barrier();
     if (lane < p.Nmax) { p.path[o + lane] = my_path; if (lane != len - 1) p.tokens[o + lane] = my_out; }
@@ -555,28 +604,62 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
       sh_i[4] = found >= 0;
       sh_d[2] = found >= 0 ? t - before : INFINITY;
     }
+  };
+  if constexpr (LARGE) {
+    if (wave == 0) walk();
+    __syncthreads();
+    if (sh_i[6]) {
+      __shared__ double exp2_table[32];
+      __shared__ float wave_max[kWalkWaves];
+      if (tid < 32) exp2_table[tid] = fspad_detail::kExp2Table[tid];
+      __syncthreads();
+      const int leaf = sh_i[5];
+      const int64_t row = o + leaf;
+      for (int c = blockIdx.x; c < p.n_chunks; c += gridDim.x)
+        form_chunk<VEC>(p.logits + row * p.row_stride, c * kMaxChunk, p.V, p.inv_temperature, exp2_table, wave_max, scan_part,
+                        p.part_max + row * p.n_chunks + c, p.part_sum + row * p.n_chunks + c);
+      // (one thread wrote them all, and one wavefront reads them: a fence in each of the sixteen took 20 us)
+      if (tid == 0) {
+        __threadfence();
+        sh_i[7] = gridDim.x > 1 ? atomicAdd(p.part_idx + b, 1) : 0;
+      }
+      __syncthreads();
+      if (sh_i[7] != (int)gridDim.x - 1) return;
+      if (wave == 0) {
+        __threadfence();
+        merge_row(tid < 16 ? leaf : FSPAD_MAX_NODES, tid & 15);
+        __builtin_amdgcn_wave_barrier();
+        M = row_M[leaf];
+        Z = row_Z[leaf];
+      }
+    } else if (blockIdx.x > 0) {
+      return;
+    }
+    if (wave == 0) settle();
+  } else if (wave == 0) {
+    walk();
+    settle();
   }
-  if constexpr (!DRAW) return;
   __syncthreads();
 
   // bonus, stage 2: inside the chunk, thread k owns chunk/1024 consecutive entries
-  const int cur = sh_i[0], len = sh_i[1], nrej = sh_i[2], chunk = sh_i[3];
+  const int stop = sh_i[0], last = sh_i[1] - 1, chunk = sh_i[3];
   if (chunk < 0) {  // no mass anywhere (cannot happen with finite logits): token 0
-    if (tid == 0) p.tokens[o + len - 1] = 0;
+    if (tid == 0) p.tokens[o + last] = 0;
     return;
   }
   DrawArgs a;
-  a.rp = p.logits + (o + cur) * p.row_stride;
+  a.rp = p.logits + (o + stop) * p.row_stride;
   a.first = chunk * p.chunk;
   a.V = p.V;
   a.M = sh_d[0];
   a.target = sh_d[2];
   a.inv_temperature = p.inv_temperature;
   a.rej_tok = rej_tok;
-  a.nrej = nrej;
+  a.nrej = sh_i[2];
   a.scan_part = scan_part;
   a.sh_wave = sh_wave;
-  a.out = p.tokens + o + len - 1;
+  a.out = p.tokens + o + last;
   a.vec = (((uintptr_t)p.logits) & 15) == 0 && (p.row_stride % 4) == 0;
   switch (p.chunk / kWalkThreads) {
     case 1: draw_in_chunk<1>(a); break;
@@ -630,7 +713,7 @@ bool rows_vectorisable(const float* logits, int64_t row_stride) {
 
 template <int MODE>
 void launch_rows(const AcceptParams& p, bool vec, hipStream_t stream) {
-  const dim3 grid((unsigned)p.n_chunks, (unsigned)(p.rows == kStopRows ? p.B : p.B * p.Nmax), p.logits2 ? 2u : 1u);
+  const dim3 grid((unsigned)p.n_chunks, (unsigned)(p.B * p.Nmax), p.logits2 ? 2u : 1u);
 #define FSPAD_ROWS(PT)                                                                                         \
   do {                                                                                                           \
     if (vec) hipLaunchKernelGGL((accept_rows_kernel<MODE, true, PT>), grid, dim3(kThreads), 0, stream, p);      \
@@ -1034,7 +1117,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_row_merge_kernel(const Dr
   const int row = blockIdx.x, arr = blockIdx.y, tid = threadIdx.x;
   const int b = row / p.Nmax, node = row - b * p.Nmax;
   if (node >= p.n_nodes[b]) return;   // rows of unused tree slots have no chunk statistics
-  if (arr && !has_child(p.parent + (int64_t)b * p.Nmax, min(p.n_nodes[b], p.Nmax), node)) return;   // (nor leaves of the draft's)
+  if (arr && !has_child(lane_parent(p.parent + (int64_t)b * p.Nmax, p.Nmax), min(p.n_nodes[b], p.Nmax), node)) return;   // (nor leaves of the draft's)
   const float* pm = (arr ? p.part_max_q : p.part_max_p) + (int64_t)row * p.n_chunks;
   const double* ps = (arr ? p.part_sum_q : p.part_sum_p) + (int64_t)row * p.n_chunks;
   float m = -INFINITY;
@@ -1396,13 +1479,17 @@ extern "C" fspad_status fspad_tree_accept_greedy_static(int32_t B, int32_t Nmax,
 }
 
 // Sampling, large calls: the rows of leaves are looked at only where the walk ends, for the last draw, and leaves are more than
-// half of a tree. From so many logits on, the first pass leaves them out, the walk runs without its draw, and a second pass adds
-// the one leaf a sequence that it stopped at. The two more launches cost about 7 us. Trees with half of their nodes leaves,
-// V = 128256, us a call: 16 x 60 nodes 133 -> 92, 16 x 20..60 nodes 94 -> 74, 6 x 60 63 -> 57, 4 x 60 49 -> 47, 3 x 60 42 -> 43,
-// 1 x 60 22 -> 26; 64 x 60 nodes, V = 32000: 132 -> 95. Drafts without branches have one leaf and lose the 7 us (64 x 6 nodes
-// 66 -> 76), whence the least number of nodes: below it most drafts are such, and trees gain little (16 x 16 50.5 -> 50.5).
+// half of a tree. From so many logits on, the first pass leaves them out, and the walk kernel forms the one that it ends at, by
+// several workgroups a sequence (accept_sample_walk_kernel). us a call, all rows formed first / with the leaf formed between two
+// more launches / now: V = 128256, 16 x 60 nodes 131 / 70 / 62, 16 x 20..60 96 / 59 / 50, 6 x 60 56 / 40 / 34, 16 x 16 nodes in
+// 60-node buffers 45 / 38 / 31; 64 x 60 nodes, V = 32000, 134 / 75 / 65. Drafts without branches have one leaf: 16 x 32 nodes
+// 69.4 / 76.2 / 69.2, 64 x 24, V = 32000, 57.4 / 62.3 / 57.4. The line counts the buffers' places, not the trees' nodes, which the
+// host does not see: of a few nodes each, what is spared is little and the leaf's row stands behind the walk (16 x 5..10
+// nodes 32.0 / 35.8 / 29.5, 6 x 5..10 21.7 / 29.2 / 23.3, 64 x 3..8, V = 32000, 30.2 / 37.0 / 31.4). Below the line the two forms
+// are level (4 x 60: 44.1 / 43.7 with the launches); the least number of nodes keeps short drafts, mostly without branches, out.
 constexpr int64_t kInnerFirst = (int64_t)40 << 20;
 constexpr int32_t kInnerFirstNodes = 24;
+constexpr int kWalkWorkgroups = 256;   // of the walk at most: one a compute unit
 
 extern "C" fspad_status fspad_tree_accept_sample(int32_t B, int32_t Nmax, int32_t V, const float* logits,
                                                  int64_t row_stride, const int32_t* draft_tokens,
@@ -1421,17 +1508,22 @@ extern "C" fspad_status fspad_tree_accept_sample(int32_t B, int32_t Nmax, int32_
   p.inv_temperature = 1.0 / (double)temperature;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
   const bool vec = rows_vectorisable(logits, row_stride);
-  if (Nmax >= kInnerFirstNodes && (int64_t)B * Nmax * V >= kInnerFirst) {
+  const bool large = Nmax >= kInnerFirstNodes && (int64_t)B * Nmax * V >= kInnerFirst && p.chunk == kMaxChunk;
+  if (large) {
     p.rows = kInnerRows;
-    launch_rows<1>(p, vec, stream);
-    if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-    hipLaunchKernelGGL((accept_sample_walk_kernel<false>), dim3((unsigned)B), dim3(kWalkThreads), 0, stream, p);
-    if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-    p.rows = kStopRows;
+    p.clear_words = reinterpret_cast<uint32_t*>(p.part_idx);   // the walk's arrival counters
+    p.clear_count = B;
   }
   launch_rows<1>(p, vec, stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-  hipLaunchKernelGGL((accept_sample_walk_kernel<true>), dim3((unsigned)B), dim3(kWalkThreads), 0, stream, p);
+  if (large) {
+    const int shares = B < kWalkWorkgroups ? kWalkWorkgroups / B : 1;
+    const dim3 grid((unsigned)(p.n_chunks < shares ? p.n_chunks : shares), (unsigned)B);
+    if (vec) hipLaunchKernelGGL((accept_sample_walk_kernel<true, true>), grid, dim3(kWalkThreads), 0, stream, p);
+    else hipLaunchKernelGGL((accept_sample_walk_kernel<true, false>), grid, dim3(kWalkThreads), 0, stream, p);
+  } else {
+    hipLaunchKernelGGL((accept_sample_walk_kernel<false, false>), dim3((unsigned)B), dim3(kWalkThreads), 0, stream, p);
+  }
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   return FSPAD_OK;
 }

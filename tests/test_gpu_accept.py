@@ -59,20 +59,36 @@ def test_ragged_n_nodes_and_padded_rows(H):
     H.assert_accept_equal(gpu, cpu, cpu[4] >= H.MARGIN)
 
 
+@pytest.mark.parametrize("to_leaf", [False, True])
 @pytest.mark.parametrize("B,N,V,row_pad,n_nodes,chain",
                          [(5, 64, 131072, 0, None, False),                       # 40 * 2^20 logits: the first size that leaves leaves out
                           (5, 64, 131071, 1, None, False),                       # the last that does not
                           (13, 33, 100003, 2, [33, 1, 2, 17] * 3 + [5], False),  # ragged, a tree that is its root alone, rows not aligned
-                          (8, 24, 220000, 0, None, True)])                       # the fewest nodes; one leaf each
-def test_large_sampling_calls(H, B, N, V, row_pad, n_nodes, chain):
+                          (8, 24, 220000, 0, None, True),                        # the fewest nodes; one leaf each
+                          (100, 24, 20000, 0, [24, 3, 9, 1] * 25, False),        # two workgroups a sequence, one with two chunks of a leaf's row
+                          (300, 24, 6000, 0, None, False),                       # one workgroup a sequence, one chunk a row
+                          (1, 64, 700001, 0, None, False)])                      # many chunks, the last of one entry
+def test_large_sampling_calls(H, B, N, V, row_pad, n_nodes, chain, to_leaf):
+    """Walks that end at inner nodes and (uniforms of zero accept every first child) at leaves, whose statistics are formed behind
+    the walk. Workspace and outputs hold what no call leaves there, so that a value that nobody formed shows."""
+    import paper_2408_15562_amd as fspad
     parent = np.broadcast_to(np.arange(-1, N - 1, dtype=np.int32), (B, N)) if chain else None
-    case = H.AcceptCase(2700 + B, B, N, V, "sample", peak=1.5, row_pad=row_pad, n_nodes=n_nodes, parent=parent)
-    first = case.gpu_sample(1.0)
+    uniforms = H.gen_uniforms(2700 + B, B, N)
+    if to_leaf:
+        uniforms[:, 0] = 0
+    case = H.AcceptCase(2700 + B, B, N, V, "sample", peak=1.5, row_pad=row_pad, n_nodes=n_nodes, parent=parent, uniforms=uniforms)
     cpu = case.cpu_sample(1.0)
     keep = cpu[4] >= H.MARGIN
     assert keep.sum() >= B - 1
-    H.assert_accept_equal(first, cpu, keep)
-    H.assert_accept_equal(case.gpu_sample(1.0), first)
+    ws = torch.empty(fspad.fspad_tree_accept_workspace_bytes(B, N, V), dtype=torch.uint8, device=H.DEV)
+    outputs = [torch.empty(shape, dtype=torch.int32, device=H.DEV) for shape in ((B, N), (B,), (B, N), (B,))]
+    for _ in range(2):
+        ws.fill_(0xFF)
+        for t in outputs:
+            t.fill_(-77)
+        fspad.fspad_tree_accept_sample(case.logits_dev, case.tokens_dev, case.parent_dev, case.n_nodes_dev, 1.0, case.uniforms_dev,
+                                       outputs=outputs, workspace=ws)
+        H.assert_accept_equal([t.cpu().numpy() for t in outputs], cpu, keep)
 
 
 def test_argmax_ties_nan_and_signed_zero(H):
