@@ -48,9 +48,14 @@ class AttnCase:
         self.mask_dev = torch.from_numpy(self.mask.view(np.int64)).to(DEV)
 
     def run_gpu(self, out_dtype=torch.float32, scale=0.0, splits=0):
-        out = fspad.fspad_tree_attn(self.q, self.k_tree, self.v_tree, self.k_cache, self.v_cache, self.kv_len,
-                                    self.n_nodes, self.mask_dev, softmax_scale=scale, out_dtype=out_dtype,
-                                    workgroups=splits)
+        # output and workspace hold NaN: an allocation may still hold the results of a call before, and an output or a
+        # partial result that nobody wrote must not pass for one
+        out = torch.full(self.q.shape, float("nan"), dtype=out_dtype, device=DEV)
+        desc = fspad.make_attn_desc(self.q, self.k_tree, self.k_cache, out_dtype, scale, splits)
+        need = fspad.fspad_tree_attn_workspace_bytes(desc, int(self.kv_len.max()))
+        workspace = torch.full((max(need, 16),), 0xFF, dtype=torch.uint8, device=DEV)
+        fspad.fspad_tree_attn(self.q, self.k_tree, self.v_tree, self.k_cache, self.v_cache, self.kv_len, self.n_nodes, self.mask_dev,
+                              out=out, workspace=workspace, desc=desc)
         torch.cuda.synchronize()
         return out
 

@@ -395,11 +395,12 @@ def test_bf16_ragged_batches_count_set_up(H, Hq, Hkv, N, D, kv_len, splits):
 
 @pytest.mark.parametrize("L,splits", [(0, 1), (5, 3), (64, 1), (95, 2), (160, 1), (256, 1), (289, 5), (1000, 1), (1000, 9), (1031, 40)])
 @pytest.mark.parametrize("N,Hq,Hkv,scale", [(33, 4, 1, 0.0), (60, 8, 2, 1.0), (17, 8, 1, 0.3)])
-def test_bf16_shared_stage_rings_and_segments(H, N, Hq, Hkv, scale, L, splits):
+@pytest.mark.parametrize("D", [64, 128])
+def test_bf16_shared_stage_rings_and_segments(H, D, N, Hq, Hkv, scale, L, splits):
     """Segments of one to sixty blocks, odd and even, one or several to a workgroup: each length wraps the rings of K/V blocks
-    elsewhere and ends the two key groups differently. Scale 1.0 spreads the scores over tens of powers of two, so that the
+    (head dim 64: the stages) elsewhere and ends the two (three) key groups differently. Scale 1.0 spreads the scores over tens of powers of two, so that the
     shifts of the softmax keep moving along the stream. A tree smaller than the batch's largest leaves slabs without rows."""
-    case = H.AttnCase(77 * N + L + splits, 2, N, Hq, Hkv, 128, L, "bf16", l_cap=L + 3, n_nodes=[N, (N + 1) // 2])
+    case = H.AttnCase(77 * N + L + splits, 2, N, Hq, Hkv, D, L, "bf16", l_cap=L + 3, n_nodes=[N, (N + 1) // 2])
     out, _, _ = _check(H, case, H.TOL["bf16"], splits=splits, **({"scale": scale} if scale else {}))
     assert torch.equal(out, case.run_gpu(splits=splits, **({"scale": scale} if scale else {})))
 
@@ -414,8 +415,8 @@ def test_bf16_shared_stage_rings_and_segments(H, N, Hq, Hkv, scale, L, splits):
 ])
 def test_bf16_shared_stage_classes(H, D, B, N, Hq, Hkv, lens, nodes):
     """Ragged batches of grouped heads: sequences whose trees fill different numbers of slab groups are planned in classes, short
-    units stay whole; every output row is written exactly once either way, rows of unused nodes as zeros, at any
-    number of workgroups."""
+    units stay whole; every output row is written either way, rows of unused nodes as zeros, at any number of workgroups
+    (outputs and workspace are NaN before each call)."""
     case = H.AttnCase(900 + B + N + D, B, N, Hq, Hkv, D, max(lens), "bf16", l_cap=max(lens) + 2, kv_len=list(lens), n_nodes=list(nodes), topk=4)
     # The weights are rounded to bf16 (2^-9 of each) in numerator and sum alike: an output is off by at most 2^-9 (sum of
     # p |v| + |output|), under 2^-8 times the same attention over |v|; the rest is fp32. (A bar in terms of the whole batch's
@@ -453,3 +454,25 @@ def test_bf16_short_ragged_units_stay_whole(H, D, N, Hq, Hkv, lens, nodes):
     assert torch.all(ws == 0xA5)
     ref, _, _ = _check(H, case, H.TOL["bf16"])
     assert torch.equal(out, ref.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,Hq,Hkv,L", [(26, 4, 4, 200), (40, 8, 2, 33), (60, 8, 2, 1000)])
+def test_bf16_non_finite_query_rows_stay_apart(H, D, N, Hq, Hkv, L):
+    """A query row of NaN, or with an infinity, makes its own output NaN and leaves every other row as it is, also those that share
+    a wavefront with it (whose softmax shifts move together)."""
+    case = H.AttnCase(980 + N + D, 2, N, Hq, Hkv, D, L, "bf16", l_cap=L + 1, n_nodes=[N, N])
+    ref = case.run_oracle()
+    clean = case.q.clone()
+    bad = torch.zeros(clean.shape[:3], dtype=torch.bool, device=H.DEV)
+    case.q[0, 3, 1] = float("nan")
+    case.q[0, 7, Hq - 1, 5] = float("inf")
+    case.q[1, N - 1, 0, D - 1] = float("-inf")
+    bad[0, 3, 1] = bad[0, 7, Hq - 1] = bad[1, N - 1, 0] = True
+    spoilt = case.q
+    for splits in (0, 1, 5):
+        case.q = spoilt
+        out = case.run_gpu(splits=splits)
+        case.q = clean
+        assert torch.all(torch.isnan(out[bad]))
+        assert H.rel_err(torch.where(bad[..., None], case.run_gpu(splits=splits), out), ref) <= H.TOL["bf16"]
