@@ -39,9 +39,12 @@ def _run(seed, B, N, V, T, useed=0, min_compared=None, **kw):
     parent, n_nodes, logits, draft_logits, tokens = _case(seed, B, N, V, T, **kw)
     uni = gen_uniforms(useed, B, N)
     pad = kw.get("row_pad", 0)
-    out = fspad.fspad_tree_accept_sample_draft(_padded(logits, pad), _padded(draft_logits, pad), torch.from_numpy(tokens).to(DEV),
-                                               torch.from_numpy(parent).to(DEV), torch.from_numpy(n_nodes).to(DEV), T,
-                                               torch.from_numpy(uni).to(DEV))
+    # workspace (NaN) and outputs hold what no call leaves there: statistics that nobody formed, or words that nobody wrote, show
+    ws = torch.full((fspad.fspad_tree_accept_sample_draft_workspace_bytes(B, N, V),), 0xFF, dtype=torch.uint8, device=DEV)
+    out = [torch.full(shape, -77, dtype=torch.int32, device=DEV) for shape in ((B, N), (B,), (B, N), (B,))]
+    fspad.fspad_tree_accept_sample_draft(_padded(logits, pad), _padded(draft_logits, pad), torch.from_numpy(tokens).to(DEV),
+                                         torch.from_numpy(parent).to(DEV), torch.from_numpy(n_nodes).to(DEV), T,
+                                         torch.from_numpy(uni).to(DEV), outputs=out, workspace=ws)
     torch.cuda.synchronize()
     ref = oracle.accept_sample_draft(logits, draft_logits, tokens, parent, n_nodes, T, uni)
     keep = ref[4] >= MARGIN
