@@ -1568,8 +1568,8 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
   AcceptParams both = pa;
   both.logits2 = draft_logits; both.part_max2 = pb.part_max; both.part_sum2 = pb.part_sum;
   both.clear_words = pb.clear_words; both.clear_count = pb.clear_count;
-  // The chip-wide walk needs less of the leaves' rows, which are more than half of a tree's: 60 nodes,
-  // V = 128256: 70.4 -> 67.7 us a call.
+  // The chip-wide walk needs less of the leaves' rows, which are more than half of a tree's: on the same six sets of inputs, 60 nodes,
+  // V = 128256, 78.5 -> 75.0 us a call (five processes, 0.951 to 0.966 of the time), 4 x 60 nodes 149 -> 132.
   // (The one-workgroup form needs all: also where it takes over from a cooperative launch that a capture refuses.)
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {

@@ -1183,7 +1183,8 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const SharedParams
 // one (17 products with 48 vector instructions among them 564 clocks, the products alone 548; beside 16x16x32 products the
 // vector instructions take 525 instead of 399). The two key groups stand half a turn apart: the turn's one barrier comes
 // after `weights` in group 0 and before it in group 1, so that the vector part of one runs beside the products of the other.
-// The copies stand behind the products: issued among them they stalled the wavefront (28 -> 37). Rings of five blocks: as four.
+// The copies stand behind the products: issued among them they stalled the wavefront (28 -> 37). Rings of five blocks: as four (which says
+// little about longer streams of copies while a segment's start waits for its whole ring, see there).
 // Against 16x16x32 tiles with the reads in front of their products: 64 / 8 heads, 16384 keys 53.9 -> 52.0 us a call, 32 / 8
 // heads, 1000 keys 15.0 -> 14.7, 4096 keys 20.3 -> 20.4.
 //
@@ -1420,7 +1421,9 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
       asm volatile("s_barrier" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
     };
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (kWideRing - 1)) : "memory");   // block 0 (and Q, requested behind it)
+    // Block 0, Q and the mask word have landed. (The products still wait for more: in front of Q's first use, in the loop below, the
+    // compiler cannot tell how many requests stand behind Q's, and waits for all: the whole ring and zero_rows' stores.)
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (kWideRing - 1)) : "memory");
     barrier();
     read_k(k, k_at);
     unsigned slot = 0;

@@ -40,7 +40,11 @@ constexpr int kSliceRows = fspad_detail::kSliceRows;   // weight rows per slice
 constexpr int kChunkK = 256;         // every k extent is a multiple of this
 constexpr int kMaxRows = 128;        // rows of X per call
 
+// Every slice is walked from a stage of its own on, kRot stages of k further than the slice before: the ranges of an XCD would
+// otherwise be at the same stage of k, or at few different ones, wherever the length of a range and a slice's stages have a common
+// divisor (4096-wide rows: six stages of 16), and rows a power-of-two pitch apart then crowd a few L2 channels.
 constexpr int kRot = 3;
+
 // How a projection is spread: its slices (of all problems that share the launch) and their stages
 // along k form one flat list, and workgroup w streams the contiguous range
 // [floor(w T / W), floor((w + 1) T / W)) of it, so that every compute unit fetches the same number of
@@ -50,7 +54,7 @@ struct Split {
   int32_t stages;     // per slice
   int32_t total;      // n_slices * stages
   int32_t n_wgs;
-  int32_t rot;        // stages of k by which the start of a slice is further than that of the slice before
+  int32_t rot;        // kRot, of as many stages
   uint32_t wgs_rcp, total_rcp, stages_rcp;   // reciprocals (div_rcp)
 };
 __device__ __forceinline__ int range_begin(const Split& s, int w) { return (int)div_rcp((unsigned)w * (unsigned)s.total, (unsigned)s.n_wgs, s.wgs_rcp); }
@@ -125,9 +129,6 @@ __global__ __launch_bounds__(64 * fspad_detail::kStreamWaves, 2) void partial_ge
   src.x[0] = p.x[0]; src.x[1] = p.x[1]; src.w[0] = p.w[0]; src.w[1] = p.w[1];
   src.split = p.split; src.n_xrows = p.rows; src.n_wrows = p.N; src.K = p.K;
   const int slice = (int)div_rcp((unsigned)t0, (unsigned)p.plan.stages, p.plan.stages_rcp);
-  // every slice is walked from a stage of its own on: the ranges of an XCD would otherwise be at the same
-  // stage of k, or at few different ones, wherever the length of a range and a slice's stages have a common
-  // divisor (4096-wide rows: six stages of 16), and rows a power-of-two pitch apart then crowd a few L2 channels
   const unsigned turned = (unsigned)slice * kRot;
   const int border = (int)(turned - (unsigned)p.plan.stages * div_rcp(turned, (unsigned)p.plan.stages, p.plan.stages_rcp));
   int at = t0 - slice * p.plan.stages + border;
