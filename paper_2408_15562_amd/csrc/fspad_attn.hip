@@ -194,6 +194,9 @@ __device__ __forceinline__ AttnArgs fetch_args(i32x4& class_wg) {
   asm volatile("s_load_dwordx16 %0, %4, 0x0\n\ts_load_dwordx16 %1, %4, 0x40\n\ts_load_dwordx16 %2, %4, 0x80\n\ts_load_dwordx4 %3, %4, %5\n\t"
                "s_waitcnt lgkmcnt(0)"
                : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(class_wg) : "s"(ka), "n"(offsetof(SharedParams, class_wg)));
+  int from_1 = class_wg[1], from_2 = class_wg[2], from_3 = class_wg[3];   // (apart too: 32 / 8 heads, 4096 keys 20.0 -> 19.8 us)
+  asm volatile("" : "+s"(from_1), "+s"(from_2), "+s"(from_3));
+  class_wg = i32x4{0, from_1, from_2, from_3};
   return args_apart(a, b, c);
 }
 // The same with what the merge needs of a sequence and the merge kernel's own arguments, which lie `tail` bytes into the segment.
