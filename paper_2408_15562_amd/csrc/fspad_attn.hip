@@ -1186,17 +1186,23 @@ __global__ __launch_bounds__(768) void tree_attn_gqa64_kernel(const SharedParams
 // one (17 products with 48 vector instructions among them 564 clocks, the products alone 548; beside 16x16x32 products the
 // vector instructions take 525 instead of 399). The two key groups stand half a turn apart: the turn's one barrier comes
 // after `weights` in group 0 and before it in group 1, so that the vector part of one runs beside the products of the other.
-// The copies stand behind the products: issued among them they stalled the wavefront (28 -> 37). Rings of five blocks: as four (which says
-// little about longer streams of copies while a segment's start waits for its whole ring, see there).
+// The copies stand behind the products: issued among them they stalled the wavefront (28 -> 37). Rings of five blocks: as four; of three, as
+// they are: as four too (64 / 8 heads, 16384 keys 45.3, with four and the query rows in the fourth slot at first 45.7 us a call).
+// What a short segment costs is its start. The products begin when block 0 is there, which takes that nothing of a segment's set-up
+// is loaded into registers (see the query rows); a segment copies the blocks that it has and no more. Against rows in registers, for
+// which the compiler waited for the whole ring, and a fixed number of copies a turn, us a call: 32 / 8 heads, 60 nodes, 300 keys 13.7 -> 12.6,
+// 1000 keys 16.4 -> 15.2, 4096 keys 19.9 -> 18.3, 8192 keys 23.6 -> 22.1; 4 sequences of 4096 keys 32.4 -> 31.2; 28 / 4 heads, 9000 keys 19.9 -> 19.4.
 // Against 16x16x32 tiles with the reads in front of their products: 64 / 8 heads, 16384 keys 53.9 -> 52.0 us a call, 32 / 8
 // heads, 1000 keys 15.0 -> 14.7, 4096 keys 20.3 -> 20.4.
 //
 // Blocks lie in LDS row by row as they are copied (whole rows per request: as 64-byte pieces a 32 / 8-head call over 4096 keys
 // took a microsecond more), with the 16-byte chunks of a K row exchanged by key (c at c ^ (key & 15)) and the 64-byte pieces of
 // a V row (d at d ^ (key & 3)): reads then touch every bank once a pass.
-constexpr int kWideRing = 4;                        // K and V blocks that a key group holds
+constexpr int kWideRing = 3;                        // K and V blocks that a key group holds
 constexpr int kWideTensor = kBlockKeys * 128 * 2;  // bytes of one tensor's block
 constexpr int kWideGroup = 2 * kWideRing * kWideTensor;
+constexpr int kWideQ = 2 * kWideGroup;              // the unit's 128 query rows, behind the rings
+constexpr int kWideMasks = kWideQ + 128 * 128 * 2;  // and the lanes' ancestor words
 // Weights stay below 2: a score that would go above moves its row's shift to 2^7 times the largest weight so far (the test is
 // the exponent's top bit of the packed weights). As with kLazyLog2, shifts move almost never after the first blocks.
 constexpr float kWideHeadroom = 7.0f;
@@ -1220,7 +1226,7 @@ __device__ __forceinline__ void pv_reading_k(f32x16 (&o)[4], const bf16x8 (&v)[2
         [v12] "v"(v[1][2]), [v13] "v"(v[1][3]), [w0] "v"(w[0]), [w1] "v"(w[1]), [ka] "v"(ka)
       : "memory");
 }
-// K operands alone (a segment's first block)
+// K operands alone (a segment's first block), and those of the query rows
 __device__ __forceinline__ void read_k(bf16x8 (&k)[8], unsigned ka) {
   unsigned a0, a1;
   asm volatile(
@@ -1232,6 +1238,12 @@ __device__ __forceinline__ void read_k(bf16x8 (&k)[8], unsigned ka) {
         [a0] "=&v"(a0), [a1] "=&v"(a1)
       : [ka] "v"(ka)
       : "memory");
+}
+// this lane's ancestor word: its halves lie 256 bytes apart
+__device__ __forceinline__ uint64_t read_mask(unsigned at) {
+  unsigned lo, hi;
+  asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %2 offset:256\n\ts_waitcnt lgkmcnt(0)" : "=&v"(lo), "=&v"(hi) : "v"(at) : "memory");
+  return ((uint64_t)hi << 32) | lo;
 }
 // S^T = K Q^T of a block, and its V operands out of LDS (r: halves of v[s][dt], four keys each). The wait states at the end are
 // those between a matrix instruction and a vector instruction that reads its result.
@@ -1299,7 +1311,7 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
   i32x4 class_wg;
   const AttnArgs p = fetch_args(class_wg);
   constexpr int D = 128, KG = 2, WAVES = 4, ROWS = 32, rows_per_unit = WAVES * ROWS;
-  __shared__ __attribute__((aligned(1024))) char lds_all[KG * kWideGroup];
+  __shared__ __attribute__((aligned(1024))) char lds_all[kWideMasks + KG * WAVES * 512];
 
   const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kg = wave_all >> 2, wave = wave_all & 3;   // key group, row slab within the workgroup
@@ -1317,6 +1329,8 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
   // this lane's operand reads of a block in slot 0
   const unsigned lds0 = (unsigned)(uintptr_t)(LdsPtr)ring;
   const unsigned k_at = lds0 + 256u * row + 16u * (h ^ (row & 15));
+  const unsigned q_at = (unsigned)(uintptr_t)(LdsPtr)lds_all + kWideQ + 8192u * wave + 256u * row + 16u * (h ^ (row & 15));
+  const unsigned mask_at = (unsigned)(uintptr_t)(LdsPtr)lds_all + kWideMasks + 512u * wave_all + 4u * lane;
   const unsigned v_at = lds0 + kWideRing * kWideTensor + 256u * (4 * h + ((lane >> 2) & 3)) + 64u * ((lane >> 2) & 3) + 32u * ((lane >> 4) & 1) + 8u * (lane & 3);
 
   const Share share = share_of(p, class_wg, blockIdx.x);
@@ -1360,9 +1374,9 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
     const char *k_src = kc + first_byte, *v_src = vc + first_byte;
     unsigned row_at[2] = {(unsigned)copy_key * cache_row_bytes, (unsigned)(copy_key + 4) * cache_row_bytes};
     auto locate_rest = [&](int i) {   // not a whole prefix block
-      const int blk = i < n_own ? blk_begin + KG * i : seg_begin;
+      const int blk = blk_begin + KG * i;
       const bool tree = blk >= n_prefix_blocks;
-      const int key0 = (tree ? blk - n_prefix_blocks : blk) * kBlockKeys, left = i < n_own ? (tree ? n : L) - key0 : 1;
+      const int key0 = (tree ? blk - n_prefix_blocks : blk) * kBlockKeys, left = (tree ? n : L) - key0;
       const unsigned rb = tree ? tree_row_bytes : cache_row_bytes;
       const int64_t at = (int64_t)key0 * rb;
       k_src = (tree ? reinterpret_cast<const char*>(p.k_tree) + tree0 : kc) + at;
@@ -1383,29 +1397,38 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
         __builtin_amdgcn_global_load_lds((GlobalPtr)(v_src + (row_at[x] + v_chunk)), (LdsPtr)(dst + kWideRing * kWideTensor + 1024 * x), 16, 0, 0);
     };
     locate(0);
-    copy_block(0);
+    if (n_own > 0) copy_block(0);
 
     // this lane's row: row rr of the kv head's N*G rows = (node, head within group)
     const int rr = slab * ROWS + row;
     const int node = (int)div_magic((unsigned)rr, p.G, p.g_magic);
     const bool exists = rr < p.Nmax * p.G, valid = exists && node < n;
     const int64_t out_row = ((int64_t)b * p.Nmax + node) * p.Hq + g * p.G + (rr - node * p.G);
-    bf16x8 q[8];
-    uint64_t tree_mask = 0;
+    // Query rows and ancestor words come through LDS too, and out of it by instructions that the compiler does not track: in front of
+    // the first use of anything loaded into registers it waits for every request in flight, a segment's first blocks among them.
+    // Sixteen rows per wavefront, four per instruction, their chunks as those of K rows; rows past the tree are its last one again.
+    {
+      const int last = n * p.G - 1;
+      char* const dst = lds_all + kWideQ + 4096 * wave_all;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) q[ks] = bf16x8{};
-    if (valid) {
-      const __bf16* qrow = reinterpret_cast<const __bf16*>(p.q) + out_row * D + 8 * h;
+      for (int x = 0; x < 4; ++x) {
+        const int at = 16 * wave_all + 4 * x + (lane >> 4), qr = min(y * rows_per_unit + at, last);
+        const int qn = (int)div_magic((unsigned)qr, p.G, p.g_magic);
+        const char* src = reinterpret_cast<const char*>(p.q) + ((((int64_t)b * p.Nmax + qn) * p.Hq + g * p.G + (qr - qn * p.G)) * (D * 2) + (int)(16u * (chunk ^ (at & 15))));
+        __builtin_amdgcn_global_load_lds((GlobalPtr)src, (LdsPtr)(dst + 1024 * x), 16, 0, 0);
+      }
+      const char* word = reinterpret_cast<const char*>(p.anc_mask) + 8 * ((int64_t)b * p.Nmax + min(node, n - 1));
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) q[ks] = *reinterpret_cast<const bf16x8*>(qrow + 16 * ks);
-      tree_mask = p.anc_mask[b * p.Nmax + node];
+      for (int x = 0; x < 2; ++x)
+        __builtin_amdgcn_global_load_lds((GlobalPtr)(word + 4 * x), (LdsPtr)(lds_all + kWideMasks + 512 * wave_all + 256 * x), 4, 0, 0);
     }
 #pragma unroll 1
-    for (int i = 1; i < kWideRing; ++i) {
+    for (int i = 1; i < min(kWideRing, n_own); ++i) {
       locate(i);
       copy_block(i * kWideTensor);
     }
-    if (seg_begin == 0 && y == 0) {
+
+    if (seg_begin == 0 && y == 0) {   // (counted as copies by the waits below, which then wait for more; behind the stream it cost as much)
       const int covered = n_groups * rows_per_unit;
       if (covered < p.Nmax * p.G) zero_rows<D, 64 * WAVES * KG>(p, b, g, covered);
     }
@@ -1419,22 +1442,34 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
     bf16x8 k[8], v[2][4], wt[2];
     u32x2 vr[16];
 
+    // All copies of this wavefront have landed but those of its last block, if there are blocks (`blocks` > 0) behind the one that
+    // is needed. (written out: the compiler's form of the choice has four more scalar instructions and a branch more in every turn)
+    auto next_landed = [](int blocks) {
+      asm volatile("s_cmp_gt_i32 %0, 0\n\ts_cbranch_scc1 .Lone%=\n\ts_waitcnt vmcnt(0)\n.Lone%=:\n\ts_waitcnt vmcnt(4)" : : "s"(blocks) : "scc", "memory");
+    };
     auto barrier = [] {
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_barrier" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
     };
-    // Block 0, Q and the mask word have landed. (The products still wait for more: in front of Q's first use, in the loop below, the
-    // compiler cannot tell how many requests stand behind Q's, and waits for all: the whole ring and zero_rows' stores.)
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (kWideRing - 1)) : "memory");
+    // Block 0, the query rows and the ancestor words have landed; blocks 1 and 2 may be in flight.
+    if (n_own > 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else next_landed(n_own - 1);
     barrier();
+    bf16x8 q[8];
+    read_k(q, q_at);
+    const uint64_t tree_mask = valid ? read_mask(mask_at) : 0ull;
+    if (!valid) {   // (products of zeros: 16 ragged sequences, 17 to 60 nodes 1 % less than with the copied row)
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) q[ks] = bf16x8{};
+    }
     read_k(k, k_at);
     unsigned slot = 0;
     for (int i = 0; i < n_own; ++i) {
       const unsigned slot_next = slot + kWideTensor == kWideRing * kWideTensor ? 0u : slot + kWideTensor;
       qk_reading_v(s, k, q, vr, v_at + slot);
       if (kg == 1) {
-        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (kWideRing - 2)) : "memory");
+        next_landed(n_own - 2 - i);
         barrier();
       }
       if (i >= n_full) {   // ragged tail or tree block
@@ -1467,7 +1502,7 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
 #pragma unroll
       for (int t = 0; t < 2; ++t) wt[t] = __builtin_bit_cast(bf16x8, u32x4{pk[4 * t], pk[4 * t + 1], pk[4 * t + 2], pk[4 * t + 3]});
       if (kg == 0) {
-        asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (kWideRing - 2)) : "memory");
+        next_landed(n_own - 2 - i);
         barrier();
       }
 #pragma unroll
@@ -1479,8 +1514,10 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
         }
       pv_reading_k(o, v, wt, k, k_at + slot_next);
       // block i is read by all four wavefronts: its place in the ring takes a later one
-      locate(i + kWideRing);
-      copy_block(slot);
+      if (i + kWideRing < n_own) {
+        locate(i + kWideRing);
+        copy_block(slot);
+      }
       slot = slot_next;
     }
     if (kg == 1 && (seg_count & 1)) barrier();   // group 0 has a block more

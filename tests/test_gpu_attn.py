@@ -405,6 +405,15 @@ def test_bf16_shared_stage_rings_and_segments(H, D, N, Hq, Hkv, scale, L, splits
     assert torch.equal(out, case.run_gpu(splits=splits, **({"scale": scale} if scale else {})))
 
 
+@pytest.mark.parametrize("blocks", range(13))
+@pytest.mark.parametrize("N", [35, 64])
+def test_bf16_shared_stage_first_and_last_blocks(H, N, blocks):
+    """One workgroup per unit, so that a key group holds none to seven blocks: fewer than its ring, as many, more; the tree in one
+    block or two and both halves of the ancestor words. The smaller tree leaves query rows past its end in a slab, and slabs without any."""
+    case = H.AttnCase(900 + N + blocks, 2, N, 8, 2, 128, 32 * blocks, "bf16", n_nodes=[N, 19])
+    _check(H, case, H.TOL["bf16"], splits=4)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("B,N,Hq,Hkv,lens,nodes", [
     (3, 60, 8, 2, (400, 90, 777), (60, 17, 33)),             # two classes of sequences, cut units
