@@ -13,7 +13,6 @@
 // descends chunk -> thread segment -> element. (Large sampling calls: see kInnerFirst.)
 #include <hip/hip_runtime.h>
 #include <algorithm>
-#include <atomic>
 #include <stdint.h>
 
 #include <mutex>
@@ -1008,19 +1007,42 @@ __global__ __launch_bounds__(kDraftThreads) void accept_sample_draft_kernel(cons
 // The same acceptance spread over the chip. With one workgroup per sequence every rejection is a
 // pass over two rows of V fp64 entries at the rate of one compute unit. Here G workgroups share a
 // sequence: each thread keeps E consecutive entries of the unnormalised p and q of the current node
-// in registers, a rejection is arithmetic on registers plus one barrier across the G workgroups
+// in registers, a rejection is arithmetic on registers plus one exchange between the G workgroups
 // (partial sums and the two entries the next test needs go through memory), and the draw is located
 // from the workgroups' totals. Every workgroup takes every decision from the same published numbers,
 // summed in the same order, so the control flow is the same in all of them.
 //
-// The barrier counts arrivals in a word that the streaming pass of the same call has set to zero;
-// the kernel is launched as a cooperative grid (all workgroups resident). A wait is bounded all the
-// same: a workgroup that sees no progress for kSpinLimit polls raises the sequence's failure word,
+// An exchange is one trip: a workgroup stores its numbers with device scope, and every workgroup polls all of them
+// until none is missing. (A stored number is its complement, so that the zero words that the launch before leaves
+// mean "not there": the complement of no sum is zero, that would be a NaN with every bit set.) Three sets of places
+// are used in turn; who has read round r knows that all are done with round r - 1, and empties its place of that set.
+//
+// The launch is an ordinary one, and whether all G workgroups run at the same time is found out on the way. Each counts
+// itself in when it starts; a workgroup whose numbers of the first round are there is running and will see the walk through.
+// The one that came first waits for the others for kArrivalTicks and then, if one has not even started (the compute units
+// may be held by another stream's kernels), closes the count and does the whole walk alone, workgroup by workgroup in a loop: the same
+// arithmetic in the same order, with a node's entries formed anew in every round from the logits and the rejections so far.
+// Nobody ever waits for a workgroup that has not started, so calls on several streams cannot hold each other up. A cooperative
+// launch, the form before, cost 14 us a call (the runtime orders it with signals), and its barrier (a fence, an arrival counter, a poll,
+// a fence, then the loads) 4 us a rejection. 60 nodes, V = 128256, 61.8 -> 32.9 us a call, both on the same inputs.
+//
+// Waits for running workgroups are bounded all the same: who sees no progress for kSpinLimit polls raises the failure bit,
 // reports path_len = n_tokens = -1 and leaves, and so does every other workgroup at its next wait.
 constexpr int kGridThreads = 256;
 constexpr int kGridWaves = kGridThreads / 64;
 constexpr int kGridMaxWgs = 64;          // workgroups per sequence, at most
 constexpr unsigned kSpinLimit = 1u << 20;
+constexpr int kGridSets = 3;             // sets of places for the exchanges
+// 100 MHz ticks. The walk alone takes some hundred microseconds, so that is what waiting for the others may cost.
+constexpr long long kArrivalTicks = 30000;
+// the word that counts a sequence's workgroups in
+constexpr uint32_t kAlone = 1u << 31;    // closed: the first one goes on alone
+constexpr uint32_t kFailed = 1u << 30;
+#ifdef FSPAD_TEST_ABSENT_WORKGROUP       // (a build for the tests: the last workgroup of every sequence is never launched)
+constexpr int kAbsent = 1;
+#else
+constexpr int kAbsent = 0;
+#endif
 
 struct DraftGridParams {
   const float* logits;
@@ -1038,23 +1060,17 @@ struct DraftGridParams {
   const double* part_sum_p;
   const float* part_max_q;
   const double* part_sum_q;
-  uint32_t* sync;      // [B][2]: arrivals, failure word
-  double* slots;       // [B][2][G][4]: per round parity and workgroup: sum of the new p, of what q keeps, of the old p
-  double* pubs;        // [B][2][4]: the next test's entry of the new p, of the old p, of q
+  uint64_t* slots;     // [B][3][G][4]: per set and workgroup: sum of the new p, of what q keeps, of the old p
+  uint64_t* pubs;      // [B][3][4]: the next test's entry of the new p, of the old p, of q
+  uint32_t* sync;      // [B]: workgroups that have started, kAlone, kFailed
+  uint32_t* clear;     // all of these, as words that the merge launch sets to zero
+  int32_t clear_count;
   double* row_stats;   // [2][B*Nmax][2]: (max, sum of exponentials) of every row of logits, then of draft_logits
+  double* tests;       // [2][B*Nmax]: p(x), then q(x), of the node's token x at its parent
   double inv_temperature;
   int32_t B, Nmax, V, n_chunks, G;
+  int32_t vec;         // rows are 16-byte aligned
 };
-
-__device__ __forceinline__ double grid_wg_sum(double v, double* sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  __syncthreads();                  // sh may still be read from the previous reduction
-  if (lane == 0) sh[wave] = v;
-  __syncthreads();
-  return (sh[0] + sh[1]) + (sh[2] + sh[3]);
-}
 
 // K sums over the workgroup at once: running sums inside the wavefronts (no LDS), the four totals of each
 // through LDS, one barrier. `sh` holds two sets of K x 4 doubles used in turn, so that a wavefront that
@@ -1085,39 +1101,35 @@ __device__ __forceinline__ float grid_wg_max(float v, float* sh) {
   return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
 }
 
-// All G workgroups of a sequence meet; what each wrote before is visible to all after. False: the wait ran out.
-__device__ __forceinline__ bool grid_barrier(uint32_t* sync, unsigned target, int* sh_ok) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    __hip_atomic_fetch_add(&sync[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned polls = 0;
-    int ok = 1;
-    while (__hip_atomic_load(&sync[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (__hip_atomic_load(&sync[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u || ++polls > kSpinLimit) {
-        __hip_atomic_store(&sync[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ok = 0;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(4);
-    }
-    __threadfence();
-    *sh_ok = ok;
-  }
-  __syncthreads();
-  return *sh_ok != 0;
+// numbers of an exchange, device scope
+__device__ __forceinline__ void publish(uint64_t* at, double v) {
+  __hip_atomic_store(at, ~(uint64_t)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ uint64_t poll(const uint64_t* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double published(uint64_t bits) { return __longlong_as_double((long long)~bits); }
 
 // Row statistics of both logit arrays from the chunk statistics of the streaming pass, for every row at once
-// (one workgroup per row and array): the walk then finds a node's (max, sum) ready instead of merging them,
-// node after node, on its critical path.
+// (one workgroup per row and array), and with them the two probabilities that the test of each child of the row's node takes:
+// the walk then finds a node's (max, sum) and its first test ready instead of forming them, node after node, on its critical path.
 __global__ __launch_bounds__(kGridThreads) void accept_row_merge_kernel(const DraftGridParams p) {
   __shared__ double sh_sums[2 * kGridWaves];
   __shared__ float sh_f[kGridWaves];
   const int row = blockIdx.x, arr = blockIdx.y, tid = threadIdx.x;
   const int b = row / p.Nmax, node = row - b * p.Nmax;
-  if (node >= p.n_nodes[b]) return;   // rows of unused tree slots have no chunk statistics
-  if (arr && !has_child(lane_parent(p.parent + (int64_t)b * p.Nmax, p.Nmax), min(p.n_nodes[b], p.Nmax), node)) return;   // (nor leaves of the draft's)
+  const int64_t o = (int64_t)b * p.Nmax;
+  for (int i = (int)((blockIdx.y * gridDim.x + blockIdx.x) * kGridThreads) + tid; i < p.clear_count; i += (int)(2 * gridDim.x * kGridThreads))
+    p.clear[i] = 0u;
+  const int my_parent = lane_parent(p.parent + o, p.Nmax);
+  const int n_all = p.n_nodes[b], n = min(n_all, p.Nmax);
+  if (node >= n_all) return;   // rows of unused tree slots have no chunk statistics
+  if (arr && !has_child(my_parent, n, node)) return;   // (nor leaves of the draft's)
+  // the logits of the children's tokens (wavefront 0, a lane each), asked for before the statistics
+  bool child = tid < 64 && my_parent == node && tid > node && tid < n;
+  float at_child = 0.f;
+  if (child) {
+    const int x = p.draft_tokens[o + tid];
+    at_child = x >= 0 && x < p.V ? (arr ? p.draft_logits : p.logits)[(o + node) * p.row_stride + x] : __builtin_nanf("");
+  }
   const float* pm = (arr ? p.part_max_q : p.part_max_p) + (int64_t)row * p.n_chunks;
   const double* ps = (arr ? p.part_sum_q : p.part_sum_p) + (int64_t)row * p.n_chunks;
   float m = -INFINITY;
@@ -1135,168 +1147,299 @@ __global__ __launch_bounds__(kGridThreads) void accept_row_merge_kernel(const Dr
     out[0] = (double)m;
     out[1] = z[0];
   }
+  if (child) {
+    const double scale = z[0] > 0.0 ? 1.0 / z[0] : 0.0;
+    p.tests[(int64_t)arr * p.B * p.Nmax + o + tid] =
+        (at_child == at_child && m > -INFINITY) ? exp_nonpos(((double)at_child - (double)m) * p.inv_temperature) * scale : 0.0;
+  }
 }
 
 template <int E>
 __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(const DraftGridParams p) {
   __shared__ double sh_d[kGridWaves];
   __shared__ double sh_sums[2 * 3 * kGridWaves];
-  __shared__ float sh_f[kGridWaves];
-  __shared__ int sh_ok;
   __shared__ int sh_w[2 * kGridWaves];
   __shared__ double sh_tot[2];
+  // of an exchange: the sums of the new p and of what q keeps, the next test's entries; how it ended
+  __shared__ double sh_round[5];
+  __shared__ int sh_how;
+  __shared__ uint32_t sh_order;
+  __shared__ double alone_slots[3][kGridMaxWgs];   // of a workgroup that goes on alone, in place of the slots in memory
   int flip = 0;
-  const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int g = blockIdx.x;
   const int G = p.G, V = p.V;
   const int64_t o = (int64_t)b * p.Nmax;
+  uint32_t* const sync = p.sync + b;
+  if (tid == 0) sh_order = __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int n = min(p.n_nodes[b], p.Nmax);
-  const float* u_acc = p.uniforms + (int64_t)b * 2 * p.Nmax;
-  const float* u_draw = u_acc + p.Nmax;
-  uint32_t* sync = p.sync + 2 * b;
-  double* slots = p.slots + (int64_t)b * 2 * G * 4;
-  double* pubs = p.pubs + (int64_t)b * 2 * 4;
-  const int e0 = (g * kGridThreads + tid) * E;   // this thread's E consecutive entries
+  uint64_t* const slots = p.slots + (int64_t)b * kGridSets * G * 4;
+  uint64_t* const pubs = p.pubs + (int64_t)b * kGridSets * 4;
 
-  if (g == 0)
-    for (int i = tid; i < p.Nmax; i += kGridThreads) { p.path[o + i] = i == 0 ? 0 : -1; p.tokens[o + i] = -1; }
-  // the tree and the uniforms go to LDS once: the walk reads them in loops
-  __shared__ int t_par[FSPAD_MAX_NODES], t_tok[FSPAD_MAX_NODES];
+  // the tree, the uniforms and what the rows' launch left go to LDS once: the walk reads them in loops
+  __shared__ int t_tok[FSPAD_MAX_NODES], t_path[FSPAD_MAX_NODES];
   __shared__ float t_ua[FSPAD_MAX_NODES], t_ud[FSPAD_MAX_NODES];
   __shared__ double t_stats[2][FSPAD_MAX_NODES][2];   // (max, sum) of every row of this sequence: logits, draft logits
+  __shared__ double t_test[2][FSPAD_MAX_NODES];
+  // rejections at the current node: the scales they were applied with, the rejected token, whether p moved
+  __shared__ double h_sp[FSPAD_MAX_NODES], h_sq[FSPAD_MAX_NODES];
+  __shared__ int h_x[FSPAD_MAX_NODES], h_moved[FSPAD_MAX_NODES];
+  static_assert(FSPAD_MAX_NODES <= 64, "a lane per node");
   for (int i = tid; i < 4 * p.Nmax; i += kGridThreads) {
     const int arr = i / (2 * p.Nmax), rest = i - arr * 2 * p.Nmax;
     t_stats[arr][rest >> 1][rest & 1] = p.row_stats[((int64_t)arr * p.B * p.Nmax + o) * 2 + rest];
   }
+  for (int i = tid; i < 2 * p.Nmax; i += kGridThreads) {
+    const int arr = i >= p.Nmax, node = i - arr * p.Nmax;
+    t_test[arr][node] = p.tests[(int64_t)arr * p.B * p.Nmax + o + node];
+  }
+  const int my_parent = lane < p.Nmax ? p.parent[o + lane] : -2;
   if (tid < FSPAD_MAX_NODES) {
     const bool ok = tid < p.Nmax;
-    t_par[tid] = ok ? p.parent[o + tid] : -2;
     t_tok[tid] = ok ? p.draft_tokens[o + tid] : -1;
-    t_ua[tid] = ok ? u_acc[tid] : 0.f;
-    t_ud[tid] = ok ? u_draw[tid] : 0.f;
+    t_ua[tid] = ok ? p.uniforms[(int64_t)b * 2 * p.Nmax + tid] : 0.f;
+    t_ud[tid] = ok ? p.uniforms[(int64_t)b * 2 * p.Nmax + p.Nmax + tid] : 0.f;
   }
   __syncthreads();
+  const uint32_t order = sh_order;
+  if (order & kAlone) return;    // too late: the first one has gone on alone
+  bool alone = false;
 
   double rp[E], rq[E];   // unnormalised p and q of the current node, once a rejection or the draw has formed them
   unsigned round = 0;
-  auto meet = [&]() {
-    ++round;
-    if (grid_barrier(sync, round * (unsigned)G, &sh_ok)) return true;
-    if (tid == 0) { p.path_len[b] = -1; p.n_tokens[b] = -1; }
-    return false;
+  double slot_z = 0.0, slot_t = 0.0;   // wavefront 0, a lane per workgroup: its sums of the new and the old p in the last round
+  int cur = 0, len = 1;
+
+  // Path and tokens but for the last one, which is its finder's. (threads of one workgroup, after a barrier behind the last step of the walk)
+  auto write_walk = [&]() {
+    for (int i = tid; i < p.Nmax; i += kGridThreads) {
+      p.path[o + i] = i < len ? t_path[i] : -1;
+      if (i != len - 1) p.tokens[o + i] = i < len ? t_tok[t_path[i + 1]] : -1;
+    }
+  };
+  auto write_last = [&](int tok) {   // one thread
+    p.tokens[o + len - 1] = tok;
+    p.path_len[b] = len;
+    p.n_tokens[b] = len;
+  };
+  // The numbers of this round's `set` from all workgroups (pub: and the next test's entries): 1: they are in sh_round and the
+  // lanes' slot_z, slot_t; 0: leave; 2: go on alone, from the root.
+  auto exchange = [&](unsigned set, bool pub) -> int {
+    if (alone) __syncthreads();
+    if (wave == 0) {
+      int how = 1;
+      double z = 0.0, s = 0.0, t = 0.0, e0 = 0.0, e1 = 0.0, e2 = 0.0;
+      if (alone) {
+        if (lane < G) { z = alone_slots[0][lane]; s = alone_slots[1][lane]; t = alone_slots[2][lane]; }
+      } else {
+        const uint64_t* const at = slots + ((int64_t)set * G + min(lane, G - 1)) * 4;
+        const uint64_t* const next = pubs + set * 4;
+        const long long began = wall_clock64();
+        for (unsigned polls = 0;; ++polls) {
+          const uint64_t a0 = poll(at), a1 = poll(at + 1), a2 = poll(at + 2);
+          uint64_t b0 = 1, b1 = 1, b2 = 1;
+          if (pub) { b0 = poll(next); b1 = poll(next + 1); b2 = poll(next + 2); }
+          const uint32_t word = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (__all(a0 != 0 && a1 != 0 && a2 != 0 && b0 != 0 && b1 != 0 && b2 != 0)) {
+            if (lane < G) { z = published(a0); s = published(a1); t = published(a2); }
+            e0 = published(b0); e1 = published(b1); e2 = published(b2);
+            break;
+          }
+          if (__any((word & (kAlone | kFailed)) != 0u)) { how = 0; break; }
+          if (round == 1 && order == 0 && wall_clock64() - began > kArrivalTicks) {
+            int closed = 0;
+            if (lane == 0 && word < (uint32_t)G) {
+              uint32_t expected = word;
+              closed = __hip_atomic_compare_exchange_strong(sync, &expected, word | kAlone, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (__any(closed)) { how = 2; break; }
+          }
+          if (polls > kSpinLimit) {
+            if (lane == 0) __hip_atomic_fetch_or(sync, kFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            how = 0;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+        if (how == 0 && lane == 0) {
+          const uint32_t word = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (word & kFailed) {
+            for (int i = 0; i < p.Nmax; ++i) { p.path[o + i] = i == 0 ? 0 : -1; p.tokens[o + i] = -1; }
+            p.path_len[b] = -1;
+            p.n_tokens[b] = -1;
+          }
+        }
+      }
+      const double Z = wave_running_sum(z), S = wave_running_sum(s);
+      slot_z = z;
+      slot_t = t;
+      if (lane == 63) {
+        sh_round[0] = Z; sh_round[1] = S;
+        if (!alone) { sh_round[2] = e0; sh_round[3] = e1; sh_round[4] = e2; }
+        sh_how = how;
+      }
+      // Who is here has all numbers of this round, so all are done with the round before: its places are emptied (they are used
+      // again in the round after the next, and this workgroup's numbers of the next one leave behind this).
+      if (!alone && how == 1 && lane == 0) {
+        const unsigned old = set == 0 ? kGridSets - 1 : set - 1;
+        uint64_t* const mine = slots + ((int64_t)old * G + g) * 4;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          __hip_atomic_store(mine + k, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (g == 0) __hip_atomic_store(pubs + old * 4 + k, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+    }
+    __syncthreads();
+    return sh_how;
+  };
+  // a workgroup's sums of a round, one thread
+  auto leave_sums = [&](unsigned set, int of, double z, double s, double t) {
+    if (alone) {
+      alone_slots[0][of] = z; alone_slots[1][of] = s; alone_slots[2][of] = t;
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the emptied places are
+      uint64_t* const mine = slots + ((int64_t)set * G + of) * 4;
+      publish(mine, z); publish(mine + 1, s); publish(mine + 2, t);
+    }
   };
 
-  int cur = 0, len = 1;
   for (;;) {
+    if (tid == 0) t_path[len - 1] = cur;
     const float* lrow = p.logits + (o + cur) * p.row_stride;
     const float* qrow = p.draft_logits + (o + cur) * p.row_stride;
     // (rows of nodes beyond the tree are never walked: their entries hold no statistics; a leaf has the maximum of its target row
     // only, which is all that the draw below takes: the rest is for tests of children)
     const double mp = t_stats[0][cur][0], zp = t_stats[0][cur][1], mq = t_stats[1][cur][0], zq = t_stats[1][cur][1];
     double sp = zp > 0.0 ? 1.0 / zp : 0.0, sq = zq > 0.0 ? 1.0 / zq : 0.0;
-    auto weight_p = [&](int v) {
-      const float a = lrow[v];
-      return (a == a && mp > -INFINITY) ? exp_nonpos(((double)a - (double)mp) * p.inv_temperature) : 0.0;
+    int rejected = 0;
+    // E entries of a row from v on as they are, past its end NaN (which weighs nothing)
+    auto row_entries = [&](const float* row, int v, float (&x)[E]) {
+      if (p.vec && v + E <= V) {
+#pragma unroll
+        for (int k = 0; k < E / 4; ++k) {
+          const f32x4 q = *reinterpret_cast<const f32x4*>(row + v + 4 * k);
+          x[4 * k] = q[0]; x[4 * k + 1] = q[1]; x[4 * k + 2] = q[2]; x[4 * k + 3] = q[3];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < E; ++j) x[j] = v + j < V ? row[v + j] : __builtin_nanf("");
+      }
     };
-    auto weight_q = [&](int v) {
-      const float c = qrow[v];
-      return (c == c && mq > -INFINITY) ? exp_nonpos(((double)c - (double)mq) * p.inv_temperature) : 0.0;
+    auto weight = [&](float a, double m) { return (a == a && m > -INFINITY) ? exp_nonpos(((double)a - m) * p.inv_temperature) : 0.0; };
+    // p and q from the logits, and the rejections so far (which only a workgroup that is alone does not have in its registers)
+    auto form = [&](int v) {
+      float xp[E], xq[E];
+      row_entries(lrow, v, xp);
+      row_entries(qrow, v, xq);
+#pragma unroll
+      for (int j = 0; j < E; ++j) { rp[j] = weight(xp[j], mp); rq[j] = weight(xq[j], mq); }
+      for (int i = 0; i < rejected; ++i) {
+        const double a = h_sp[i], c = h_sq[i];
+        const int x = h_x[i], moved = h_moved[i];
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+          const double r = fmax(rp[j] * a - rq[j] * c, 0.0);
+          if (moved) rp[j] = r;
+          if (v + j == x) rq[j] = 0.0;
+        }
+      }
+    };
+    auto form_p = [&](int v) {   // p alone, for a draw at a node without a rejection
+      float xp[E];
+      row_entries(lrow, v, xp);
+#pragma unroll
+      for (int j = 0; j < E; ++j) rp[j] = weight(xp[j], mp);
     };
 
-    bool filled = false;
-    int total_at = 2;             // which slot entry holds the workgroups' totals of the p in the registers
-    double pub_p = 0.0, pub_q = 0.0;   // the entries of p and q for the child under test, once filled
-    int next = -1;
-    for (int c = cur + 1; c < n && len < p.Nmax; ++c) {
-      if (t_par[c] != cur) continue;
+    bool moved = false;                // the last round's totals of the p in the registers are those of the new p
+    double pub_p = 0.0, pub_q = 0.0;   // the entries of p and q for the child under test, behind a rejection
+    int next = -1, how = 1;
+    unsigned long long children = __ballot(my_parent == cur && lane > cur && lane < n);
+    while (children && len < p.Nmax) {
+      const int c = __ffsll(children) - 1;
+      children &= children - 1;
       const int x = t_tok[c];
       const bool valid = x >= 0 && x < V;
       double px = 0.0, qx = 0.0;
-      if (valid && filled) {
-        px = pub_p * sp; qx = pub_q * sq;
-      } else if (valid) {
-        const float a = lrow[x], d = qrow[x];
-        px = (a == a && mp > -INFINITY) ? exp_nonpos(((double)a - (double)mp) * p.inv_temperature) * sp : 0.0;
-        qx = (d == d && mq > -INFINITY) ? exp_nonpos(((double)d - (double)mq) * p.inv_temperature) * sq : 0.0;
+      if (valid) {
+        px = rejected ? pub_p * sp : t_test[0][c];
+        qx = rejected ? pub_q * sq : t_test[1][c];
       }
       if ((double)t_ua[c] * qx < px) { next = c; break; }
       // rejected: p <- max(p - q, 0), renormalised; q loses x and is renormalised. The sibling tested
       // next (if any) needs its entries of the new p and q: their owner publishes them in the same round.
-      int x2 = -1;
-      for (int c2 = c + 1; c2 < n; ++c2)
-        if (t_par[c2] == cur) { x2 = t_tok[c2]; break; }
-      const unsigned buf = (round + 1u) & 1u;
+      const int x2 = children ? t_tok[__ffsll(children) - 1] : -1;
+      const unsigned set = ++round % kGridSets;
       double rn[E];
-      double z = 0.0, s = 0.0, told = 0.0;
+      for (int of = alone ? 0 : g; of < (alone ? G : g + 1); ++of) {
+        const int e0 = (of * kGridThreads + tid) * E;   // this thread's E consecutive entries
+        if (alone || !rejected) form(e0);
+        double three[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        const int v = e0 + j;
-        double qv, pold, r;
-        if (!filled) {
-          qv = v < V ? weight_q(v) : 0.0;
-          pold = v < V ? weight_p(v) : 0.0;
-        } else {
-          qv = rq[j];
-          pold = rp[j];
+        for (int j = 0; j < E; ++j) {
+          const int v = e0 + j;
+          const double qv = rq[j], pold = rp[j];
+          const double r = fmax(pold * sp - qv * sq, 0.0);
+          const double keep = (valid && v == x) ? 0.0 : qv;
+          rn[j] = r; rq[j] = keep;
+          three[0] += r; three[1] += keep; three[2] += pold;
+          if (v == x2 && v < V) {
+            if (alone) { sh_round[2] = r; sh_round[3] = pold; sh_round[4] = keep; }
+            else { publish(pubs + set * 4, r); publish(pubs + set * 4 + 1, pold); publish(pubs + set * 4 + 2, keep); }
+          }
         }
-        r = fmax(pold * sp - qv * sq, 0.0);
-        const double keep = (valid && v == x) ? 0.0 : qv;
-        rn[j] = r; rp[j] = pold; rq[j] = keep;
-        z += r; s += keep; told += pold;
-        if (v == x2 && v < V) { pubs[buf * 4 + 0] = r; pubs[buf * 4 + 1] = pold; pubs[buf * 4 + 2] = keep; }
-      }
-      {
-        double three[3] = {z, s, told};
         grid_wg_sums<3>(three, sh_sums, flip);
-        z = three[0]; s = three[1]; told = three[2];
+        if (tid == 0) leave_sums(set, of, three[0], three[1], three[2]);
       }
-      if (tid == 0) {
-        double* mine = slots + ((int64_t)buf * G + g) * 4;
-        mine[0] = z; mine[1] = s; mine[2] = told;
-      }
-      if (!meet()) return;
-      // (every load of the round goes out before the first is used: one trip to memory, not three)
-      const double* sl = slots + (int64_t)(round & 1u) * G * 4;
-      const double part_z = tid < G ? sl[tid * 4] : 0.0, part_s = tid < G ? sl[tid * 4 + 1] : 0.0;
-      const double pub_new = pubs[(round & 1u) * 4], pub_old = pubs[(round & 1u) * 4 + 1], pub_keep = pubs[(round & 1u) * 4 + 2];
-      double both[2] = {part_z, part_s};
-      grid_wg_sums<2>(both, sh_sums, flip);
-      const double Z = both[0], S = both[1];
-      const bool moved = Z > 0.0;            // else p = q exactly: p is kept
+      how = exchange(set, x2 >= 0 && x2 < V);
+      if (how != 1) break;
+      const double Z = sh_round[0], S = sh_round[1];
+      moved = Z > 0.0;                       // else p = q exactly: p is kept
+      if (tid == 0) { h_sp[rejected] = sp; h_sq[rejected] = sq; h_x[rejected] = valid ? x : -1; h_moved[rejected] = moved; }
+      ++rejected;
       if (moved) {
 #pragma unroll
         for (int j = 0; j < E; ++j) rp[j] = rn[j];
         sp = 1.0 / Z;
       }
-      total_at = moved ? 0 : 2;
       sq = S > 0.0 ? 1.0 / S : sq;
-      filled = true;
-      pub_p = moved ? pub_new : pub_old;
-      pub_q = pub_keep;
+      pub_p = moved ? sh_round[2] : sh_round[3];
+      pub_q = sh_round[4];
+      if (alone) __syncthreads();   // (the history and the next round's entries go through LDS)
     }
-    if (next >= 0) {
-      if (g == 0 && tid == 0) { p.tokens[o + len - 1] = t_tok[next]; p.path[o + len] = next; }
+    if (how == 1 && next >= 0) {
       ++len;
       cur = next;
       continue;
     }
 
     // no child accepted: inverse-CDF draw from the current p, located from the workgroups' totals
-    if (!filled) {
-      double told = 0.0;
+    if (how == 1 && !rejected) {
+      const unsigned set = ++round % kGridSets;
+      for (int of = alone ? 0 : g; of < (alone ? G : g + 1); ++of) {
+        form_p((of * kGridThreads + tid) * E);
+        double told[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        rp[j] = e0 + j < V ? weight_p(e0 + j) : 0.0;
-        told += rp[j];
+        for (int j = 0; j < E; ++j) told[2] += rp[j];
+        grid_wg_sums<3>(told, sh_sums, flip);
+        if (tid == 0) leave_sums(set, of, 0.0, 0.0, told[2]);
       }
-      told = grid_wg_sum(told, sh_d);
-      if (tid == 0) slots[((int64_t)((round + 1u) & 1u) * G + g) * 4 + 2] = told;
-      if (!meet()) return;
-      total_at = 2;
+      how = exchange(set, false);
+      moved = false;
+    }
+    if (how == 0) return;
+    if (how == 2) {
+      alone = true;
+      cur = 0;
+      len = 1;
+      __syncthreads();   // sh_how is read
+      continue;
     }
     // wavefront 0, one lane per workgroup (G <= 64): running sum of the totals, first workgroup above t
     static_assert(kGridMaxWgs <= 64, "one lane per workgroup");
     if (wave == 0) {
-      const double mine = lane < G ? slots[((int64_t)(round & 1u) * G + lane) * 4 + total_at] : 0.0;
+      const double mine = moved ? slot_z : slot_t;   // (0 in lanes past the workgroups)
       const double incl = wave_running_sum(mine);
       const double total = __shfl(incl, 63);
       const double t = (double)t_ud[cur] * total;
@@ -1311,10 +1454,20 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     const double target = sh_tot[0];
     __syncthreads();   // sh_w is written again below
     if (owner < 0) {                                            // no mass at all: token 0
-      if (g == 0 && tid == 0) { p.tokens[o + len - 1] = 0; p.path_len[b] = len; p.n_tokens[b] = len; }
+      if (g == 0 || alone) {
+        write_walk();
+        if (tid == 0) write_last(0);
+      }
       return;
     }
+    if (alone) {
+      g = owner;
+      if (rejected) form((g * kGridThreads + tid) * E);
+      else form_p((g * kGridThreads + tid) * E);
+    }
     if (g != owner) return;
+    write_walk();
+    const int e0 = (g * kGridThreads + tid) * E;
     double local = 0.0;
     int last_here = -1;
 #pragma unroll
@@ -1323,7 +1476,6 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
       if (rp[j] > 0.0) last_here = e0 + j;
     }
     const double incl = wave_running_sum(local);
-    __syncthreads();
     if (lane == 63) sh_d[wave] = incl;
     __syncthreads();
     double wave_base = 0.0;
@@ -1349,7 +1501,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
       last_any = max(last_any, sh_w[kGridWaves + w]);
     }
     if (first_thread == kNone) {
-      if (tid == 0) { p.tokens[o + len - 1] = last_any < 0 ? 0 : last_any; p.path_len[b] = len; p.n_tokens[b] = len; }
+      if (tid == 0) write_last(last_any < 0 ? 0 : last_any);
       return;
     }
     if (tid == first_thread) {
@@ -1361,48 +1513,30 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
         run += rp[j];
         if (!done && run > target && rp[j] > 0.0) { pick = e0 + j; done = true; }
       }
-      p.tokens[o + len - 1] = pick;
-      p.path_len[b] = len;
-      p.n_tokens[b] = len;
+      write_last(pick);
     }
     return;
   }
 }
 
-struct GridPlan { int G, E; size_t slots_at, pubs_at, stats_at; };
+struct GridPlan { int G, E; size_t pubs_at, sync_at, stats_at, tests_at; };
 // E = 0: the chip-wide form does not apply (too many sequences, a vocabulary beyond 64 x 256 x 32 entries or too
-// small to hold the exchange area in the workspace's row buffers, or no cooperative launch on this device).
+// small to hold the exchange area in the workspace's row buffers).
 GridPlan plan_draft_grid(int32_t B, int32_t Nmax, int32_t V) {
-  GridPlan pl{0, 0, 0, 0, 0};
+  GridPlan pl{};
   if (B > 256) return pl;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
-    (void)hipGetLastError();
-    return pl;
-  }
-  static std::atomic<int> coop_known[64];   // 0: not asked yet, 1: no, 2: yes (asked once per device)
-  int known = coop_known[dev].load(std::memory_order_relaxed);
-  if (known == 0) {
-    int coop = 0;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess) {
-      (void)hipGetLastError();
-      coop = 0;
-    }
-    known = coop ? 2 : 1;
-    coop_known[dev].store(known, std::memory_order_relaxed);
-  }
-  if (known != 2) return pl;
   const int max_g = std::min(kGridMaxWgs, 256 / B);
   const int64_t per = ((int64_t)V + (int64_t)max_g * kGridThreads - 1) / ((int64_t)max_g * kGridThreads);
   const int E = per <= 4 ? 4 : per <= 8 ? 8 : per <= 16 ? 16 : per <= 32 ? 32 : 0;
   if (E == 0) return pl;
   const int G = (int)(((int64_t)V + (int64_t)kGridThreads * E - 1) / ((int64_t)kGridThreads * E));
-  const size_t slots_at = ((size_t)B * 2 * sizeof(uint32_t) + 255) & ~(size_t)255;
-  const size_t pubs_at = slots_at + (size_t)B * 2 * G * 4 * sizeof(double);
-  const size_t stats_at = pubs_at + (size_t)B * 2 * 4 * sizeof(double);
-  const size_t end = stats_at + (size_t)2 * B * Nmax * 2 * sizeof(double);
-  if (end > (size_t)B * 3 * (size_t)V * 8) return pl;
-  pl.G = G; pl.E = E; pl.slots_at = slots_at; pl.pubs_at = pubs_at; pl.stats_at = stats_at;
+  pl.pubs_at = (size_t)B * kGridSets * G * 4 * sizeof(uint64_t);
+  pl.sync_at = pl.pubs_at + (size_t)B * kGridSets * 4 * sizeof(uint64_t);
+  pl.stats_at = pl.sync_at + (((size_t)B * sizeof(uint32_t) + 15) & ~(size_t)15);
+  pl.tests_at = pl.stats_at + (size_t)2 * B * Nmax * 2 * sizeof(double);
+  const size_t end = pl.tests_at + (size_t)2 * B * Nmax * sizeof(double);
+  if (end > (size_t)B * 3 * (size_t)V * 8) return GridPlan{};
+  pl.G = G; pl.E = E;
   return pl;
 }
 
@@ -1556,28 +1690,18 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
   fill_params(pb, B, Nmax, V, draft_logits, row_stride, draft_tokens, parent, n_nodes, path, path_len, tokens, n_tokens,
               ws + region);
   pa.inv_temperature = pb.inv_temperature = 1.0 / (double)temperature;
-  // Chip-wide form: G workgroups a sequence, E entries a thread, if the shape allows it and the device
-  // runs cooperative grids; else one workgroup a sequence.
+  // Chip-wide form: G workgroups a sequence, E entries a thread, if the shape allows it; else one workgroup a sequence.
   const GridPlan plan = plan_draft_grid(B, Nmax, V);
   char* const work = ws + 2 * region;
-  if (plan.E != 0) {
-    pb.clear_words = reinterpret_cast<uint32_t*>(work);
-    pb.clear_count = 2 * B;
-  }
+  const bool vec = rows_vectorisable(logits, row_stride) && rows_vectorisable(draft_logits, row_stride);
   // one streaming launch over both logit arrays (grid.z picks the array)
   AcceptParams both = pa;
   both.logits2 = draft_logits; both.part_max2 = pb.part_max; both.part_sum2 = pb.part_sum;
-  both.clear_words = pb.clear_words; both.clear_count = pb.clear_count;
   // The chip-wide walk needs less of the leaves' rows, which are more than half of a tree's: on the same six sets of inputs, 60 nodes,
   // V = 128256, 78.5 -> 75.0 us a call (five processes, 0.951 to 0.966 of the time), 4 x 60 nodes 149 -> 132.
-  // (The one-workgroup form needs all: also where it takes over from a cooperative launch that a capture refuses.)
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
-    (void)hipGetLastError();
-    capture = hipStreamCaptureStatusActive;
-  }
-  both.rows = plan.E != 0 && capture == hipStreamCaptureStatusNone ? kSpareLeaves : kAllRows;
-  launch_rows<1>(both, rows_vectorisable(logits, row_stride) && rows_vectorisable(draft_logits, row_stride), stream);
+  // (The one-workgroup form needs all.)
+  both.rows = plan.E != 0 ? kSpareLeaves : kAllRows;
+  launch_rows<1>(both, vec, stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   if (plan.E != 0) {
     DraftGridParams gp{};
@@ -1585,30 +1709,25 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
     gp.draft_tokens = draft_tokens; gp.parent = parent; gp.n_nodes = n_nodes; gp.uniforms = uniforms;
     gp.path = path; gp.path_len = path_len; gp.tokens = tokens; gp.n_tokens = n_tokens;
     gp.part_max_p = pa.part_max; gp.part_sum_p = pa.part_sum; gp.part_max_q = pb.part_max; gp.part_sum_q = pb.part_sum;
-    gp.sync = reinterpret_cast<uint32_t*>(work);
-    gp.slots = reinterpret_cast<double*>(work + plan.slots_at);
-    gp.pubs = reinterpret_cast<double*>(work + plan.pubs_at);
+    gp.slots = reinterpret_cast<uint64_t*>(work);
+    gp.pubs = reinterpret_cast<uint64_t*>(work + plan.pubs_at);
+    gp.sync = reinterpret_cast<uint32_t*>(work + plan.sync_at);
+    gp.clear = reinterpret_cast<uint32_t*>(work);
+    gp.clear_count = (int32_t)(plan.stats_at / 4);
     gp.row_stats = reinterpret_cast<double*>(work + plan.stats_at);
+    gp.tests = reinterpret_cast<double*>(work + plan.tests_at);
     gp.inv_temperature = pa.inv_temperature;
-    gp.B = B; gp.Nmax = Nmax; gp.V = V; gp.n_chunks = pa.n_chunks; gp.G = plan.G;
+    gp.B = B; gp.Nmax = Nmax; gp.V = V; gp.n_chunks = pa.n_chunks; gp.G = plan.G; gp.vec = vec;
     hipLaunchKernelGGL(accept_row_merge_kernel, dim3((unsigned)(B * Nmax), 2u), dim3(kGridThreads), 0, stream, gp);
     if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-    void* args[] = {&gp};
-    const dim3 grid((unsigned)plan.G, (unsigned)B), block(kGridThreads);
-    hipError_t err = hipErrorInvalidValue;
+    const dim3 grid((unsigned)std::max(1, plan.G - kAbsent), (unsigned)B), block(kGridThreads);
     switch (plan.E) {
-      case 4: err = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&accept_sample_draft_grid_kernel<4>), grid, block, args, 0, stream); break;
-      case 8: err = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&accept_sample_draft_grid_kernel<8>), grid, block, args, 0, stream); break;
-      case 16: err = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&accept_sample_draft_grid_kernel<16>), grid, block, args, 0, stream); break;
-      case 32: err = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&accept_sample_draft_grid_kernel<32>), grid, block, args, 0, stream); break;
+      case 4: hipLaunchKernelGGL(accept_sample_draft_grid_kernel<4>, grid, block, 0, stream, gp); break;
+      case 8: hipLaunchKernelGGL(accept_sample_draft_grid_kernel<8>, grid, block, 0, stream, gp); break;
+      case 16: hipLaunchKernelGGL(accept_sample_draft_grid_kernel<16>, grid, block, 0, stream, gp); break;
+      default: hipLaunchKernelGGL(accept_sample_draft_grid_kernel<32>, grid, block, 0, stream, gp); break;
     }
-    if (err == hipSuccess) return FSPAD_OK;
-    (void)hipGetLastError();   // the launch was refused (a capture in progress, say): the one-workgroup form below
-    if (both.rows != kAllRows) {
-      both.rows = kAllRows;
-      launch_rows<1>(both, rows_vectorisable(logits, row_stride) && rows_vectorisable(draft_logits, row_stride), stream);
-      if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-    }
+    return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
   }
   DraftAcceptParams p{};
   p.logits = logits; p.draft_logits = draft_logits; p.row_stride = row_stride;

@@ -213,3 +213,43 @@ def test_captured_call_replays_like_eager():
         graph.replay()
         for a, b in zip(eager, snapshot()):
             assert torch.equal(a, b)
+
+
+def _absent_call(B, N, V, T, dev, outputs, workspace):
+    """The same entry point of the build whose chip-wide walks lack the last workgroup of every sequence."""
+    import ctypes
+
+    from paper_2408_15562_amd import build
+    f = ctypes.CDLL(build.ABSENT_LIB_PATH).fspad_tree_accept_sample_draft
+    vp = ctypes.c_void_p
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_int32] * 3 + [vp, vp, ctypes.c_int64] + [vp] * 3 + [ctypes.c_float] + [vp] * 6 + [ctypes.c_size_t, vp]
+    logits, draft_logits, tokens, parent, n_nodes, uni = dev
+    return f(B, N, V, logits.data_ptr(), draft_logits.data_ptr(), logits.stride(1), tokens.data_ptr(), parent.data_ptr(), n_nodes.data_ptr(),
+             T, uni.data_ptr(), *(t.data_ptr() for t in outputs), workspace.data_ptr(), workspace.numel(),
+             torch.cuda.current_stream().cuda_stream)
+
+
+@pytest.mark.parametrize("B,N,V,pad", [(1, 26, 2000, 0), (2, 40, 20000, 4), (1, 60, 128256, 0), (3, 30, 50257, 1), (40, 8, 5000, 0),
+                                       (1, 12, 300001, 0), (2, 1, 4097, 0)])
+@pytest.mark.parametrize("noise", [0.3, 1.0])
+def test_walk_without_one_of_its_workgroups(B, N, V, pad, noise):
+    """Every share of entries per thread, rows of any alignment: the workgroup that came first goes on alone, with the outputs of
+    the full walk (the same arithmetic) and of the oracle. A second call through the same workspace does the same."""
+    import paper_2408_15562_amd as fspad
+    T = 0.9
+    parent, n_nodes, logits, draft_logits, tokens = _case(8100 + B + N + V, B, N, V, T, peak=2.0, noise=noise)
+    uni = gen_uniforms(3, B, N)
+    dev = [_padded(logits, pad), _padded(draft_logits, pad)] + [torch.from_numpy(a).to(DEV) for a in (tokens, parent, n_nodes, uni)]
+    full = fspad.fspad_tree_accept_sample_draft(*dev[:5], T, dev[5])
+    ws = torch.full((fspad.fspad_tree_accept_sample_draft_workspace_bytes(B, N, V),), 0xFF, dtype=torch.uint8, device=DEV)
+    ref = oracle.accept_sample_draft(logits, draft_logits, tokens, parent, n_nodes, T, uni)
+    keep = ref[4] >= MARGIN
+    assert keep.sum() >= max(1, B - 1)
+    for _ in range(2):
+        out = [torch.full(shape, -77, dtype=torch.int32, device=DEV) for shape in ((B, N), (B,), (B, N), (B,))]
+        assert _absent_call(B, N, V, T, dev, out, ws) == 0
+        torch.cuda.synchronize()
+        for name, g, f, c in zip(("path", "path_len", "tokens", "n_tokens"), out, full, ref[:4]):
+            assert torch.equal(g, f), name
+            np.testing.assert_array_equal(g.cpu().numpy()[keep], c[keep], err_msg=name)
