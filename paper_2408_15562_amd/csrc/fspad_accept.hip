@@ -268,6 +268,73 @@ __global__ __launch_bounds__(kThreads) void accept_greedy_walk_kernel(const Acce
   fspad_detail::greedy_descend(amax, n, p.Nmax, lane, o, b, my_par, my_tok, p.path, p.tokens, p.path_len, p.n_tokens);
 }
 
+// The same in one launch where a row has up to kSmallVocab logits: sixteen to a lane, a wavefront for up to four rows, whose loads are
+// under way together and with the tree's. Such a call is launches and trips to memory: 26 rows of 1000 5.3 -> 4.4 us, a call's
+// share of a graph of a hundred, and 17.0 -> 13.9 us the step of attention, acceptance and commit around it. One workgroup per sequence
+// takes longer the more rows it has (us before / so, rows of 1000: 32 5.3 / 4.8, 40 5.3 / 5.3, 64 5.3 / 7.6, unaligned 26 5.4 / 4.6), two
+// launches the more sequences there are (40 rows each: 8 5.6 / 5.5, 32 8.2 / 5.6; 60 rows each: 12 5.9 / 7.4, 20 8.2 / 7.4, 64 13.5 / 7.5,
+// 512 70 / 25).
+constexpr int kSmallVocab = 1024;
+constexpr int kSmallNodes = 40;         // up to so many rows a sequence, or
+constexpr int64_t kSmallRowsInAll = 1200;   // from so many in all
+constexpr int kSmallWaves = 16;
+constexpr int kSmallRows = FSPAD_MAX_NODES / kSmallWaves;   // per wavefront
+template <bool VEC>
+__global__ __launch_bounds__(64 * kSmallWaves) void accept_greedy_small_kernel(const AcceptParams p) {
+  constexpr int kPieces = kSmallVocab / 256;   // of four logits a lane
+  __shared__ int amax[FSPAD_MAX_NODES];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t o = (int64_t)b * p.Nmax;
+  const int V = p.V;
+  auto entry = [&](int k, int j) { return VEC ? (k * 64 + lane) * 4 + j : (4 * k + j) * 64 + lane; };   // (increasing in every lane)
+  float x[kSmallRows][4 * kPieces];
+#pragma unroll
+  for (int r = 0; r < kSmallRows; ++r) {
+    if (wave + r * kSmallWaves >= p.Nmax) break;   // (rows of unused tree slots are asked for: which these are is known a trip later)
+    const float* row = p.logits + (o + wave + r * kSmallWaves) * p.row_stride;
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) {
+      if constexpr (VEC) {   // (V is a multiple of four; a piece past the end: the row's first)
+        const f32x4 v = *reinterpret_cast<const f32x4*>(row + (entry(k, 0) < V ? entry(k, 0) : 0));
+        x[r][4 * k] = v[0]; x[r][4 * k + 1] = v[1]; x[r][4 * k + 2] = v[2]; x[r][4 * k + 3] = v[3];
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[r][4 * k + j] = row[min(entry(k, j), V - 1)];
+      }
+    }
+  }
+  const int n = p.n_nodes[b];
+  int my_par = -2, my_tok = -1;
+  if (wave == 0 && lane < min(n, p.Nmax)) {
+    my_par = p.parent[o + lane];
+    my_tok = p.draft_tokens[o + lane];
+  }
+#pragma unroll
+  for (int r = 0; r < kSmallRows; ++r) {
+    const int node = wave + r * kSmallWaves;
+    if (node >= n || node >= p.Nmax) break;
+    float best = -INFINITY;
+    int idx = kNone;
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int e = entry(k, j);
+        if (e < V && x[r][4 * k + j] > best) { best = x[r][4 * k + j]; idx = e; }   // (a NaN is above nothing)
+      }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const float ov = __shfl_xor(best, off);
+      const int oi = __shfl_xor(idx, off);
+      take_better(best, idx, ov, oi);
+    }
+    if (lane == 0) amax[node] = idx == kNone ? 0 : idx;   // a row with nothing above -inf: token 0
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  fspad_detail::greedy_descend(amax, n, p.Nmax, lane, o, b, my_par, my_tok, p.path, p.tokens, p.path_len, p.n_tokens);
+}
+
 // ------------------------------------------------------------------------------------------------
 // The sampling walk runs with 1024 threads: its code runs once per call, so what it costs is the
 // longest chain of dependent fp64 instructions in any one thread and the number of instruction lines
@@ -1559,6 +1626,12 @@ extern "C" fspad_status fspad_tree_accept_greedy(int32_t B, int32_t Nmax, int32_
   AcceptParams p{};
   fill_params(p, B, Nmax, V, logits, row_stride, draft_tokens, parent, n_nodes, path, path_len, tokens, n_tokens, workspace);
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
+  if (V <= kSmallVocab && (Nmax <= kSmallNodes || (int64_t)B * Nmax >= kSmallRowsInAll)) {
+    const dim3 grid((unsigned)B), block(64 * kSmallWaves);
+    if (rows_vectorisable(logits, row_stride) && V % 4 == 0) hipLaunchKernelGGL(accept_greedy_small_kernel<true>, grid, block, 0, stream, p);
+    else hipLaunchKernelGGL(accept_greedy_small_kernel<false>, grid, block, 0, stream, p);
+    return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
+  }
   launch_rows<0>(p, rows_vectorisable(logits, row_stride), stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   hipLaunchKernelGGL(accept_greedy_walk_kernel, dim3((unsigned)B), dim3(kThreads), 0, stream, p);

@@ -107,6 +107,25 @@ def test_argmax_ties_nan_and_signed_zero(H):
     assert gpu[0][0].tolist() == [0, 1, -1] and gpu[2][0].tolist() == [10, 0, -1]
 
 
+@pytest.mark.parametrize("V", [1, 3, 4, 255, 256, 257, 1000, 1021, 1024, 1025])
+@pytest.mark.parametrize("B,N,pad", [(1, 1, 0), (3, 16, 3), (2, 17, 4), (2, 40, 1), (2, 41, 0), (19, 64, 0)])
+def test_greedy_small_vocabularies(H, B, N, V, pad):
+    """Around the sizes of the one-launch form: pieces of a row, rows of a wavefront, padded and unaligned rows, ragged trees; ties
+    across lanes and pieces, NaN, rows without a finite entry."""
+    n_nodes = [N] + [max(1, (7 * b) % (N + 1)) for b in range(1, B)]
+    logits = np.round(np.random.default_rng([V, N]).normal(0, 1.5, (B, N, V))).astype(np.float32)   # few values: ties everywhere
+    logits[0, 0, V // 2] = np.nan
+    logits[-1, -1] = -np.inf
+    logits[0, N // 2] = np.nan
+    from workloads import gen_trees
+    parent, n_nodes = gen_trees(3100 + V, B, N, 6, min(10, max(1, N - 1)), n_nodes=n_nodes)
+    rng = np.random.default_rng(V)
+    best = np.where(np.isnan(logits), -np.inf, logits).argmax(2)   # most nodes carry their parent's token, so walks go on
+    tokens = np.where(rng.random((B, N)) < 0.8, np.take_along_axis(best, np.maximum(parent, 0), 1), rng.integers(0, V, (B, N))).astype(np.int32)
+    case = H.AcceptCase(3100 + V, B, N, V, "greedy", row_pad=pad, parent=parent, n_nodes=n_nodes, logits=logits, tokens=tokens)
+    H.assert_accept_equal(case.gpu_greedy(), case.cpu_greedy())
+
+
 def test_sampling_enumeration_on_gpu(H):
     """The two-level, 4-token-vocabulary case of the oracle pins on a 10-point midpoint grid:
     the GPU must agree with the oracle on every one of the 10^4 walks, and the counts of the two
