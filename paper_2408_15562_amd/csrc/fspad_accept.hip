@@ -60,10 +60,7 @@ struct AcceptParams {
 };
 
 constexpr int32_t kAllRows = 0;
-// rows of leaves: of the first array the maximum alone, of the second nothing (the chip-wide walk of sampled drafts
-// tests no child there: it draws from weights that it forms itself, and the draft's row is not looked at)
-constexpr int32_t kSpareLeaves = 1;
-constexpr int32_t kInnerRows = 2;   // nodes that have children
+constexpr int32_t kInnerRows = 1;   // nodes that have children
 
 // Has a node a child among the n nodes of its tree (n <= Nmax), as the walk would test it? my_parent: of the node that is this
 // lane's number. (the same answer in every lane)
@@ -120,12 +117,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
   const int n = p.n_nodes[b];
   if (node >= n) return;  // rows of unused tree slots are never read
   const bool second = blockIdx.z != 0;
-  bool max_only = false;
-  if (MODE == 1 && p.rows != kAllRows) {
-    const bool leaf = !has_child(my_parent, min(n, p.Nmax), node);
-    if (leaf && (second || p.rows == kInnerRows)) return;
-    max_only = leaf && p.rows == kSpareLeaves;
-  }
+  if (MODE == 1 && p.rows == kInnerRows && !has_child(my_parent, min(n, p.Nmax), node)) return;
   const float* rp = (second ? p.logits2 : p.logits) + (int64_t)row * p.row_stride;
   float* const part_max = second ? p.part_max2 : p.part_max;
   double* const part_sum = second ? p.part_sum2 : p.part_sum;
@@ -170,7 +162,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
 #pragma unroll
     for (int k = 1; k < kPerThread; ++k) mt = fmaxf(mt, x[k]);
     double st = 0.0;
-    if (mt > -INFINITY && !max_only) {
+    if (mt > -INFINITY) {
       const double mtd = (double)mt;
 #pragma unroll
       for (int k = 0; k < kPerThread; ++k) st += exp_nonpos_table(((double)x[k] - mtd) * p.inv_temperature, exp2_table);
@@ -181,7 +173,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
     if (lane == 0) sh_max[wave] = mw;
     __syncthreads();
     const float mc = fmaxf(fmaxf(sh_max[0], sh_max[1]), fmaxf(sh_max[2], sh_max[3]));
-    double sum = mt > -INFINITY && !max_only ? st * exp_nonpos(((double)mt - (double)mc) * p.inv_temperature) : 0.0;
+    double sum = mt > -INFINITY ? st * exp_nonpos(((double)mt - (double)mc) * p.inv_temperature) : 0.0;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
     if (lane == 0) sh_sum[wave] = sum;
@@ -1189,7 +1181,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_row_merge_kernel(const Dr
   const int my_parent = lane_parent(p.parent + o, p.Nmax);
   const int n_all = p.n_nodes[b], n = min(n_all, p.Nmax);
   if (node >= n_all) return;   // rows of unused tree slots have no chunk statistics
-  if (arr && !has_child(my_parent, n, node)) return;   // (nor leaves of the draft's)
+  if (!has_child(my_parent, n, node)) return;   // (nor those of leaves: no child is tested there, and the draw takes none)
   // the logits of the children's tokens (wavefront 0, a lane each), asked for before the statistics
   bool child = tid < 64 && my_parent == node && tid > node && tid < n;
   float at_child = 0.f;
@@ -1225,6 +1217,7 @@ template <int E>
 __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(const DraftGridParams p) {
   __shared__ double sh_d[kGridWaves];
   __shared__ double sh_sums[2 * 3 * kGridWaves];
+  __shared__ float sh_f[kGridWaves];
   __shared__ int sh_w[2 * kGridWaves];
   __shared__ double sh_tot[2];
   // of an exchange: the sums of the new p and of what q keeps, the next test's entries; how it ended
@@ -1375,8 +1368,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     if (tid == 0) t_path[len - 1] = cur;
     const float* lrow = p.logits + (o + cur) * p.row_stride;
     const float* qrow = p.draft_logits + (o + cur) * p.row_stride;
-    // (rows of nodes beyond the tree are never walked: their entries hold no statistics; a leaf has the maximum of its target row
-    // only, which is all that the draw below takes: the rest is for tests of children)
+    // (rows of nodes beyond the tree are never walked; a leaf's hold no statistics either, which are for the tests of children)
     const double mp = t_stats[0][cur][0], zp = t_stats[0][cur][1], mq = t_stats[1][cur][0], zq = t_stats[1][cur][1];
     double sp = zp > 0.0 ? 1.0 / zp : 0.0, sq = zq > 0.0 ? 1.0 / zq : 0.0;
     int rejected = 0;
@@ -1412,11 +1404,17 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
         }
       }
     };
-    auto form_p = [&](int v) {   // p alone, for a draw at a node without a rejection
+    // p alone, for a draw at a node without a rejection, with the shift that a workgroup's own entries give: the largest of them
+    auto form_p = [&](int v) -> float {
       float xp[E];
       row_entries(lrow, v, xp);
+      float most = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < E; ++j) rp[j] = weight(xp[j], mp);
+      for (int j = 0; j < E; ++j) most = fmaxf(most, xp[j]);   // (a NaN is left out)
+      most = grid_wg_max(most, sh_f);
+#pragma unroll
+      for (int j = 0; j < E; ++j) rp[j] = weight(xp[j], (double)most);
+      return most;
     };
 
     bool moved = false;                // the last round's totals of the p in the registers are those of the new p
@@ -1485,12 +1483,12 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     if (how == 1 && !rejected) {
       const unsigned set = ++round % kGridSets;
       for (int of = alone ? 0 : g; of < (alone ? G : g + 1); ++of) {
-        form_p((of * kGridThreads + tid) * E);
-        double told[3] = {0.0, 0.0, 0.0};
+        const float most = form_p((of * kGridThreads + tid) * E);
+        double told[1] = {0.0};
 #pragma unroll
-        for (int j = 0; j < E; ++j) told[2] += rp[j];
-        grid_wg_sums<3>(told, sh_sums, flip);
-        if (tid == 0) leave_sums(set, of, 0.0, 0.0, told[2]);
+        for (int j = 0; j < E; ++j) told[0] += rp[j];
+        grid_wg_sums<1>(told, sh_sums, flip);
+        if (tid == 0) leave_sums(set, of, (double)most, 0.0, told[0]);
       }
       how = exchange(set, false);
       moved = false;
@@ -1506,14 +1504,22 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     // wavefront 0, one lane per workgroup (G <= 64): running sum of the totals, first workgroup above t
     static_assert(kGridMaxWgs <= 64, "one lane per workgroup");
     if (wave == 0) {
-      const double mine = moved ? slot_z : slot_t;   // (0 in lanes past the workgroups)
+      double mine = moved ? slot_z : slot_t, scale = 1.0;   // (0 in lanes past the workgroups)
+      if (!rejected) {   // the workgroups' weights have shifts of their own: slot_z
+        double most = mine > 0.0 ? slot_z : -INFINITY;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) most = fmax(most, __shfl_xor(most, off));
+        if (mine > 0.0) scale = exp_nonpos((slot_z - most) * p.inv_temperature);
+        mine *= scale;
+      }
       const double incl = wave_running_sum(mine);
       const double total = __shfl(incl, 63);
       const double t = (double)t_ud[cur] * total;
       const unsigned long long mass = __ballot(mine > 0.0), hit = __ballot(mine > 0.0 && incl > t);
       const int first = hit ? __ffsll(hit) - 1 : (mass ? 63 - __clzll(mass) : -1);
       // (no crossing by rounding: the last workgroup with mass, to its last entry with mass)
-      const double left = hit ? t - (__shfl(incl, first < 0 ? 0 : first) - __shfl(mine, first < 0 ? 0 : first)) : INFINITY;
+      const int at = first < 0 ? 0 : first;
+      const double left = hit ? (t - (__shfl(incl, at) - __shfl(mine, at))) / __shfl(scale, at) : INFINITY;
       if (lane == 0) { sh_w[0] = first; sh_tot[0] = left; }
     }
     __syncthreads();
@@ -1770,10 +1776,9 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
   // one streaming launch over both logit arrays (grid.z picks the array)
   AcceptParams both = pa;
   both.logits2 = draft_logits; both.part_max2 = pb.part_max; both.part_sum2 = pb.part_sum;
-  // The chip-wide walk needs less of the leaves' rows, which are more than half of a tree's: on the same six sets of inputs, 60 nodes,
-  // V = 128256, 78.5 -> 75.0 us a call (five processes, 0.951 to 0.966 of the time), 4 x 60 nodes 149 -> 132.
-  // (The one-workgroup form needs all.)
-  both.rows = plan.E != 0 ? kSpareLeaves : kAllRows;
+  // The chip-wide walk needs nothing of the leaves' rows, which are more than half of a tree's: no child is tested there, and the
+  // draw forms its weights itself (60 nodes, V = 128256, two sets of inputs: the maximum of every row formed 37.0 and 34.7 us, now 34.3 and 31.7). The one-workgroup form needs all.
+  both.rows = plan.E != 0 ? kInnerRows : kAllRows;
   launch_rows<1>(both, vec, stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   if (plan.E != 0) {
