@@ -1369,8 +1369,8 @@ __global__ __launch_bounds__(512) void tree_attn_gqa128_kernel(const SharedParam
     const int64_t first_byte = (int64_t)blk_begin * kBlockKeys * cache_row_bytes;
     const int64_t step = (int64_t)(KG * kBlockKeys) * cache_row_bytes;
 
-    // Where this wavefront's copies of block i of its key group come from. Every turn copies four pieces, so that the count of
-    // copies in flight tells what has landed; past the last block it is the segment's first row.
+    // Where this wavefront's copies of block i of its key group come from: four pieces a block, so that the count of
+    // copies in flight tells what has landed.
     const char *k_src = kc + first_byte, *v_src = vc + first_byte;
     unsigned row_at[2] = {(unsigned)copy_key * cache_row_bytes, (unsigned)(copy_key + 4) * cache_row_bytes};
     auto locate_rest = [&](int i) {   // not a whole prefix block
@@ -1638,40 +1638,38 @@ __global__ __launch_bounds__(256) void tree_attn_combine_kernel(const MergeParam
     const int64_t slot_floats = (int64_t)rows_per_unit * (D + 2);
     const float* o_base = p.part + (int64_t)slot * slot_floats + (SHARED ? partial_index<D>(lr, piece) : lr * D + d0);
     const float* ml_base = p.part + (int64_t)slot * slot_floats + (int64_t)rows_per_unit * D + 2 * lr;
-    // slots in index order (deterministic), up to eight at a time so that their loads are in flight together
+    // slots in index order (deterministic), eight at a time so that their loads are in flight together
     float M = kNegBig, denom = 0.f;
-    auto take = [&](auto count, int s0) {
-      constexpr int N = decltype(count)::value;
-      float2 ml[N];
-      f32x4 o[N];
+    for (int s0 = 0; s0 < n_seg; s0 += 8) {
+      float2 ml[8];
+      f32x4 o[8];
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
+      for (int k = 0; k < 8; ++k) {
         const int sidx = min(s0 + k, n_seg - 1);  // clamped duplicates get zero weight below
-        ml[k] = *reinterpret_cast<const float2*>(ml_base + sidx * slot_floats);
-        o[k] = *reinterpret_cast<const f32x4*>(o_base + sidx * slot_floats);
+        // Grouped heads: two, four or eight, as the unit has them. A ragged batch's units are cut in two or three, and eight loads of
+        // which five repeat the last one cost the texture path as much as eight: 16 sequences of 131 to 6011 keys 12.3 -> 8.6 us. (Sixteen
+        // changed nothing for units of sixteen pieces; elsewhere units have their eight, and the choice costs 0.1 us.)
+        if (!SHARED || k < 2 || n_seg - s0 > (k < 4 ? 2 : 4)) {
+          ml[k] = *reinterpret_cast<const float2*>(ml_base + sidx * slot_floats);
+          o[k] = *reinterpret_cast<const f32x4*>(o_base + sidx * slot_floats);
+        } else {
+          ml[k] = make_float2(kNegBig, 0.f);
+          o[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
       }
       float mx = M;
 #pragma unroll
-      for (int k = 0; k < N; ++k) mx = fmaxf(mx, ml[k].x);
+      for (int k = 0; k < 8; ++k) mx = fmaxf(mx, ml[k].x);
       const float a = __builtin_amdgcn_exp2f(M - mx);
       acc *= a;
       denom *= a;
       M = mx;
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
+      for (int k = 0; k < 8; ++k) {
         const float wgt = (s0 + k < n_seg) ? __builtin_amdgcn_exp2f(ml[k].x - M) : 0.f;
         denom += wgt * ml[k].y;
         acc += wgt * o[k];
       }
-    };
-    // (Grouped heads: a ragged batch's units are cut in two or three, and eight loads of which five repeat the last one cost the
-    // texture path as much as eight: 16 sequences of 131 to 6011 keys 12.3 -> 8.6 us. Sixteen at a time changed nothing for units
-    // of sixteen pieces; elsewhere units have their eight, and the choice costs 0.2 us of 16.)
-    for (int s0 = 0; s0 < n_seg; s0 += 8) {
-      const int left = n_seg - s0;
-      if (!SHARED || left > 4) take(std::integral_constant<int, 8>{}, s0);
-      else if (left > 2) take(std::integral_constant<int, 4>{}, s0);
-      else take(std::integral_constant<int, 2>{}, s0);
     }
     acc *= 1.0f / denom;
   }
