@@ -10,7 +10,8 @@
 // exp((l-max)/T)) for sampling. The second, one workgroup per sequence, merges the
 // chunk statistics of every row at once, walks the tree with wavefront ballots
 // out of LDS and, for sampling, draws the last token by an inverse-CDF search that
-// descends chunk -> thread segment -> element. (Large sampling calls: see kInnerFirst.)
+// descends chunk -> thread segment -> element. (Large sampling calls: see kInnerFirst; greedy calls of small vocabularies, one
+// launch: see kSmallVocab.)
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <stdint.h>

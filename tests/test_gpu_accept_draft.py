@@ -71,8 +71,8 @@ def test_both_launch_forms(B, N, V):
 
 
 def test_one_workspace_call_after_call():
-    """The chip-wide form keeps its arrival counts in the workspace and has the streaming pass of every
-    call set them to zero: calls that follow one another through one workspace (a larger problem, then a
+    """The chip-wide form exchanges its sums through the workspace and has an earlier launch of every
+    call set these places to zero: calls that follow one another through one workspace (a larger problem, then a
     smaller one, then the first again) each match the oracle."""
     import paper_2408_15562_amd as fspad
     shapes = [(2, 40, 20000), (1, 12, 3000), (2, 40, 20000)]
