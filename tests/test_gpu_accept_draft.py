@@ -253,3 +253,26 @@ def test_walk_without_one_of_its_workgroups(B, N, V, pad, noise):
         for name, g, f, c in zip(("path", "path_len", "tokens", "n_tokens"), out, full, ref[:4]):
             assert torch.equal(g, f), name
             np.testing.assert_array_equal(g.cpu().numpy()[keep], c[keep], err_msg=name)
+
+
+def test_calls_on_two_streams_at_once():
+    """Walks of two streams share the compute units, whole or in part: both end, with the outputs of calls that follow one another."""
+    import paper_2408_15562_amd as fspad
+    B, N, V, T = 4, 40, 60000, 1.0
+    streams, preps, outs = [torch.cuda.Stream() for _ in range(2)], [], []
+    for i, stream in enumerate(streams):
+        parent, n_nodes, logits, draft_logits, tokens = _case(8300 + i, B, N, V, T, peak=2.0, noise=0.7)
+        dev = [torch.from_numpy(a).to(DEV) for a in (logits, draft_logits, tokens, parent, n_nodes, gen_uniforms(i, B, N))]
+        alone = fspad.fspad_tree_accept_sample_draft(*dev[:5], T, dev[5])
+        out = [torch.full(shape, -77, dtype=torch.int32, device=DEV) for shape in ((B, N), (B,), (B, N), (B,))]
+        ws = torch.empty(fspad.fspad_tree_accept_sample_draft_workspace_bytes(B, N, V), dtype=torch.uint8, device=DEV)
+        preps.append(fspad.fspad_tree_accept_sample_draft(*dev[:5], T, dev[5], outputs=out, workspace=ws, stream=stream, prepare=True))
+        outs.append((out, alone))
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for call in preps:
+            call()
+    torch.cuda.synchronize()
+    for out, alone in outs:
+        for a, b in zip(out, alone):
+            assert torch.equal(a, b)
