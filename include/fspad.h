@@ -229,7 +229,7 @@ fspad_status fspad_tree_accept_sample(int32_t B, int32_t Nmax, int32_t V,
  *
  *   logits, draft_logits  dev [B,Nmax,V] fp32 with the same row_stride (>= V); row (b,i) of
  *                draft_logits is the distribution node i's children were drawn from. NaN
- *                entries carry no mass.
+ *                entries carry no mass; a row of logits with +infinity has none at all (token 0).
  *   draft_tokens, parent, n_nodes, temperature, uniforms, path, path_len, tokens, n_tokens:
  *                as for fspad_tree_accept_sample (tokens outside [0,V) are never accepted)
  *   workspace    dev, 16-byte aligned, >= fspad_tree_accept_sample_draft_workspace_bytes(B,Nmax,V)

@@ -1508,7 +1508,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     if (wave == 0) {
       double mine = moved ? slot_z : slot_t, scale = 1.0;   // (0 in lanes past the workgroups)
       if (!rejected) {   // the workgroups' weights have shifts of their own: slot_z
-        double most = mine > 0.0 ? slot_z : -INFINITY;
+        double most = lane < G ? slot_z : -INFINITY;   // (a largest entry of +infinity is the whole row's: no entry has mass then)
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) most = fmax(most, __shfl_xor(most, off));
         if (mine > 0.0) scale = exp_nonpos((slot_z - most) * p.inv_temperature);

@@ -179,6 +179,30 @@ def test_random_shape(draw):
          n_nodes=n_nodes, row_pad=int(rng.choice([0, 0, 4])), depth=8, topk=int(rng.integers(3, 11)), min_compared=max(1, B - 1))
 
 
+@pytest.mark.parametrize("B,V", [(2, 60000), (1, 128256), (6, 128256), (260, 600)])
+def test_plus_infinity_leaves_a_row_without_mass(B, V):
+    """A logit of +infinity leaves no entry of its row with mass, whichever workgroup holds it: token 0 comes out, as the oracle
+    says, of a leaf's row and of an inner row whose child is rejected, in every form of the call."""
+    import paper_2408_15562_amd as fspad
+    N = 3
+    rng = np.random.default_rng(V)
+    for at in (0, V // 2, V - 1):
+        logits = rng.normal(0, 2, (B, N, V)).astype(np.float32)
+        draft_logits = rng.normal(0, 2, (B, N, V)).astype(np.float32)
+        logits[:, :, at] = np.inf
+        parent = np.tile(np.array([-1, 0, 0], np.int32), (B, 1))
+        n_nodes = np.where(np.arange(B) % 2, 3, 1).astype(np.int32)     # roots alone, and roots with two children
+        tokens = rng.integers(1, V - 1, (B, N)).astype(np.int32)
+        uni = gen_uniforms(at, B, N)
+        out = fspad.fspad_tree_accept_sample_draft(*(torch.from_numpy(a).to(DEV) for a in (logits, draft_logits, tokens, parent, n_nodes)),
+                                                   0.9, torch.from_numpy(uni).to(DEV))
+        torch.cuda.synchronize()
+        with np.errstate(invalid="ignore"):
+            ref = oracle.accept_sample_draft(logits[:2], draft_logits[:2], tokens[:2], parent[:2], n_nodes[:2], 0.9, uni[:2])
+        assert (ref[2][:, 0] == 0).all() and (ref[1] == 1).all()
+        assert (out[1].cpu().numpy() == 1).all() and (out[2].cpu().numpy()[:, 0] == 0).all()
+
+
 def test_captured_call_replays_like_eager():
     import paper_2408_15562_amd as fspad
     B, N, V, T = 3, 30, 5000, 1.0
