@@ -10,8 +10,8 @@ _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libfspad.so")
 ROOFS_LIB_PATH = os.path.join(_HERE, "libfspad_roofs.so")   # the benchmark's measurement kernels, not the product
-# acceptance kernels of which the last workgroup of every sequence is left out, for the tests
-ABSENT_LIB_PATH = os.path.join(_HERE, "libfspad_absent.so")
+# the acceptance kernels with workgroups that start late, for the tests
+LATE_LIB_PATH = os.path.join(_HERE, "libfspad_late.so")
 OBJ_DIR = os.path.join(_HERE, "_build")
 SOURCES = ["fspad_host.cpp", "fspad_attn.hip", "fspad_accept.hip", "fspad_commit.hip", "fspad_tree.hip", "fspad_lmhead.hip",
            "fspad_topk.hip", "fspad_draft.hip"]
@@ -75,7 +75,7 @@ def build(force: bool = True, verbose: bool = False, defines=(), out: str = LIB_
         raise RuntimeError("link failed:\n" + proc.stdout + proc.stderr)
     if out == LIB_PATH:
         build_roofs(force=not only_changed)
-        build_absent(force=not only_changed)
+        build_late(force=not only_changed)
     if verbose:
         print("".join(log for _, log in results) + proc.stderr)
     return out
@@ -92,16 +92,16 @@ def build_roofs(force: bool = True) -> str:
     return ROOFS_LIB_PATH
 
 
-def build_absent(force: bool = True) -> str:
-    """The acceptance calls with a workgroup missing from every chip-wide walk: what the walk does where the device cannot
-    run all of them, without a device that is busy."""
+def build_late(force: bool = True) -> str:
+    """The acceptance calls with a chip-wide walk whose workgroups, from a number on that the caller sets, start late: what the
+    walk does where the device cannot run all of them at once, without a device that is busy. For the tests."""
     src = os.path.join(CSRC, "fspad_accept.hip")
-    if not force and os.path.exists(ABSENT_LIB_PATH) and os.path.getmtime(ABSENT_LIB_PATH) > max(os.path.getmtime(d) for d in _deps()):
-        return ABSENT_LIB_PATH
-    proc = subprocess.run(["hipcc"] + _FLAGS + ["-DFSPAD_TEST_ABSENT_WORKGROUP", "-shared", "-o", ABSENT_LIB_PATH, src], capture_output=True, text=True)
+    if not force and os.path.exists(LATE_LIB_PATH) and os.path.getmtime(LATE_LIB_PATH) > max(os.path.getmtime(d) for d in _deps()):
+        return LATE_LIB_PATH
+    proc = subprocess.run(["hipcc"] + _FLAGS + ["-DFSPAD_TEST_LATE_WORKGROUPS", "-shared", "-o", LATE_LIB_PATH, src], capture_output=True, text=True)
     if proc.returncode != 0:
         raise RuntimeError("hipcc failed on fspad_accept.hip:\n" + proc.stdout + proc.stderr)
-    return ABSENT_LIB_PATH
+    return LATE_LIB_PATH
 
 
 if __name__ == "__main__":

@@ -1079,9 +1079,10 @@ __global__ __launch_bounds__(kDraftThreads) void accept_sample_draft_kernel(cons
 //
 // The launch is an ordinary one, and whether all G workgroups run at the same time is found out on the way. Each counts
 // itself in when it starts; a workgroup whose numbers of the first round are there is running and will see the walk through.
-// The one that came first waits for the others for kArrivalTicks and then, if one has not even started (the compute units
-// may be held by another stream's kernels), closes the count and does the whole walk alone, workgroup by workgroup in a loop: the same
-// arithmetic in the same order, with a node's entries formed anew in every round from the logits and the rejections so far.
+// The one that came first waits for the others (the compute units may be held by another stream's kernels) for as long as the walk
+// would take those who are there, see wait_ticks, and then, if one has not even started, closes the count. Those who came
+// until then are the team: they take the G shares in turn, from the root on, with the same arithmetic in the same order. Who has more
+// shares than registers forms a node's entries anew in every round, from the logits and the rejections so far; who comes later leaves at once.
 // Nobody ever waits for a workgroup that has not started, so calls on several streams cannot hold each other up. A cooperative
 // launch, the form before, cost 14 us a call (the runtime orders it with signals), and its barrier (a fence, an arrival counter, a poll,
 // a fence, then the loads) 4 us a rejection. 60 nodes, V = 128256, 61.8 -> 32.9 us a call, both on the same inputs.
@@ -1093,16 +1094,11 @@ constexpr int kGridWaves = kGridThreads / 64;
 constexpr int kGridMaxWgs = 64;          // workgroups per sequence, at most
 constexpr unsigned kSpinLimit = 1u << 20;
 constexpr int kGridSets = 3;             // sets of places for the exchanges
-// 100 MHz ticks. The walk alone takes some hundred microseconds, so that is what waiting for the others may cost.
-constexpr long long kArrivalTicks = 30000;
-// the word that counts a sequence's workgroups in
-constexpr uint32_t kAlone = 1u << 31;    // closed: the first one goes on alone
+// the word that counts a sequence's workgroups in (low byte)
+constexpr uint32_t kClosed = 1u << 31;   // the count is closed; those who came until then, in the second byte, go on
 constexpr uint32_t kFailed = 1u << 30;
-#ifdef FSPAD_TEST_ABSENT_WORKGROUP       // (a build for the tests: the last workgroup of every sequence is never launched)
-constexpr int kAbsent = 1;
-#else
-constexpr int kAbsent = 0;
-#endif
+constexpr uint32_t kCount = 0xff;
+static_assert(kGridMaxWgs <= (int)kCount, "a byte each");
 
 struct DraftGridParams {
   const float* logits;
@@ -1122,14 +1118,19 @@ struct DraftGridParams {
   const double* part_sum_q;
   uint64_t* slots;     // [B][3][G][4]: per set and workgroup: sum of the new p, of what q keeps, of the old p
   uint64_t* pubs;      // [B][3][4]: the next test's entry of the new p, of the old p, of q
-  uint32_t* sync;      // [B]: workgroups that have started, kAlone, kFailed
+  uint32_t* sync;      // [B]: workgroups that have started, kClosed with the team's size, kFailed
   uint32_t* clear;     // all of these, as words that the merge launch sets to zero
   int32_t clear_count;
   double* row_stats;   // [2][B*Nmax][2]: (max, sum of exponentials) of every row of logits, then of draft_logits
   double* tests;       // [2][B*Nmax]: p(x), then q(x), of the node's token x at its parent
   double inv_temperature;
+  int64_t wait_ticks;  // what the first workgroup waits for the others, times the shares of a team of those who are there
   int32_t B, Nmax, V, n_chunks, G;
   int32_t vec;         // rows are 16-byte aligned
+#ifdef FSPAD_TEST_LATE_WORKGROUPS
+  int32_t late_from;   // workgroups of a sequence from this one on count themselves in when the count is closed, or late_ticks late
+  int64_t late_ticks;
+#endif
 };
 
 // K sums over the workgroup at once: running sums inside the wavefronts (no LDS), the four totals of each
@@ -1224,15 +1225,20 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
   __shared__ double sh_tot[2];
   // of an exchange: the sums of the new p and of what q keeps, the next test's entries; how it ended
   __shared__ double sh_round[5];
-  __shared__ int sh_how;
+  __shared__ int sh_how, sh_team;
   __shared__ uint32_t sh_order;
-  __shared__ double alone_slots[3][kGridMaxWgs];   // of a workgroup that goes on alone, in place of the slots in memory
   int flip = 0;
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int g = blockIdx.x;
-  const int G = p.G, V = p.V;
+  const int g = blockIdx.x, G = p.G, V = p.V;
   const int64_t o = (int64_t)b * p.Nmax;
   uint32_t* const sync = p.sync + b;
+#ifdef FSPAD_TEST_LATE_WORKGROUPS
+  if (g >= p.late_from)
+    for (const long long began = wall_clock64(); wall_clock64() - began < p.late_ticks;) {
+      if (__hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kClosed) break;
+      __builtin_amdgcn_s_sleep(16);
+    }
+#endif
   if (tid == 0) sh_order = __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int n = min(p.n_nodes[b], p.Nmax);
   uint64_t* const slots = p.slots + (int64_t)b * kGridSets * G * 4;
@@ -1263,9 +1269,11 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     t_ud[tid] = ok ? p.uniforms[(int64_t)b * 2 * p.Nmax + p.Nmax + tid] : 0.f;
   }
   __syncthreads();
-  const uint32_t order = sh_order;
-  if (order & kAlone) return;    // too late: the first one has gone on alone
-  bool alone = false;
+  const uint32_t order = __builtin_amdgcn_readfirstlane(sh_order);
+  if (order & kClosed) return;   // too late: the others have gone on
+  // this workgroup's shares of the entries: its own one, or every step-th of a team's
+  int first = g, step = G;
+  bool team = false;
 
   double rp[E], rq[E];   // unnormalised p and q of the current node, once a rejection or the draw has formed them
   unsigned round = 0;
@@ -1285,85 +1293,79 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     p.n_tokens[b] = len;
   };
   // The numbers of this round's `set` from all workgroups (pub: and the next test's entries): 1: they are in sh_round and the
-  // lanes' slot_z, slot_t; 0: leave; 2: go on alone, from the root.
+  // lanes' slot_z, slot_t; 0: leave; 2: go on as a team of sh_team, from the root.
   auto exchange = [&](unsigned set, bool pub) -> int {
-    if (alone) __syncthreads();
     if (wave == 0) {
-      int how = 1;
+      int how = 1, size = 0;
       double z = 0.0, s = 0.0, t = 0.0, e0 = 0.0, e1 = 0.0, e2 = 0.0;
-      if (alone) {
-        if (lane < G) { z = alone_slots[0][lane]; s = alone_slots[1][lane]; t = alone_slots[2][lane]; }
-      } else {
-        const uint64_t* const at = slots + ((int64_t)set * G + min(lane, G - 1)) * 4;
-        const uint64_t* const next = pubs + set * 4;
-        const long long began = wall_clock64();
-        for (unsigned polls = 0;; ++polls) {
-          const uint64_t a0 = poll(at), a1 = poll(at + 1), a2 = poll(at + 2);
-          uint64_t b0 = 1, b1 = 1, b2 = 1;
-          if (pub) { b0 = poll(next); b1 = poll(next + 1); b2 = poll(next + 2); }
-          const uint32_t word = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (__all(a0 != 0 && a1 != 0 && a2 != 0 && b0 != 0 && b1 != 0 && b2 != 0)) {
-            if (lane < G) { z = published(a0); s = published(a1); t = published(a2); }
-            e0 = published(b0); e1 = published(b1); e2 = published(b2);
-            break;
-          }
-          if (__any((word & (kAlone | kFailed)) != 0u)) { how = 0; break; }
-          if (round == 1 && order == 0 && wall_clock64() - began > kArrivalTicks) {
-            int closed = 0;
-            if (lane == 0 && word < (uint32_t)G) {
-              uint32_t expected = word;
-              closed = __hip_atomic_compare_exchange_strong(sync, &expected, word | kAlone, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            if (__any(closed)) { how = 2; break; }
-          }
-          if (polls > kSpinLimit) {
-            if (lane == 0) __hip_atomic_fetch_or(sync, kFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            how = 0;
-            break;
-          }
-          __builtin_amdgcn_s_sleep(1);
+      const uint64_t* const at = slots + ((int64_t)set * G + min(lane, G - 1)) * 4;
+      const uint64_t* const next = pubs + set * 4;
+      const long long began = wall_clock64();
+      for (unsigned polls = 0;; ++polls) {
+        const uint64_t a0 = poll(at), a1 = poll(at + 1), a2 = poll(at + 2);
+        uint64_t b0 = 1, b1 = 1, b2 = 1;
+        if (pub) { b0 = poll(next); b1 = poll(next + 1); b2 = poll(next + 2); }
+        const uint32_t polled = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (waited for only if the numbers are not there)
+        if (__all(a0 != 0 && a1 != 0 && a2 != 0 && b0 != 0 && b1 != 0 && b2 != 0)) {
+          if (lane < G) { z = published(a0); s = published(a1); t = published(a2); }
+          e0 = published(b0); e1 = published(b1); e2 = published(b2);
+          break;
         }
-        if (how == 0 && lane == 0) {
-          const uint32_t word = __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (word & kFailed) {
-            for (int i = 0; i < p.Nmax; ++i) { p.path[o + i] = i == 0 ? 0 : -1; p.tokens[o + i] = -1; }
-            p.path_len[b] = -1;
-            p.n_tokens[b] = -1;
+        const uint32_t word = __builtin_amdgcn_readfirstlane(polled);
+        if (word & kFailed) { how = 0; break; }
+        if (!team && (word & kClosed)) { how = 2; size = (word >> 8) & kCount; break; }
+        if (round == 1 && order == 0 && word < (uint32_t)G && wall_clock64() - began > p.wait_ticks * ((G + (int)word - 1) / (int)word)) {
+          int closed = 0;
+          if (lane == 0) {
+            uint32_t expected = word;
+            closed = __hip_atomic_compare_exchange_strong(sync, &expected, word | (word << 8) | kClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
+          if (__any(closed)) { how = 2; size = word; break; }
         }
+        if (polls > kSpinLimit) {
+          if (lane == 0) __hip_atomic_fetch_or(sync, kFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          how = 0;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+      if (how == 0 && lane == 0) {
+        for (int i = 0; i < p.Nmax; ++i) { p.path[o + i] = i == 0 ? 0 : -1; p.tokens[o + i] = -1; }
+        p.path_len[b] = -1;
+        p.n_tokens[b] = -1;
       }
       const double Z = wave_running_sum(z), S = wave_running_sum(s);
       slot_z = z;
       slot_t = t;
       if (lane == 63) {
-        sh_round[0] = Z; sh_round[1] = S;
-        if (!alone) { sh_round[2] = e0; sh_round[3] = e1; sh_round[4] = e2; }
+        sh_round[0] = Z; sh_round[1] = S; sh_round[2] = e0; sh_round[3] = e1; sh_round[4] = e2;
         sh_how = how;
+        sh_team = size;
       }
       // Who is here has all numbers of this round, so all are done with the round before: its places are emptied (they are used
-      // again in the round after the next, and this workgroup's numbers of the next one leave behind this).
-      if (!alone && how == 1 && lane == 0) {
+      // again in the round after the next, and this workgroup's numbers of the next one leave behind this). In a team's first round
+      // these are the places of round 1: what was stored there has arrived, see below, before its writer's numbers of this round left.
+      if (how == 1) {
         const unsigned old = set == 0 ? kGridSets - 1 : set - 1;
-        uint64_t* const mine = slots + ((int64_t)old * G + g) * 4;
+        if (lane * step < G - first) {   // (lane 0 alone, but in a team)
+          uint64_t* const place = slots + (old * (unsigned)G + (unsigned)(first + lane * step)) * 4u;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          __hip_atomic_store(mine + k, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (g == 0) __hip_atomic_store(pubs + old * 4 + k, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          for (int k = 0; k < 3; ++k) __hip_atomic_store(place + k, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (first == 0 && lane == 0) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) __hip_atomic_store(pubs + old * 4 + k, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
     }
     __syncthreads();
     return sh_how;
   };
-  // a workgroup's sums of a round, one thread
+  // the sums of a share in a round, thread 0
   auto leave_sums = [&](unsigned set, int of, double z, double s, double t) {
-    if (alone) {
-      alone_slots[0][of] = z; alone_slots[1][of] = s; alone_slots[2][of] = t;
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the emptied places are
-      uint64_t* const mine = slots + ((int64_t)set * G + of) * 4;
-      publish(mine, z); publish(mine + 1, s); publish(mine + 2, t);
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the emptied places are (this wavefront's lanes have emptied them)
+    uint64_t* const mine = slots + ((int64_t)set * G + of) * 4;
+    publish(mine, z); publish(mine + 1, s); publish(mine + 2, t);
   };
 
   for (;;) {
@@ -1388,7 +1390,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
       }
     };
     auto weight = [&](float a, double m) { return (a == a && m > -INFINITY) ? exp_nonpos(((double)a - m) * p.inv_temperature) : 0.0; };
-    // p and q from the logits, and the rejections so far (which only a workgroup that is alone does not have in its registers)
+    // p and q of a share from the logits, and the rejections so far (which only a team does not have in its registers)
     auto form = [&](int v) {
       float xp[E], xq[E];
       row_entries(lrow, v, xp);
@@ -1439,9 +1441,9 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
       const int x2 = children ? t_tok[__ffsll(children) - 1] : -1;
       const unsigned set = ++round % kGridSets;
       double rn[E];
-      for (int of = alone ? 0 : g; of < (alone ? G : g + 1); ++of) {
+      for (int of = first; of < G; of += step) {
         const int e0 = (of * kGridThreads + tid) * E;   // this thread's E consecutive entries
-        if (alone || !rejected) form(e0);
+        if (team || !rejected) form(e0);
         double three[3] = {0.0, 0.0, 0.0};
 #pragma unroll
         for (int j = 0; j < E; ++j) {
@@ -1451,10 +1453,14 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
           const double keep = (valid && v == x) ? 0.0 : qv;
           rn[j] = r; rq[j] = keep;
           three[0] += r; three[1] += keep; three[2] += pold;
-          if (v == x2 && v < V) {
-            if (alone) { sh_round[2] = r; sh_round[3] = pold; sh_round[4] = keep; }
-            else { publish(pubs + set * 4, r); publish(pubs + set * 4 + 1, pold); publish(pubs + set * 4 + 2, keep); }
-          }
+        }
+        // (behind the loop: as a branch for every entry in it, 32 rejections of V = 500 000 took 155 us instead of 131)
+        if ((unsigned)x2 - (unsigned)e0 < (unsigned)E && x2 < V) {
+          double r = rn[0], pold = rp[0], keep = rq[0];
+#pragma unroll
+          for (int j = 1; j < E; ++j)
+            if (e0 + j == x2) { r = rn[j]; pold = rp[j]; keep = rq[j]; }
+          publish(pubs + set * 4, r); publish(pubs + set * 4 + 1, pold); publish(pubs + set * 4 + 2, keep);
         }
         grid_wg_sums<3>(three, sh_sums, flip);
         if (tid == 0) leave_sums(set, of, three[0], three[1], three[2]);
@@ -1473,7 +1479,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
       sq = S > 0.0 ? 1.0 / S : sq;
       pub_p = moved ? sh_round[2] : sh_round[3];
       pub_q = sh_round[4];
-      if (alone) __syncthreads();   // (the history and the next round's entries go through LDS)
+      if (team) __syncthreads();   // (the history goes through LDS)
     }
     if (how == 1 && next >= 0) {
       ++len;
@@ -1484,7 +1490,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     // no child accepted: inverse-CDF draw from the current p, located from the workgroups' totals
     if (how == 1 && !rejected) {
       const unsigned set = ++round % kGridSets;
-      for (int of = alone ? 0 : g; of < (alone ? G : g + 1); ++of) {
+      for (int of = first; of < G; of += step) {
         const float most = form_p((of * kGridThreads + tid) * E);
         double told[1] = {0.0};
 #pragma unroll
@@ -1497,10 +1503,13 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     }
     if (how == 0) return;
     if (how == 2) {
-      alone = true;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // what this workgroup has stored in round 1 has arrived
+      first = (int)order;
+      step = __builtin_amdgcn_readfirstlane(sh_team);
+      team = true;
       cur = 0;
       len = 1;
-      __syncthreads();   // sh_how is read
+      __syncthreads();   // sh_how and sh_team are read
       continue;
     }
     // wavefront 0, one lane per workgroup (G <= 64): running sum of the totals, first workgroup above t
@@ -1529,20 +1538,19 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     const double target = sh_tot[0];
     __syncthreads();   // sh_w is written again below
     if (owner < 0) {                                            // no mass at all: token 0
-      if (g == 0 || alone) {
+      if (first == 0) {
         write_walk();
         if (tid == 0) write_last(0);
       }
       return;
     }
-    if (alone) {
-      g = owner;
-      if (rejected) form((g * kGridThreads + tid) * E);
-      else form_p((g * kGridThreads + tid) * E);
-    }
-    if (g != owner) return;
+    if (owner % step != first) return;
     write_walk();
-    const int e0 = (g * kGridThreads + tid) * E;
+    const int e0 = (owner * kGridThreads + tid) * E;
+    if (team) {
+      if (rejected) form(e0);
+      else form_p(e0);
+    }
     double local = 0.0;
     int last_here = -1;
 #pragma unroll
@@ -1616,6 +1624,13 @@ GridPlan plan_draft_grid(int32_t B, int32_t Nmax, int32_t V) {
 }
 
 }  // namespace
+
+#ifdef FSPAD_TEST_LATE_WORKGROUPS   // (a build for the tests, which set these: see DraftGridParams)
+extern "C" {
+int32_t fspad_test_late_from = 64;
+int64_t fspad_test_late_ticks = 0;
+}
+#endif
 
 extern "C" size_t fspad_tree_accept_workspace_bytes(int32_t B, int32_t Nmax, int32_t V) {
   if (B < 1 || Nmax < 1 || V < 1) return 0;
@@ -1798,9 +1813,19 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
     gp.tests = reinterpret_cast<double*>(work + plan.tests_at);
     gp.inv_temperature = pa.inv_temperature;
     gp.B = B; gp.Nmax = Nmax; gp.V = V; gp.n_chunks = pa.n_chunks; gp.G = plan.G; gp.vec = vec;
+    // About what a share costs a team in a walk of a root, a few rejections and a draw (100 MHz ticks; 3 us a share and round with four
+    // entries a thread, 10 with 32), so that a call takes at most about twice as long as if it had known. Walks with the given number of
+    // workgroups there, wait and all, us: 60 nodes, V = 128256 (63 shares): 1 1480, 4 405, 16 134, 32 to 62 87, all 37; 32 rejections
+    // at the root: 1 10800, 16 790, all 104; V = 500 000 (62 shares of 32 entries a thread), draw at the root 2760, all 16. The form
+    // before waited 300 us and then walked alone, however many were there: 790, 10100 and 580.
+    gp.wait_ticks = 100 * (8 + plan.E);
+#ifdef FSPAD_TEST_LATE_WORKGROUPS
+    gp.late_from = fspad_test_late_from;
+    gp.late_ticks = fspad_test_late_ticks;
+#endif
     hipLaunchKernelGGL(accept_row_merge_kernel, dim3((unsigned)(B * Nmax), 2u), dim3(kGridThreads), 0, stream, gp);
     if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
-    const dim3 grid((unsigned)std::max(1, plan.G - kAbsent), (unsigned)B), block(kGridThreads);
+    const dim3 grid((unsigned)plan.G, (unsigned)B), block(kGridThreads);
     switch (plan.E) {
       case 4: hipLaunchKernelGGL(accept_sample_draft_grid_kernel<4>, grid, block, 0, stream, gp); break;
       case 8: hipLaunchKernelGGL(accept_sample_draft_grid_kernel<8>, grid, block, 0, stream, gp); break;

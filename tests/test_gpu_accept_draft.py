@@ -239,44 +239,112 @@ def test_captured_call_replays_like_eager():
             assert torch.equal(a, b)
 
 
-def _absent_call(B, N, V, T, dev, outputs, workspace):
-    """The same entry point of the build whose chip-wide walks lack the last workgroup of every sequence."""
+@pytest.fixture(scope="module")
+def late_call():
+    """The same entry point of the build whose chip-wide walks have late workgroups: from the late_from-th of every sequence on they
+    count themselves in when the others have gone on, or late_us after their start."""
     import ctypes
 
     from paper_2408_15562_amd import build
-    f = ctypes.CDLL(build.ABSENT_LIB_PATH).fspad_tree_accept_sample_draft
+    lib = ctypes.CDLL(build.build_late(force=False))
+    f = lib.fspad_tree_accept_sample_draft
     vp = ctypes.c_void_p
     f.restype = ctypes.c_int
     f.argtypes = [ctypes.c_int32] * 3 + [vp, vp, ctypes.c_int64] + [vp] * 3 + [ctypes.c_float] + [vp] * 6 + [ctypes.c_size_t, vp]
-    logits, draft_logits, tokens, parent, n_nodes, uni = dev
-    return f(B, N, V, logits.data_ptr(), draft_logits.data_ptr(), logits.stride(1), tokens.data_ptr(), parent.data_ptr(), n_nodes.data_ptr(),
-             T, uni.data_ptr(), *(t.data_ptr() for t in outputs), workspace.data_ptr(), workspace.numel(),
-             torch.cuda.current_stream().cuda_stream)
+
+    def call(late_from, late_us, B, N, V, T, dev, outputs, workspace):
+        ctypes.c_int32.in_dll(lib, "fspad_test_late_from").value = late_from
+        ctypes.c_int64.in_dll(lib, "fspad_test_late_ticks").value = int(100 * late_us)
+        logits, draft_logits, tokens, parent, n_nodes, uni = dev
+        return f(B, N, V, logits.data_ptr(), draft_logits.data_ptr(), logits.stride(1), tokens.data_ptr(), parent.data_ptr(),
+                 n_nodes.data_ptr(), T, uni.data_ptr(), *(t.data_ptr() for t in outputs), workspace.data_ptr(), workspace.numel(),
+                 torch.cuda.current_stream().cuda_stream)
+    return call
 
 
-@pytest.mark.parametrize("B,N,V,pad", [(1, 26, 2000, 0), (2, 40, 20000, 4), (1, 60, 128256, 0), (3, 30, 50257, 1), (40, 8, 5000, 0),
-                                       (1, 12, 300001, 0), (2, 1, 4097, 0)])
-@pytest.mark.parametrize("noise", [0.3, 1.0])
-def test_walk_without_one_of_its_workgroups(B, N, V, pad, noise):
-    """Every share of entries per thread, rows of any alignment: the workgroup that came first goes on alone, with the outputs of
-    the full walk (the same arithmetic) and of the oracle. A second call through the same workspace does the same."""
+def _late_case(seed, B, N, V, T, noise, pad=0, wide=False):
+    """Inputs on the device, outputs of the full walk, and a workspace of NaN."""
     import paper_2408_15562_amd as fspad
-    T = 0.9
-    parent, n_nodes, logits, draft_logits, tokens = _case(8100 + B + N + V, B, N, V, T, peak=2.0, noise=noise)
+    parent, n_nodes, logits, draft_logits, tokens = _case(seed, B, N, V, T, peak=2.0, noise=noise)
+    if wide:   # every node a child of the root, and none of them accepted
+        parent, n_nodes = np.zeros((B, N), np.int32), np.full(B, N, np.int32)
+        parent[:, 0] = -1
+        tokens[:, 1::2] = V
+        tokens[:, 2::2] = draft_logits[:, 0].argmax(1)[:, None]
+        logits[np.arange(B), 0, tokens[:, 2]] = -20.0
     uni = gen_uniforms(3, B, N)
     dev = [_padded(logits, pad), _padded(draft_logits, pad)] + [torch.from_numpy(a).to(DEV) for a in (tokens, parent, n_nodes, uni)]
     full = fspad.fspad_tree_accept_sample_draft(*dev[:5], T, dev[5])
     ws = torch.full((fspad.fspad_tree_accept_sample_draft_workspace_bytes(B, N, V),), 0xFF, dtype=torch.uint8, device=DEV)
-    ref = oracle.accept_sample_draft(logits, draft_logits, tokens, parent, n_nodes, T, uni)
+    return dev, full, ws, oracle.accept_sample_draft(logits, draft_logits, tokens, parent, n_nodes, T, uni)
+
+
+@pytest.mark.parametrize("B,N,V,pad", [(1, 26, 2000, 0), (2, 40, 20000, 4), (1, 60, 128256, 0), (3, 30, 50257, 1), (40, 8, 5000, 0),
+                                       (5, 20, 128256, 0), (1, 12, 300001, 0), (2, 1, 4097, 0)])
+@pytest.mark.parametrize("noise", [0.3, 1.0])
+@pytest.mark.parametrize("there", [1, 2, 3, 7, 62])
+def test_walk_by_the_workgroups_that_are_there(late_call, B, N, V, pad, noise, there):
+    """Shares of 4, 8, 16 and 32 entries per thread, rows of any alignment, one workgroup or several that take all shares: the outputs
+    of the full walk (the same arithmetic) and of the oracle. Who comes late finds the count closed and touches nothing.
+    A second call through the same workspace does the same."""
+    T = 0.9
+    dev, full, ws, ref = _late_case(8100 + B + N + V, B, N, V, T, noise, pad)
     keep = ref[4] >= MARGIN
     assert keep.sum() >= max(1, B - 1)
     for _ in range(2):
         out = [torch.full(shape, -77, dtype=torch.int32, device=DEV) for shape in ((B, N), (B,), (B, N), (B,))]
-        assert _absent_call(B, N, V, T, dev, out, ws) == 0
+        assert late_call(there, 50e3, B, N, V, T, dev, out, ws) == 0
         torch.cuda.synchronize()
         for name, g, f, c in zip(("path", "path_len", "tokens", "n_tokens"), out, full, ref[:4]):
             assert torch.equal(g, f), name
             np.testing.assert_array_equal(g.cpu().numpy()[keep], c[keep], err_msg=name)
+
+
+@pytest.mark.parametrize("B,N,V", [(1, 33, 60000), (2, 20, 300001)])
+@pytest.mark.parametrize("there", [1, 5])
+def test_many_rejections_by_the_workgroups_that_are_there(late_call, B, N, V, there):
+    """More rounds than places to exchange in, on shares whose entries are formed anew in every one."""
+    T = 1.0
+    dev, full, ws, ref = _late_case(8500 + V, B, N, V, T, 1.0, wide=True)
+    assert ref[1].tolist() == [1] * B
+    out = [torch.full(shape, -77, dtype=torch.int32, device=DEV) for shape in ((B, N), (B,), (B, N), (B,))]
+    assert late_call(there, 50e3, B, N, V, T, dev, out, ws) == 0
+    torch.cuda.synchronize()
+    for g, f in zip(out, full):
+        assert torch.equal(g, f)
+
+
+def test_workgroups_that_come_as_the_count_is_closed(late_call):
+    """Starts from 0 to some 70 us late, the first workgroup's wait (24 us here) among them: whether the count is closed before,
+    after or while they come, the outputs are those of the full walk."""
+    B, N, V, T = 3, 40, 60000, 0.9
+    dev, full, ws, _ = _late_case(8600, B, N, V, T, 0.7)
+    for there in (40, 58):
+        for late_us in [0, 5, 10] + list(range(15, 45)) + [50, 60, 70]:
+            out = [torch.full(shape, -77, dtype=torch.int32, device=DEV) for shape in ((B, N), (B,), (B, N), (B,))]
+            assert late_call(there, late_us, B, N, V, T, dev, out, ws) == 0
+            torch.cuda.synchronize()
+            for g, f in zip(out, full):
+                assert torch.equal(g, f), (there, late_us)
+
+
+def test_a_walk_without_all_of_its_workgroups_is_not_a_walk_alone(late_call):
+    """Where a fourth of the workgroups are there, the call takes a small part of what one of them alone takes: all of them go on."""
+    B, N, V, T = 1, 33, 128256, 1.0
+    dev, full, ws, _ = _late_case(8700, B, N, V, T, 1.0, wide=True)
+    out = [torch.full(shape, -77, dtype=torch.int32, device=DEV) for shape in ((B, N), (B,), (B, N), (B,))]
+    took = {}
+    for there in (1, 16):
+        for _ in range(3):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            assert late_call(there, 50e3, B, N, V, T, dev, out, ws) == 0
+            b.record()
+            torch.cuda.synchronize()
+            took[there] = min(took.get(there, np.inf), a.elapsed_time(b))
+        for g, f in zip(out, full):
+            assert torch.equal(g, f)
+    assert took[16] < 0.25 * took[1], took   # (63 shares: 4 of them at most instead of 63, and the waits shorter likewise)
 
 
 def test_calls_on_two_streams_at_once():
