@@ -75,7 +75,6 @@ def build(force: bool = True, verbose: bool = False, defines=(), out: str = LIB_
         raise RuntimeError("link failed:\n" + proc.stdout + proc.stderr)
     if out == LIB_PATH:
         build_roofs(force=not only_changed)
-        build_late(force=not only_changed)
     if verbose:
         print("".join(log for _, log in results) + proc.stderr)
     return out
@@ -94,7 +93,7 @@ def build_roofs(force: bool = True) -> str:
 
 def build_late(force: bool = True) -> str:
     """The acceptance calls with a chip-wide walk whose workgroups, from a number on that the caller sets, start late: what the
-    walk does where the device cannot run all of them at once, without a device that is busy. For the tests."""
+    walk does where the device cannot run all of them at once, without a device that is busy. For the tests, which ask for it."""
     src = os.path.join(CSRC, "fspad_accept.hip")
     if not force and os.path.exists(LATE_LIB_PATH) and os.path.getmtime(LATE_LIB_PATH) > max(os.path.getmtime(d) for d in _deps()):
         return LATE_LIB_PATH
