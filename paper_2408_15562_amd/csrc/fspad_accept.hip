@@ -262,14 +262,17 @@ __global__ __launch_bounds__(kThreads) void accept_greedy_walk_kernel(const Acce
 }
 
 // The same in one launch where a row has up to kSmallVocab logits: sixteen to a lane, a wavefront for up to four rows, whose loads are
-// under way together and with the tree's. Such a call is launches and trips to memory: 26 rows of 1000 5.3 -> 4.4 us, a call's
-// share of a graph of a hundred, and 17.0 -> 13.9 us the step of attention, acceptance and commit around it. One workgroup per sequence
-// takes longer the more rows it has (us before / so, rows of 1000: 32 5.3 / 4.8, 40 5.3 / 5.3, 64 5.3 / 7.6, unaligned 26 5.4 / 4.6), two
-// launches the more sequences there are (40 rows each: 8 5.6 / 5.5, 32 8.2 / 5.6; 60 rows each: 12 5.9 / 7.4, 20 8.2 / 7.4, 64 13.5 / 7.5,
-// 512 70 / 25).
+// under way together and with the tree's. (Four rows of sixteen are 64 of the 128 registers that a wavefront of sixteen can have: longer
+// rows would need a loop. Rows of unused tree slots are not read: waiting for the number of nodes first costs 0.13 us.) Such a call is
+// launches and trips to memory, us by two launches / so, rows of 1000, a call's share of a graph of a hundred: 1 row 4.6 / 2.6, 16 5.2 / 3.3,
+// 26 5.1 / 4.5, 32 5.2 / 4.9, not aligned 5.3 / 5.1; and 17.0 -> 13.9 the step of attention, acceptance and commit around 26. One workgroup per
+// sequence takes longer the more rows it has, two launches the more there are in all: 8 x 36 5.43 / 5.41, not aligned 5.7 / 5.6, 1 x 40 5.2 / 5.35, not
+// aligned 5.3 / 5.6, 25 x 48 8.1 / 6.9, 17 x 60 6.1 / 7.6, 20 x 60 8.1 / 7.6, 19 x 64 8.1 / 8.3, 21 x 64 8.5 / 8.4, 64 x 64 14.0 / 8.4, 512 x 64 74 / 27.5
+// and with 4 nodes each 42 / 5.0.
 constexpr int kSmallVocab = 1024;
-constexpr int kSmallNodes = 40;         // up to so many rows a sequence, or
-constexpr int64_t kSmallRowsInAll = 1200;   // from so many in all
+bool takes_small_greedy(int32_t B, int32_t Nmax, int32_t V) {
+  return V <= kSmallVocab && (Nmax <= 40 || (int64_t)B * Nmax >= 1200);
+}
 constexpr int kSmallWaves = 16;
 constexpr int kSmallRows = FSPAD_MAX_NODES / kSmallWaves;   // per wavefront
 template <bool VEC>
@@ -279,11 +282,17 @@ __global__ __launch_bounds__(64 * kSmallWaves) void accept_greedy_small_kernel(c
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t o = (int64_t)b * p.Nmax;
   const int V = p.V;
+  const int n = p.n_nodes[b];
+  int my_par = -2, my_tok = -1;
+  if (wave == 0 && lane < min(n, p.Nmax)) {
+    my_par = p.parent[o + lane];
+    my_tok = p.draft_tokens[o + lane];
+  }
   auto entry = [&](int k, int j) { return VEC ? (k * 64 + lane) * 4 + j : (4 * k + j) * 64 + lane; };   // (increasing in every lane)
   float x[kSmallRows][4 * kPieces];
 #pragma unroll
   for (int r = 0; r < kSmallRows; ++r) {
-    if (wave + r * kSmallWaves >= p.Nmax) break;   // (rows of unused tree slots are asked for: which these are is known a trip later)
+    if (wave + r * kSmallWaves >= min(n, p.Nmax)) break;   // rows of unused tree slots are never read
     const float* row = p.logits + (o + wave + r * kSmallWaves) * p.row_stride;
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
@@ -295,12 +304,6 @@ __global__ __launch_bounds__(64 * kSmallWaves) void accept_greedy_small_kernel(c
         for (int j = 0; j < 4; ++j) x[r][4 * k + j] = row[min(entry(k, j), V - 1)];
       }
     }
-  }
-  const int n = p.n_nodes[b];
-  int my_par = -2, my_tok = -1;
-  if (wave == 0 && lane < min(n, p.Nmax)) {
-    my_par = p.parent[o + lane];
-    my_tok = p.draft_tokens[o + lane];
   }
 #pragma unroll
   for (int r = 0; r < kSmallRows; ++r) {
@@ -1649,7 +1652,7 @@ extern "C" fspad_status fspad_tree_accept_greedy(int32_t B, int32_t Nmax, int32_
   AcceptParams p{};
   fill_params(p, B, Nmax, V, logits, row_stride, draft_tokens, parent, n_nodes, path, path_len, tokens, n_tokens, workspace);
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-  if (V <= kSmallVocab && (Nmax <= kSmallNodes || (int64_t)B * Nmax >= kSmallRowsInAll)) {
+  if (takes_small_greedy(B, Nmax, V)) {
     const dim3 grid((unsigned)B), block(64 * kSmallWaves);
     if (rows_vectorisable(logits, row_stride) && V % 4 == 0) hipLaunchKernelGGL(accept_greedy_small_kernel<true>, grid, block, 0, stream, p);
     else hipLaunchKernelGGL(accept_greedy_small_kernel<false>, grid, block, 0, stream, p);

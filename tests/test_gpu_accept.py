@@ -126,6 +126,33 @@ def test_greedy_small_vocabularies(H, B, N, V, pad):
     H.assert_accept_equal(case.gpu_greedy(), case.cpu_greedy())
 
 
+def test_rows_of_unused_slots_are_not_read():
+    """Small vocabularies: a batch of trees of two nodes in 64 slots takes a small part of the time of full trees."""
+    import paper_2408_15562_amd as fspad
+    B, N, V = 1000, 64, 1000
+    logits = torch.randn((B, N, V), device="cuda:0")
+    tokens = torch.zeros((B, N), dtype=torch.int32, device="cuda:0")
+    parent = torch.zeros_like(tokens)
+    parent[:, 0] = -1
+    out = [torch.empty(shape, dtype=torch.int32, device="cuda:0") for shape in ((B, N), (B,), (B, N), (B,))]
+    ws = torch.empty(fspad.fspad_tree_accept_workspace_bytes(B, N, V), dtype=torch.uint8, device="cuda:0")
+    took = {}
+    for n in (2, N):
+        n_nodes = torch.full((B,), n, dtype=torch.int32, device="cuda:0")
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+            for _ in range(20):
+                fspad.fspad_tree_accept_greedy(logits, tokens, parent, n_nodes, outputs=out, workspace=ws)
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            took[n] = min(took.get(n, np.inf), a.elapsed_time(b))
+    assert took[2] < 0.4 * took[N], took   # (rows read in whole: 0.7 of it; not read: a thirty-second of the rows, and the launches)
+
+
 def test_sampling_enumeration_on_gpu(H):
     """The two-level, 4-token-vocabulary case of the oracle pins on a 10-point midpoint grid:
     the GPU must agree with the oracle on every one of the 10^4 walks, and the counts of the two
