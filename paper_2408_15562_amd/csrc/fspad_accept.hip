@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void accept_greedy_walk_kernel(const Acce
 // and with 4 nodes each 42 / 5.0.
 constexpr int kSmallVocab = 1024;
 bool takes_small_greedy(int32_t B, int32_t Nmax, int32_t V) {
-  return V <= kSmallVocab && (Nmax <= 40 || (int64_t)B * Nmax >= 1200);
+  return V <= kSmallVocab && (Nmax <= 36 || (int64_t)B * Nmax >= (Nmax <= 60 ? 1200 : 1300));
 }
 constexpr int kSmallWaves = 16;
 constexpr int kSmallRows = FSPAD_MAX_NODES / kSmallWaves;   // per wavefront

@@ -108,7 +108,8 @@ def test_argmax_ties_nan_and_signed_zero(H):
 
 
 @pytest.mark.parametrize("V", [1, 3, 4, 255, 256, 257, 1000, 1021, 1024, 1025])
-@pytest.mark.parametrize("B,N,pad", [(1, 1, 0), (3, 16, 3), (2, 17, 4), (2, 40, 1), (2, 41, 0), (19, 64, 0)])
+@pytest.mark.parametrize("B,N,pad", [(1, 1, 0), (3, 16, 3), (2, 17, 4), (2, 40, 1), (2, 41, 0), (19, 64, 0),
+                                     (2, 36, 1), (2, 37, 0), (20, 60, 0), (21, 62, 0)])
 def test_greedy_small_vocabularies(H, B, N, V, pad):
     """Around the sizes of the one-launch form: pieces of a row, rows of a wavefront, padded and unaligned rows, ragged trees; ties
     across lanes and pieces, NaN, rows without a finite entry."""
