@@ -1115,16 +1115,15 @@ struct DraftGridParams {
   int32_t* path_len;
   int32_t* tokens;
   int32_t* n_tokens;
-  const float* part_max_p;
-  const double* part_sum_p;
-  const float* part_max_q;
-  const double* part_sum_q;
+  float* part_max_p;   // chunk statistics of every row of logits, then of draft_logits; the merge launch leaves the row's own
+  double* part_sum_p;  // (maximum, sum of exponentials) in place of its first chunk's
+  float* part_max_q;
+  double* part_sum_q;
   uint64_t* slots;     // [B][3][G][4]: per set and workgroup: sum of the new p, of what q keeps, of the old p
   uint64_t* pubs;      // [B][3][4]: the next test's entry of the new p, of the old p, of q
   uint32_t* sync;      // [B]: workgroups that have started, kClosed with the team's size, kFailed
   uint32_t* clear;     // all of these, as words that the merge launch sets to zero
   int32_t clear_count;
-  double* row_stats;   // [2][B*Nmax][2]: (max, sum of exponentials) of every row of logits, then of draft_logits
   double* tests;       // [2][B*Nmax]: p(x), then q(x), of the node's token x at its parent
   double inv_temperature;
   int64_t wait_ticks;  // what the first workgroup waits for the others, times the shares of a team of those who are there
@@ -1187,8 +1186,8 @@ __global__ __launch_bounds__(kGridThreads) void accept_row_merge_kernel(const Dr
   // of the children's tokens (wavefront 0, a lane each) a trip later: 60 nodes, V = 128256, a call 34.3 -> 33.9 us.
   const int my_parent = lane_parent(p.parent + o, p.Nmax);
   const int my_token = p.draft_tokens[o + min(tid & 63, p.Nmax - 1)];
-  const float* pm = (arr ? p.part_max_q : p.part_max_p) + (int64_t)row * p.n_chunks;
-  const double* ps = (arr ? p.part_sum_q : p.part_sum_p) + (int64_t)row * p.n_chunks;
+  float* const pm = (arr ? p.part_max_q : p.part_max_p) + (int64_t)row * p.n_chunks;
+  double* const ps = (arr ? p.part_sum_q : p.part_sum_p) + (int64_t)row * p.n_chunks;
   const float own_max = pm[min(tid, p.n_chunks - 1)];
   const double own_sum = ps[min(tid, p.n_chunks - 1)];
   const int n_all = p.n_nodes[b], n = min(n_all, p.Nmax);
@@ -1207,10 +1206,9 @@ __global__ __launch_bounds__(kGridThreads) void accept_row_merge_kernel(const Dr
   }
   int flip = 0;
   grid_wg_sums<1>(z, sh_sums, flip);
-  if (tid == 0) {
-    double* out = p.row_stats + ((int64_t)arr * p.B * p.Nmax + row) * 2;
-    out[0] = (double)m;
-    out[1] = z[0];
+  if (tid == 0) {   // (every thread's loads are done: they are in the sums)
+    pm[0] = m;
+    ps[0] = z[0];
   }
   if (child) {
     const double scale = z[0] > 0.0 ? 1.0 / z[0] : 0.0;
@@ -1256,12 +1254,10 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
   __shared__ double h_sp[FSPAD_MAX_NODES], h_sq[FSPAD_MAX_NODES];
   __shared__ int h_x[FSPAD_MAX_NODES], h_moved[FSPAD_MAX_NODES];
   static_assert(FSPAD_MAX_NODES <= 64, "a lane per node");
-  for (int i = tid; i < 4 * p.Nmax; i += kGridThreads) {
-    const int arr = i / (2 * p.Nmax), rest = i - arr * 2 * p.Nmax;
-    t_stats[arr][rest >> 1][rest & 1] = p.row_stats[((int64_t)arr * p.B * p.Nmax + o) * 2 + rest];
-  }
   for (int i = tid; i < 2 * p.Nmax; i += kGridThreads) {
     const int arr = i >= p.Nmax, node = i - arr * p.Nmax;
+    t_stats[arr][node][0] = (double)(arr ? p.part_max_q : p.part_max_p)[(o + node) * p.n_chunks];
+    t_stats[arr][node][1] = (arr ? p.part_sum_q : p.part_sum_p)[(o + node) * p.n_chunks];
     t_test[arr][node] = p.tests[(int64_t)arr * p.B * p.Nmax + o + node];
   }
   const int my_parent = lane < p.Nmax ? p.parent[o + lane] : -2;
@@ -1605,7 +1601,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
   }
 }
 
-struct GridPlan { int G, E; size_t pubs_at, sync_at, stats_at, tests_at; };
+struct GridPlan { int G, E; size_t pubs_at, sync_at, tests_at; };
 // E = 0: the chip-wide form does not apply (too many sequences, a vocabulary beyond 64 x 256 x 32 entries or too
 // small to hold the exchange area in the workspace's row buffers).
 GridPlan plan_draft_grid(int32_t B, int32_t Nmax, int32_t V) {
@@ -1618,8 +1614,7 @@ GridPlan plan_draft_grid(int32_t B, int32_t Nmax, int32_t V) {
   const int G = (int)(((int64_t)V + (int64_t)kGridThreads * E - 1) / ((int64_t)kGridThreads * E));
   pl.pubs_at = (size_t)B * kGridSets * G * 4 * sizeof(uint64_t);
   pl.sync_at = pl.pubs_at + (size_t)B * kGridSets * 4 * sizeof(uint64_t);
-  pl.stats_at = pl.sync_at + (((size_t)B * sizeof(uint32_t) + 15) & ~(size_t)15);
-  pl.tests_at = pl.stats_at + (size_t)2 * B * Nmax * 2 * sizeof(double);
+  pl.tests_at = pl.sync_at + (((size_t)B * sizeof(uint32_t) + 15) & ~(size_t)15);
   const size_t end = pl.tests_at + (size_t)2 * B * Nmax * sizeof(double);
   if (end > (size_t)B * 3 * (size_t)V * 8) return GridPlan{};
   pl.G = G; pl.E = E;
@@ -1811,8 +1806,7 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
     gp.pubs = reinterpret_cast<uint64_t*>(work + plan.pubs_at);
     gp.sync = reinterpret_cast<uint32_t*>(work + plan.sync_at);
     gp.clear = reinterpret_cast<uint32_t*>(work);
-    gp.clear_count = (int32_t)(plan.stats_at / 4);
-    gp.row_stats = reinterpret_cast<double*>(work + plan.stats_at);
+    gp.clear_count = (int32_t)(plan.tests_at / 4);
     gp.tests = reinterpret_cast<double*>(work + plan.tests_at);
     gp.inv_temperature = pa.inv_temperature;
     gp.B = B; gp.Nmax = Nmax; gp.V = V; gp.n_chunks = pa.n_chunks; gp.G = plan.G; gp.vec = vec;

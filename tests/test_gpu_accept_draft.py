@@ -70,6 +70,38 @@ def test_both_launch_forms(B, N, V):
     _run(6100 + B + V, B, N, V, 0.9, peak=2.0, noise=0.5, min_compared=B - max(1, B // 40))
 
 
+@pytest.mark.parametrize("B,N", [(1, 64), (3, 26)])
+@pytest.mark.parametrize("V", [20, 40, 51, 53, 60, 93, 120, 137])
+def test_smallest_vocabularies(B, N, V):
+    """Around the vocabulary from which the exchange area fits in the workspace's rows."""
+    _run(6300 + V, B, N, V, 0.9, peak=1.0, noise=0.7, topk=8, min_compared=max(1, B - 1))
+
+
+def test_small_vocabularies_take_the_form_of_larger_ones():
+    """64 nodes: a vocabulary of 120 entries takes no longer than one of 1000, which it does in the general form."""
+    import paper_2408_15562_amd as fspad
+    N, T, took = 64, 1.0, {}
+    for V in (120, 1000):
+        parent, n_nodes, logits, draft_logits, tokens = _case(68, 1, N, V, T, peak=2.0)
+        parent[:], n_nodes[:], tokens[:] = 0, N, V    # the root rejects 63 children
+        parent[:, 0] = -1
+        dev = [torch.from_numpy(a).to(DEV) for a in (logits, draft_logits, tokens, parent, n_nodes, gen_uniforms(1, 1, N))]
+        out = [torch.empty(shape, dtype=torch.int32, device=DEV) for shape in ((1, N), (1,), (1, N), (1,))]
+        ws = torch.empty(fspad.fspad_tree_accept_sample_draft_workspace_bytes(1, N, V), dtype=torch.uint8, device=DEV)
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+            for _ in range(20):
+                fspad.fspad_tree_accept_sample_draft(*dev[:5], T, dev[5], outputs=out, workspace=ws)
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            took[V] = min(took.get(V, np.inf), a.elapsed_time(b))
+    assert took[120] < 1.1 * took[1000], took   # (the general form: 1.22 of it, this one 0.96)
+
+
 def test_one_workspace_call_after_call():
     """The chip-wide form exchanges its sums through the workspace and has an earlier launch of every
     call set these places to zero: calls that follow one another through one workspace (a larger problem, then a
