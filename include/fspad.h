@@ -236,12 +236,13 @@ fspad_status fspad_tree_accept_sample(int32_t B, int32_t Nmax, int32_t V,
  *                (3 V fp64 entries per sequence and the chunk statistics of both logit arrays); two
  *                calls that may overlap need different ones
  * All arithmetic that takes a decision is fp64. With at most 256 sequences and a vocabulary of at
- * most 524288 entries a sequence is walked by up to 64 workgroups that keep their shares of the
- * node's two rows in registers and exchange their sums after every rejection; if some of them cannot
- * run (other streams hold the compute units) those that can take all shares, with the same result,
- * after a wait of about the time that this takes them. Larger calls take one workgroup per sequence.
- * Either way the cost is a few passes over the two rows of every node on the accepted path (not over
- * all B*Nmax rows).
+ * most 8192 * min(64, 256 / B) entries (the quotient rounded down: 524288 up to 4 sequences, 8192
+ * from 129 on) and at least about 8 + 2 Nmax / 3, a sequence is walked by up to 64 workgroups that
+ * keep their shares of the node's two rows in registers and exchange their sums after every
+ * rejection; if some of them cannot run (other streams hold the compute units) those that can take
+ * all shares, with the same result, after a wait of about the time that this takes them. Other calls
+ * take one workgroup per sequence. Either way the cost is a few passes over the two rows of every
+ * node on the accepted path (not over all B*Nmax rows).
  * Error reporting on the device: path_len[b] = n_tokens[b] = -1 says that the workgroups of
  * sequence b, all of them running, stopped waiting for one another after about a million polls; the other
  * outputs of that sequence are then undefined. It does not happen on a working device: nobody waits for a

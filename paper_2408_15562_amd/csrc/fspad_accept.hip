@@ -11,7 +11,7 @@
 // chunk statistics of every row at once, walks the tree with wavefront ballots
 // out of LDS and, for sampling, draws the last token by an inverse-CDF search that
 // descends chunk -> thread segment -> element. (Large sampling calls: see kInnerFirst; greedy calls of small vocabularies, one
-// launch: see kSmallVocab.)
+// launch: see accept_greedy_small_kernel.)
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <stdint.h>
@@ -1602,8 +1602,8 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
 }
 
 struct GridPlan { int G, E; size_t pubs_at, sync_at, tests_at; };
-// E = 0: the chip-wide form does not apply (too many sequences, a vocabulary beyond 64 x 256 x 32 entries or too
-// small to hold the exchange area in the workspace's row buffers).
+// E = 0: the chip-wide form does not apply (too many sequences, a vocabulary beyond 256 x 32 entries for each of the workgroups
+// that a sequence can have, or too small to hold the exchange area in the workspace's row buffers).
 GridPlan plan_draft_grid(int32_t B, int32_t Nmax, int32_t V) {
   GridPlan pl{};
   if (B > 256) return pl;

@@ -380,7 +380,8 @@ def test_a_walk_without_all_of_its_workgroups_is_not_a_walk_alone(late_call):
 
 
 def test_calls_on_two_streams_at_once():
-    """Walks of two streams share the compute units, whole or in part: both end, with the outputs of calls that follow one another."""
+    """Calls in flight on two streams, each with a workspace of its own (the chip holds the 236 workgroups of both): the outputs of
+    calls that follow one another. (What a walk does without some of its workgroups: the tests with late ones.)"""
     import paper_2408_15562_amd as fspad
     B, N, V, T = 4, 40, 60000, 1.0
     streams, preps, outs = [torch.cuda.Stream() for _ in range(2)], [], []
