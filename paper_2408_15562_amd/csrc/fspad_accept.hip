@@ -1102,6 +1102,7 @@ constexpr uint32_t kClosed = 1u << 31;   // the count is closed; those who came 
 constexpr uint32_t kFailed = 1u << 30;
 constexpr uint32_t kCount = 0xff;
 static_assert(kGridMaxWgs <= (int)kCount, "a byte each");
+constexpr int64_t kShortestWait = 2000;  // 100 MHz ticks: what a whole walk takes
 
 struct DraftGridParams {
   const float* logits;
@@ -1313,7 +1314,7 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
         const uint32_t word = __builtin_amdgcn_readfirstlane(polled);
         if (word & kFailed) { how = 0; break; }
         if (!team && (word & kClosed)) { how = 2; size = (word >> 8) & kCount; break; }
-        if (round == 1 && order == 0 && word < (uint32_t)G && wall_clock64() - began > p.wait_ticks * ((G + (int)word - 1) / (int)word)) {
+        if (round == 1 && order == 0 && word < (uint32_t)G && wall_clock64() - began > max(kShortestWait, p.wait_ticks * ((G + (int)word - 1) / (int)word))) {
           int closed = 0;
           if (lane == 0) {
             uint32_t expected = word;
@@ -1810,12 +1811,12 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
     gp.tests = reinterpret_cast<double*>(work + plan.tests_at);
     gp.inv_temperature = pa.inv_temperature;
     gp.B = B; gp.Nmax = Nmax; gp.V = V; gp.n_chunks = pa.n_chunks; gp.G = plan.G; gp.vec = vec;
-    // About what a share costs a team in a walk of a root, a few rejections and a draw (100 MHz ticks; 3 us a share and round with four
-    // entries a thread, 10 with 32), so that a call takes at most about twice as long as if it had known. Walks with the given number of
-    // workgroups there, wait and all, us: 60 nodes, V = 128256 (63 shares): 1 1480, 4 405, 16 134, 32 to 62 87, all 37; 32 rejections
-    // at the root: 1 10800, 16 790, all 104; V = 500 000 (62 shares of 32 entries a thread), draw at the root 2760, all 16. The form
-    // before waited 300 us and then walked alone, however many were there: 790, 10100 and 580.
-    gp.wait_ticks = 100 * (8 + plan.E);
+    // About what a share costs a team in the walk of a tree whose tests reject a few times (E entries a thread; a share's round takes 3 us
+    // with 8, 9 with 32), so that a call takes at most about twice as long as if it had known. Walks with the given number of workgroups
+    // there, wait and all, us: 60 nodes, V = 128256 (63 shares, E = 8): 1 770, 4 226, 16 87, 32 to 62 76, all 37; 32 rejections at the
+    // root: 1 10100, 16 744, all 104; V = 500 000 (62 shares, E = 32): 32300, 2210, 131, only a draw there 1490, 119, 17. A form that waited 300 us and
+    // then walked alone, however many were there: 790, 10100, 32900 and 580.
+    gp.wait_ticks = 60 * plan.E;
 #ifdef FSPAD_TEST_LATE_WORKGROUPS
     gp.late_from = fspad_test_late_from;
     gp.late_ticks = fspad_test_late_ticks;

@@ -347,7 +347,7 @@ def test_many_rejections_by_the_workgroups_that_are_there(late_call, B, N, V, th
 
 
 def test_workgroups_that_come_as_the_count_is_closed(late_call):
-    """Starts from 0 to some 70 us late, the first workgroup's wait (24 us here) among them: whether the count is closed before,
+    """Starts from 0 to some 70 us late, the first workgroup's wait (20 us here) among them: whether the count is closed before,
     after or while they come, the outputs are those of the full walk."""
     B, N, V, T = 3, 40, 60000, 0.9
     dev, full, ws, _ = _late_case(8600, B, N, V, T, 0.7)
