@@ -1924,6 +1924,38 @@ int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool uniform, 
   return (int)wgs;
 }
 
+// Fewer pieces than plan_wgs gives the units of an equal batch, down to whole ones, where the merge costs more than the shorter streams
+// spare. What a call takes beyond its fixed part, in hundredths of a turn (one block of every key-splitting wavefront: 0.8 us with shared
+// stages, 1.6 where every wavefront fetches its own K and V, D = 128): its longest stream, and where units are cut the second launch, its
+// trips to memory (eight pieces a trip), a megabyte of partial results written and read, a piece that every merging thread reads. Fitted to 489
+// calls (1 to 14 sequences, 24 to 30000 keys, 8 to 60 nodes, 2 to 120 units), each timed with up to twenty counts. Measured, us a call
+// with all compute units in use -> so: 32 / 8 heads, 60 nodes: 1000 keys 16.7 -> 15.5, 2048 keys 19.9 -> 17.1; four sequences of it, 330 keys 18.4 -> 12.6;
+// 12 / 2 heads, 48 nodes, 8192 keys 22.5 -> 19.4; 32 heads, 26 nodes, 2048 keys 15.6 -> 14.8; 16 heads, 700 keys 12.6 -> 10.8. The other way round:
+// 64 / 8 heads, 4096 keys, 8 pieces 24.1, 6 24.3; 5 x 40 / 8 heads, 40 nodes, 1000 keys, 3 pieces 19.1, whole 22.8. The fit is good to a few tenths of a
+// turn, so less than 0.3 of one does not count: over those calls 0.965 of the time on the mean, the worst 1.05.
+// (Above 256 workgroups of 16-row tiles compute units hold one or two: not this rule's business.)
+int64_t fewer_pieces(const Plan& pl, int64_t units, int64_t blocks_per_unit, int64_t wgs) {
+  struct Costs { int cut, trip, megabyte, piece; };
+  int64_t most = wgs / units;
+  if (most * units > kComputeUnits) most = kComputeUnits / units;
+  if (most < 2) return wgs;
+  const Costs c = pl.shared_stage ? (pl.D == 128 ? Costs{140, 105, 36, 31} : Costs{260, 40, 27, 25})
+                  : pl.WS > 1     ? Costs{200, 120, 18, 0}
+                  : pl.D == 128   ? Costs{145, 85, 26, 22}
+                                  : Costs{320, 120, 110, 0};
+  const int KW = key_waves(pl);
+  auto cost = [&](int64_t pieces) {
+    const int64_t blocks = (blocks_per_unit + pieces - 1) / pieces, turns = (blocks + KW - 1) / KW;
+    const int64_t cut = c.cut + c.trip * ((pieces + 7) / 8) + c.piece * pieces + c.megabyte * pieces * units * pl.rows_per_unit * pl.D / (1 << 18);
+    return 100 * turns + (pieces > 1 ? cut : 0);
+  };
+  const int64_t with_most = cost(most);
+  int64_t best = most, least = with_most;
+  for (int64_t pieces = most - 1; pieces >= 1; --pieces)
+    if (const int64_t x = cost(pieces); x < least) { least = x; best = pieces; }
+  return with_most - least >= 30 ? best * units : wgs;
+}
+
 int host_owner_of(int64_t x, int64_t T, int W) {
   int w = (int)((x * W) / T);
   if (((int64_t)(w + 1) * T) / W <= x) ++w;
@@ -2237,6 +2269,7 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       // 16 to 26 keys, trees of 11 to 26 nodes 10.2 us, planned as a ragged batch 17.4)
       int64_t wgs = plan_wgs(pl, total, units, uniform, d.workgroups);
       if (wgs > full_wgs) wgs = uniform && full_wgs >= units ? full_wgs / units * units : full_wgs;
+      if (uniform && d.workgroups == 0 && units > 0) wgs = fewer_pieces(pl, units, total / units, wgs);   // (the workspace stays that of plan_wgs)
       sl.setup = uniform || total + units * setup_blocks(pl) > kMaxFlatBlocks ? 0 : setup_blocks(pl);
       // Short units of a ragged batch that fit the chip stay whole, as those of an equal one do (plan_wgs): a workgroup each, and
       // so much set-up that the even division falls into it. Whole units leave no partial results, so the workspace does not bound

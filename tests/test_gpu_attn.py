@@ -360,6 +360,17 @@ def test_bf16_workgroups_aligned_with_units(H, B, Hkv, G, N, L):
     _check(H, case, H.TOL["bf16"])
 
 
+# Equal units in fewer pieces than there are compute units for, down to whole ones: every row of the costs (grouped heads of both head
+# dims, one and two slabs a workgroup, 16-row tiles), 1, up to 8 and more pieces, trees of different sizes in equally many blocks.
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,L,n_nodes", [
+    (3, 28, 4, 26, 128, 161, None), (1, 12, 2, 48, 128, 1500, None), (1, 12, 2, 48, 128, 5000, None), (2, 64, 8, 33, 128, 100, [33, 64 - 31]),
+    (1, 12, 2, 60, 64, 91, None), (2, 28, 4, 40, 64, 1460, [40, 33]), (1, 16, 16, 26, 128, 700, None), (1, 32, 32, 8, 128, 700, None),
+    (1, 8, 8, 26, 64, 700, None), (1, 8, 8, 60, 64, 288, None), (1, 28, 4, 10, 128, 3000, None), (2, 12, 2, 16, 128, 450, [16, 1])])
+def test_bf16_equal_units_in_fewer_pieces(H, B, Hq, Hkv, N, D, L, n_nodes):
+    case = H.AttnCase(B + Hq + N + L, B, N, Hq, Hkv, D, L, "bf16", n_nodes=None if n_nodes is None else np.array(n_nodes, np.int32))
+    _check(H, case, H.TOL["bf16"])
+
+
 @pytest.mark.parametrize("B,Hkv,G,N,D", [(8, 48, 1, 17, 128), (2, 200, 1, 32, 128), (8, 50, 2, 13, 128), (3, 128, 1, 33, 64),
                                          (10, 40, 3, 16, 64)])
 @pytest.mark.parametrize("L", [0, 33, 300])
