@@ -49,6 +49,7 @@ struct AcceptParams {
   int32_t* part_idx;   // greedy  [rows][chunks]
   double* part_sum;    // sampling [rows][chunks]
   double inv_temperature;
+  double table_scale;  // of exp_nonpos_table: 256 log2(e) / T
   int32_t B, Nmax, V, n_chunks;
   int32_t chunk;       // logits per (row, chunk) workgroup: 256 * PT
   uint32_t* clear_words;   // words this launch sets to zero for the kernel behind it (may be null)
@@ -93,6 +94,35 @@ __device__ __forceinline__ double wave_running_sum(double v) {
 
 __device__ __forceinline__ float clean(float x) { return (x != x) ? -INFINITY : x; }  // NaN ranks lowest
 
+// The largest of the numbers among x (-infinity where there is none): two at a time, NaNs dropped by the instruction. (With the mode bit
+// that kernels start with a signalling NaN would come back as a quiet one, and the compiler puts an instruction in front of every
+// operand to make sure that there is none.)
+template <int N>
+__device__ __forceinline__ float max_of_numbers(const float (&x)[N]) {
+  static_assert(N % 2 == 0, "pairs");
+  float m;
+  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0\n\tv_mov_b32 %0, 0xff800000" : "=v"(m));
+#pragma unroll
+  for (int k = 0; k < N; k += 2) asm("v_max3_f32 %0, %0, %1, %2" : "+v"(m) : "v"(x[k]), "v"(x[k + 1]));
+  return m;
+}
+
+// The largest m of a wavefront's lanes, in every lane.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_larger(float m) {
+  const int bits = __builtin_bit_cast(int, m);
+  return fmaxf(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(bits, bits, CTRL, ROW_MASK, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max(float m) {
+  m = dpp_larger<0x111, 0xf>(m);
+  m = dpp_larger<0x112, 0xf>(m);
+  m = dpp_larger<0x114, 0xf>(m);
+  m = dpp_larger<0x118, 0xf>(m);
+  m = dpp_larger<0x142, 0xa>(m);
+  m = dpp_larger<0x143, 0xc>(m);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, m), 63));
+}
+
 // (value, index) with "larger value, then lower index" order
 __device__ __forceinline__ void take_better(float& v, int& i, float ov, int oi) {
   if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
@@ -108,7 +138,8 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
   __shared__ float sh_max[4];
   __shared__ int sh_idx[4];
   __shared__ double sh_sum[4];
-  __shared__ double exp2_table[32];
+  __shared__ double exp2_table[fspad_detail::kExp2Entries];
+  static_assert(fspad_detail::kExp2Entries == kThreads, "an entry a thread");
   const int row = blockIdx.y, chunk = blockIdx.x;
   const int b = row / p.Nmax, node = row - b * p.Nmax;
   // (asked for together with the tree's size: behind it the first logits were a trip later)
@@ -124,7 +155,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
   double* const part_sum = second ? p.part_sum2 : p.part_sum;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int base = chunk * kChunk;
-  const double root = MODE == 1 && tid < 32 ? fspad_detail::kExp2Table[tid] : 0.0;
+  const double root = MODE == 1 ? fspad_detail::kExp2Table[tid] : 0.0;
 
   float x[kPerThread];
   if constexpr (VEC) {
@@ -133,10 +164,11 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
       const int e0 = base + (k * kThreads + tid) * 4;
       if (e0 + 3 < p.V) {
         const f32x4 v = *reinterpret_cast<const f32x4*>(rp + e0);
-        x[4 * k] = clean(v[0]); x[4 * k + 1] = clean(v[1]); x[4 * k + 2] = clean(v[2]); x[4 * k + 3] = clean(v[3]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[4 * k + j] = MODE == 1 ? v[j] : clean(v[j]);   // (sampling: a NaN is dropped where it is used)
       } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[4 * k + j] = (e0 + j < p.V) ? clean(rp[e0 + j]) : -INFINITY;
+        for (int j = 0; j < 4; ++j) x[4 * k + j] = (e0 + j < p.V) ? (MODE == 1 ? rp[e0 + j] : clean(rp[e0 + j])) : -INFINITY;
       }
     }
   } else {
@@ -149,39 +181,33 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) asm volatile("" : "+v"(x[k]));   // (or the loads move under the tests below)
 #pragma unroll
-    for (int k = 0; k < kPerThread; ++k) x[k] = base + ((k >> 2) * kThreads + tid) * 4 + (k & 3) < p.V ? clean(x[k]) : -INFINITY;
+    for (int k = 0; k < kPerThread; ++k) x[k] = base + ((k >> 2) * kThreads + tid) * 4 + (k & 3) < p.V ? (MODE == 1 ? x[k] : clean(x[k])) : -INFINITY;
   }
 
   const int64_t slot = (int64_t)row * p.n_chunks + chunk;
   if (MODE == 1) {
-    if (tid < 32) exp2_table[tid] = root;
+    exp2_table[tid] = root;
     __syncthreads();
-    // sampling: each thread sums exp((x - its own max)/T) over its entries as soon as they arrive
-    // (fp64, no waiting for the rest of the workgroup); the threads' (max, sum) pairs are then merged
-    // into the chunk's: sum_c = sum_t sum_t * exp((max_t - max_c)/T).
-    float mt = x[0];
-#pragma unroll
-    for (int k = 1; k < kPerThread; ++k) mt = fmaxf(mt, x[k]);
+    // sampling: each wavefront sums exp((x - its own max)/T) over its entries as soon as they arrive (fp64, no waiting for the rest
+    // of the workgroup); the wavefronts' (max, sum) pairs are then merged into the chunk's: sum_c = sum_w sum_w * exp((max_w - max_c)/T).
+    // (A maximum and a weight of its own for every thread, with exchanges through LDS, was a sixth of the instructions.)
+    const float mw = wave_max(max_of_numbers(x));
     double st = 0.0;
-    if (mt > -INFINITY) {
-      const double mtd = (double)mt;
+    if (mw > -INFINITY) {
+      const double mwd = (double)mw;
 #pragma unroll
-      for (int k = 0; k < kPerThread; ++k) st += exp_nonpos_table(((double)x[k] - mtd) * p.inv_temperature, exp2_table);
+      for (int k = 0; k < kPerThread; ++k) st += exp_nonpos_table((double)x[k] - mwd, p.table_scale, exp2_table);
     }
-    float mw = mt;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
-    if (lane == 0) sh_max[wave] = mw;
+    st = wave_running_sum(st);
+    if (lane == 63) { sh_max[wave] = mw; sh_sum[wave] = st; }
     __syncthreads();
-    const float mc = fmaxf(fmaxf(sh_max[0], sh_max[1]), fmaxf(sh_max[2], sh_max[3]));
-    double sum = mt > -INFINITY ? st * exp_nonpos(((double)mt - (double)mc) * p.inv_temperature) : 0.0;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-    if (lane == 0) sh_sum[wave] = sum;
-    __syncthreads();
-    if (tid == 0) {
-      part_max[slot] = mc;
-      part_sum[slot] = (sh_sum[0] + sh_sum[1]) + (sh_sum[2] + sh_sum[3]);
+    if (tid < 4) {
+      const float own = sh_max[tid];
+      const float mc = fmaxf(fmaxf(sh_max[0], sh_max[1]), fmaxf(sh_max[2], sh_max[3]));
+      double sum = own > -INFINITY ? sh_sum[tid] * exp_nonpos(((double)own - (double)mc) * p.inv_temperature) : 0.0;
+      sum += __shfl_xor(sum, 1);
+      sum += __shfl_xor(sum, 2);
+      if (tid == 0) { part_max[slot] = mc; part_sum[slot] = sum; }
     }
     return;
   }
@@ -439,7 +465,7 @@ __device__ __forceinline__ void draw_in_chunk(const DrawArgs& a) {
 // A chunk's statistics by the walk's workgroup, as the first pass forms them but for the order of the sum. wave_max, wave_sum: LDS,
 // one slot a wavefront.
 template <bool VEC>
-__device__ __forceinline__ void form_chunk(const float* rp, int base, int V, double inv_temperature, const double* exp2_table,
+__device__ __forceinline__ void form_chunk(const float* rp, int base, int V, double table_scale, const double* exp2_table,
                                            float* wave_max, double* wave_sum, float* out_max, double* out_sum) {
   constexpr int E = kMaxChunk / kWalkThreads;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -472,7 +498,7 @@ __device__ __forceinline__ void form_chunk(const float* rp, int base, int V, dou
   double sum = 0.0;
   if (mc > -INFINITY) {
 #pragma unroll
-    for (int k = 0; k < E; ++k) sum += exp_nonpos_table(((double)x[k] - (double)mc) * inv_temperature, exp2_table);
+    for (int k = 0; k < E; ++k) sum += exp_nonpos_table((double)x[k] - (double)mc, table_scale, exp2_table);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
@@ -671,14 +697,14 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
     if (wave == 0) walk();
     __syncthreads();
     if (sh_i[6]) {
-      __shared__ double exp2_table[32];
+      __shared__ double exp2_table[fspad_detail::kExp2Entries];
       __shared__ float wave_max[kWalkWaves];
-      if (tid < 32) exp2_table[tid] = fspad_detail::kExp2Table[tid];
+      if (tid < fspad_detail::kExp2Entries) exp2_table[tid] = fspad_detail::kExp2Table[tid];
       __syncthreads();
       const int leaf = sh_i[5];
       const int64_t row = o + leaf;
       for (int c = blockIdx.x; c < p.n_chunks; c += gridDim.x)
-        form_chunk<VEC>(p.logits + row * p.row_stride, c * kMaxChunk, p.V, p.inv_temperature, exp2_table, wave_max, scan_part,
+        form_chunk<VEC>(p.logits + row * p.row_stride, c * kMaxChunk, p.V, p.table_scale, exp2_table, wave_max, scan_part,
                         p.part_max + row * p.n_chunks + c, p.part_sum + row * p.n_chunks + c);
       // (one thread wrote them all, and one wavefront reads them: a fence in each of the sixteen took 20 us)
       if (tid == 0) {
@@ -767,6 +793,7 @@ void fill_params(AcceptParams& p, int32_t B, int32_t Nmax, int32_t V, const floa
   p.part_idx = reinterpret_cast<int32_t*>(p.part_max + slots);
   p.uniforms = nullptr;
   p.inv_temperature = 1.0;
+  p.table_scale = fspad_detail::kExp2PerE;
 }
 
 bool rows_vectorisable(const float* logits, int64_t row_stride) {
@@ -1735,6 +1762,7 @@ extern "C" fspad_status fspad_tree_accept_sample(int32_t B, int32_t Nmax, int32_
   fill_params(p, B, Nmax, V, logits, row_stride, draft_tokens, parent, n_nodes, path, path_len, tokens, n_tokens, workspace);
   p.uniforms = uniforms;
   p.inv_temperature = 1.0 / (double)temperature;
+  p.table_scale = fspad_detail::kExp2PerE / (double)temperature;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
   const bool vec = rows_vectorisable(logits, row_stride);
   const bool large = Nmax >= kInnerFirstNodes && (int64_t)B * Nmax * V >= kInnerFirst && p.chunk == kMaxChunk;
@@ -1785,6 +1813,7 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
   fill_params(pb, B, Nmax, V, draft_logits, row_stride, draft_tokens, parent, n_nodes, path, path_len, tokens, n_tokens,
               ws + region);
   pa.inv_temperature = pb.inv_temperature = 1.0 / (double)temperature;
+  pa.table_scale = pb.table_scale = fspad_detail::kExp2PerE / (double)temperature;
   // Chip-wide form: G workgroups a sequence, E entries a thread, if the shape allows it; else one workgroup a sequence.
   const GridPlan plan = plan_draft_grid(B, Nmax, V);
   char* const work = ws + 2 * region;

@@ -127,6 +127,28 @@ def test_greedy_small_vocabularies(H, B, N, V, pad):
     H.assert_accept_equal(case.gpu_greedy(), case.cpu_greedy())
 
 
+@pytest.mark.parametrize("V", [1, 2, 3, 255, 1023, 1025, 4099, 33001])
+@pytest.mark.parametrize("T", [1.0, 0.05, 40.0])
+@pytest.mark.parametrize("pad", [0, 1, 4])
+def test_sampling_rows_with_nan_and_infinity(H, V, T, pad):
+    """NaNs of both kinds and -infinity in every wavefront's entries, a row of nothing else, spread over many octaves: the row statistics
+    drop them. (The oracle ranks a NaN lowest too.) Steps that a rounding of the sums could turn are left out, as everywhere."""
+    B, N = 2, 20
+    rng = np.random.default_rng(V)
+    logits = (3.0 * rng.standard_normal((B, N, V))).astype(np.float32)
+    if V > 3:
+        hit = rng.random((B, N, V))
+        logits[hit < 0.05] = np.nan
+        logits.view(np.uint32)[(hit > 0.05) & (hit < 0.08)] = 0x7fa00001   # a signalling one
+        logits[(hit > 0.08) & (hit < 0.2)] = -np.inf
+        logits[(hit > 0.2) & (hit < 0.25)] = -1.0e30
+    logits[0, 1] = np.nan
+    logits[1, 2] = -np.inf
+    case = H.AcceptCase(70 + V, B, N, V, "sample", logits=logits, tokens=rng.integers(0, V, (B, N)).astype(np.int32), row_pad=pad)
+    cpu = case.cpu_sample(T)
+    H.assert_accept_equal(case.gpu_sample(T), cpu, keep=cpu[4] >= H.MARGIN)
+
+
 def test_rows_of_unused_slots_are_not_read():
     """Small vocabularies: a batch of trees of two nodes in 64 slots takes a small part of the time of full trees."""
     import paper_2408_15562_amd as fspad
