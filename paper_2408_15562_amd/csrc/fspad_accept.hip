@@ -27,6 +27,7 @@ namespace {
 using fspad_detail::exp_nonpos;
 using fspad_detail::exp_nonpos_table;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_at_4;   // rows of any alignment: the load takes it
 
 constexpr int kThreads = 256;
 constexpr int kMinChunk = 1024;           // logits per workgroup of the streaming kernel: 1024 .. 8192,
@@ -130,8 +131,10 @@ __device__ __forceinline__ void take_better(float& v, int& i, float ov, int oi) 
 
 // ------------------------------------------------------------------------------------------------
 // Streaming pass. MODE 0: greedy (max, argmax). MODE 1: sampling (max, sum of exp).
-// VEC: rows are 16-byte aligned so that float4 loads are legal.
-template <int MODE, bool VEC, int PT>
+// Sixteen bytes per lane and load whatever the rows' alignment (4 bytes at least): entry by entry, as rows that are not 16-byte aligned were
+// read before, the texture path takes four times the requests. us a call, entry by entry -> so: 3 x 60 rows of 151001, sampling 43.6 -> 33.8,
+// greedy 31.7 -> 24.9, sampled drafts 68.5 -> 50.9; 8 x 60 rows of 50257 41.7 -> 31.1, 30.6 -> 21.0, 66.4 -> 49.1 (with half the instructions a weight).
+template <int MODE, int PT>
 __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParams p) {
   constexpr int kChunk = kThreads * PT;
   constexpr int kPerThread = PT;
@@ -158,30 +161,17 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
   const double root = MODE == 1 ? fspad_detail::kExp2Table[tid] : 0.0;
 
   float x[kPerThread];
-  if constexpr (VEC) {
 #pragma unroll
-    for (int k = 0; k < kPerThread / 4; ++k) {
-      const int e0 = base + (k * kThreads + tid) * 4;
-      if (e0 + 3 < p.V) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(rp + e0);
+  for (int k = 0; k < kPerThread / 4; ++k) {
+    const int e0 = base + (k * kThreads + tid) * 4;
+    if (e0 + 3 < p.V) {
+      const f32x4_at_4 v = *reinterpret_cast<const f32x4_at_4*>(rp + e0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[4 * k + j] = MODE == 1 ? v[j] : clean(v[j]);   // (sampling: a NaN is dropped where it is used)
-      } else {
+      for (int j = 0; j < 4; ++j) x[4 * k + j] = MODE == 1 ? v[j] : clean(v[j]);   // (sampling: a NaN is dropped where it is used)
+    } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[4 * k + j] = (e0 + j < p.V) ? (MODE == 1 ? rp[e0 + j] : clean(rp[e0 + j])) : -INFINITY;
-      }
+      for (int j = 0; j < 4; ++j) x[4 * k + j] = (e0 + j < p.V) ? (MODE == 1 ? rp[e0 + j] : clean(rp[e0 + j])) : -INFINITY;
     }
-  } else {
-    // rows of any alignment, entry by entry: every load goes out before the first value is looked at (past the end:
-    // the last entry, dropped below). Under a test of its own each load was a round trip after the last:
-    // sampling, 3 x 60 rows of 151001: 66 -> 51 us. (The vector form above is faster as it is: greedy, 16 x 60 rows of
-    // 128256, 94 us against 109 us with all loads first, which takes twice the registers.)
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k) x[k] = rp[min(base + ((k >> 2) * kThreads + tid) * 4 + (k & 3), p.V - 1)];
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k) asm volatile("" : "+v"(x[k]));   // (or the loads move under the tests below)
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k) x[k] = base + ((k >> 2) * kThreads + tid) * 4 + (k & 3) < p.V ? (MODE == 1 ? x[k] : clean(x[k])) : -INFINITY;
   }
 
   const int64_t slot = (int64_t)row * p.n_chunks + chunk;
@@ -377,7 +367,6 @@ struct DrawArgs {
   double* scan_part;        // LDS scratch: kWalkWaves doubles
   int* sh_wave;             // LDS scratch: 2 * kWalkWaves ints
   int32_t* out;
-  bool vec;                 // rows are 16-byte aligned
 };
 
 template <int E>
@@ -389,8 +378,8 @@ __device__ __forceinline__ void draw_in_chunk(const DrawArgs& a) {
 #pragma unroll
     for (int k = 0; k < E / 4; ++k) {
       const int e = e0 + 4 * k;
-      if (a.vec && e + 3 < a.V) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(a.rp + e);
+      if (e + 3 < a.V) {
+        const f32x4_at_4 v = *reinterpret_cast<const f32x4_at_4*>(a.rp + e);
         lx[4 * k] = v[0]; lx[4 * k + 1] = v[1]; lx[4 * k + 2] = v[2]; lx[4 * k + 3] = v[3];
       } else {
 #pragma unroll
@@ -464,7 +453,6 @@ __device__ __forceinline__ void draw_in_chunk(const DrawArgs& a) {
 
 // A chunk's statistics by the walk's workgroup, as the first pass forms them but for the order of the sum. wave_max, wave_sum: LDS,
 // one slot a wavefront.
-template <bool VEC>
 __device__ __forceinline__ void form_chunk(const float* rp, int base, int V, double table_scale, const double* exp2_table,
                                            float* wave_max, double* wave_sum, float* out_max, double* out_sum) {
   constexpr int E = kMaxChunk / kWalkThreads;
@@ -473,8 +461,8 @@ __device__ __forceinline__ void form_chunk(const float* rp, int base, int V, dou
 #pragma unroll
   for (int k = 0; k < E / 4; ++k) {
     const int e0 = base + (k * kWalkThreads + tid) * 4;
-    if (VEC && e0 + 3 < V) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(rp + e0);
+    if (e0 + 3 < V) {
+      const f32x4_at_4 v = *reinterpret_cast<const f32x4_at_4*>(rp + e0);
 #pragma unroll
       for (int j = 0; j < 4; ++j) x[4 * k + j] = v[j];
     } else {
@@ -523,7 +511,7 @@ __device__ __forceinline__ void form_chunk(const float* rp, int base, int V, dou
 // LARGE (kInnerFirst): leaves have no statistics, and the walk looks at none of theirs. If it ends at one, that row's are formed
 // now: every one of the sequence's gridDim.x workgroups walks the tree, to the same end, and takes its share of the chunks; the
 // last to finish (an arrival counter, part_idx[b]) draws. Where the walk ends at an inner node the first one goes on alone.
-template <bool LARGE, bool VEC>
+template <bool LARGE>
 __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const AcceptParams p) {
   __shared__ int rej_tok[FSPAD_MAX_NODES];
   __shared__ double rej_w[FSPAD_MAX_NODES];
@@ -704,7 +692,7 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
       const int leaf = sh_i[5];
       const int64_t row = o + leaf;
       for (int c = blockIdx.x; c < p.n_chunks; c += gridDim.x)
-        form_chunk<VEC>(p.logits + row * p.row_stride, c * kMaxChunk, p.V, p.table_scale, exp2_table, wave_max, scan_part,
+        form_chunk(p.logits + row * p.row_stride, c * kMaxChunk, p.V, p.table_scale, exp2_table, wave_max, scan_part,
                         p.part_max + row * p.n_chunks + c, p.part_sum + row * p.n_chunks + c);
       // (one thread wrote them all, and one wavefront reads them: a fence in each of the sixteen took 20 us)
       if (tid == 0) {
@@ -748,7 +736,6 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
   a.scan_part = scan_part;
   a.sh_wave = sh_wave;
   a.out = p.tokens + o + last;
-  a.vec = (((uintptr_t)p.logits) & 15) == 0 && (p.row_stride % 4) == 0;
   switch (p.chunk / kWalkThreads) {
     case 1: draw_in_chunk<1>(a); break;
     case 2: draw_in_chunk<2>(a); break;
@@ -801,20 +788,14 @@ bool rows_vectorisable(const float* logits, int64_t row_stride) {
 }
 
 template <int MODE>
-void launch_rows(const AcceptParams& p, bool vec, hipStream_t stream) {
-  const dim3 grid((unsigned)p.n_chunks, (unsigned)(p.B * p.Nmax), p.logits2 ? 2u : 1u);
-#define FSPAD_ROWS(PT)                                                                                         \
-  do {                                                                                                           \
-    if (vec) hipLaunchKernelGGL((accept_rows_kernel<MODE, true, PT>), grid, dim3(kThreads), 0, stream, p);      \
-    else hipLaunchKernelGGL((accept_rows_kernel<MODE, false, PT>), grid, dim3(kThreads), 0, stream, p);         \
-  } while (0)
+void launch_rows(const AcceptParams& p, hipStream_t stream) {
+  const dim3 grid((unsigned)p.n_chunks, (unsigned)(p.B * p.Nmax), p.logits2 ? 2u : 1u), block(kThreads);
   switch (p.chunk / kThreads) {
-    case 4: FSPAD_ROWS(4); break;
-    case 8: FSPAD_ROWS(8); break;
-    case 16: FSPAD_ROWS(16); break;
-    default: FSPAD_ROWS(32); break;
+    case 4: hipLaunchKernelGGL((accept_rows_kernel<MODE, 4>), grid, block, 0, stream, p); break;
+    case 8: hipLaunchKernelGGL((accept_rows_kernel<MODE, 8>), grid, block, 0, stream, p); break;
+    case 16: hipLaunchKernelGGL((accept_rows_kernel<MODE, 16>), grid, block, 0, stream, p); break;
+    default: hipLaunchKernelGGL((accept_rows_kernel<MODE, 32>), grid, block, 0, stream, p); break;
   }
-#undef FSPAD_ROWS
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1156,7 +1137,6 @@ struct DraftGridParams {
   double inv_temperature;
   int64_t wait_ticks;  // what the first workgroup waits for the others, times the shares of a team of those who are there
   int32_t B, Nmax, V, n_chunks, G;
-  int32_t vec;         // rows are 16-byte aligned
 #ifdef FSPAD_TEST_LATE_WORKGROUPS
   int32_t late_from;   // workgroups of a sequence from this one on count themselves in when the count is closed, or late_ticks late
   int64_t late_ticks;
@@ -1405,10 +1385,10 @@ __global__ __launch_bounds__(kGridThreads) void accept_sample_draft_grid_kernel(
     int rejected = 0;
     // E entries of a row from v on as they are, past its end NaN (which weighs nothing)
     auto row_entries = [&](const float* row, int v, float (&x)[E]) {
-      if (p.vec && v + E <= V) {
+      if (v + E <= V) {
 #pragma unroll
         for (int k = 0; k < E / 4; ++k) {
-          const f32x4 q = *reinterpret_cast<const f32x4*>(row + v + 4 * k);
+          const f32x4_at_4 q = *reinterpret_cast<const f32x4_at_4*>(row + v + 4 * k);
           x[4 * k] = q[0]; x[4 * k + 1] = q[1]; x[4 * k + 2] = q[2]; x[4 * k + 3] = q[3];
         }
       } else {
@@ -1681,7 +1661,7 @@ extern "C" fspad_status fspad_tree_accept_greedy(int32_t B, int32_t Nmax, int32_
     else hipLaunchKernelGGL(accept_greedy_small_kernel<false>, grid, block, 0, stream, p);
     return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
   }
-  launch_rows<0>(p, rows_vectorisable(logits, row_stride), stream);
+  launch_rows<0>(p, stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   hipLaunchKernelGGL(accept_greedy_walk_kernel, dim3((unsigned)B), dim3(kThreads), 0, stream, p);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
@@ -1764,22 +1744,20 @@ extern "C" fspad_status fspad_tree_accept_sample(int32_t B, int32_t Nmax, int32_
   p.inv_temperature = 1.0 / (double)temperature;
   p.table_scale = fspad_detail::kExp2PerE / (double)temperature;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-  const bool vec = rows_vectorisable(logits, row_stride);
   const bool large = Nmax >= kInnerFirstNodes && (int64_t)B * Nmax * V >= kInnerFirst && p.chunk == kMaxChunk;
   if (large) {
     p.rows = kInnerRows;
     p.clear_words = reinterpret_cast<uint32_t*>(p.part_idx);   // the walk's arrival counters
     p.clear_count = B;
   }
-  launch_rows<1>(p, vec, stream);
+  launch_rows<1>(p, stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   if (large) {
     const int shares = B < kWalkWorkgroups ? kWalkWorkgroups / B : 1;
     const dim3 grid((unsigned)(p.n_chunks < shares ? p.n_chunks : shares), (unsigned)B);
-    if (vec) hipLaunchKernelGGL((accept_sample_walk_kernel<true, true>), grid, dim3(kWalkThreads), 0, stream, p);
-    else hipLaunchKernelGGL((accept_sample_walk_kernel<true, false>), grid, dim3(kWalkThreads), 0, stream, p);
+    hipLaunchKernelGGL(accept_sample_walk_kernel<true>, grid, dim3(kWalkThreads), 0, stream, p);
   } else {
-    hipLaunchKernelGGL((accept_sample_walk_kernel<false, false>), dim3((unsigned)B), dim3(kWalkThreads), 0, stream, p);
+    hipLaunchKernelGGL(accept_sample_walk_kernel<false>, dim3((unsigned)B), dim3(kWalkThreads), 0, stream, p);
   }
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   return FSPAD_OK;
@@ -1817,14 +1795,13 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
   // Chip-wide form: G workgroups a sequence, E entries a thread, if the shape allows it; else one workgroup a sequence.
   const GridPlan plan = plan_draft_grid(B, Nmax, V);
   char* const work = ws + 2 * region;
-  const bool vec = rows_vectorisable(logits, row_stride) && rows_vectorisable(draft_logits, row_stride);
   // one streaming launch over both logit arrays (grid.z picks the array)
   AcceptParams both = pa;
   both.logits2 = draft_logits; both.part_max2 = pb.part_max; both.part_sum2 = pb.part_sum;
   // The chip-wide walk needs nothing of the leaves' rows, which are more than half of a tree's: no child is tested there, and the
   // draw forms its weights itself (60 nodes, V = 128256, two sets of inputs: the maximum of every row formed 37.0 and 34.7 us, now 34.3 and 31.7). The one-workgroup form needs all.
   both.rows = plan.E != 0 ? kInnerRows : kAllRows;
-  launch_rows<1>(both, vec, stream);
+  launch_rows<1>(both, stream);
   if (hipGetLastError() != hipSuccess) return FSPAD_ERR_HIP;
   if (plan.E != 0) {
     DraftGridParams gp{};
@@ -1839,7 +1816,7 @@ extern "C" fspad_status fspad_tree_accept_sample_draft(int32_t B, int32_t Nmax, 
     gp.clear_count = (int32_t)(plan.tests_at / 4);
     gp.tests = reinterpret_cast<double*>(work + plan.tests_at);
     gp.inv_temperature = pa.inv_temperature;
-    gp.B = B; gp.Nmax = Nmax; gp.V = V; gp.n_chunks = pa.n_chunks; gp.G = plan.G; gp.vec = vec;
+    gp.B = B; gp.Nmax = Nmax; gp.V = V; gp.n_chunks = pa.n_chunks; gp.G = plan.G;
     // About what a share costs a team in the walk of a tree whose tests reject a few times (E entries a thread; a share's round takes 3 us
     // with 8, 9 with 32), so that a call takes at most about twice as long as if it had known. Walks with the given number of workgroups
     // there, wait and all, us: 60 nodes, V = 128256 (63 shares, E = 8): 1 770, 4 226, 16 87, 32 to 62 76, all 37; 32 rejections at the
