@@ -8,8 +8,7 @@
 // (16 bytes per lane), keeps it in registers as order-preserving integer keys, and leaves the
 // chunk's maximum, its sum of exponentials and its own k best entries. The second, one workgroup
 // per row, picks the k best of the chunks' candidates and turns them into log-probabilities.
-// "k best" is k rounds of a workgroup-wide maximum over packed (key, ~token) words: a thread
-// re-scans its registers only when it owned the winner.
+// Entries are compared as packed (key, ~token) words.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -27,7 +26,7 @@ struct TopkParams {
   int64_t row_stride;
   int32_t* tokens;        // [rows][k]
   float* logp;            // [rows][k]
-  unsigned long long* cand;  // [rows][n_chunks][k] packed (key << 32 | ~token), 0 = none
+  unsigned long long* cand;  // [rows][k][n_chunks] packed (key << 32 | ~token), 0 = none
   float* chunk_max;       // [rows][n_chunks]
   double* chunk_sum;      // [rows][n_chunks]  sum of exp(l - chunk_max)
   int32_t rows, V, k, n_chunks, chunk;
@@ -43,185 +42,263 @@ __device__ __forceinline__ unsigned key_of(float x) {
 __device__ __forceinline__ float value_of(unsigned key) {
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
-__device__ __forceinline__ unsigned long long pack(unsigned key, int token) {
-  return ((unsigned long long)key << 32) | (unsigned)(0xffffffffu - (unsigned)token);
-}
 __device__ __forceinline__ int token_of(unsigned long long w) { return (int)(0xffffffffu - (unsigned)w); }
 
-// One step of a maximum over lanes with a data-parallel-primitive lane pattern (no LDS round trip)
+// The value of the lane that a data-parallel-primitive lane pattern pairs this one with (no LDS round trip)
 template <int CTRL>
-__device__ __forceinline__ unsigned long long dpp_max_u64(unsigned long long x) {
-  const int lo = (int)(unsigned)x, hi = (int)(unsigned)(x >> 32);
-  const unsigned olo = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
-  const unsigned ohi = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
-  const unsigned long long o = ((unsigned long long)ohi << 32) | olo;
-  return o > x ? o : x;
+__device__ __forceinline__ unsigned dpp(unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp(unsigned long long x) {
+  return ((unsigned long long)dpp<CTRL>((unsigned)(x >> 32)) << 32) | dpp<CTRL>((unsigned)x);
+}
+__device__ __forceinline__ unsigned lane_of(unsigned x, int lane) { return (unsigned)__builtin_amdgcn_readlane((int)x, lane); }
+__device__ __forceinline__ unsigned long long lane_of(unsigned long long x, int lane) {
+  return ((unsigned long long)lane_of((unsigned)(x >> 32), lane) << 32) | lane_of((unsigned)x, lane);
 }
 
-// Maximum over the 64 lanes, the same value in every lane: neighbours, pairs, mirrored halves of
+// Reduction over the 64 lanes, the same value in every lane: neighbours, pairs, mirrored halves of
 // eight and of sixteen lanes (after which a row of 16 agrees), then the four rows through scalars.
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x) {
-  x = dpp_max_u64<0xB1>(x);    // quad_perm [1,0,3,2]
-  x = dpp_max_u64<0x4E>(x);    // quad_perm [2,3,0,1]
-  x = dpp_max_u64<0x141>(x);   // row_half_mirror
-  x = dpp_max_u64<0x140>(x);   // row_mirror
-  unsigned long long m = 0ull;
-#pragma unroll
-  for (int row = 0; row < 4; ++row) {
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, 16 * row);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), 16 * row);
-    const unsigned long long o = ((unsigned long long)hi << 32) | lo;
-    m = o > m ? o : m;
-  }
-  return m;
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_reduce(T x, Op op) {
+  x = op(x, dpp<0xB1>(x));    // quad_perm [1,0,3,2]
+  x = op(x, dpp<0x4E>(x));    // quad_perm [2,3,0,1]
+  x = op(x, dpp<0x141>(x));   // row_half_mirror
+  x = op(x, dpp<0x140>(x));   // row_mirror
+  return op(op(lane_of(x, 0), lane_of(x, 16)), op(lane_of(x, 32), lane_of(x, 48)));
+}
+template <typename T>
+__device__ __forceinline__ T wave_max(T x) { return wave_reduce(x, [](T a, T b) { return b > a ? b : a; }); }
+__device__ __forceinline__ double wave_sum(double x) {
+  const auto add = [](unsigned long long a, unsigned long long b) {
+    return (unsigned long long)__double_as_longlong(__longlong_as_double((long long)a) + __longlong_as_double((long long)b));
+  };
+  return __longlong_as_double((long long)wave_reduce((unsigned long long)__double_as_longlong(x), add));
 }
 
-// Workgroup-wide maximum of one word per thread; every thread gets it. `slots` is 2 x 4 words of
-// LDS, alternated by `round`, so that one barrier per call is enough.
-__device__ __forceinline__ unsigned long long block_max_u64(unsigned long long x, unsigned long long* slots, int round) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  x = wave_max_u64(x);
-  unsigned long long* s = slots + (round & 1) * 4;
-  if (lane == 0) s[wave] = x;
-  __syncthreads();
-  unsigned long long m = s[0];
+// The k best of a workgroup's words (key above, `low(q)` below; key 0: no entry), in two barriers.
+// `prepare` finds a bound that at least k entries reach, the k-th largest of the maxima of 32 groups of
+// threads (every 32nd: neighbours may hold what one chunk has left), and the largest key; `gather` sets aside the few entries that reach it (of random ones k to 1.4 k);
+// `emit` counts for each of them the ones above it, which is its place. Before, k rounds of a
+// workgroup-wide maximum with a barrier each, in which the winner's thread looked its registers through
+// again, were most of both kernels. Where more than kListed entries reach the bound (many equal logits) those
+// rounds still do it.
+//
+// Bound by latency: two launches of 1.6 us, a trip to memory and some 1000 clocks of dependent instructions each. In a
+// graph, before (k rounds, the loads of a chunk one behind the other) and now: 4 rows of 32000, k = 4 10.0 -> 6.9 us,
+// 40 rows of 32000, k = 10 19.0 -> 8.4, 30 rows of 151001, k = 10 34.0 -> 11.8, 80 rows of 128256, k = 10 48.1 -> 19.3,
+// 16 rows of 32000, k = 16 22.6 -> 7.9. Rounds over the lanes of a wavefront, without barriers, took 10.5 us at 40 x 32000;
+// 64 groups 8.9; groups of neighbouring threads 11.7 at 16 x 32000 (k = 16: a chunk's list came to few of them).
+// Rows of seven distinct values (those rounds): 18.9 -> 18.8.
+constexpr int kWaves = kThreads / 64, kListed = kThreads, kGroups = 32;
+template <int PT>
+struct BlockBest {
+  struct Shared {
+    unsigned long long list[kListed];
+    unsigned long long slots[2 * kWaves];
+    unsigned group[kWaves][kGroups], best[kWaves], bound[kWaves];
+    int count;
+  };
+  Shared& s;
+  unsigned (&key)[PT];
+  const int k, tid = threadIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+
+  __device__ __forceinline__ BlockBest(Shared& shared, unsigned (&keys)[PT], int k_) : s(shared), key(keys), k(k_) {}
+
+  // (a barrier; returns the largest key)
+  __device__ __forceinline__ unsigned prepare() {
+    unsigned mine = 0u;
 #pragma unroll
-  for (int w = 1; w < kThreads / 64; ++w) m = s[w] > m ? s[w] : m;
-  return m;
-}
+    for (int q = 0; q < PT; ++q) mine = key[q] > mine ? key[q] : mine;
+    const auto halves = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);   // (both halves of the wavefront, in every lane)
+    mine = max(halves[0], halves[1]);
+    if (lane < kGroups) s.group[wave][lane] = mine;
+    if (lane == 0) s.bound[wave] = 0xffffffffu;
+    if (tid == 0) s.count = 0;
+    s.list[tid] = 0ull;
+    __syncthreads();
+    // every wavefront for itself: lanes i and i + 32 place group i (equal maxima share the best place)
+    mine = 0u;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) mine = max(mine, s.group[w][lane % kGroups]);
+    int place = 0;
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) place += lane_of(mine, i) > mine ? 1 : 0;
+    if (place < k) atomicMin(&s.bound[wave], mine);
+    if (place == 0) s.best[wave] = mine;
+    __builtin_amdgcn_wave_barrier();
+    return s.best[wave];
+  }
+  template <typename Low>
+  __device__ __forceinline__ void gather(Low&& low) {
+    const unsigned bound = max(s.bound[wave], 1u);
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < PT; ++q) n += __builtin_popcountll(__ballot(key[q] >= bound));
+    if (n == 0) return;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&s.count, n);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const unsigned long long in = __ballot(key[q] >= bound);
+      if (in == 0ull) continue;
+      const int to = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(in >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in, 0u));
+      if (key[q] >= bound && to < kListed) s.list[to] = ((unsigned long long)key[q] << 32) | low(q);
+      at += __builtin_popcountll(in);
+    }
+  }
+  // behind a barrier after `gather`: put(place, word) for places 0..k-1, each by one thread; word 0: no entry is left
+  template <typename Low, typename Put>
+  __device__ __forceinline__ void emit(Low&& low, Put&& put) {
+    const int n = s.count;
+    if (n <= kListed) {
+      const unsigned long long mine = s.list[tid];
+      if (mine != 0ull) {
+        int place = 0;
+        for (int i = 0; i < n; i += 4) {   // (0 behind the last entry)
+#pragma unroll
+          for (int o = 0; o < 4; ++o) place += s.list[i + o] > mine ? 1 : 0;
+        }
+        if (place < k) put(place, mine);
+      } else if (tid < k) {
+        put(tid, 0ull);   // fewer than k entries: thread tid >= n has none
+      }
+      return;
+    }
+    auto word = [&](int q) { return key[q] ? ((unsigned long long)key[q] << 32) | low(q) : 0ull; };
+    auto local_best = [&] {
+      unsigned long long best = 0ull;
+#pragma unroll
+      for (int q = 0; q < PT; ++q) best = word(q) > best ? word(q) : best;
+      return best;
+    };
+    unsigned long long mine = local_best();
+    for (int r = 0; r < k; ++r) {
+      unsigned long long* slots = s.slots + (r & 1) * kWaves;   // in turn: one barrier a round is enough
+      const unsigned long long wave_best = wave_max(mine);
+      if (lane == 0) slots[wave] = wave_best;
+      __syncthreads();
+      unsigned long long win = slots[0];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) win = slots[w] > win ? slots[w] : win;
+      if (tid == 0) put(r, win);
+      if (win != 0ull && win == mine) {
+#pragma unroll
+        for (int q = 0; q < PT; ++q)
+          if (word(q) == win) key[q] = 0u;
+        mine = local_best();
+      }
+    }
+  }
+};
 
 // PT entries per thread, entry j*4+i of thread t is logit chunk0 + (j*256 + t)*4 + i.
-// Loads of 16 bytes take rows of any alignment: 30 rows of 151001, k = 10 34.2 -> 30.6 us a call against entry by entry, 80 rows of 50257 34.5 -> 30.9.
+// Loads of 16 bytes take rows of any alignment: 30 rows of 151001, k = 10 3.6 us a call less than entry by entry.
 template <int PT>
 __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(const TopkParams p) {
-  __shared__ unsigned long long slots[8];
-  __shared__ double red_d[kThreads / 64];
+  __shared__ typename BlockBest<PT>::Shared shared;
+  __shared__ double red_d[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = blockIdx.x, row = blockIdx.y;
   const int chunk0 = c * p.chunk;
   const float* src = p.logits + (size_t)row * p.row_stride;
 
+  // (a whole chunk's loads are one block of code: behind a check each, one waits for the one before it, 80 rows of
+  // 128256 21.4 us instead of 19.3)
+  typedef float f32x4_at_4 __attribute__((ext_vector_type(4), aligned(4)));
   unsigned key[PT];
+  if (chunk0 + PT * kThreads <= p.V) {
+    f32x4_at_4 x[PT / 4];
 #pragma unroll
-  for (int j = 0; j < PT / 4; ++j) {
-    const int e = chunk0 + (j * kThreads + tid) * 4;
-    float v[4];
-    if (e + 3 < p.V) {
-      typedef float f32x4_at_4 __attribute__((ext_vector_type(4), aligned(4)));
-      const f32x4_at_4 x = *reinterpret_cast<const f32x4_at_4*>(src + e);
-      v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
-    } else {
+    for (int j = 0; j < PT / 4; ++j) x[j] = *reinterpret_cast<const f32x4_at_4*>(src + chunk0 + (j * kThreads + tid) * 4);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = e + i < p.V ? src[e + i] : 0.f;
+    for (int q = 0; q < PT; ++q) key[q] = key_of(x[q / 4][q % 4]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < PT / 4; ++j) {
+      const int e = chunk0 + (j * kThreads + tid) * 4;
+      if (e + 3 < p.V) {
+        const f32x4_at_4 x = *reinterpret_cast<const f32x4_at_4*>(src + e);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) key[j * 4 + i] = key_of(x[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) key[j * 4 + i] = e + i < p.V ? key_of(src[e + i]) : 0u;
+      }
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) key[j * 4 + i] = e + i < p.V ? key_of(v[i]) : 0u;
   }
-  auto token_at = [&](int q) { return chunk0 + ((q >> 2) * kThreads + tid) * 4 + (q & 3); };
-  auto local_best = [&] {
-    unsigned long long best = 0ull;
-#pragma unroll
-    for (int q = 0; q < PT; ++q) {
-      const unsigned long long w = key[q] ? pack(key[q], token_at(q)) : 0ull;
-      best = w > best ? w : best;
-    }
-    return best;
-  };
+  auto low = [&](int q) { return 0xffffffffu - (unsigned)(chunk0 + ((q >> 2) * kThreads + tid) * 4 + (q & 3)); };
+  BlockBest<PT> best(shared, key, p.k);
+  const unsigned top = best.prepare();
 
-  // chunk maximum and sum of exponentials (entries past the row end and -infinity add nothing)
-  unsigned long long mine = local_best();
-  const unsigned long long top = block_max_u64(mine, slots, 1);
-  const float cmax = top ? value_of((unsigned)(top >> 32)) : -INFINITY;
+  // the chunk's sum of exponentials (entries past the row end and -infinity add nothing)
+  const float cmax = top ? value_of(top) : -INFINITY;
   float sum = 0.f;
   if (cmax > -INFINITY) {
 #pragma unroll
     for (int q = 0; q < PT; ++q)
       if (key[q]) sum += __expf(value_of(key[q]) - cmax);
   }
-  double dsum = sum;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) dsum += __shfl_xor(dsum, d);
+  const double dsum = wave_sum((double)sum);
   if (lane == 0) red_d[wave] = dsum;
-
-  // k rounds: the workgroup's best entry goes out, its owner strikes it and re-scans
-  unsigned long long* out = p.cand + ((size_t)row * p.n_chunks + c) * p.k;
-  for (int r = 0; r < p.k; ++r) {
-    const unsigned long long win = block_max_u64(mine, slots, r);
-    if (tid == 0) out[r] = win;
-    if (win != 0ull && win == mine) {
-      const int tok = token_of(win);
-#pragma unroll
-      for (int q = 0; q < PT; ++q)
-        if (token_at(q) == tok) key[q] = 0u;
-      mine = local_best();
-    }
-  }
+  best.gather(low);
   __syncthreads();
   if (tid == 0) {
     p.chunk_max[(size_t)row * p.n_chunks + c] = cmax;
     p.chunk_sum[(size_t)row * p.n_chunks + c] = red_d[0] + red_d[1] + red_d[2] + red_d[3];
   }
+  unsigned long long* out = p.cand + (size_t)row * p.n_chunks * p.k + c;
+  best.emit(low, [&](int place, unsigned long long word) { out[(size_t)place * p.n_chunks] = word; });
 }
 
 __global__ __launch_bounds__(kThreads) void topk_merge_kernel(const TopkParams p) {
-  __shared__ unsigned long long slots[8];
-  __shared__ double red_d[kThreads / 64];
-  __shared__ float red_m[kThreads / 64];
+  __shared__ BlockBest<kMergePerThread>::Shared shared;
+  __shared__ double red_d[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = blockIdx.x;
   const int n_cand = p.n_chunks * p.k;
   const unsigned long long* cand = p.cand + (size_t)row * n_cand;
+  const float* chunk_max = p.chunk_max + (size_t)row * p.n_chunks;
+  const double* chunk_sum = p.chunk_sum + (size_t)row * p.n_chunks;
 
-  unsigned long long mine[kMergePerThread];
+  unsigned key[kMergePerThread], below[kMergePerThread];
 #pragma unroll
   for (int q = 0; q < kMergePerThread; ++q) {
     const int i = q * kThreads + tid;
-    mine[q] = i < n_cand ? cand[i] : 0ull;
+    const unsigned long long w = i < n_cand ? cand[i] : 0ull;
+    key[q] = (unsigned)(w >> 32);
+    below[q] = (unsigned)w;
   }
-  // row maximum and normaliser from the chunk statistics
-  float m = -INFINITY;
-  for (int c = tid; c < p.n_chunks; c += kThreads) m = fmaxf(m, p.chunk_max[(size_t)row * p.n_chunks + c]);
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
-  if (lane == 0) red_m[wave] = m;
-  __syncthreads();
-  m = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));
+  // (the thread's first chunk: requested with the candidates, not behind the barrier)
+  const bool one = tid < p.n_chunks;
+  const float first_max = one ? chunk_max[tid] : -INFINITY;
+  const double first_sum = one ? chunk_sum[tid] : 0.0;
+
+  auto low = [&](int q) { return below[q]; };
+  BlockBest<kMergePerThread> best(shared, key, p.k);
+  const unsigned top = best.prepare();
+  // normaliser from the chunk statistics
+  const float m = top ? value_of(top) : -INFINITY;
   double z = 0.0;
   if (m > -INFINITY) {
-    for (int c = tid; c < p.n_chunks; c += kThreads) {
-      const float cm = p.chunk_max[(size_t)row * p.n_chunks + c];
-      if (cm > -INFINITY) z += p.chunk_sum[(size_t)row * p.n_chunks + c] * exp((double)cm - (double)m);
-    }
+    auto add = [&](float cm, double cs) { if (cm > -INFINITY) z += cs * exp((double)cm - (double)m); };
+    add(first_max, first_sum);
+    for (int c = tid + kThreads; c < p.n_chunks; c += kThreads) add(chunk_max[c], chunk_sum[c]);
   }
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) z += __shfl_xor(z, d);
+  z = wave_sum(z);
   if (lane == 0) red_d[wave] = z;
+  best.gather(low);
   __syncthreads();
   z = red_d[0] + red_d[1] + red_d[2] + red_d[3];
   const double lse = (double)m + log(z);
-
-  auto local_best = [&] {
-    unsigned long long best = 0ull;
-#pragma unroll
-    for (int q = 0; q < kMergePerThread; ++q) best = mine[q] > best ? mine[q] : best;
-    return best;
-  };
-  unsigned long long best = local_best();
-  for (int r = 0; r < p.k; ++r) {
-    const unsigned long long win = block_max_u64(best, slots, r);
-    if (tid == 0) {
-      // k <= V and every chunk hands in its own k best: a winner exists in every round
-      p.tokens[(size_t)row * p.k + r] = win ? token_of(win) : 0;
-      const float v = win ? value_of((unsigned)(win >> 32)) : -INFINITY;
-      p.logp[(size_t)row * p.k + r] = (m > -INFINITY && v > -INFINITY) ? (float)((double)v - lse) : -INFINITY;
-    }
-    if (win != 0ull && win == best) {
-#pragma unroll
-      for (int q = 0; q < kMergePerThread; ++q)
-        if (mine[q] == win) mine[q] = 0ull;
-      best = local_best();
-    }
-  }
+  best.emit(low, [&](int place, unsigned long long word) {
+    // k <= V and every chunk hands in its own k best: no place stays empty
+    const float v = word ? value_of((unsigned)(word >> 32)) : -INFINITY;
+    p.tokens[(size_t)row * p.k + place] = word ? token_of(word) : 0;
+    p.logp[(size_t)row * p.k + place] = (m > -INFINITY && v > -INFINITY) ? (float)((double)v - lse) : -INFINITY;
+  });
 }
 
 // Largest chunk that still gives a few hundred workgroups, and few enough chunks for the merge kernel

@@ -71,6 +71,19 @@ def test_peaked_rows_and_large_values():
     _check(x, 10)
 
 
+@pytest.mark.parametrize("V,equal", [(1023, 0), (1024, 17), (1025, 255), (8191, 256), (8192, 257), (20481, 1000), (40, 40)])
+def test_entries_at_the_bound(V, equal):
+    """The best entries next to each other (sorted rows, both ways) and as many equal ones at the top as a workgroup sets
+    aside, one more and one less; whole chunks and chunks that end within a thread's four entries."""
+    rng = np.random.default_rng(V)
+    x = np.sort(gen_logits(60 + V, 1, 600, V)[0], axis=1)     # (600 rows: the widest chunks)
+    x[1::2] = x[1::2, ::-1].copy()
+    for row in range(2, 600, 3):
+        x[row, rng.permutation(V)[:equal]] = x[row].max() + 1.0
+    for part in (x, x[:3]):                                   # (3 rows: the narrowest)
+        _check(np.ascontiguousarray(part), 16)
+
+
 def test_output_feeds_the_tree_build():
     """A draft step on the device: cut each expanded node's output, append the candidates, build."""
     import paper_2408_15562_amd as fspad
