@@ -67,42 +67,64 @@ struct Partials {
   const float* base;
   Split split;
   int32_t rows;
+
   // Sums over the slots of 4 consecutive columns each (from the first slice `slice0` of a problem), in workgroup order.
-  // The slots of a slice are some two to nine; the loads of kInFlight of them, of all N sums, are under way together
-  // (one by one each was a round trip to
-  // memory: draft step of 4 rows 194 -> 190 us, six such passes).
+  // The slots of a slice are some two to nine, and the passes that sum them are bound by their trips to memory. `request`
+  // sends for up to 2 * kInFlight slots of all N sums at once, and a kernel requests whatever else it reads (residual, gain)
+  // beside it, so that one trip is over at `finish` (slots behind those are fetched there). With the slots four at a time,
+  // the residual behind the sums, the gains behind the normalisation's barrier and the rotary angles (a trip for the
+  // position, sine and cosine in fp64) before the first slot, a draft step of 4 rows took 174.8 us instead of 171.8, one of
+  // 40 rows (6656 / 17920) 479.5 instead of 475.0; with the slots one by one some 4 us more.
+  static constexpr int kInFlight = 4;
   template <int N>
-  __device__ __forceinline__ void sum(const int (&slice0)[N], int row, const int (&col)[N], f32x4 (&a)[N]) const {
-    constexpr int kInFlight = 4;
-    const size_t slot = (size_t)rows * kSliceRows;
+  struct Sums {
     const float* p[N];
-    int n[N], longest = 0;
+    int n[N], longest;
+    f32x4 v[2][N][kInFlight];
+  };
+  template <int N>
+  __device__ __forceinline__ void request(const int (&slice0)[N], int row, const int (&col)[N], Sums<N>& s) const {
+    const size_t slot = (size_t)rows * kSliceRows;
+    s.longest = 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int slice = slice0[i] + col[i] / kSliceRows;
       const int w0 = owner_of(split, slice * split.stages), w1 = owner_of(split, slice * split.stages + split.stages - 1);
-      p[i] = base + (size_t)(slice + w0) * slot + (size_t)row * kSliceRows + col[i] % kSliceRows;
-      n[i] = w1 - w0 + 1;
-      longest = max(longest, n[i]);
-      a[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      s.p[i] = base + (size_t)(slice + w0) * slot + (size_t)row * kSliceRows + col[i] % kSliceRows;
+      s.n[i] = w1 - w0 + 1;
+      s.longest = max(s.longest, s.n[i]);
     }
-    for (int s0 = 0; s0 < longest; s0 += kInFlight) {
-      f32x4 v[N][kInFlight];
+    fetch(s, 0, s.v[0]);
+    if (s.longest > kInFlight) fetch(s, kInFlight, s.v[1]);
+  }
+  template <int N>
+  __device__ __forceinline__ void finish(Sums<N>& s, f32x4 (&a)[N]) const {
 #pragma unroll
-      for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int k = 0; k < kInFlight; ++k) v[i][k] = *reinterpret_cast<const f32x4*>(p[i] + (size_t)min(s0 + k, n[i] - 1) * slot);
-#pragma unroll
-      for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int k = 0; k < kInFlight; ++k)
-          if (s0 + k < n[i]) a[i] += v[i][k];
+    for (int i = 0; i < N; ++i) a[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    add(s, 0, s.v[0], a);
+    if (s.longest > kInFlight) add(s, kInFlight, s.v[1], a);
+    for (int s0 = 2 * kInFlight; s0 < s.longest; s0 += kInFlight) {
+      fetch(s, s0, s.v[0]);
+      add(s, s0, s.v[0], a);
     }
   }
-  __device__ __forceinline__ f32x4 sum(int slice0, int row, int col) const {
-    f32x4 a[1];
-    sum<1>({slice0}, row, {col}, a);
-    return a[0];
+
+ private:
+  template <int N>
+  __device__ __forceinline__ void fetch(const Sums<N>& s, int s0, f32x4 (&v)[N][kInFlight]) const {
+    const size_t slot = (size_t)rows * kSliceRows;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k) v[i][k] = *reinterpret_cast<const f32x4*>(s.p[i] + (size_t)min(s0 + k, s.n[i] - 1) * slot);
+  }
+  template <int N>
+  __device__ __forceinline__ void add(const Sums<N>& s, int s0, const f32x4 (&v)[N][kInFlight], f32x4 (&a)[N]) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k)
+        if (s0 + k < s.n[i]) a[i] += v[i][k];
   }
 };
 
@@ -160,39 +182,25 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams p) {
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
   const int row = blockIdx.y, col = 4 * (int)(blockIdx.x * 256 + threadIdx.x);
   if (col >= p.N) return;
-  const size_t q = ((size_t)row * p.N + col) / 4;
-  f32x4 a, b;
-  if (MODE == 0) {
-    f32x4 both[2];
-    p.part.sum<2>({0, (p.N + kSliceRows - 1) / kSliceRows}, row, {col, col}, both);
-    a = both[0];
-    b = both[1];
-  } else {
-    a = p.part.sum(0, row, col);
-  }
+  const int half_n = p.N / 2;
+  const bool second = MODE == 2 && col >= half_n;
+  const size_t at = MODE == 2 ? ((size_t)row * half_n + (second ? col - half_n : col)) * 2 : ((size_t)row * p.N + col) * 2;   // bytes
+  constexpr int kSums = MODE == 0 ? 2 : 1;
+  int slice0[kSums] = {0}, cols[kSums] = {col};
+  if constexpr (MODE == 0) { slice0[1] = (p.N + kSliceRows - 1) / kSliceRows; cols[1] = col; }
+  Partials::Sums<kSums> sums;
+  p.part.request<kSums>(slice0, row, cols, sums);
+  bf16x4 r = {0, 0, 0, 0};
+  if (MODE == 2 || (MODE == 1 && p.residual)) r = *reinterpret_cast<const bf16x4*>(p.f + at);
+  f32x4 a[kSums];
+  p.part.finish<kSums>(sums, a);
   bf16x4 o;
-  if (MODE == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = (__bf16)(b[i] / (1.0f + __expf(-b[i])) * a[i]);   // a: up, b: gate
-  } else if (MODE == 1) {
-    if (p.residual) {
-      const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.f + 8 * q);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] += (float)r[i];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = (__bf16)a[i];
-  } else {
-    const int half_n = p.N / 2;
-    const bool second = col >= half_n;
-    const size_t at = ((size_t)row * half_n + (second ? col - half_n : col)) * 2;   // bytes
-    const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.f + at);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = (__bf16)(a[i] + (float)r[i]);
-    *reinterpret_cast<bf16x4*>((second ? p.out2 : p.out) + at) = o;
-    return;
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (MODE == 0) o[i] = (__bf16)(a[1][i] / (1.0f + __expf(-a[1][i])) * a[0][i]);   // 0: up, 1: gate
+    else o[i] = (__bf16)(MODE == 2 || p.residual ? a[0][i] + (float)r[i] : a[0][i]);
   }
-  *reinterpret_cast<bf16x4*>(p.out + 8 * q) = o;
+  *reinterpret_cast<bf16x4*>((second ? p.out2 : p.out) + at) = o;
 }
 
 // RMSNorm of one row per workgroup: out = x / sqrt(mean(x^2) + eps) * gain, fp32 arithmetic, one
@@ -205,16 +213,25 @@ struct RmsNormParams {
   float eps;
 };
 __global__ __launch_bounds__(256) void rms_norm_kernel(const RmsNormParams p) {
+  constexpr int kKept = 4;   // of a thread's pieces, in registers
   __shared__ float wave_sum[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const char* xr = p.x + (size_t)blockIdx.x * p.Hd * 2;
   const int n_vec = p.Hd / 8;
+  const auto vec = [](const char* at, int v) { return *reinterpret_cast<const bf16x8*>(at + 16 * v); };
+  bf16x8 x[kKept], gain[kKept];
+#pragma unroll
+  for (int k = 0; k < kKept; ++k)
+    if (const int v = tid + 256 * k; v < n_vec) { x[k] = vec(xr, v); gain[k] = vec(p.gain, v); }
   float ss = 0.f;
-  for (int v = tid; v < n_vec; v += 256) {
-    const bf16x8 xv = *reinterpret_cast<const bf16x8*>(xr + 16 * v);
+  auto square = [&](const bf16x8& xv) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) { const float t = (float)xv[i]; ss += t * t; }
-  }
+  };
+#pragma unroll
+  for (int k = 0; k < kKept; ++k)
+    if (tid + 256 * k < n_vec) square(x[k]);
+  for (int v = tid + 256 * kKept; v < n_vec; v += 256) square(vec(xr, v));
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
   if (lane == 0) wave_sum[wave] = ss;
@@ -222,19 +239,22 @@ __global__ __launch_bounds__(256) void rms_norm_kernel(const RmsNormParams p) {
   const float total = (wave_sum[0] + wave_sum[1]) + (wave_sum[2] + wave_sum[3]);
   const float inv = 1.0f / sqrtf(total / (float)p.Hd + p.eps);
   char* outr = p.out + (size_t)blockIdx.x * p.Hd * 2;
-  for (int v = tid; v < n_vec; v += 256) {
-    const bf16x8 xv = *reinterpret_cast<const bf16x8*>(xr + 16 * v);
-    const bf16x8 gv = *reinterpret_cast<const bf16x8*>(p.gain + 16 * v);
+  auto scale = [&](int v, const bf16x8& xv, const bf16x8& gv) {
     bf16x8 o;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = (__bf16)((float)xv[i] * inv * (float)gv[i]);
     *reinterpret_cast<bf16x8*>(outr + 16 * v) = o;
-  }
+  };
+#pragma unroll
+  for (int k = 0; k < kKept; ++k)
+    if (const int v = tid + 256 * k; v < n_vec) scale(v, x[k], gain[k]);
+  for (int v = tid + 256 * kKept; v < n_vec; v += 256) scale(v, vec(xr, v), vec(p.gain, v));
 }
 
 // Output projection's epilogue and the normalisation that follows it, one row per workgroup:
 // h = sum of the partials + residual (rounded to bf16, written), then out = rmsnorm(h) of the rounded
-// values, as rms_norm_kernel would compute it from h. Every thread re-reads only what it wrote. 1024
+// values, as rms_norm_kernel would compute it from h. What a thread wrote of h stays in its registers (of rows of more than
+// 1024 * 4 * kKept entries the rest is read back, by the same thread). 1024
 // threads: with the few rows of a draft step the row's loads must all be in flight at once.
 struct CombineNormParams {
   Partials part;
@@ -247,22 +267,42 @@ struct CombineNormParams {
 };
 __global__ __launch_bounds__(1024) void combine_norm_kernel(const CombineNormParams p) {
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+  constexpr int kKept = 2;   // of a thread's quads, in registers
   __shared__ float wave_sum[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const size_t row_at = (size_t)blockIdx.x * p.Hd;
   const int n_quads = p.Hd / 4;
+  const auto quad = [](const char* at, size_t i) { return *reinterpret_cast<const bf16x4*>(at + 2 * i); };
+  Partials::Sums<1> sums[kKept];
+  bf16x4 kept[kKept], gain[kKept];
+#pragma unroll
+  for (int k = 0; k < kKept; ++k)
+    if (const int q = tid + 1024 * k; q < n_quads) {
+      p.part.request<1>({0}, blockIdx.x, {4 * q}, sums[k]);
+      kept[k] = quad(p.residual, row_at + 4 * q);
+      gain[k] = quad(p.gain, 4 * q);
+    }
   float ss = 0.f;
-  for (int q = tid; q < n_quads; q += 1024) {
-    const f32x4 a = p.part.sum(0, blockIdx.x, 4 * q);
-    const bf16x4 r = *reinterpret_cast<const bf16x4*>(p.residual + (row_at + 4 * q) * 2);
+  auto state = [&](int q, Partials::Sums<1>& sum, const bf16x4& r) {   // four entries of h
+    f32x4 a[1];
+    p.part.finish<1>(sum, a);
     bf16x4 o;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      o[i] = (__bf16)(a[i] + (float)r[i]);
+      o[i] = (__bf16)(a[0][i] + (float)r[i]);
       const float t = (float)o[i];
       ss += t * t;
     }
     *reinterpret_cast<bf16x4*>(p.h + (row_at + 4 * q) * 2) = o;
+    return o;
+  };
+#pragma unroll
+  for (int k = 0; k < kKept; ++k)
+    if (const int q = tid + 1024 * k; q < n_quads) kept[k] = state(q, sums[k], kept[k]);
+  for (int q = tid + 1024 * kKept; q < n_quads; q += 1024) {
+    Partials::Sums<1> sum;
+    p.part.request<1>({0}, blockIdx.x, {4 * q}, sum);
+    state(q, sum, quad(p.residual, row_at + 4 * q));
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
@@ -272,14 +312,16 @@ __global__ __launch_bounds__(1024) void combine_norm_kernel(const CombineNormPar
 #pragma unroll
   for (int i = 0; i < 16; ++i) total += wave_sum[i];
   const float inv = 1.0f / sqrtf(total / (float)p.Hd + p.eps);
-  for (int q = tid; q < n_quads; q += 1024) {
-    const bf16x4 hv = *reinterpret_cast<const bf16x4*>(p.h + (row_at + 4 * q) * 2);
-    const bf16x4 gv = *reinterpret_cast<const bf16x4*>(p.gain + 8 * q);
+  auto scale = [&](int q, const bf16x4& hv, const bf16x4& gv) {
     bf16x4 o;
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = (__bf16)((float)hv[i] * inv * (float)gv[i]);
     *reinterpret_cast<bf16x4*>(p.out + (row_at + 4 * q) * 2) = o;
-  }
+  };
+#pragma unroll
+  for (int k = 0; k < kKept; ++k)
+    if (const int q = tid + 1024 * k; q < n_quads) scale(q, kept[k], gain[k]);
+  for (int q = tid + 1024 * kKept; q < n_quads; q += 1024) scale(q, quad(p.h, row_at + 4 * q), quad(p.gain, 4 * q));
 }
 
 // Sum of the q / k / v projection's partials, rotary encoding of the query and key heads, scatter
@@ -303,6 +345,9 @@ __global__ __launch_bounds__(256) void qkv_rope_kernel(const QkvRopeParams p) {
   __shared__ float2 turn[64];   // cosine and sine of entry i
   const int quad_shift = p.D == 128 ? 4 : 3, heads = p.Hq + 2 * p.Hkv, half = p.D / 2;
   const int row = blockIdx.y, t = (int)(blockIdx.x * 256 + threadIdx.x);
+  const int j = t & ((1 << quad_shift) - 1), head = t >> quad_shift;
+  Partials::Sums<2> sums;
+  if (head < heads) p.part.request<2>({0, 0}, row, {head * p.D + 4 * j, head * p.D + 4 * j + half}, sums);   // (on their way beside the angles)
   if ((int)threadIdx.x < half) {
     const double ang = (double)p.positions[row] * exp2((double)threadIdx.x * p.neg_log2_theta_2_over_d);
     double sn, cs;
@@ -310,10 +355,9 @@ __global__ __launch_bounds__(256) void qkv_rope_kernel(const QkvRopeParams p) {
     turn[threadIdx.x] = make_float2((float)cs, (float)sn);
   }
   __syncthreads();
-  const int j = t & ((1 << quad_shift) - 1), head = t >> quad_shift;
   if (head >= heads) return;
   f32x4 ab[2];
-  p.part.sum<2>({0, 0}, row, {head * p.D + 4 * j, head * p.D + 4 * j + half}, ab);
+  p.part.finish<2>(sums, ab);
   const f32x4 a = ab[0], b = ab[1];
   char* dst;
   if (head < p.Hq) dst = p.q + ((size_t)row * p.Hq + head) * p.D * 2;

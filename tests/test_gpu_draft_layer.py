@@ -80,6 +80,15 @@ def test_shapes(B, Nmax, Hd, I, Hq, Hkv, D, kv_len, n_nodes):
     _run(200 + Nmax + Hd // 256, B, Nmax, Hd, I, Hq, Hkv, D, kv_len, n_nodes)
 
 
+@pytest.mark.parametrize("B,Nmax,Hd,I,Hq,Hkv,D", [
+    (1, 5, 8192, 256, 2, 1, 128),     # rows of the normalisations just fit the registers, 17 partial sums of a q / k / v column
+    (1, 3, 8448, 512, 2, 1, 128),     # and are longer than that
+    (2, 33, 256, 256, 32, 4, 128),    # 16 partial sums of a column of the output projection, 66 rows
+])
+def test_long_rows_and_many_partial_sums(B, Nmax, Hd, I, Hq, Hkv, D):
+    _run(Hd + Nmax, B, Nmax, Hd, I, Hq, Hkv, D, [37] * B)
+
+
 def test_repeatable_and_other_constants():
     a = _run(5, 2, 12, 256, 512, 4, 2, 64, [90, 45], theta=500000.0, eps=1e-6)
     b = _run(5, 2, 12, 256, 512, 4, 2, 64, [90, 45], theta=500000.0, eps=1e-6)
