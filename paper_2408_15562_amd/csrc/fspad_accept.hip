@@ -129,6 +129,22 @@ __device__ __forceinline__ void take_better(float& v, int& i, float ov, int oi) 
   if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
 }
 
+// The best of the 64 lanes in that order, in every lane (v is no NaN): the largest value, and nearly always one lane
+// that has it. (Values and indices exchanged step by step are twelve trips through LDS, some 800 clocks.)
+__device__ __forceinline__ void wave_best(float& v, int& i) {
+  const float top = wave_max(v);
+  const unsigned long long at = __ballot(v == top);
+  int first = __builtin_amdgcn_readlane(i, __builtin_ctzll(at));
+  if ((at & (at - 1)) != 0ull) {
+    int x = v == top ? i : kNone;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) x = min(x, __shfl_xor(x, off));
+    first = x;
+  }
+  v = top;
+  i = first;
+}
+
 // ------------------------------------------------------------------------------------------------
 // Streaming pass. MODE 0: greedy (max, argmax). MODE 1: sampling (max, sum of exp).
 // Sixteen bytes per lane and load whatever the rows' alignment (4 bytes at least): entry by entry, as rows that are not 16-byte aligned were
@@ -211,12 +227,7 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
       if (x[4 * k + j] > best) { best = x[4 * k + j]; idx = base + (k * kThreads + tid) * 4 + j; }
 
   // workgroup (max, index): wavefront butterflies, then 4 partials through LDS
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const float ov = __shfl_xor(best, off);
-    const int oi = __shfl_xor(idx, off);
-    take_better(best, idx, ov, oi);
-  }
+  wave_best(best, idx);
   if (lane == 0) { sh_max[wave] = best; sh_idx[wave] = idx; }
   __syncthreads();
   best = sh_max[0]; idx = sh_idx[0];
@@ -229,7 +240,6 @@ __global__ __launch_bounds__(kThreads) void accept_rows_kernel(const AcceptParam
 // Greedy: merge chunk argmaxes per node, then wavefront 0 descends while a child carries the
 // target's token.
 __global__ __launch_bounds__(kThreads) void accept_greedy_walk_kernel(const AcceptParams p) {
-  __shared__ int amax[FSPAD_MAX_NODES];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = p.n_nodes[b];
   const int64_t o = (int64_t)b * p.Nmax;
@@ -265,29 +275,26 @@ __global__ __launch_bounds__(kThreads) void accept_greedy_walk_kernel(const Acce
     q_idx[wave][lane] = idx;
   }
   __syncthreads();
-  if (wave == 0 && lane < n) {
-    float best = q_best[0][lane];
-    int idx = q_idx[0][lane];
-#pragma unroll
-    for (int w = 1; w < 4; ++w) take_better(best, idx, q_best[w][lane], q_idx[w][lane]);
-    amax[lane] = idx == kNone ? 0 : idx;  // a row with nothing above -inf: token 0
-  }
-  __syncthreads();
   if (wave != 0) return;
-  fspad_detail::greedy_descend(amax, n, p.Nmax, lane, o, b, my_par, my_tok, p.path, p.tokens, p.path_len, p.n_tokens);
+  float best = q_best[0][lane];
+  int idx = q_idx[0][lane];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) take_better(best, idx, q_best[w][lane], q_idx[w][lane]);
+  idx = idx == kNone ? 0 : idx;  // a row with nothing above -inf: token 0
+  fspad_detail::greedy_descend(idx, n, p.Nmax, lane, o, b, my_par, my_tok, p.path, p.tokens, p.path_len, p.n_tokens);
 }
 
 // The same in one launch where a row has up to kSmallVocab logits: sixteen to a lane, a wavefront for up to four rows, whose loads are
 // under way together and with the tree's. (Four rows of sixteen are 64 of the 128 registers that a wavefront of sixteen can have: longer
 // rows would need a loop. Rows of unused tree slots are not read: waiting for the number of nodes first costs 0.13 us.) Such a call is
-// launches and trips to memory, us by two launches / so, rows of 1000, a call's share of a graph of a hundred: 1 row 4.6 / 2.6, 16 5.2 / 3.3,
-// 26 5.1 / 4.5, 32 5.2 / 4.9, not aligned 5.3 / 5.1; and 17.0 -> 13.9 the step of attention, acceptance and commit around 26. One workgroup per
-// sequence takes longer the more rows it has, two launches the more there are in all: 8 x 36 5.43 / 5.41, not aligned 5.7 / 5.6, 1 x 40 5.2 / 5.35, not
-// aligned 5.3 / 5.6, 25 x 48 8.1 / 6.9, 17 x 60 6.1 / 7.6, 20 x 60 8.1 / 7.6, 19 x 64 8.1 / 8.3, 21 x 64 8.5 / 8.4, 64 x 64 14.0 / 8.4, 512 x 64 74 / 27.5
-// and with 4 nodes each 42 / 5.0.
+// launches and trips to memory, us by two launches / so, rows of 1000, a call's share of a graph of fifty: 1 x 20 5.05 / 3.14, 1 x 26 5.35 / 3.58, 1 x 36
+// 5.27 / 4.00, 1 x 48 5.47 / 4.93, 4 x 60 5.63 / 5.46, 16 x 60 6.14 / 5.63, 25 x 48 8.29 / 5.32, 200 x 20 12.9 / 3.7; not aligned (rows of 997) 1 x 36 5.33 /
+// 4.41, 1 x 60 5.28 / 5.44, 16 x 60 6.23 / 5.83. One workgroup per sequence takes longer the more rows it has, two launches the more there are in all: 1 x 64
+// 5.47 / 5.75, 8 x 64 5.69 / 6.00, 20 x 64 8.19 / 6.08, 64 x 64 13.1 / 6.1. (Before the best of a wavefront came from a maximum and a ballot (wave_best) 1 x 26 took
+// 5.11 / 1 x 32 5.38 us in one launch, and more than 36 rows were left to two.)
 constexpr int kSmallVocab = 1024;
 bool takes_small_greedy(int32_t B, int32_t Nmax, int32_t V) {
-  return V <= kSmallVocab && (Nmax <= 36 || (int64_t)B * Nmax >= (Nmax <= 60 ? 1200 : 1300));
+  return V <= kSmallVocab && (Nmax <= 60 || (int64_t)B * Nmax >= 1200);
 }
 constexpr int kSmallWaves = 16;
 constexpr int kSmallRows = FSPAD_MAX_NODES / kSmallWaves;   // per wavefront
@@ -334,17 +341,12 @@ __global__ __launch_bounds__(64 * kSmallWaves) void accept_greedy_small_kernel(c
         const int e = entry(k, j);
         if (e < V && x[r][4 * k + j] > best) { best = x[r][4 * k + j]; idx = e; }   // (a NaN is above nothing)
       }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const float ov = __shfl_xor(best, off);
-      const int oi = __shfl_xor(idx, off);
-      take_better(best, idx, ov, oi);
-    }
+    wave_best(best, idx);
     if (lane == 0) amax[node] = idx == kNone ? 0 : idx;   // a row with nothing above -inf: token 0
   }
   __syncthreads();
   if (wave != 0) return;
-  fspad_detail::greedy_descend(amax, n, p.Nmax, lane, o, b, my_par, my_tok, p.path, p.tokens, p.path_len, p.n_tokens);
+  fspad_detail::greedy_descend(amax[lane], n, p.Nmax, lane, o, b, my_par, my_tok, p.path, p.tokens, p.path_len, p.n_tokens);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -358,7 +358,6 @@ __global__ __launch_bounds__(kWalkThreads) void lm_head_walk_kernel(const LmWalk
   constexpr int kParts = kWalkThreads / 64;
   __shared__ float q_best[kParts][FSPAD_MAX_NODES];
   __shared__ int q_idx[kParts][FSPAD_MAX_NODES];
-  __shared__ int target[FSPAD_MAX_NODES];
   const int b = blockIdx.x, lane = threadIdx.x & 63, part = threadIdx.x >> 6;
   const int n = min(p.n_nodes[b], p.Nmax);
   const int64_t o = (int64_t)b * p.Nmax;
@@ -379,9 +378,9 @@ __global__ __launch_bounds__(kWalkThreads) void lm_head_walk_kernel(const LmWalk
         int ix[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-          const int c = c0 + kParts * k;
-          v[k] = c < p.n_slices ? p.part_max[c * rows + o + lane] : -INFINITY;
-          ix[k] = c < p.n_slices ? p.part_idx[c * rows + o + lane] : kNone;
+          const int c = min(c0 + kParts * k, p.n_slices - 1);   // (the last one again changes nothing)
+          v[k] = p.part_max[c * rows + o + lane];
+          ix[k] = p.part_idx[c * rows + o + lane];
         }
 #pragma unroll
         for (int k = 0; k < 16; ++k) take_better(best, idx, v[k], ix[k]);
@@ -392,24 +391,16 @@ __global__ __launch_bounds__(kWalkThreads) void lm_head_walk_kernel(const LmWalk
   }
   __syncthreads();
   if (part != 0) return;
-  if (lane < p.Nmax) {
-    float best = -INFINITY;
-    int idx = kNone;
-    if (lane < n) {
-      best = q_best[0][lane];
-      idx = q_idx[0][lane];
+  float best = q_best[0][lane];
+  int idx = q_idx[0][lane];
 #pragma unroll
-      for (int w = 1; w < kParts; ++w) take_better(best, idx, q_best[w][lane], q_idx[w][lane]);
-      if (idx == kNone) idx = 0;  // a row with nothing above -inf: token 0
-      target[lane] = idx;
-    }
+  for (int w = 1; w < kParts; ++w) take_better(best, idx, q_best[w][lane], q_idx[w][lane]);
+  if (idx == kNone) idx = 0;  // a row with nothing above -inf: token 0
+  if (lane < p.Nmax) {
     if (p.node_target) p.node_target[o + lane] = lane < n ? idx : -1;
     if (p.node_top) p.node_top[o + lane] = lane < n ? best : -INFINITY;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  fspad_detail::greedy_descend(target, n, p.Nmax, lane, o, b, my_par, my_tok, p.path, p.tokens, p.path_len, p.n_tokens);
+  fspad_detail::greedy_descend(idx, n, p.Nmax, lane, o, b, my_par, my_tok, p.path, p.tokens, p.path_len, p.n_tokens);
 }
 
 struct LmSampleWalkParams {
