@@ -1818,9 +1818,12 @@ __global__ __launch_bounds__(64 * WAVES) void tree_attn_f32_kernel(const AttnPar
     float M = sh_m[0][t], num = 0.f, den = 0.f;
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sh_m[w][t]);
+    // (t is the same in a whole wavefront, whose lane w forms the share of wavefront w)
+    const float own = sh_m[lane % WAVES][t];
+    const float share = own > -INFINITY ? expf(own - M) : 0.f;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {   // in wavefront order: deterministic
-      const float a = sh_m[w][t] > -INFINITY ? expf(sh_m[w][t] - M) : 0.f;
+      const float a = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, share), w));
       den += a * sh_l[w][t];
       num += a * sh_o[w][t][d];
     }
@@ -2155,8 +2158,13 @@ void launch_f32(const AttnParams& prm, hipStream_t stream) {
   for (int b = 0; b < prm.B; ++b) longest = prm.seq[b].kv_len > longest ? prm.seq[b].kv_len : longest;
   const bool single = longest <= (few ? kTile / 2 : 2 * kTile);
   const bool one = few || single;
+  // Sixteen wavefronts where eight take more than a turn and no compute unit gets a second workgroup. us by eight / sixteen, 8 heads of
+  // 64: 26 nodes, 256 keys 5.38 / 5.27, 500 6.93 / 6.67, 700 8.52 / 7.43, 4 nodes, 1000 keys 10.3 / 9.0; 16 heads of 128, 16 nodes, 130
+  // keys 5.92 / 5.41; 8 of 128, 30 nodes, 400 keys 9.12 / 8.12. (Twelve keys' loads a lane in one turn instead of eight in two: 5.38 -> 5.32.)
+  const bool wide = (int64_t)prm.B * prm.Hq * prm.Nmax <= kComputeUnits && longest + prm.Nmax > kF32Waves * kTile;
   const dim3 grid((unsigned)prm.Hq, (unsigned)(one ? prm.Nmax : (prm.Nmax + 1) / 2), (unsigned)prm.B), block(64 * kF32Waves);
   if (single) hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1, 1>), grid, dim3(64), 0, stream, prm);
+  else if (wide) hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1, 2 * kF32Waves>), grid, dim3(2 * 64 * kF32Waves), 0, stream, prm);
   else if (one) hipLaunchKernelGGL((tree_attn_f32_kernel<D, 1, kF32Waves>), grid, block, 0, stream, prm);
   else hipLaunchKernelGGL((tree_attn_f32_kernel<D, 2, kF32Waves>), grid, block, 0, stream, prm);
 }
