@@ -35,54 +35,65 @@ __device__ __forceinline__ unsigned ordered_bits(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// What a candidate waits for its parent to leave: a word of which 0 says "not yet". Every thread repeats its look
+// until all of its wavefront have an answer, without a barrier: a parent's index is smaller than its child's, and a
+// candidate without a valid one answers at once, so that the answers follow from one another and each loop ends. (In
+// rounds between barriers a level took some 500 clocks.) An answer is one 64-bit store, read by one 64-bit load.
+template <typename Answer>
+__device__ __forceinline__ void follow_parents(unsigned long long* words, int c, int parent, bool pending, Answer&& answer) {
+  while (__ballot(pending) != 0ull) {
+    if (pending) {
+      const unsigned long long of_parent = __hip_atomic_load(&words[parent], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (of_parent != 0ull) {
+        __hip_atomic_store(&words[c], answer(of_parent), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        pending = false;
+      }
+    }
+  }
+}
+
+// Bound by latency: a launch of 1.6 us, a trip to memory (what a thread reads is requested at once: candidates past
+// n_cand are read too, and not used), the levels of the tree twice, m comparisons a candidate (of 32 bits, with the index only
+// among a wavefront's own, they took longer: 26 nodes 5.4 us), the ancestors' chain. us a call in a graph, with the number of
+// candidates, the candidates and the tokens in three trips and barriers between the levels -> now: 26 of 85 candidates 7.6 -> 4.6, 60 of
+// 511 14.4 -> 9.3, 8 trees of 48 of 211 7.5 -> 5.4.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void tree_build_kernel(const BuildParams p) {
   constexpr int kWavesPerWg = THREADS / 64;
   typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-  __shared__ float joint[THREADS];
   __shared__ __attribute__((aligned(16))) unsigned long long keys[THREADS];   // 0: not a competitor
+  __shared__ unsigned long long words[2][THREADS];   // joint scores, decisions (follow_parents)
   __shared__ int16_t node_of[THREADS];   // node index of a kept candidate, else -1
-  __shared__ uint8_t state[THREADS];     // pass 1: scored; pass 2: 1 kept, 0 dropped, 2 undecided
   __shared__ int16_t node_par[FSPAD_MAX_NODES];
   __shared__ int wave_count[kWavesPerWg];
   const int b = blockIdx.x, c = threadIdx.x, lane = c & 63, wave = c >> 6;   // candidate c belongs to thread c
+  const size_t at = (size_t)b * p.M + (c < p.M ? c : 0);
+  const int read_parent = p.cand_parent[at], my_token = p.cand_token[at];
+  const float read_logp = p.cand_logp[at];
   int m = p.n_cand[b];
   m = m < 1 ? 1 : (m > p.M ? p.M : m);
   m = m > THREADS ? THREADS : m;
-  const int32_t* cp = p.cand_parent + (size_t)b * p.M;
-  const float* lp = p.cand_logp + (size_t)b * p.M;
 
-  float my_lp = 0.f;
-  int my_par = -2;          // -1 root, -2 unreachable / no candidate
-  bool pending = false;
-  if (c < m) {
-    const int pc = cp[c];
-    const float v = lp[c];
-    my_par = c == 0 ? -1 : ((pc >= 0 && pc < c) ? pc : -2);
-    my_lp = (v != v) ? -INFINITY : v;
-    pending = my_par >= 0;
-    state[c] = c == 0 ? 1 : 0;
-    joint[c] = c == 0 ? 0.f : -INFINITY;   // a candidate that is never reached keeps -infinity
-  }
+  // 1. joint scores: bit 33 an answer, bit 32 reached from the root, below it the score
+  constexpr unsigned long long kAnswer = 2ull << 32, kReached = 3ull << 32;
+  const bool inner = c > 0 && c < m;
+  int my_par = inner && read_parent >= 0 && read_parent < c ? read_parent : -2;   // -1 root, -2 unreachable / no candidate
+  if (c == 0) my_par = -1;
+  const float my_lp = (read_logp != read_logp) ? -INFINITY : read_logp;
+  const unsigned long long lowest = kAnswer | __float_as_uint(-INFINITY);   // a candidate that is never reached keeps -infinity
+  words[0][c] = c == 0 ? kReached : (my_par >= 0 ? 0ull : lowest);
+  words[1][c] = 0ull;
   __syncthreads();
-
-  // 1. joint scores: a candidate is scored in the round after its parent was
-  for (;;) {
-    const bool newly = pending && state[my_par];
-    if (newly) {
-      joint[c] = joint[my_par] + my_lp;
-      pending = false;
-    }
-    __syncthreads();   // all reads of state[] of this round are done
-    if (newly) state[c] = 1;
-    if (!__syncthreads_or(newly)) break;
-  }
-  // candidates that were never reached (bad parent index somewhere above them) cannot be kept
-  if (pending) my_par = -2;
+  follow_parents(words[0], c, my_par, my_par >= 0, [&](unsigned long long up) {
+    return (up & (1ull << 32)) ? kReached | __float_as_uint(__uint_as_float((unsigned)up) + my_lp) : lowest;
+  });
+  const unsigned long long scored = words[0][c];   // (this thread's own store)
+  if (!(scored & (1ull << 32))) my_par = -2;       // not reached (bad parent index somewhere above): cannot be kept
+  const float joint = __uint_as_float((unsigned)scored);
 
   // 2. rank among the non-root candidates: higher joint first, then lower index
   const unsigned long long mine =
-      (c > 0 && c < m) ? (((unsigned long long)ordered_bits(joint[c]) << 32) | (0xffffffffu - (unsigned)c)) : 0ull;
+      inner ? (((unsigned long long)ordered_bits(joint) << 32) | (0xffffffffu - (unsigned)c)) : 0ull;
   keys[c] = mine;
   __syncthreads();
   int rank = 0;
@@ -98,29 +109,15 @@ __global__ __launch_bounds__(THREADS) void tree_build_kernel(const BuildParams p
       rank += (int)(k0 > mine) + (int)(k1 > mine);
     }
   }
-  pending = false;
-  __syncthreads();   // state[] is reused below
-  if (c < m) {
-    const bool top = c > 0 && rank < p.n_keep - 1 && my_par >= 0;
-    state[c] = c == 0 ? 1 : (top ? 2 : 0);
-    pending = top;
-  }
-  __syncthreads();
 
-  // 3. closure: an undecided candidate is kept once its parent is, dropped once its parent is
-  for (;;) {
-    uint8_t decided = 2;
-    if (pending) {
-      const uint8_t ps = state[my_par];
-      if (ps != 2) { decided = ps; pending = false; }
-    }
-    __syncthreads();
-    if (decided != 2) state[c] = decided;
-    if (!__syncthreads_or(decided != 2)) break;
-  }
+  // 3. closure: a candidate among the best is kept once its parent is, dropped once its parent is (1 dropped, 2 kept)
+  const bool top = inner && rank < p.n_keep - 1 && my_par >= 0;
+  if (!top)   // (others may be waiting for it already)
+    __hip_atomic_store(&words[1][c], c == 0 ? 2ull : 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  follow_parents(words[1], c, my_par, top, [&](unsigned long long up) { return up; });
 
   // 4. node index = kept candidates before it
-  const int kept = (c < m && state[c] == 1) ? 1 : 0;
+  const int kept = words[1][c] == 2ull ? 1 : 0;
   int incl = kept;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -145,7 +142,7 @@ __global__ __launch_bounds__(THREADS) void tree_build_kernel(const BuildParams p
     const int pi = c == 0 ? -1 : node_of[my_par];
     node_par[my_node] = (int16_t)pi;
     out_par[my_node] = pi;
-    out_tok[my_node] = p.cand_token[(size_t)b * p.M + c];
+    out_tok[my_node] = my_token;
     out_cand[my_node] = c;
   }
   __syncthreads();

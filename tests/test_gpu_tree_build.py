@@ -48,6 +48,43 @@ def test_padding_chain_and_nan():
     assert got[2].tolist() == [30, 30]      # a NaN edge ranks its subtree last (-infinity), it does not remove it
 
 
+@pytest.mark.parametrize("m", [63, 64, 65, 256, 257, 512, 513, 1024])
+def test_parents_in_other_wavefronts(m):
+    """Chains that cross the wavefronts, parents that do not exist (themselves, later ones, negative ones) and everything below
+    them, rows with candidates behind n_cand whose entries would matter if they were used."""
+    rng = np.random.default_rng(m)
+    par = np.stack([np.maximum(0, np.arange(m) - step) for step in (1, 40, 64)] + [rng.integers(0, np.maximum(1, np.arange(m)))]).astype(np.int32)
+    par[:, 0] = -1
+    hit = rng.random(par.shape) < 0.02
+    hit[:, 0] = False
+    par = np.where(hit, rng.choice([-1, -7, m - 1, m + 3], par.shape), par).astype(np.int32)
+    logp = np.where(rng.random(par.shape) < 0.1, -0.5, -rng.random(par.shape)).astype(np.float32)
+    tok = rng.integers(0, 32000, par.shape).astype(np.int32)
+    n_cand = np.array([m, max(1, m - 1), max(1, m // 2), m], np.int32)
+    parent, tokens, n_nodes, mask, cand = _run(par, tok, logp, n_cand, 60, 64)
+    for b in range(len(par)):   # (the oracle knows no candidates without a parent: they cannot be kept, nor what hangs on them)
+        joint, reached = np.full(n_cand[b], -np.inf, np.float32), np.zeros(n_cand[b], bool)
+        joint[0], reached[0] = 0.0, True
+        for c in range(1, n_cand[b]):
+            up = par[b, c]
+            if 0 <= up < c and reached[up]:
+                joint[c], reached[c] = joint[up] + logp[b, c], True
+        best = set(np.argsort(-joint[1:], kind="stable")[:59] + 1)
+        node = {0: 0}
+        for c in range(1, n_cand[b]):
+            if c in best and reached[c] and par[b, c] in node:
+                node[c] = len(node)
+        words = []
+        for c in node:
+            words.append((words[node[par[b, c]]] if c else 0) | 1 << len(words))
+        kept, rest = list(node), [-1] * (64 - len(node))
+        assert n_nodes[b] == len(kept)
+        assert cand[b].tolist() == kept + rest
+        assert tokens[b].tolist() == tok[b, kept].tolist() + rest
+        assert parent[b].tolist() == [-1] + [node[par[b, c]] for c in kept[1:]] + rest
+        assert mask[b].tolist() == words + [0] * len(rest)
+
+
 def test_built_tree_feeds_the_verification_calls():
     """The emitted arrays are exactly what attention and acceptance take: run both on them and
     compare with the oracle fed from the oracle's own tree."""
