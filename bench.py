@@ -470,15 +470,15 @@ def run_workload(args, workload, steps_arg, warmup_arg, primary):
     step_roofline.update(algorithmic_bytes=cfg.step_bytes(), algorithmic_flops=cfg.step_flops())
 
     # the acceptance call (row pass + walk) against its own roofs: the logits are read once (HBM); the
-    # sampling form also evaluates one fp64 exponential per logit: cast, scale, range reduction, an
-    # 11-term polynomial, scaling and the sum: 27 fp64 vector operations of which 15 are fused
-    # multiply-adds, counted as 42 flops, against the fp64 vector peak of 256 CUs x 4 SIMDs x 16 lanes
+    # sampling form also evaluates one fp64 exponential per logit: cast, difference, limit, scale, range reduction,
+    # a degree-4 polynomial, scaling and the sum: 13 fp64 vector operations of which 4 are fused
+    # multiply-adds, counted as 17 flops, against the fp64 vector peak of 256 CUs x 4 SIMDs x 16 lanes
     # x 2 flops x 2.4 GHz = 78.6 TFLOP/s
     accept_s = float(np.percentile(accept_ms, 50)) * 1e-3
     accept_roofline = dict(bound="hbm", achieved=cfg.logit_bytes() / accept_s / 1e9, peak=HBM_PEAK_GBS, unit="GB/s")
     accept_roofline["frac"] = accept_roofline["achieved"] / HBM_PEAK_GBS
     if accept == "sample" and not args.lm_head:
-        fp64_tflops = B * N * V * 42 / accept_s / 1e12
+        fp64_tflops = B * N * V * 17 / accept_s / 1e12
         accept_roofline.update(alu_fp64_tflops=fp64_tflops, alu_fp64_peak=78.6, alu_fp64_frac=fp64_tflops / 78.6)
     accept_roofline.update(kernel="acceptance call (row pass + walk)", call_us_p50=accept_s * 1e6, algorithmic_bytes=cfg.logit_bytes())
 
