@@ -15,7 +15,7 @@ LATE_LIB_PATH = os.path.join(_HERE, "libfspad_late.so")
 OBJ_DIR = os.path.join(_HERE, "_build")
 SOURCES = ["fspad_host.cpp", "fspad_attn.hip", "fspad_accept.hip", "fspad_commit.hip", "fspad_tree.hip", "fspad_lmhead.hip",
            "fspad_topk.hip", "fspad_draft.hip"]
-HEADERS = ["greedy_walk.h", "stream_gemm.h", "exp_nonpos.h"]
+HEADERS = ["attn_plan.h", "greedy_walk.h", "stream_gemm.h", "exp_nonpos.h"]
 
 _FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
           # packed fp32 VALU ops are kept off on the test machines
