@@ -106,38 +106,6 @@ inline int plan_wgs(const Plan& pl, int64_t total_blocks, int64_t units, bool un
   return (int)wgs;
 }
 
-// Fewer pieces than plan_wgs gives the units of an equal batch, down to whole ones, where the merge costs more than the shorter streams
-// spare. What a call takes beyond its fixed part, in hundredths of a turn (one block of every key-splitting wavefront: 0.8 us with shared
-// stages, 1.6 where every wavefront fetches its own K and V, D = 128): its longest stream, and where units are cut the second launch, its
-// trips to memory (eight pieces a trip), a megabyte of partial results written and read, a piece that every merging thread reads. Fitted to 489
-// calls (1 to 14 sequences, 24 to 30000 keys, 8 to 60 nodes, 2 to 120 units), each timed with up to twenty counts. Measured, us a call
-// with all compute units in use -> so: 32 / 8 heads, 60 nodes: 1000 keys 16.7 -> 15.5, 2048 keys 19.9 -> 17.1; four sequences of it, 330 keys 18.4 -> 12.6;
-// 12 / 2 heads, 48 nodes, 8192 keys 22.5 -> 19.4; 32 heads, 26 nodes, 2048 keys 15.6 -> 14.8; 16 heads, 700 keys 12.6 -> 10.8. The other way round:
-// 64 / 8 heads, 4096 keys, 8 pieces 24.1, 6 24.3; 5 x 40 / 8 heads, 40 nodes, 1000 keys, 3 pieces 19.1, whole 22.8. The fit is good to a few tenths of a
-// turn, so less than 0.3 of one does not count: over those calls 0.965 of the time on the mean, the worst 1.05.
-// (Above 256 workgroups of 16-row tiles compute units hold one or two: not this rule's business.)
-inline int64_t fewer_pieces(const Plan& pl, int64_t units, int64_t blocks_per_unit, int64_t wgs) {
-  struct Costs { int cut, trip, megabyte, piece; };
-  int64_t most = wgs / units;
-  if (most * units > kComputeUnits) most = kComputeUnits / units;
-  if (most < 2) return wgs;
-  const Costs c = pl.shared_stage ? (pl.D == 128 ? Costs{140, 105, 36, 31} : Costs{260, 40, 27, 25})
-                  : pl.WS > 1     ? Costs{200, 120, 18, 0}
-                  : pl.D == 128   ? Costs{145, 85, 26, 22}
-                                  : Costs{320, 120, 110, 0};
-  const int KW = key_waves(pl);
-  auto cost = [&](int64_t pieces) {
-    const int64_t blocks = (blocks_per_unit + pieces - 1) / pieces, turns = (blocks + KW - 1) / KW;
-    const int64_t cut = c.cut + c.trip * ((pieces + 7) / 8) + c.piece * pieces + c.megabyte * pieces * units * pl.rows_per_unit * pl.D / (1 << 18);
-    return 100 * turns + (pieces > 1 ? cut : 0);
-  };
-  const int64_t with_most = cost(most);
-  int64_t best = most, least = with_most;
-  for (int64_t pieces = most - 1; pieces >= 1; --pieces)
-    if (const int64_t x = cost(pieces); x < least) { least = x; best = pieces; }
-  return with_most - least >= 30 ? best * units : wgs;
-}
-
 }  // namespace fspad_detail
 
 #endif

@@ -30,7 +30,6 @@ namespace {
 using fspad_detail::bf16x8;
 using fspad_detail::blocks_of;
 using fspad_detail::div_rcp;
-using fspad_detail::fewer_pieces;
 using fspad_detail::kBlockKeys;
 using fspad_detail::kComputeUnits;
 using fspad_detail::key_waves;
@@ -2159,7 +2158,6 @@ extern "C" fspad_status fspad_tree_attn(const fspad_attn_desc* desc, const void*
       // 16 to 26 keys, trees of 11 to 26 nodes 10.2 us, planned as a ragged batch 17.4)
       int64_t wgs = plan_wgs(pl, total, units, uniform, d.workgroups);
       if (wgs > full_wgs) wgs = uniform && full_wgs >= units ? full_wgs / units * units : full_wgs;
-      if (uniform && d.workgroups == 0 && units > 0) wgs = fewer_pieces(pl, units, total / units, wgs);   // (the workspace stays that of plan_wgs)
       sl.setup = uniform || total + units * setup_blocks(pl) > kMaxFlatBlocks ? 0 : setup_blocks(pl);
       // Short units of a ragged batch that fit the chip stay whole, as those of an equal one do (plan_wgs): a workgroup each, and
       // so much set-up that the even division falls into it. Whole units leave no partial results, so the workspace does not bound

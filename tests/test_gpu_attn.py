@@ -360,15 +360,25 @@ def test_bf16_workgroups_aligned_with_units(H, B, Hkv, G, N, L):
     _check(H, case, H.TOL["bf16"])
 
 
-# Equal units in fewer pieces than there are compute units for, down to whole ones: every row of the costs (grouped heads of both head
-# dims, one and two slabs a workgroup, 16-row tiles), 1, up to 8 and more pieces, trees of different sizes in equally many blocks.
+# Equal units in pieces: grouped heads of both head dims, one and two slabs a workgroup, 16-row tiles, 2, up to 8 and more pieces, trees of
+# different sizes in equally many blocks.
 @pytest.mark.parametrize("B,Hq,Hkv,N,D,L,n_nodes", [
     (3, 28, 4, 26, 128, 161, None), (1, 12, 2, 48, 128, 1500, None), (1, 12, 2, 48, 128, 5000, None), (2, 64, 8, 33, 128, 100, [33, 64 - 31]),
     (1, 12, 2, 60, 64, 91, None), (2, 28, 4, 40, 64, 1460, [40, 33]), (1, 16, 16, 26, 128, 700, None), (1, 32, 32, 8, 128, 700, None),
     (1, 8, 8, 26, 64, 700, None), (1, 8, 8, 60, 64, 288, None), (1, 28, 4, 10, 128, 3000, None), (2, 12, 2, 16, 128, 450, [16, 1])])
-def test_bf16_equal_units_in_fewer_pieces(H, B, Hq, Hkv, N, D, L, n_nodes):
+def test_bf16_equal_units_in_pieces(H, B, Hq, Hkv, N, D, L, n_nodes):
     case = H.AttnCase(B + Hq + N + L, B, N, Hq, Hkv, D, L, "bf16", n_nodes=None if n_nodes is None else np.array(n_nodes, np.int32))
     _check(H, case, H.TOL["bf16"])
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,L,workgroups", [
+    (1, 32, 32, 26, 128, 2048, 256), (1, 32, 32, 4, 128, 2048, 256), (1, 32, 8, 60, 128, 4096, 256), (4, 32, 8, 60, 128, 330, 256),
+    (8, 16, 16, 10, 64, 1200, 512), (2, 12, 2, 1, 128, 5030, 80), (1, 16, 16, 4, 128, 8300, 512), (2, 64, 8, 12, 128, 1188, 160)])
+def test_bf16_equal_units_take_all_compute_units(H, B, Hq, Hkv, N, D, L, workgroups):
+    """The built-in count is the one that fills the chip. The largest weight of every stream is exact in bf16, so fewer, longer streams are further
+    from a 64-bit evaluation (4 to 17 % where the count was halved or the units left whole)."""
+    case = H.AttnCase(B + Hq + N + L, B, N, Hq, Hkv, D, L, "bf16", n_nodes=[N] * B)
+    assert torch.equal(case.run_gpu(), case.run_gpu(splits=workgroups))
 
 
 @pytest.mark.parametrize("B,Hkv,G,N,D", [(8, 48, 1, 17, 128), (2, 200, 1, 32, 128), (8, 50, 2, 13, 128), (3, 128, 1, 33, 64),
