@@ -641,7 +641,9 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
   };
   auto settle = [&] {    // the results but for the last token, and the chunk that holds it; wavefront 0
     if (lane < nrej) { rej_tok[lane] = my_rej; rej_w[lane] = my_rej_w; }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (lane < p.Nmax) { p.path[o + lane] = my_path; if (lane != len - 1) p.tokens[o + lane] = my_out; }
     if (lane == 0) {
       p.path_len[b] = len; p.n_tokens[b] = len;
@@ -706,7 +708,9 @@ __global__ __launch_bounds__(kWalkThreads) void accept_sample_walk_kernel(const 
       if (wave == 0) {
         __threadfence();
         merge_row(tid < 16 ? leaf : FSPAD_MAX_NODES, tid & 15);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         M = row_M[leaf];
         Z = row_Z[leaf];
       }

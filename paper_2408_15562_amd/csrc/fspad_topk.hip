@@ -127,7 +127,9 @@ struct BlockBest {
     for (int i = 0; i < kGroups; ++i) place += lane_of(mine, i) > mine ? 1 : 0;
     if (place < k) atomicMin(&s.bound[wave], mine);
     if (place == 0) s.best[wave] = mine;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     return s.best[wave];
   }
   template <typename Low>

@@ -35,3 +35,17 @@ def test_wait_states_own_what_they_protect():
             seen += 1
             assert re.search(r'v_mfma|global_store|"\+v"\(', stmt), f"{os.path.basename(path)}:{line}: {stmt}"
     assert seen >= 4
+
+
+def test_wave_barriers_stand_between_fences():
+    """A wave barrier keeps instructions in place, not memory accesses: what lanes leave each other in LDS is ordered by the fences around it
+    (left out, a read may be moved to where only some lanes' writes have been seen; at wavefront scope they cost no instruction)."""
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.h"))):
+        lines = [x.strip() for x in open(path).read().split("\n")]
+        for i, x in enumerate(lines):
+            if x.startswith("__builtin_amdgcn_wave_barrier()"):
+                seen += 1
+                assert lines[i - 1].startswith("__builtin_amdgcn_fence(__ATOMIC_RELEASE"), f"{os.path.basename(path)}:{i + 1}"
+                assert lines[i + 1].startswith("__builtin_amdgcn_fence(__ATOMIC_ACQUIRE"), f"{os.path.basename(path)}:{i + 1}"
+    assert seen >= 4
