@@ -95,9 +95,10 @@ __device__ __forceinline__ double wave_running_sum(double v) {
 
 __device__ __forceinline__ float clean(float x) { return (x != x) ? -INFINITY : x; }  // NaN ranks lowest
 
-// The largest of the numbers among x (-infinity where there is none): two at a time, NaNs dropped by the instruction. (With the mode bit
-// that kernels start with a signalling NaN would come back as a quiet one, and the compiler puts an instruction in front of every
-// operand to make sure that there is none.)
+// The largest of the numbers among x (-infinity where there is none): two at a time, NaNs dropped by the instruction. (With the IEEE bit of the mode
+// register, which kernels start with and the compiler counts on, a signalling NaN would come back as a quiet one, and the compiler puts an
+// instruction in front of every operand to make sure that there is none. The bit is off for these instructions alone: m ties them, first to last, to the
+// statements that clear and set it; what else the compiler moves in between are loads, conversions and integers.)
 template <int N>
 __device__ __forceinline__ float max_of_numbers(const float (&x)[N]) {
   static_assert(N % 2 == 0, "pairs");
@@ -105,6 +106,7 @@ __device__ __forceinline__ float max_of_numbers(const float (&x)[N]) {
   asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0\n\tv_mov_b32 %0, 0xff800000" : "=v"(m));
 #pragma unroll
   for (int k = 0; k < N; k += 2) asm("v_max3_f32 %0, %0, %1, %2" : "+v"(m) : "v"(x[k]), "v"(x[k + 1]));
+  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 1" : "+v"(m));
   return m;
 }
 

@@ -49,3 +49,23 @@ def test_wave_barriers_stand_between_fences():
                 assert lines[i - 1].startswith("__builtin_amdgcn_fence(__ATOMIC_RELEASE"), f"{os.path.basename(path)}:{i + 1}"
                 assert lines[i + 1].startswith("__builtin_amdgcn_fence(__ATOMIC_ACQUIRE"), f"{os.path.basename(path)}:{i + 1}"
     assert seen >= 4
+
+
+def test_mode_bits_are_put_back():
+    """A bit of the mode register that a function clears is set again before it ends, by a statement that its last result passes through."""
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.h"))):
+        text = open(path).read()
+        state = {}
+        for line, stmt in _asm_statements(text):
+            for bit, value in re.findall(r"s_setreg_imm32_b32 hwreg\(HW_REG_MODE, (\d+), 1\), ([01])", stmt):
+                where = f"{os.path.basename(path)}:{line}"
+                if value == "0":
+                    assert not state.get(bit), f"{where}: cleared twice"
+                    state[bit] = where
+                    seen += 1
+                else:
+                    assert state.pop(bit, None), f"{where}: set without having been cleared"
+                    assert '"+v"(' in stmt, f"{where}: nothing keeps it behind what needs the bit off"
+        assert not state, f"left cleared: {state}"
+    assert seen >= 1
