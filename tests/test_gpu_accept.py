@@ -127,26 +127,83 @@ def test_greedy_small_vocabularies(H, B, N, V, pad):
     H.assert_accept_equal(case.gpu_greedy(), case.cpu_greedy())
 
 
+def _with_nan_and_infinity(rng, logits):
+    """NaNs of both kinds, -infinity and very low entries all over; a whole wavefront's share of NaN in every third row, whole chunks (of
+    any size that calls of these shapes take) of -infinity in the next. In place; the rows stay with a finite entry."""
+    B, N, V = logits.shape
+    if V <= 3:
+        return
+    hit = rng.random(logits.shape, dtype=np.float32)
+    hit[..., V - 1] = 1.0
+    logits[hit < 0.05] = np.nan
+    logits.view(np.uint32)[(hit > 0.05) & (hit < 0.08)] = 0x7fa00001   # a signalling one
+    logits[(hit > 0.08) & (hit < 0.2)] = -np.inf
+    logits[(hit > 0.2) & (hit < 0.25)] = -1.0e30
+    logits[:, ::3, 256:min(512, V - 1)] = np.nan
+    logits[:, 1::3, :min(8192, V - 1)] = -np.inf
+
+
+def _first_children_accepted(logits, parent):
+    """Tokens with which a walk whose acceptance uniforms are zero takes every first child of a row with a finite entry."""
+    best = np.where(np.isnan(logits), -np.inf, logits).argmax(2)
+    return np.ascontiguousarray(np.take_along_axis(best, np.maximum(parent, 0), 1).astype(np.int32))
+
+
 @pytest.mark.parametrize("V", [1, 2, 3, 255, 1023, 1025, 4099, 33001])
 @pytest.mark.parametrize("T", [1.0, 0.05, 40.0])
 @pytest.mark.parametrize("pad", [0, 1, 4])
 def test_sampling_rows_with_nan_and_infinity(H, V, T, pad):
-    """NaNs of both kinds and -infinity in every wavefront's entries, a row of nothing else, spread over many octaves: the row statistics
-    drop them. (The oracle ranks a NaN lowest too.) Steps that a rounding of the sums could turn are left out, as everywhere."""
-    B, N = 2, 20
+    """NaNs of both kinds and -infinity in every wavefront's entries, in all of a wavefront's and of a chunk's, spread over many octaves: the row
+    statistics drop them. Rows of nothing else, which give token 0, at the root (two sequences) and behind an accepted child (two): these
+    the oracle decides by its fallback, so they are compared whatever the margin; the others where a rounding of the sums cannot turn a step."""
+    B, N = 8, 20
     rng = np.random.default_rng(V)
     logits = (3.0 * rng.standard_normal((B, N, V))).astype(np.float32)
-    if V > 3:
-        hit = rng.random((B, N, V))
-        logits[hit < 0.05] = np.nan
-        logits.view(np.uint32)[(hit > 0.05) & (hit < 0.08)] = 0x7fa00001   # a signalling one
-        logits[(hit > 0.08) & (hit < 0.2)] = -np.inf
-        logits[(hit > 0.2) & (hit < 0.25)] = -1.0e30
-    logits[0, 1] = np.nan
-    logits[1, 2] = -np.inf
-    case = H.AcceptCase(70 + V, B, N, V, "sample", logits=logits, tokens=rng.integers(0, V, (B, N)).astype(np.int32), row_pad=pad)
-    cpu = case.cpu_sample(T)
-    H.assert_accept_equal(case.gpu_sample(T), cpu, keep=cpu[4] >= H.MARGIN)
+    _with_nan_and_infinity(rng, logits)
+    from workloads import gen_trees
+    parent, n_nodes = gen_trees(70 + V, B, N, 6, 10)
+    for b, node, nothing in ((0, 0, np.nan), (1, 0, -np.inf), (2, 1, np.nan), (3, 1, -np.inf)):
+        logits[b, node] = nothing
+    tokens = _first_children_accepted(logits, parent)
+    uniforms = H.gen_uniforms(70 + V, B, N)
+    uniforms[2:5, 0] = 0     # sequences 2 to 4 take every first child; 4 walks to a leaf
+    case = H.AcceptCase(70 + V, B, N, V, "sample", parent=parent, n_nodes=n_nodes, logits=logits, tokens=tokens, uniforms=uniforms, row_pad=pad)
+    with np.errstate(invalid="ignore"):
+        cpu = case.cpu_sample(T)
+    assert cpu[1][:4].tolist() == [1, 1, 2, 2] and cpu[2][:2, 0].tolist() == [0, 0] and cpu[2][2:4, 1].tolist() == [0, 0] and cpu[1][4] > 2
+    keep = cpu[4] >= H.MARGIN
+    assert keep[4:].sum() >= 3
+    keep[:4] = True
+    H.assert_accept_equal(case.gpu_sample(T), cpu, keep=keep)
+
+
+@pytest.mark.parametrize("B,V,pad", [(13, 100003, 0), (13, 100003, 2), (300, 4999, 1)])
+def test_large_sampling_calls_with_nan_and_infinity(H, B, V, pad):
+    """The form that leaves the leaves' rows to the walk: chains that are accepted to their leaf, whose row is nothing but NaN, nothing but
+    -infinity, both among finite entries (whole chunks of them too) or ordinary; and chains that meet such a row on the way."""
+    N = 33
+    assert B * N * V >= 40 << 20
+    rng = np.random.default_rng(B)
+    logits = rng.standard_normal((B, N, V), dtype=np.float32)
+    odd = logits[:, [0, 7, N - 1]]
+    _with_nan_and_infinity(rng, odd)
+    logits[:, [0, 7, N - 1]] = odd
+    nothing = np.zeros(B, bool)
+    for b in range(B):
+        if b % 5 < 4:
+            logits[b, 9 if b % 5 > 1 else N - 1] = (np.nan, -np.inf)[b % 2]
+            nothing[b] = True
+    parent = np.broadcast_to(np.arange(-1, N - 1, dtype=np.int32), (B, N))
+    uniforms = H.gen_uniforms(B, B, N)
+    uniforms[:, 0] = 0
+    case = H.AcceptCase(B, B, N, V, "sample", parent=parent, logits=logits, tokens=_first_children_accepted(logits, parent), uniforms=uniforms, row_pad=pad)
+    with np.errstate(invalid="ignore"):
+        cpu = case.cpu_sample(1.0)
+    assert (cpu[1][nothing] == np.where(np.arange(B) % 5 > 1, 10, N)[nothing]).all() and (cpu[1][~nothing] == N).all()
+    keep = cpu[4] >= H.MARGIN
+    assert keep[~nothing].all() and (~nothing).any()
+    keep[nothing] = True
+    H.assert_accept_equal(case.gpu_sample(1.0), cpu, keep=keep)
 
 
 def test_rows_of_unused_slots_are_not_read():

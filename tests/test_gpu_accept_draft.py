@@ -235,6 +235,47 @@ def test_plus_infinity_leaves_a_row_without_mass(B, V):
         assert (out[1].cpu().numpy() == 1).all() and (out[2].cpu().numpy()[:, 0] == 0).all()
 
 
+@pytest.mark.parametrize("B,N,V,pad", [(6, 20, 1025, 0), (6, 20, 33001, 1), (2, 26, 128256, 0), (260, 4, 600, 0), (3, 9, 90, 3)])
+@pytest.mark.parametrize("T", [1.0, 0.7])
+def test_rows_with_nan_and_infinity(B, N, V, pad, T):
+    """NaNs of both kinds and -infinity among the target's and the draft's entries (not at the children's tokens, which were drawn), in all of a
+    wavefront's and of a chunk's, draft rows of leaves all NaN (nobody asks for them); roots whose target row is nothing but NaN or -infinity,
+    which reject their children and give token 0, compared whatever the oracle's margin."""
+    import paper_2408_15562_amd as fspad
+    parent, n_nodes, logits, draft_logits, tokens = _case(7300 + V, B, N, V, T, peak=2.0, noise=0.5)
+    rng = np.random.default_rng(V)
+    own = np.zeros((B, N, V), bool)
+    b, c = np.nonzero(parent >= 0)
+    own[b, parent[b, c], tokens[b, c]] = True
+    for x in (logits, draft_logits):
+        hit = rng.random((B, N, V), dtype=np.float32)
+        x[(hit < 0.05) & ~own] = np.nan
+        x.view(np.uint32)[(hit > 0.05) & (hit < 0.08) & ~own] = 0x7fa00001
+        x[(hit > 0.08) & (hit < 0.2) & ~own] = -np.inf
+        part = np.zeros((B, N, V), bool)
+        part[:, ::3, 256:512] = True
+        part[:, 1::3, 1024:min(10240, V // 2)] = True
+        x[part & ~own] = (np.nan, -np.inf)[x is logits]
+    leaf = np.ones((B, N), bool)
+    leaf[b, parent[b, c]] = False
+    draft_logits[leaf] = np.nan
+    nothing = np.arange(B) % 3 < 2 if B > 2 else np.arange(B) < 1
+    for i in np.nonzero(nothing)[0]:
+        logits[i, 0] = (np.nan, -np.inf)[i % 2]
+    uni = gen_uniforms(5, B, N)
+    out = fspad.fspad_tree_accept_sample_draft(_padded(logits, pad), _padded(draft_logits, pad), *(torch.from_numpy(a).to(DEV) for a in (tokens, parent, n_nodes)),
+                                               T, torch.from_numpy(uni).to(DEV))
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        ref = oracle.accept_sample_draft(logits, draft_logits, tokens, parent, n_nodes, T, uni)
+    assert (ref[1][nothing] == 1).all() and (ref[2][nothing, 0] == 0).all()
+    keep = ref[4] >= MARGIN
+    assert keep[~nothing].sum() >= max(1, (~nothing).sum() - 1)
+    keep[nothing] = True
+    for name, g, r in zip(("path", "path_len", "tokens", "n_tokens"), out, ref[:4]):
+        np.testing.assert_array_equal(g.cpu().numpy()[keep], r[keep], err_msg=name)
+
+
 def test_captured_call_replays_like_eager():
     import paper_2408_15562_amd as fspad
     B, N, V, T = 3, 30, 5000, 1.0
