@@ -290,13 +290,14 @@ __global__ __launch_bounds__(kThreads) void accept_greedy_walk_kernel(const Acce
 // under way together and with the tree's. (Four rows of sixteen are 64 of the 128 registers that a wavefront of sixteen can have: longer
 // rows would need a loop. Rows of unused tree slots are not read: waiting for the number of nodes first costs 0.13 us.) Such a call is
 // launches and trips to memory, us by two launches / so, rows of 1000, a call's share of a graph of fifty: 1 x 20 5.05 / 3.14, 1 x 26 5.35 / 3.58, 1 x 36
-// 5.27 / 4.00, 1 x 48 5.47 / 4.93, 4 x 60 5.63 / 5.46, 16 x 60 6.14 / 5.63, 25 x 48 8.29 / 5.32, 200 x 20 12.9 / 3.7; not aligned (rows of 997) 1 x 36 5.33 /
-// 4.41, 1 x 60 5.28 / 5.44, 16 x 60 6.23 / 5.83. One workgroup per sequence takes longer the more rows it has, two launches the more there are in all: 1 x 64
-// 5.47 / 5.75, 8 x 64 5.69 / 6.00, 20 x 64 8.19 / 6.08, 64 x 64 13.1 / 6.1. (Before the best of a wavefront came from a maximum and a ballot (wave_best) 1 x 26 took
-// 5.11 / 1 x 32 5.38 us in one launch, and more than 36 rows were left to two.)
+// 5.27 / 4.00, 1 x 48 5.47 / 4.93, 4 x 60 5.63 / 5.46, 16 x 60 6.14 / 5.63, 25 x 48 8.29 / 5.32, 200 x 20 12.9 / 3.7. One workgroup per sequence takes longer the more rows it
+// has, two launches the more there are in all: 1 x 64 5.47 / 5.75, 8 x 64 5.69 / 6.00, 20 x 64 8.19 / 6.08, 64 x 64 13.1 / 6.1. Rows that are not aligned are read entry
+// by entry here, 16 bytes a lane by two launches, so the line lies lower for few sequences (one launch / two, rows of 997 and of 1000 a stride of 1001 apart): 1 x 48 0.95 and 0.94, 4 x 48
+// 0.94 and 0.96, 1 x 56 1.04 and 1.04, 2 x 60 1.04 and 1.03, 4 x 60 1.01 and 1.03, 8 x 60 0.99 and 1.02, 16 x 52 0.93 and 0.95, 16 x 60 0.94 and 0.98.
 constexpr int kSmallVocab = 1024;
-bool takes_small_greedy(int32_t B, int32_t Nmax, int32_t V) {
-  return V <= kSmallVocab && (Nmax <= 60 || (int64_t)B * Nmax >= 1200);
+bool takes_small_greedy(int32_t B, int32_t Nmax, int32_t V, bool aligned) {
+  const int64_t rows = (int64_t)B * Nmax;
+  return V <= kSmallVocab && (Nmax <= 48 || (Nmax <= 60 && (aligned || rows >= 480)) || rows >= 1200);
 }
 constexpr int kSmallWaves = 16;
 constexpr int kSmallRows = FSPAD_MAX_NODES / kSmallWaves;   // per wavefront
@@ -1663,9 +1664,10 @@ extern "C" fspad_status fspad_tree_accept_greedy(int32_t B, int32_t Nmax, int32_
   AcceptParams p{};
   fill_params(p, B, Nmax, V, logits, row_stride, draft_tokens, parent, n_nodes, path, path_len, tokens, n_tokens, workspace);
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-  if (takes_small_greedy(B, Nmax, V)) {
+  const bool aligned = rows_vectorisable(logits, row_stride) && V % 4 == 0;
+  if (takes_small_greedy(B, Nmax, V, aligned)) {
     const dim3 grid((unsigned)B), block(64 * kSmallWaves);
-    if (rows_vectorisable(logits, row_stride) && V % 4 == 0) hipLaunchKernelGGL(accept_greedy_small_kernel<true>, grid, block, 0, stream, p);
+    if (aligned) hipLaunchKernelGGL(accept_greedy_small_kernel<true>, grid, block, 0, stream, p);
     else hipLaunchKernelGGL(accept_greedy_small_kernel<false>, grid, block, 0, stream, p);
     return hipGetLastError() == hipSuccess ? FSPAD_OK : FSPAD_ERR_HIP;
   }

@@ -127,6 +127,20 @@ def test_greedy_small_vocabularies(H, B, N, V, pad):
     H.assert_accept_equal(case.gpu_greedy(), case.cpu_greedy())
 
 
+@pytest.mark.parametrize("B,N,V,pad,one_launch", [
+    (1, 48, 1000, 1, True), (1, 49, 1000, 1, False), (2, 60, 997, 0, False), (7, 60, 997, 0, False), (8, 60, 997, 0, True), (1, 60, 1000, 0, True),
+    (1, 60, 1000, 4, True), (1, 61, 1000, 0, False), (20, 64, 997, 0, True), (1, 20, 1025, 0, False)])
+def test_greedy_launch_forms(H, B, N, V, pad, one_launch):
+    """Which small calls take one launch (it leaves the workspace as it is): up to 60 rows a sequence, up to 48 where they are not aligned and the
+    batch has fewer than 480, any from 1200 rows on."""
+    import paper_2408_15562_amd as fspad
+    case = H.AcceptCase(3500 + N, B, N, V, "greedy", row_pad=pad, peak=1.5)
+    ws = torch.full((fspad.fspad_tree_accept_workspace_bytes(B, N, V),), 0xA5, dtype=torch.uint8, device=H.DEV)
+    out = fspad.fspad_tree_accept_greedy(case.logits_dev, case.tokens_dev, case.parent_dev, case.n_nodes_dev, workspace=ws)
+    H.assert_accept_equal([t.cpu().numpy() for t in out], case.cpu_greedy())
+    assert bool((ws == 0xA5).all()) == one_launch
+
+
 def _with_nan_and_infinity(rng, logits):
     """NaNs of both kinds, -infinity and very low entries all over; a whole wavefront's share of NaN in every third row, whole chunks (of
     any size that calls of these shapes take) of -infinity in the next. In place; the rows stay with a finite entry."""
