@@ -471,7 +471,7 @@ def run_workload(args, workload, steps_arg, warmup_arg, primary):
 
     # the acceptance call (row pass + walk) against its own roofs: the logits are read once (HBM); the
     # sampling form also evaluates one fp64 exponential per logit: cast, difference, limit, scale, range reduction,
-    # a degree-4 polynomial, scaling and the sum: 13 fp64 vector operations of which 4 are fused
+    # a degree-4 polynomial, scaling and the sum: 12 fp64 vector operations of which 5 are fused
     # multiply-adds, counted as 17 flops, against the fp64 vector peak of 256 CUs x 4 SIMDs x 16 lanes
     # x 2 flops x 2.4 GHz = 78.6 TFLOP/s
     accept_s = float(np.percentile(accept_ms, 50)) * 1e-3

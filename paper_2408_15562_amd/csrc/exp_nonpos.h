@@ -42,8 +42,10 @@ __device__ __forceinline__ double exp_nonpos(double x) {
 // The same for a loop over many arguments, with a table of 2^(j/256) in LDS (table-driven exponential after Tang): exp((x - m)/T) with
 // the argument z = (x - m) * (256 log2(e) / T), which `scale` carries, in 256ths of an octave: z = 256 n + j + f, |f| <= 1/2, where f is
 // exact, and 2^(f/256) is a degree-4 Taylor polynomial (truncation below 4e-17 relative). Twelve fp64 instructions
-// per weight of a sum, conversion and addition among them; with 32 entries, ln2 taken off in two parts and degree 5 (2.3e-15) it was
-// sixteen and the scale apart. Sums of rows are as close to 64 bits as then or closer (3000 rows of N(0, 3^2): mean error 0.4 to 1.0 of it). Lanes
+// per weight of a sum, five of them fused (the last product goes into the sum); with 32 entries, ln2 taken off in two parts and degree 5 (2.3e-15) it was
+// sixteen and the scale apart. Sums of rows, which is all that takes these weights, are as close to 64 bits as then or closer (3000 rows of N(0, 3^2): mean error 0.4 to
+// 1.0 of it). A single weight is closer near the maximum and further off far below it, where the scale's rounding grows with the distance: T = 1, within 20 of the
+// maximum 2.5e-15 -> 1.8e-15 relative, within 50 2.5e-15 -> 5.8e-15, within 700 -> 4.9e-14. Lanes
 // that meet on a bank wait, beside the arithmetic. NaN and -infinity weigh as -708 does (3e-308, which moves no sum that holds a 1).
 constexpr int kExp2Entries = 256;
 constexpr double kExp2PerE = 369.3299304675746;   // 256 log2(e)
