@@ -255,7 +255,9 @@ __global__ __launch_bounds__(256) void rms_norm_kernel(const RmsNormParams p) {
 // h = sum of the partials + residual (rounded to bf16, written), then out = rmsnorm(h) of the rounded
 // values, as rms_norm_kernel would compute it from h. What a thread wrote of h stays in its registers (of rows of more than
 // 1024 * 4 * kKept entries the rest is read back, by the same thread). 1024
-// threads: with the few rows of a draft step the row's loads must all be in flight at once.
+// threads: with the few rows of a draft step the row's loads must all be in flight at once. (What is under way takes 88 registers, one workgroup a compute unit
+// where 36 had room for two, and the other passes 63 to 100; with up to 128 rows, the most a call takes, there are no more workgroups than compute units: 60 calls
+// of 32 to 128 rows, hidden size 1024 to 6656, took 0.95 to 1.00 of the time, 4 x 16 rows of 1024 45.6 -> 43.8 us, 8 x 16 of 6656 404.8 -> 402.2.)
 struct CombineNormParams {
   Partials part;
   const char* residual;    // [rows][Hd] bf16
