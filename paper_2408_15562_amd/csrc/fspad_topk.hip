@@ -82,15 +82,18 @@ __device__ __forceinline__ double wave_sum(double x) {
 // threads (every 32nd: neighbours may hold what one chunk has left), and the largest key; `gather` sets aside the few entries that reach it (of random ones k to 1.4 k);
 // `emit` counts for each of them the ones above it, which is its place. Before, k rounds of a
 // workgroup-wide maximum with a barrier each, in which the winner's thread looked its registers through
-// again, were most of both kernels. Where more than kListed entries reach the bound (many equal logits) those
-// rounds still do it.
+// again, were most of both kernels. Where more than kListed entries reach the bound (many equal logits) it
+// is found once more by whole words (`gather_by_word`); where they still do (the best ones in a few groups) those rounds do it.
 //
 // Bound by latency: two launches of 1.6 us, a trip to memory and some 1000 clocks of dependent instructions each. In a
 // graph, before (k rounds, the loads of a chunk one behind the other) and now: 4 rows of 32000, k = 4 10.0 -> 6.9 us,
 // 40 rows of 32000, k = 10 19.0 -> 8.4, 30 rows of 151001, k = 10 34.0 -> 11.8, 80 rows of 128256, k = 10 48.1 -> 19.3,
 // 16 rows of 32000, k = 16 22.6 -> 7.9. Rounds over the lanes of a wavefront, without barriers, took 10.5 us at 40 x 32000;
 // 64 groups 8.9; groups of neighbouring threads 11.7 at 16 x 32000 (k = 16: a chunk's list came to few of them).
-// Rows of seven distinct values (those rounds): 18.9 -> 18.8.
+// Where more than kListed entries reach the bound (a chunk of a masked vocabulary, nothing but -infinity), k rounds took longer behind it than without, and
+// the bound by whole words takes their place. us a call, k rounds for every row / behind the first bound / now: 10 rows of 128256 with five finite entries, k = 16
+// 25.8 / 34.3 / 13.2, 40 rows of 128255 with sixty, k = 10 33.1 / 37.0 / 20.4, 40 rows of 32000 with seven distinct values 19.3 / 12.6 / 12.8; with
+// k = 4 the rounds are few: 4 constant rows of 32000 10.0 / 10.8 / 10.9, with five finite entries 9.9 / 9.2 / 9.3.
 constexpr int kWaves = kThreads / 64, kListed = kThreads, kGroups = 32;
 template <int PT>
 struct BlockBest {
@@ -98,6 +101,7 @@ struct BlockBest {
     unsigned long long list[kListed];
     unsigned long long slots[2 * kWaves];
     unsigned group[kWaves][kGroups], best[kWaves], bound[kWaves];
+    unsigned long long word_group[kWaves][kGroups];
     int count;
   };
   Shared& s;
@@ -135,48 +139,16 @@ struct BlockBest {
   template <typename Low>
   __device__ __forceinline__ void gather(Low&& low) {
     const unsigned bound = max(s.bound[wave], 1u);
-    int n = 0;
-#pragma unroll
-    for (int q = 0; q < PT; ++q) n += __builtin_popcountll(__ballot(key[q] >= bound));
-    if (n == 0) return;
-    int at = 0;
-    if (lane == 0) at = atomicAdd(&s.count, n);
-    at = __builtin_amdgcn_readfirstlane(at);
-#pragma unroll
-    for (int q = 0; q < PT; ++q) {
-      const unsigned long long in = __ballot(key[q] >= bound);
-      if (in == 0ull) continue;
-      const int to = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(in >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in, 0u));
-      if (key[q] >= bound && to < kListed) s.list[to] = ((unsigned long long)key[q] << 32) | low(q);
-      at += __builtin_popcountll(in);
-    }
+    set_aside([&](int q) { return key[q] >= bound; }, low);
   }
   // behind a barrier after `gather`: put(place, word) for places 0..k-1, each by one thread; word 0: no entry is left
   template <typename Low, typename Put>
   __device__ __forceinline__ void emit(Low&& low, Put&& put) {
     const int n = s.count;
-    if (n <= kListed) {
-      const unsigned long long mine = s.list[tid];
-      if (mine != 0ull) {
-        int place = 0;
-        for (int i = 0; i < n; i += 4) {   // (0 behind the last entry)
-#pragma unroll
-          for (int o = 0; o < 4; ++o) place += s.list[i + o] > mine ? 1 : 0;
-        }
-        if (place < k) put(place, mine);
-      } else if (tid < k) {
-        put(tid, 0ull);   // fewer than k entries: thread tid >= n has none
-      }
-      return;
-    }
-    auto word = [&](int q) { return key[q] ? ((unsigned long long)key[q] << 32) | low(q) : 0ull; };
-    auto local_best = [&] {
-      unsigned long long best = 0ull;
-#pragma unroll
-      for (int q = 0; q < PT; ++q) best = word(q) > best ? word(q) : best;
-      return best;
-    };
-    unsigned long long mine = local_best();
+    if (__builtin_expect(n <= kListed, 1)) return emit_listed(n, put);
+    const int by_word = gather_by_word(low);
+    if (by_word <= kListed) return emit_listed(by_word, put);
+    unsigned long long mine = local_best(low);
     for (int r = 0; r < k; ++r) {
       unsigned long long* slots = s.slots + (r & 1) * kWaves;   // in turn: one barrier a round is enough
       const unsigned long long wave_best = wave_max(mine);
@@ -189,10 +161,82 @@ struct BlockBest {
       if (win != 0ull && win == mine) {
 #pragma unroll
         for (int q = 0; q < PT; ++q)
-          if (word(q) == win) key[q] = 0u;
-        mine = local_best();
+          if (word(q, low) == win) key[q] = 0u;
+        mine = local_best(low);
       }
     }
+  }
+
+ private:
+  template <typename Put>
+  __device__ __forceinline__ void emit_listed(int n, Put& put) {
+    const unsigned long long mine = s.list[tid];
+    if (mine != 0ull) {
+      int place = 0;
+      for (int i = 0; i < n; i += 4) {   // (0 behind the last entry)
+#pragma unroll
+        for (int o = 0; o < 4; ++o) place += s.list[i + o] > mine ? 1 : 0;
+      }
+      if (place < k) put(place, mine);
+    } else if (tid < k) {
+      put(tid, 0ull);   // fewer than k entries: thread tid >= n has none
+    }
+  }
+  template <typename Low>
+  __device__ __forceinline__ unsigned long long word(int q, Low& low) const { return key[q] ? ((unsigned long long)key[q] << 32) | low(q) : 0ull; }
+  template <typename Low>
+  __device__ __forceinline__ unsigned long long local_best(Low& low) const {
+    unsigned long long best = 0ull;
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const unsigned long long w = word(q, low);
+      best = w > best ? w : best;
+    }
+    return best;
+  }
+  template <typename In, typename Low>
+  __device__ __forceinline__ void set_aside(In&& in_list, Low& low) {
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < PT; ++q) n += __builtin_popcountll(__ballot(in_list(q)));
+    if (n == 0) return;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&s.count, n);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const bool mine = in_list(q);
+      const unsigned long long in = __ballot(mine);
+      if (in == 0ull) continue;
+      const int to = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(in >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in, 0u));
+      if (mine && to < kListed) s.list[to] = ((unsigned long long)key[q] << 32) | low(q);
+      at += __builtin_popcountll(in);
+    }
+  }
+  // `prepare` and `gather` once more, by whole words, which are all different: of equal entries (of a masked vocabulary's -infinities) those with
+  // the lowest tokens. Called by all threads; three barriers; returns how many reach the bound.
+  template <typename Low>
+  __device__ __forceinline__ int gather_by_word(Low& low) {
+    unsigned long long mine = local_best(low);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(mine >> 32), (unsigned)(mine >> 32), false, false);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)mine, (unsigned)mine, false, false);
+    mine = max(((unsigned long long)hi[0] << 32) | lo[0], ((unsigned long long)hi[1] << 32) | lo[1]);
+    __syncthreads();   // (all have read the count)
+    if (lane < kGroups) s.word_group[wave][lane] = mine;
+    if (tid == 0) s.count = 0;
+    s.list[tid] = 0ull;
+    __syncthreads();
+    mine = 0ull;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) mine = max(mine, s.word_group[w][lane % kGroups]);
+    int place = 0;
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) place += lane_of(mine, i) > mine ? 1 : 0;
+    const unsigned long long at = __ballot(place == k - 1);   // (none: fewer than k groups have an entry, and all entries are taken)
+    const unsigned long long bound = at != 0ull ? max(lane_of(mine, __builtin_ctzll(at)), 1ull) : 1ull;
+    set_aside([&](int q) { return word(q, low) >= bound; }, low);
+    __syncthreads();
+    return s.count;
   }
 };
 

@@ -84,6 +84,63 @@ def test_entries_at_the_bound(V, equal):
         _check(np.ascontiguousarray(part), 16)
 
 
+def _masked(rows, V):
+    """Rows of a masked vocabulary: none, one, 5, k + 1 finite entries, 300 equal ones at the top, constant rows, half of the vocabulary, and as many large entries
+    as a workgroup sets aside, and more, all with threads of one group (neighbours of four, every 128th)."""
+    x = gen_logits(70 + V, 1, rows, V)[0]
+    rng = np.random.default_rng(V)
+    for row in range(rows):
+        kind = row % 9
+        if kind < 5:
+            keep = rng.permutation(V)[:(0, 1, 5, 17, 300)[kind]]
+            values = x[row, keep] if kind < 4 else np.float32(2.0)
+            x[row] = -np.inf
+            x[row, keep] = values
+        elif kind == 5:
+            x[row] = 0.5
+        elif kind == 6:
+            x[row, (V + 1) // 2:] = -np.inf
+        else:
+            x[row, (np.arange(V) // 4) % 32 == 7] += 100.0 if kind == 7 else np.float32(np.inf)
+    return x
+
+
+@pytest.mark.parametrize("rows,V", [(9, 257), (9, 1000), (27, 1025), (9, 8193), (18, 32000), (600, 8192), (9, 128256)])
+@pytest.mark.parametrize("k", [1, 10, 16])
+def test_masked_vocabularies(rows, V, k):
+    """More entries at the bound than a workgroup sets aside: equal ones, which the lower tokens win, and different ones that one group of threads holds."""
+    x = _masked(rows, V)
+    x[np.isposinf(x)] = 300.0
+    _check(x, min(k, V))
+
+
+def test_masked_vocabularies_take_about_what_ordinary_rows_take():
+    """Rows with five finite entries, of which every chunk but a few is nothing but -infinity (one round for each of the k entries: 3.8 times)."""
+    import paper_2408_15562_amd as fspad
+    rows, V, k = 10, 128256, 16
+    x = torch.randn((rows, V), device=DEV)
+    masked = torch.full_like(x, -np.inf)
+    masked[:, 17::V // 5] = 1.0
+    out = torch.empty((rows, k), dtype=torch.int32, device=DEV), torch.empty((rows, k), dtype=torch.float32, device=DEV)
+    ws = torch.empty(fspad.fspad_draft_topk_workspace_bytes(rows, V, k), dtype=torch.uint8, device=DEV)
+    took = []
+    for logits in (x, masked):
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+            for _ in range(20):
+                fspad.fspad_draft_topk(logits, k, outputs=out, workspace=ws)
+        best = np.inf
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        took.append(best)
+    assert took[1] < 2.0 * took[0], took
+
+
 def test_output_feeds_the_tree_build():
     """A draft step on the device: cut each expanded node's output, append the candidates, build."""
     import paper_2408_15562_amd as fspad
