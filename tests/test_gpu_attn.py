@@ -312,7 +312,7 @@ def test_missing_workspace_is_an_error_not_a_crash(H):
 @pytest.mark.parametrize("L", [0, 7, 8, 9, 16, 17, 31, 32, 33, 64, 65, 255, 257, 700])
 def test_fp32_nodes_per_workgroup(H, D, N, Hq, Hkv, L):
     """One and two nodes per workgroup (by heads x nodes), at the edges of the wavefronts' key tiles
-    (16 or 32 keys, eight wavefronts) and of the form of one wavefront (up to 8 or 16 keys, with more than 768 rows up
+    (16 or 32 keys, eight wavefronts; sixteen where few rows would take a second turn) and of the form of one wavefront (up to 8 or 16 keys, with more than 768 rows up
     to 32 or 64), with ragged trees. Tree rows that a node does not see may hold
     anything: the rows past n_nodes are NaN here."""
     case = H.AttnCase(900 + N + L, 2, N, Hq, Hkv, D, L, "f32", l_cap=L + 2, kv_len=[L, L // 2], n_nodes=[N, max(1, N // 2)])

@@ -81,8 +81,8 @@ def test_shapes(B, Nmax, Hd, I, Hq, Hkv, D, kv_len, n_nodes):
 
 
 @pytest.mark.parametrize("B,Nmax,Hd,I,Hq,Hkv,D", [
-    (1, 5, 8192, 256, 2, 1, 128),     # rows of the normalisations just fit the registers, 17 partial sums of a q / k / v column
-    (1, 3, 8448, 512, 2, 1, 128),     # and are longer than that
+    (1, 5, 8192, 256, 2, 1, 128),     # rows of the normalisations just fit the registers, 16 partial sums of a q / k / v column
+    (1, 3, 8448, 512, 2, 1, 128),     # and are longer than that, 17 partial sums
     (2, 33, 256, 256, 32, 4, 128),    # 16 partial sums of a column of the output projection, 66 rows
 ])
 def test_long_rows_and_many_partial_sums(B, Nmax, Hd, I, Hq, Hkv, D):
